@@ -310,12 +310,41 @@ struct Slice { int64_t V_total, v_begin; };
 // Per-row variant: the forward writes one loss per row (label-smoothed by eps), the backward takes one
 // upstream gradient per row (device arrays of N floats).
 struct PerRow { float* loss_rows_out; const float* grad_rows; float eps; };
+// Device words of the caller that receive the range flag and the number of counted rows (either may be null).
+struct StatusOut { int32_t* status; int64_t* n_valid; };
+
+// The window merge.  While a row's parts fit one batch of loads, one thread merges them; otherwise 16 threads do where
+// the block sums of 64-row blocks fit the arrays (they are padded to 64 entries, and many windows mean few row blocks),
+// and 4 threads in 256-row blocks elsewhere.  `launch` gets the kernel's shape: rows, threads per row, loads in flight.
+constexpr int MERGE_ONE_BATCH = 8;
+template <int R, int G, int LOADS> struct MergeShape { static constexpr int ROWS = R, GROUPS = G, U = LOADS; };
+template <typename F>
+int merge_dispatch(int64_t N, int n_parts, F launch) {
+  auto blocks = [&](auto shape) {
+    const int n_blk = (int)ceil_div(N, decltype(shape)::ROWS);
+    launch(shape, n_blk);
+    return n_blk;
+  };
+  if (n_parts <= MERGE_ONE_BATCH) return blocks(MergeShape<256, 1, 8>{});
+  if (ceil_div(N, 64) <= ALIGN / 4) return blocks(MergeShape<64, 16, 16>{});
+  return blocks(MergeShape<256, 4, 16>{});
+}
+// Returns the number of blocks (entries of the block sums).
+int launch_merge(const float* pm, const float* pa, const float* pz, int n_parts, int64_t stride, const int64_t* y, int N,
+                 int64_t V_total, int64_t ignore_index, float* lse_out, const LossOut& o, bool fused,
+                 float* loss_rows_out, const float* zbar, float eps, hipStream_t st) {
+  return merge_dispatch(N, n_parts, [&](auto shape, int n_blk) {
+    using S = decltype(shape);
+    merge_rows_kernel<S::ROWS, S::GROUPS, S::U><<<n_blk, S::ROWS * S::GROUPS, 0, st>>>(
+        pm, pa, pz, n_parts, stride, y, N, V_total, ignore_index, lse_out, o, fused, loss_rows_out, zbar, eps);
+  });
+}
 
 template <typename T, typename U, typename L>
 flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t* y, int64_t ignore_index,
                       int mean, float* loss_out, float* lse_out, char* ws, hipStream_t st, Slice slice,
                       float* m_out = nullptr, float* a_out = nullptr, float* zt_out = nullptr,
-                      PerRow rows = PerRow{nullptr, nullptr, 0.f}) {
+                      PerRow rows = PerRow{nullptr, nullptr, 0.f}, StatusOut so = StatusOut{nullptr, nullptr}) {
   if (prepare_kernels<T, L>() != hipSuccess) return FLCE_ERR_HIP;
   Header* hdr = reinterpret_cast<Header*>(ws);
   float* part = reinterpret_cast<float*>(ws + p.off_part);
@@ -348,18 +377,22 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
         if constexpr (L::TRANSPOSING)
           fwd_tiles_kernel<T, L, true><<<grid, L::THREADS, L::LDS, st>>>(
               static_cast<const T*>(H), HT, static_cast<const T*>(W), y, (int)p.N, (int)p.d, (int)p.V, ignore_index,
-              slice.V_total, slice.v_begin, p.n_rb, p.n_win, p.n_vt, part, item0);
+              slice.V_total, slice.v_begin, p.n_rb, p.n_win, p.n_vt, part, item0, hdr);
       } else {
         fwd_tiles_kernel<T, L, false><<<grid, L::THREADS, L::LDS, st>>>(
             static_cast<const T*>(H), nullptr, static_cast<const T*>(W), y, (int)p.N, (int)p.d, (int)p.V, ignore_index,
-            slice.V_total, slice.v_begin, p.n_rb, p.n_win, p.n_vt, part, item0);
+            slice.V_total, slice.v_begin, p.n_rb, p.n_win, p.n_vt, part, item0, hdr);
       }
     }
   }
   {
     ProfScope ps(FLCE_PROF_FWD_EPILOGUE, st);
     if (m_out) {
-      merge_rows_partial_kernel<<<p.n_rb, 256, 0, st>>>(part, p.n_win, p.npad, (int)p.N, m_out, a_out, zt_out);
+      merge_dispatch(p.N, p.n_win, [&](auto shape, int n_blk) {
+        using S = decltype(shape);
+        merge_rows_partial_kernel<S::ROWS, S::GROUPS, S::U><<<n_blk, S::ROWS * S::GROUPS, 0, st>>>(
+            part, p.n_win, p.npad, (int)p.N, m_out, a_out, zt_out);
+      });
     } else {
       const int64_t plane = (int64_t)p.n_win * p.npad;
       const float* zbar = nullptr;
@@ -374,12 +407,11 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
                                                             1.0f / (float)p.V, zb);
         zbar = zb;
       }
-      merge_rows_kernel<<<p.n_rb, 256, 0, st>>>(part, part + plane, part + 2 * plane, p.n_win, p.npad, y, (int)p.N,
-                                                slice.V_total, ignore_index, lse_out, blk_loss, blk_cnt, blk_oor,
-                                                rows.loss_rows_out, zbar, rows.eps);
       // the per-row call has no scalar loss to hand out: the sum goes to a spare word of the header block
       float* scalar = loss_out ? loss_out : reinterpret_cast<float*>(ws + 64);
-      finalize_loss_kernel<<<1, 256, 0, st>>>(blk_loss, blk_cnt, blk_oor, p.n_rb, mean, hdr, scalar);
+      launch_merge(part, part + plane, part + 2 * plane, p.n_win, p.npad, y, (int)p.N, slice.V_total, ignore_index, lse_out,
+                   LossOut{blk_loss, blk_cnt, blk_oor, hdr, scalar, mean, so.status, so.n_valid}, /*fused=*/true,
+                   rows.loss_rows_out, zbar, rows.eps, st);
     }
   }
   return hipGetLastError() == hipSuccess ? FLCE_OK : FLCE_ERR_HIP;
@@ -583,15 +615,6 @@ hipError_t static_scratch(void** out) {
   return hipSuccess;
 }
 
-// Hands the status header of a finished forward to the caller's own device words (either may be null).
-__global__ void export_header_kernel(const Header* __restrict__ hdr, int32_t* __restrict__ status_out,
-                                     int64_t* __restrict__ n_valid_out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    if (status_out) *status_out = hdr->status;
-    if (n_valid_out) *n_valid_out = hdr->n_valid;
-  }
-}
-
 }  // namespace
 }  // namespace flce
 
@@ -647,7 +670,8 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
                                 int64_t V, int64_t ignore_index, flce_reduction reduction, flce_dtype dt,
                                 float* loss_out, float* lse_out, void* workspace, size_t workspace_bytes,
                                 void* hip_stream, flce::Slice slice, float* m_out, float* a_out, float* zt_out,
-                                flce::PerRow rows = flce::PerRow{nullptr, nullptr, 0.f}, bool allow_h_copy = true) {
+                                flce::PerRow rows = flce::PerRow{nullptr, nullptr, 0.f}, bool allow_h_copy = true,
+                                flce::StatusOut so = flce::StatusOut{nullptr, nullptr}) {
   const bool partial = m_out || a_out || zt_out;
   if (!H || !W || !targets) return FLCE_ERR_BAD_ARG;
   if (partial ? (!m_out || !a_out || !zt_out) : ((!loss_out && !rows.loss_rows_out) || !lse_out))
@@ -668,13 +692,13 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
     if (p.fast)
       return flce::forward_t<flce::bf16_t, uint16_t, flce::FastLoop>(p, H, W, targets, ignore_index, mean, loss_out,
                                                                      lse_out, ws, st, slice, m_out, a_out, zt_out,
-                                                                     rows);
+                                                                     rows, so);
     return flce::forward_t<flce::bf16_t, uint16_t, flce::GenericLoop<flce::bf16_t>>(
-        p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows);
+        p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
   }
   return flce::forward_t<float, uint32_t, flce::GenericLoop<float>>(p, H, W, targets, ignore_index, mean, loss_out,
                                                                     lse_out, ws, st, slice, m_out, a_out, zt_out,
-                                                                    rows);
+                                                                    rows, so);
 }
 
 static flce_status backward_impl(const void* H, const void* W, const int64_t* targets, const float* lse, int64_t N,
@@ -736,16 +760,10 @@ flce_status flce_forward_static(const void* H, const void* W, const int64_t* tar
   if ((size_t)p.fwd_bytes > flce::STATIC_SCRATCH_BYTES) return FLCE_ERR_WORKSPACE;
   void* ws = nullptr;
   if (flce::static_scratch(&ws) != hipSuccess) return FLCE_ERR_HIP;
-  const flce_status st = forward_impl(H, W, targets, N, d, V, ignore_index, reduction, dt, loss_out, lse_out, ws,
-                                      flce::STATIC_SCRATCH_BYTES, hip_stream, flce::Slice{V, 0}, nullptr, nullptr,
-                                      nullptr, flce::PerRow{nullptr, nullptr, 0.f}, /*allow_h_copy=*/false);
-  if (st != FLCE_OK) return st;
-  if (status_out || n_valid_out) {
-    flce::export_header_kernel<<<1, 64, 0, static_cast<hipStream_t>(hip_stream)>>>(
-        static_cast<const flce::Header*>(ws), status_out, n_valid_out);
-    if (hipGetLastError() != hipSuccess) return FLCE_ERR_HIP;
-  }
-  return FLCE_OK;
+  return forward_impl(H, W, targets, N, d, V, ignore_index, reduction, dt, loss_out, lse_out, ws,
+                      flce::STATIC_SCRATCH_BYTES, hip_stream, flce::Slice{V, 0}, nullptr, nullptr, nullptr,
+                      flce::PerRow{nullptr, nullptr, 0.f}, /*allow_h_copy=*/false,
+                      flce::StatusOut{status_out, n_valid_out});
 }
 
 flce_status flce_forward_rows(const void* H, const void* W, const int64_t* targets, int64_t N, int64_t d, int64_t V,
@@ -801,11 +819,11 @@ flce_status flce_merge_partials(const float* m_parts, const float* a_parts, cons
   int* blk_cnt = reinterpret_cast<int*>(ws + flce::ALIGN + blk);
   int* blk_oor = reinterpret_cast<int*>(ws + flce::ALIGN + 2 * blk);
   flce::ProfScope ps(FLCE_PROF_FWD_EPILOGUE, st);
-  flce::merge_rows_kernel<<<n_rb, 256, 0, st>>>(m_parts, a_parts, zt_parts, n_parts, N, targets, (int)N, V_total,
-                                                ignore_index, lse_out, blk_loss, blk_cnt, blk_oor, nullptr, nullptr,
-                                                0.f);
-  flce::finalize_loss_kernel<<<1, 256, 0, st>>>(blk_loss, blk_cnt, blk_oor, n_rb, reduction == FLCE_REDUCE_MEAN, hdr,
-                                                loss_out);
+  // no tile kernel has run before this merge to zero the arrival count: the sum of several blocks is a launch of its own
+  const flce::LossOut o{blk_loss, blk_cnt, blk_oor, hdr, loss_out, reduction == FLCE_REDUCE_MEAN, nullptr, nullptr};
+  const int n_blk = flce::launch_merge(m_parts, a_parts, zt_parts, n_parts, N, targets, (int)N, V_total, ignore_index,
+                                       lse_out, o, /*fused=*/false, nullptr, nullptr, 0.f, st);
+  flce::finalize_loss_kernel<<<1, 256, 0, st>>>(o, n_blk);
   return hipGetLastError() == hipSuccess ? FLCE_OK : FLCE_ERR_HIP;
 }
 

@@ -3,8 +3,8 @@
 //   forward : fwd_tiles_kernel  (logit tiles on MFMA, online max / sum-exp and target
 //             gather per lane: Alg. 1 in tile form; one workgroup per row block x
 //             vocabulary window: Section 3.2.1)
-//             merge_rows_kernel + finalize_loss_kernel (the merging epilogue of
-//             Section 3.2.1, lse = m + ln a, per-row loss, fixed-order sums)
+//             merge_rows_kernel (the merging epilogue of Section 3.2.1, lse = m + ln a,
+//             per-row loss, fixed-order sums; finalize_loss_kernel for a merge on its own)
 //   backward: compact_targets_kernel + prep_rows_kernel (n_valid, range flag, and the
 //             rows that count packed together: ignored rows have a zero row of G; a second
 //             copy of them transposed (generic loop) or pre-tiled (tuned loop))
@@ -143,7 +143,7 @@ struct Header {
   int32_t pad0;
   int64_t n_valid;     // number of counted rows
   float loss_sum;      // un-normalised sum of per-row losses (forward only)
-  float pad1;
+  uint32_t arrived;    // blocks of the window merge that have handed in their sums (forward only)
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -220,8 +220,9 @@ template <typename T, typename L, bool HKR>
 __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
     const T* __restrict__ H, const T* __restrict__ HT, const T* __restrict__ W, const int64_t* __restrict__ y,
     int N, int d, int V, int64_t ignore_index, int64_t V_total, int64_t v_begin, int n_rb, int n_win, int n_vt,
-    float* __restrict__ part, int item_begin) {
+    float* __restrict__ part, int item_begin, Header* __restrict__ hdr) {
   extern __shared__ __align__(16) char lds[];
+  if (blockIdx.x == 0 && threadIdx.x == 0) hdr->arrived = 0;   // for the merge that follows on the stream
   // One workgroup per item (row block x window); a launch covers the items item_begin .. item_begin + gridDim.x - 1
   // of the raster (the host launches at most one round of workgroups at a time: all of them start together, and the
   // workgroups of an XCD stay close enough to each other to share the operands of their raster patch in its L2).
@@ -348,79 +349,159 @@ __device__ __forceinline__ float block_sum_256(float v, float* sh) {
   return r;
 }
 
-// One thread per row: merge the partials (m, a, z_target) of `n_parts` windows or vocabulary
-// slices in their order (part k of row n at pm[k * stride + n], likewise pa, pz).
-__device__ __forceinline__ void merge_parts_of_row(const float* __restrict__ pm, const float* __restrict__ pa,
-                                                   const float* __restrict__ pz, int n_parts, int64_t stride, int n,
-                                                   float& M, float& A, float& z) {
-  // The parts are taken eight at a time with all their loads issued before the first use (a part past the end
-  // re-reads the last one and is not used): the parts of one row lie in different memory rows, and a load per loop
-  // trip would make the merge wait for memory once per part.  The arithmetic and its order are those of the plain loop.
-  constexpr int U = 8;
-  M = NEG_INF;
-  for (int w0 = 0; w0 < n_parts; w0 += U) {
-    float mw[U], aw[U];
+// Sum over the 64 lanes of a wavefront in a fixed tree (every lane gets it).
+template <typename V>
+__device__ __forceinline__ V wave_sum(V v) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t o = (int64_t)min(w0 + u, n_parts - 1) * stride + n;
-      mw[u] = pm[o]; aw[u] = pa[o];
-    }
+  for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s, 64);
+  return v;
+}
+
+// The partials (m, a, z_target) of a row's `n_parts` windows or vocabulary slices, merged (part k of row n at
+// pm[k * stride + n], likewise pa, pz).  A block has ROWS rows x GROUPS threads; group g takes a contiguous run of the
+// parts, U of them at a time with all their loads in flight together (a part past the end re-reads the last one and is
+// not used), and the groups' results are merged through LDS in group order: every sum has a fixed order.
+// What bounds it is memory latency: the parts of one row lie in different memory rows, and where there are many parts
+// there are few rows (windows = max(4, 256 / row blocks)): a thread per row took 45 us for 77 rows of 197 windows and
+// 40 us for 500 rows of 128 windows, 16 threads per row with 16 loads each take 7.9 and 9.8 us (the loss included).
+// Returns with the row's (M, A, z) valid in the threads of group 0.
+template <int ROWS, int GROUPS, int U>
+__device__ __forceinline__ void merge_parts(const float* __restrict__ pm, const float* __restrict__ pa,
+                                            const float* __restrict__ pz, int n_parts, int64_t stride, int n, int N,
+                                            float& M, float& A, float& z) {
+  const int g = threadIdx.x / ROWS;
+  const int per = (n_parts + GROUPS - 1) / GROUPS;
+  const int w_end = min(n_parts, (g + 1) * per);
+  M = NEG_INF; A = 0.f; z = 0.f;
+  if (n < N) {
+    for (int w0 = g * per; w0 < w_end; w0 += U) {
+      float mw[U], aw[U], zw[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (w0 + u < n_parts && aw[u] > 0.f) M = fmaxf(M, mw[u]);
-  }
-  A = 0.f; z = 0.f;
-  for (int w0 = 0; w0 < n_parts; w0 += U) {
-    float mw[U], aw[U], zw[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t o = (int64_t)min(w0 + u, n_parts - 1) * stride + n;
-      mw[u] = pm[o]; aw[u] = pa[o]; zw[u] = pz[o];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (w0 + u < n_parts) {
-        if (aw[u] > 0.f) A += aw[u] * fast_exp2((mw[u] - M) * LOG2E);
-        z += zw[u];
+      for (int u = 0; u < U; ++u) {
+        const int64_t o = (int64_t)min(w0 + u, w_end - 1) * stride + n;
+        mw[u] = pm[o]; aw[u] = pa[o]; zw[u] = pz[o];
       }
+      float Mn = M;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (w0 + u < w_end && aw[u] > 0.f) Mn = fmaxf(Mn, mw[u]);
+      if (A > 0.f) A *= fast_exp2((M - Mn) * LOG2E);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (w0 + u < w_end) {
+          if (aw[u] > 0.f) A += aw[u] * fast_exp2((mw[u] - Mn) * LOG2E);
+          z += zw[u];
+        }
+      M = Mn;
+    }
+  }
+  if constexpr (GROUPS > 1) {
+    __shared__ float sm[GROUPS][ROWS], sa[GROUPS][ROWS], sz[GROUPS][ROWS];
+    const int t = threadIdx.x % ROWS;
+    sm[g][t] = M; sa[g][t] = A; sz[g][t] = z;
+    __syncthreads();
+    if (g == 0) {
+      float gm[GROUPS], ga[GROUPS];
+      z = 0.f;
+#pragma unroll
+      for (int k = 0; k < GROUPS; ++k) { gm[k] = sm[k][t]; ga[k] = sa[k][t]; z += sz[k][t]; }
+      merge_fixed<GROUPS>(gm, ga, M, A);
+    }
+  }
+}
+
+// Where the reduced loss of a call goes.
+struct LossOut {
+  float* blk_loss; int* blk_cnt; int* blk_oor;      // one entry per block of the merge
+  Header* hdr; float* loss; int mean;
+  int32_t* status; int64_t* n_valid;                // the caller's own words, or null
+};
+
+// The second half of the reduction, by one block: fixed-order fp64 sum of the per-block partials, normalisation, header.
+__device__ __forceinline__ void finalize_loss(const LossOut& o, int n_blk) {
+  __shared__ double sl[16];
+  __shared__ long long sc[16];
+  __shared__ int so[16];
+  double l = 0.0; long long c = 0; int bad = 0;
+  for (int b = threadIdx.x; b < n_blk; b += blockDim.x) {
+    // (written by other blocks of this launch when the merge calls this: read past this XCD's own caches)
+    l += (double)__hip_atomic_load(o.blk_loss + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    c += __hip_atomic_load(o.blk_cnt + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bad |= __hip_atomic_load(o.blk_oor + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  l = wave_sum(l); c = wave_sum(c); bad = __ballot(bad != 0) != 0ull;
+  const int wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+  if ((threadIdx.x & 63) == 0) { sl[wave] = l; sc[wave] = c; so[wave] = bad; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double total = 0.0; long long nv = 0; int any = 0;
+    for (int w = 0; w < n_waves; ++w) { total += sl[w]; nv += sc[w]; any |= so[w]; }
+    double loss = total;
+    if (o.mean) loss = nv > 0 ? total / (double)nv : 0.0;
+    o.hdr->status = any ? 4 : 0;
+    o.hdr->pad0 = 0;
+    o.hdr->n_valid = nv;
+    o.hdr->loss_sum = (float)total;
+    *o.loss = (float)loss;
+    if (o.status) *o.status = any ? 4 : 0;
+    if (o.n_valid) *o.n_valid = nv;
   }
 }
 
 // lse = M + ln A, loss_i = lse - z_target for counted rows (optionally label-smoothed and written out
-// per row); per-block sums in a fixed tree.
-__global__ __launch_bounds__(256) void merge_rows_kernel(
+// per row); per-block sums in a fixed tree, and the call's loss from them: by the block that hands its sums in last
+// (hdr->arrived, zeroed by the forward's tile kernel; whichever block that is, it adds all of them in block order), or,
+// when `fused` is 0, by finalize_loss_kernel.  One launch instead of three (the sum and the copy of the header to the
+// caller's words each took 4.7 us, nearly all of it the launch).
+template <int ROWS, int GROUPS, int U>
+__global__ __launch_bounds__(ROWS * GROUPS) void merge_rows_kernel(
     const float* __restrict__ pm, const float* __restrict__ pa, const float* __restrict__ pz, int n_parts,
     int64_t stride, const int64_t* __restrict__ y, int N, int64_t V_total, int64_t ignore_index,
-    float* __restrict__ lse_out, float* __restrict__ blk_loss, int* __restrict__ blk_cnt, int* __restrict__ blk_oor,
-    float* __restrict__ loss_rows_out, const float* __restrict__ zbar, float eps) {
-  __shared__ float sh[256];
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  float loss = 0.f, cnt = 0.f, bad = 0.f;
-  if (n < N) {
-    float M, A, z;
-    merge_parts_of_row(pm, pa, pz, n_parts, stride, n, M, A, z);
-    const float lse = M + logf(A);
-    lse_out[n] = lse;
-    bool oor;
-    if (target_counts(y[n], ignore_index, V_total, oor)) {
-      loss = lse - z;
-      // label smoothing: the target distribution keeps 1 - eps on y_i and spreads eps evenly, so
-      // the row's loss mixes in eps * (lse - mean_v Z_iv)
-      if (zbar) loss = (1.f - eps) * loss + eps * (lse - zbar[n]);
-      cnt = 1.f;
+    float* __restrict__ lse_out, LossOut o, int fused, float* __restrict__ loss_rows_out,
+    const float* __restrict__ zbar, float eps) {
+  constexpr int WAVES = ROWS / 64;     // of group 0
+  __shared__ float sl[WAVES];
+  __shared__ int sc[WAVES], so[WAVES], last;
+  const int n = blockIdx.x * ROWS + threadIdx.x % ROWS;
+  float M, A, z;
+  merge_parts<ROWS, GROUPS, U>(pm, pa, pz, n_parts, stride, n, N, M, A, z);
+  if (threadIdx.x < ROWS) {
+    float loss = 0.f;
+    bool counts = false, oor = false;
+    if (n < N) {
+      const float lse = M + logf(A);
+      lse_out[n] = lse;
+      counts = target_counts(y[n], ignore_index, V_total, oor);
+      if (counts) {
+        loss = lse - z;
+        // label smoothing: the target distribution keeps 1 - eps on y_i and spreads eps evenly, so
+        // the row's loss mixes in eps * (lse - mean_v Z_iv)
+        if (zbar) loss = (1.f - eps) * loss + eps * (lse - zbar[n]);
+      }
+      if (loss_rows_out) loss_rows_out[n] = loss;
     }
-    if (oor) bad = 1.f;
-    if (loss_rows_out) loss_rows_out[n] = loss;
+    loss = wave_sum(loss);
+    const int cnt = __popcll(__ballot(counts)), bad = __ballot(oor) != 0ull;
+    if ((threadIdx.x & 63) == 0) { const int w = threadIdx.x >> 6; sl[w] = loss; sc[w] = cnt; so[w] = bad; }
   }
-  const float bl = block_sum_256(loss, sh);
-  const float bc = block_sum_256(cnt, sh);     // <= 256: exact in fp32
-  const float bb = block_sum_256(bad, sh);
+  __syncthreads();
   if (threadIdx.x == 0) {
-    blk_loss[blockIdx.x] = bl;
-    blk_cnt[blockIdx.x] = (int)bc;
-    blk_oor[blockIdx.x] = bb > 0.f ? 1 : 0;
+    float l = 0.f;
+    int c = 0, bad = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { l += sl[w]; c += sc[w]; bad |= so[w]; }
+    o.blk_loss[blockIdx.x] = l;
+    o.blk_cnt[blockIdx.x] = c;
+    o.blk_oor[blockIdx.x] = bad;
+    last = 0;
+    if (fused)
+      last = __hip_atomic_fetch_add(&o.hdr->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
   }
+  __syncthreads();
+  if (last) finalize_loss(o, gridDim.x);
 }
+
+__global__ __launch_bounds__(256) void finalize_loss_kernel(LossOut o, int n_blk) { finalize_loss(o, n_blk); }
 
 // mean_v Z_iv = H_i . (sum_v W_v) / V, for label smoothing: the column sums of W in two fixed-order
 // steps (1024-row chunks, then the chunks in order), then one dot product per row.
@@ -467,48 +548,17 @@ __global__ __launch_bounds__(256) void mean_logit_kernel(const T* __restrict__ H
 
 // The window merge of a call that covers one vocabulary slice: the slice's (m, a, z_target) per row,
 // to be merged with the other slices' later (Section 3.2, "Model Parallelism": tensor parallelism).
-__global__ __launch_bounds__(256) void merge_rows_partial_kernel(const float* __restrict__ part, int n_win,
-                                                                 int64_t npad, int N, float* __restrict__ m_out,
-                                                                 float* __restrict__ a_out,
-                                                                 float* __restrict__ zt_out) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
+template <int ROWS, int GROUPS, int U>
+__global__ __launch_bounds__(ROWS * GROUPS) void merge_rows_partial_kernel(const float* __restrict__ part, int n_win,
+                                                                          int64_t npad, int N,
+                                                                          float* __restrict__ m_out,
+                                                                          float* __restrict__ a_out,
+                                                                          float* __restrict__ zt_out) {
+  const int n = blockIdx.x * ROWS + threadIdx.x % ROWS;
   float M, A, z;
-  merge_parts_of_row(part, part + (int64_t)n_win * npad, part + 2 * (int64_t)n_win * npad, n_win, npad, n, M, A, z);
-  m_out[n] = M; a_out[n] = A; zt_out[n] = z;
-}
-
-// One block: fixed-order fp64 sum of the per-block partials, normalisation, header.
-__global__ __launch_bounds__(256) void finalize_loss_kernel(
-    const float* __restrict__ blk_loss, const int* __restrict__ blk_cnt, const int* __restrict__ blk_oor, int n_blk,
-    int mean, Header* __restrict__ hdr, float* __restrict__ loss_out) {
-  __shared__ double sl[256];
-  __shared__ long long sc[256];
-  __shared__ int so[256];
-  double l = 0.0; long long c = 0; int o = 0;
-  for (int b = threadIdx.x; b < n_blk; b += 256) { l += (double)blk_loss[b]; c += blk_cnt[b]; o |= blk_oor[b]; }
-  sl[threadIdx.x] = l; sc[threadIdx.x] = c; so[threadIdx.x] = o;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      sl[threadIdx.x] += sl[threadIdx.x + s];
-      sc[threadIdx.x] += sc[threadIdx.x + s];
-      so[threadIdx.x] |= so[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double total = sl[0];
-    const long long nv = sc[0];
-    double loss = total;
-    if (mean) loss = nv > 0 ? total / (double)nv : 0.0;
-    hdr->status = so[0] ? 4 : 0;
-    hdr->pad0 = 0;
-    hdr->n_valid = nv;
-    hdr->loss_sum = (float)total;
-    hdr->pad1 = 0.f;
-    *loss_out = (float)loss;
-  }
+  merge_parts<ROWS, GROUPS, U>(part, part + (int64_t)n_win * npad, part + 2 * (int64_t)n_win * npad, n_win, npad, n, N,
+                               M, A, z);
+  if (threadIdx.x < ROWS && n < N) { m_out[n] = M; a_out[n] = A; zt_out[n] = z; }
 }
 
 // Backward's integer pass over the targets (exact): n_valid, the range flag, and the
@@ -557,7 +607,7 @@ __global__ __launch_bounds__(1024) void compact_targets_kernel(const int64_t* __
     hdr->pad0 = 0;
     hdr->n_valid = total;
     hdr->loss_sum = 0.f;
-    hdr->pad1 = 0.f;
+    hdr->arrived = 0;
   }
 }
 
