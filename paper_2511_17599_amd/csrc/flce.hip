@@ -401,10 +401,11 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
         float* wsum = reinterpret_cast<float*>(ws + p.off_wsum);
         float* zb = reinterpret_cast<float*>(ws + p.off_zbar);
         const int n_chunks = (int)ceil_div(p.V, 1024);
-        colsum_chunks_kernel<T><<<n_chunks, 256, 0, st>>>(static_cast<const T*>(W), (int)p.V, (int)p.d, wpart);
-        colsum_finish_kernel<<<(unsigned)ceil_div(p.d, 256), 256, 0, st>>>(wpart, n_chunks, (int)p.d, wsum);
-        mean_logit_kernel<T><<<(unsigned)p.N, 256, 0, st>>>(static_cast<const T*>(H), wsum, (int)p.d,
-                                                            1.0f / (float)p.V, zb);
+        colsum_chunks_kernel<T><<<dim3((unsigned)n_chunks, (unsigned)ceil_div(p.d, 16 * Vec16<T>::N)), 256, 0, st>>>(
+            static_cast<const T*>(W), (int)p.V, (int)p.d, wpart);
+        colsum_finish_kernel<<<(unsigned)ceil_div(p.d, 64), 64, 0, st>>>(wpart, n_chunks, (int)p.d, wsum);
+        mean_logit_kernel<T><<<(unsigned)ceil_div(p.N, 4), 256, 0, st>>>(static_cast<const T*>(H), wsum, (int)p.N, (int)p.d,
+                                                                         1.0f / (float)p.V, zb);
         zbar = zb;
       }
       // the per-row call has no scalar loss to hand out: the sum goes to a spare word of the header block
