@@ -24,6 +24,10 @@ namespace {
 
 constexpr int64_t ALIGN = 256;
 constexpr int NUM_CU = 256;   // MI355X; the plan must not depend on a device query
+// Most K slices of a contraction launch.  One output tile (256 rows, d <= 256) over a long vocabulary is where many help:
+// 256 rows, d = 128, V = 82194 has 321 K tiles; with 8 slices (8 busy CUs)
+// the whole step took 318 us, with 64 it takes 134 (200 x 1024 x 50257: 317 and 210).
+constexpr int MAX_SPLIT = 64;
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -191,16 +195,15 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   // extent is cut into slices whose fp32 tiles are summed in slice order by a second kernel.
   const int64_t n_mt = ceil_div(d, TILE);
   auto auto_split = [&](int64_t tiles, int64_t k_tiles) -> int {
-    // How full the rounds of workgroups are, discounted for the partial-sum traffic of each extra
-    // slice (about 30 % of a tile's time when K is 16 tiles, less in proportion for longer K); a
-    // split has to win by 5 %.
+    // Time of the launch in units of one 256-element K tile of the main loop (6.2 us in bf16): rounds of workgroups
+    // times (K tiles of a slice + 1.2 for filling the pipeline and writing the tile out), plus, for a split, 0.8 for the
+    // launch that adds the slices and 0.02 per fp32 tile written and read back; a split has to win by 5 %.
     int best = 1;
-    double best_score = 0.0;
-    for (int sp = 1; sp <= 8 && (sp == 1 || k_tiles / sp >= 2); ++sp) {
-      const int64_t wg = tiles * sp;
-      const double fill = (double)wg / (double)(ceil_div(wg, NUM_CU) * NUM_CU);
-      const double score = fill / (1.0 + (4.8 / (double)k_tiles) * (sp - 1));
-      if (score > best_score * (sp == 1 ? 1.0 : 1.05)) { best_score = score; best = sp; }
+    double best_cost = 0.0;
+    for (int sp = 1; sp <= MAX_SPLIT && sp <= k_tiles; ++sp) {
+      const double cost = (double)ceil_div(tiles * sp, NUM_CU) * ((double)ceil_div(k_tiles, sp) + 1.2) +
+                          (sp > 1 ? 0.8 + 0.02 * (double)(tiles * sp) : 0.0);
+      if (sp == 1 || cost < best_cost * (best == 1 ? 0.95 : 1.0)) { best_cost = cost; best = sp; }
     }
     return best;
   };
@@ -531,7 +534,8 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
       } else {
         contract_kernel<T, L, OPS_KC><<<x.n_nt * x.n_mt * x.n_split, L::THREADS, L::LDS, st>>>(x);
       }
-      if (x.n_split > 1) splitk_reduce_kernel<T><<<x.n_nt * TILE, 256, 0, st>>>(x);
+      if (x.n_split > 1)
+        splitk_reduce_kernel<T><<<(unsigned)ceil_div((int64_t)x.n_nt * TILE * (d / 4), 256), 256, 0, st>>>(x);
     };
     TailSplit ts{0, 1};
     if constexpr (L::TRANSPOSING) ts = tail_split(a.n_nt, a.n_mt, a.n_split, a.k_elems / TILE);

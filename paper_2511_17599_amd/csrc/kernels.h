@@ -1216,13 +1216,16 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
   }
 }
 
-// Second half of a split-K contraction: one block per output row of the launch; adds the K
+// Second half of a split-K contraction: one thread per four output elements; adds the K
 // slices in slice order (fixed), then the running sum / Gamma / rounding exactly as the
-// unsplit epilogue would.
+// unsplit epilogue would.  Memory bound; the loads of eight slices are in flight together.
 template <typename T>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(ContractArgs<T> a) {
-  const int n = a.out_row0 + blockIdx.x;
-  if (n >= a.out_rows) return;
+  const int d4 = a.d / 4;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int row = (int)(i / d4), m = (int)(i - (int64_t)row * d4) * 4;
+  const int n = a.out_row0 + row;
+  if (row >= a.n_nt * TILE || n >= a.out_rows) return;
   const int nv = (int)a.hdr->n_valid;
   int64_t orow = n;
   if (a.flags & ROWS_COMPACT) {
@@ -1232,18 +1235,24 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(ContractArgs<T> a) {
   }
   float scale = a.grad_loss;
   if (a.mean) scale = nv > 0 ? a.grad_loss / (float)nv : 0.f;
-  const int d = a.d;
-  for (int m = threadIdx.x * 4; m < d; m += 256 * 4) {
-    const int64_t off = (int64_t)(n - a.acc_row0) * d + m;
-    f32x4 v = *reinterpret_cast<const f32x4*>(a.partial + off);
-    for (int z = 1; z < a.n_split; ++z) v += *reinterpret_cast<const f32x4*>(a.partial + z * a.partial_stride + off);
-    float* ap = a.accbuf + off;
-    if (a.flags & READ_ACC) v += *reinterpret_cast<const f32x4*>(ap);
-    if (a.flags & WRITE_ACC) *reinterpret_cast<f32x4*>(ap) = v;
-    if (a.flags & WRITE_OUT)
-      Pack4<T>::store(a.out + orow * d + m, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f,
-                      v[3] * scale + 0.f);
+  const int64_t off = (int64_t)(n - a.acc_row0) * a.d + m;
+  f32x4 v = *reinterpret_cast<const f32x4*>(a.partial + off);
+  constexpr int U = 8;
+  for (int z0 = 1; z0 < a.n_split; z0 += U) {
+    f32x4 t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      t[u] = *reinterpret_cast<const f32x4*>(a.partial + (int64_t)min(z0 + u, a.n_split - 1) * a.partial_stride + off);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (z0 + u < a.n_split) v += t[u];
   }
+  float* ap = a.accbuf + off;
+  if (a.flags & READ_ACC) v += *reinterpret_cast<const f32x4*>(ap);
+  if (a.flags & WRITE_ACC) *reinterpret_cast<f32x4*>(ap) = v;
+  if (a.flags & WRITE_OUT)
+    Pack4<T>::store(a.out + orow * a.d + m, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f,
+                    v[3] * scale + 0.f);
 }
 
 // Alg. 4, scalar branch: out = Gamma * in, elementwise, Gamma from the header's n_valid.
