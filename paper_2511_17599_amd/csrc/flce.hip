@@ -72,6 +72,7 @@ struct Plan {
   int64_t N, d, V;
   int esize;
   int n_rb, n_vt;          // 256-row tiles of tokens / vocabulary
+  int tile;                // output tile edge of the main loop (fp32: 128 or 64)
   int64_t npad;
   // forward
   int n_win;
@@ -127,6 +128,11 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.esize = dt == FLCE_DTYPE_BF16 ? 2 : 4;
   p.n_rb = (int)ceil_div(N, TILE);
   p.n_vt = (int)ceil_div(V, TILE);
+  p.tile = TILE;
+  // fp32: 64-row tiles while there are too few 128-row ones to give every CU more than one (whole steps: 256 x 256 x 4096,
+  // 64 tiles of 128: 77 us with 64-row tiles against 118; 1024 x 512 x 4096, 256 tiles: 211 / 220; 1000 x 256 x 6400, 400
+  // tiles: 190 / 185; 2048 x 256 x 16000, 2000 tiles: 715 / 586).
+  if (dt == FLCE_DTYPE_F32) p.tile = ceil_div(N, 128) * ceil_div(V, 128) < 320 ? 64 : 128;
   p.npad = (int64_t)p.n_rb * TILE;
 
   // Windows (Section 3.2.1): enough (row block, window) workgroups to cover the CUs.
@@ -184,35 +190,39 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.off_lsec = o;   o = align_up(o + p.npad * 4, ALIGN);
   p.off_gamc = o;   o = align_up(o + p.npad * 4, ALIGN);
   p.off_G = o;      o = align_up(o + nc_pad * p.ld_v * p.esize, ALIGN);
-  // K-contiguous copies, only for main loops that cannot read an operand across memory rows
-  p.off_HT = o;     if (!p.fast) o = align_up(o + d * p.npad * p.esize, ALIGN);
+  // K-contiguous copies, only for the main loop that cannot read an operand across memory rows
+  const bool copies = dt == FLCE_DTYPE_BF16 && !p.fast;
+  p.off_HT = o;     if (copies) o = align_up(o + d * p.npad * p.esize, ALIGN);
                     else if (p.hkr) o = align_up(o + packed_block_offset(p.n_rb, (int)d), ALIGN);
-  p.off_WT = o;     if (!p.fast) o = align_up(o + d * p.ld_v * p.esize, ALIGN);
-  p.off_GT = o;     if (!p.fast) o = align_up(o + vc_pad * p.ld_n * p.esize, ALIGN);
+  p.off_WT = o;     if (copies) o = align_up(o + d * p.ld_v * p.esize, ALIGN);
+  p.off_GT = o;     if (copies) o = align_up(o + vc_pad * p.ld_n * p.esize, ALIGN);
   p.off_dHacc = o;  if (p.n_vch > 1) o = align_up(o + N * d * 4, ALIGN);
   p.off_dWacc = o;  if (p.n_nch > 1) o = align_up(o + vc_pad * d * 4, ALIGN);
   // Split-K for launches with too few output tiles to occupy the CUs (small N or small d): the K
   // extent is cut into slices whose fp32 tiles are summed in slice order by a second kernel.
-  const int64_t n_mt = ceil_div(d, TILE);
+  const int64_t n_mt = ceil_div(d, p.tile), unit = TILE / p.tile;
   auto auto_split = [&](int64_t tiles, int64_t k_tiles) -> int {
-    // Time of the launch in units of one 256-element K tile of the main loop (6.2 us in bf16): rounds of workgroups
-    // times (K tiles of a slice + 1.2 for filling the pipeline and writing the tile out), plus, for a split, 0.8 for the
-    // launch that adds the slices and 0.02 per fp32 tile written and read back; a split has to win by 5 %.
+    // Time of the launch in units of one K tile of the main loop (K elements = tile edge): rounds of workgroups times
+    // (K tiles of a slice + `ends` for filling the pipeline and writing the tile out), plus, for a split, the launch that
+    // adds the slices and the fp32 tiles written and read back; a split has to win by 5 %.  A K tile takes 6.2 us in
+    // bf16, and at fp32 (two workgroups share a CU) 6.8 us per CU with 128-tiles, 0.85 with 64-tiles.
+    const double ends = p.tile == 64 ? 3.5 : 1.2, launch = p.tile == 64 ? 6.0 : 0.8,
+                 per_tile = p.tile == TILE ? 0.02 : p.tile == 128 ? 0.005 : 0.01;
     int best = 1;
     double best_cost = 0.0;
     for (int sp = 1; sp <= MAX_SPLIT && sp <= k_tiles; ++sp) {
-      const double cost = (double)ceil_div(tiles * sp, NUM_CU) * ((double)ceil_div(k_tiles, sp) + 1.2) +
-                          (sp > 1 ? 0.8 + 0.02 * (double)(tiles * sp) : 0.0);
+      const double cost = (double)ceil_div(tiles * sp, NUM_CU) * ((double)ceil_div(k_tiles, sp) + ends) +
+                          (sp > 1 ? launch + per_tile * (double)(tiles * sp) : 0.0);
       if (sp == 1 || cost < best_cost * (best == 1 ? 0.95 : 1.0)) { best_cost = cost; best = sp; }
     }
     return best;
   };
   p.split_dh = tn.splitk_dh;
   p.split_dw = tn.splitk_dw;
-  if (p.split_dh == 0) p.split_dh = auto_split(p.nc_tiles * n_mt, p.vc_tiles);
-  if (p.split_dw == 0) p.split_dw = auto_split(p.vc_tiles * n_mt, p.nc_tiles);
-  p.split_dh = (int)std::min<int64_t>(p.split_dh, p.vc_tiles);
-  p.split_dw = (int)std::min<int64_t>(p.split_dw, p.nc_tiles);
+  if (p.split_dh == 0) p.split_dh = auto_split(p.nc_tiles * unit * n_mt, p.vc_tiles * unit);
+  if (p.split_dw == 0) p.split_dw = auto_split(p.vc_tiles * unit * n_mt, p.nc_tiles * unit);
+  p.split_dh = (int)std::min<int64_t>(p.split_dh, p.vc_tiles * unit);
+  p.split_dw = (int)std::min<int64_t>(p.split_dw, p.nc_tiles * unit);
   p.off_partial = o;
   {
     int64_t bytes = 0;
@@ -278,16 +288,21 @@ template <typename T, typename L>
 hipError_t set_lds_allowances() {
   hipError_t e;
   if ((e = allow_big_lds(fwd_tiles_kernel<T, L, false>, L::LDS)) != hipSuccess) return e;
-  if ((e = allow_big_lds(recompute_kernel<T, L, false>, L::LDS)) != hipSuccess) return e;
-  if ((e = allow_big_lds(recompute_kernel<T, L, false, true>, L::LDS)) != hipSuccess) return e;
-  if constexpr (L::TRANSPOSING) {
+  if constexpr (L::TUNED) {
     if ((e = allow_big_lds(fwd_tiles_kernel<T, L, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, true, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(contract_kernel<T, L, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(contract_kernel<T, L, OPS_DW_TR>, L::LDS)) != hipSuccess) return e;
   } else {
-    if ((e = allow_big_lds(contract_kernel<T, L, OPS_KC>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(recompute_kernel<T, L, false>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(recompute_kernel<T, L, false, true>, L::LDS)) != hipSuccess) return e;
+    if constexpr (L::TRANSPOSING) {
+      if ((e = allow_big_lds(contract_kernel<T, L, OPS_DH_F32>, L::LDS)) != hipSuccess) return e;
+      if ((e = allow_big_lds(contract_kernel<T, L, OPS_DW_F32>, L::LDS)) != hipSuccess) return e;
+    } else {
+      if ((e = allow_big_lds(contract_kernel<T, L, OPS_KC>, L::LDS)) != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }
@@ -358,13 +373,14 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
   // (256 items, whole raster groups of 8 row blocks when the window count divides 32): a larger grid's later rounds
   // drift apart over the ~100 tiles of an item and stop sharing their operands in the L2 (measured at 512 row blocks:
   // 361 GB of fabric traffic per forward against 192 GB that the raster should need).
-  const int items = p.n_rb * p.n_win;
-  const int per_launch = L::TRANSPOSING ? NUM_CU : items;
+  const int n_rb = (int)ceil_div(p.N, L::TILE), n_vt = (int)ceil_div(p.V, L::TILE);
+  const int items = n_rb * p.n_win;
+  const int per_launch = L::TUNED ? NUM_CU : items;
   bool hkr = false;
-  if constexpr (L::TRANSPOSING) hkr = p.hkr;
+  if constexpr (L::TUNED) hkr = p.hkr;
   T* HT = nullptr;
   if (hkr) {
-    if constexpr (L::TRANSPOSING) {
+    if constexpr (L::TUNED) {
       HT = reinterpret_cast<T*>(ws + p.off_fHT);
       // the pre-tiled copy of H, zero padded to whole row blocks: the forward's second operand
       ProfScope ps(FLCE_PROF_FWD_EPILOGUE, st);
@@ -377,14 +393,14 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
     for (int item0 = 0; item0 < items; item0 += per_launch) {
       const int grid = std::min(per_launch, items - item0);
       if (hkr) {
-        if constexpr (L::TRANSPOSING)
+        if constexpr (L::TUNED)
           fwd_tiles_kernel<T, L, true><<<grid, L::THREADS, L::LDS, st>>>(
               static_cast<const T*>(H), HT, static_cast<const T*>(W), y, (int)p.N, (int)p.d, (int)p.V, ignore_index,
-              slice.V_total, slice.v_begin, p.n_rb, p.n_win, p.n_vt, part, item0, hdr);
+              slice.V_total, slice.v_begin, n_rb, p.n_win, n_vt, part, p.npad, item0, hdr);
       } else {
         fwd_tiles_kernel<T, L, false><<<grid, L::THREADS, L::LDS, st>>>(
             static_cast<const T*>(H), nullptr, static_cast<const T*>(W), y, (int)p.N, (int)p.d, (int)p.V, ignore_index,
-            slice.V_total, slice.v_begin, p.n_rb, p.n_win, p.n_vt, part, item0, hdr);
+            slice.V_total, slice.v_begin, n_rb, p.n_win, n_vt, part, p.npad, item0, hdr);
       }
     }
   }
@@ -426,7 +442,7 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
                        int64_t ignore_index, int mean, float grad_loss, void* dH, void* dW, char* ws,
                        hipStream_t st, Slice slice, PerRow rows = PerRow{nullptr, nullptr, 0.f}) {
   if (prepare_kernels<T, L>() != hipSuccess) return FLCE_ERR_HIP;
-  if (L::TRANSPOSING && !p.hkr) return FLCE_ERR_UNSUPPORTED;   // (no caller plans a backward without the copies of H)
+  if (L::TUNED && !p.hkr) return FLCE_ERR_UNSUPPORTED;   // (no caller plans a backward without the copies of H)
   const int N = (int)p.N, d = (int)p.d, V = (int)p.V;
   Header* hdr = reinterpret_cast<Header*>(ws);
   T* Hc = reinterpret_cast<T*>(ws + p.off_Hc);
@@ -441,7 +457,10 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
   float* dHacc = reinterpret_cast<float*>(ws + p.off_dHacc);
   float* dWacc = reinterpret_cast<float*>(ws + p.off_dWacc);
   const int64_t vc_pad = (int64_t)p.vc_tiles * TILE, nc_pad = (int64_t)p.nc_tiles * TILE;
-  const int n_mt = (int)ceil_div(d, TILE);
+  const int n_mt = (int)ceil_div(d, L::TILE);
+  // the plan counts 256-row tiles; this loop's tiles may be a half or a quarter of that
+  constexpr int UNIT = TILE / L::TILE;
+  const int all_vt = (int)ceil_div(p.V, L::TILE), all_nt = (int)ceil_div(p.N, L::TILE);
   const int npad = (int)p.npad;
 
   {
@@ -451,13 +470,14 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     // lse and Gamma per compact row, zero rows of dH, and the counted rows of H packed together, twice: with the
     // generic loop as they are (Hc) and transposed [d][npad] (the dW contraction's K-contiguous operand); with the
     // tuned loop pre-tiled for the recompute (in HT's place) and pre-tiled the other way round for dW (in Hc's place)
-    if constexpr (L::TRANSPOSING)
+    if constexpr (L::TUNED)
       prep_rows_tiled_kernel<<<dim3((unsigned)(p.npad / 32), (unsigned)n_mt), 256, 0, st>>>(
           static_cast<const char*>(H), d, rowmap, npad, reinterpret_cast<char*>(HT), reinterpret_cast<char*>(Hc), lse,
           lse_c, rows.grad_rows, gam_c, y, N, slice.V_total, ignore_index, static_cast<char*>(dH));
     else
       prep_rows_kernel<U><<<dim3((unsigned)(p.npad / 64), (unsigned)ceil_div(d, 64)), 256, 0, st>>>(
-          static_cast<const U*>(H), d, rowmap, reinterpret_cast<U*>(Hc), reinterpret_cast<U*>(HT), p.npad, lse, lse_c,
+          static_cast<const U*>(H), d, rowmap, reinterpret_cast<U*>(Hc),
+          L::TRANSPOSING ? nullptr : reinterpret_cast<U*>(HT), p.npad, lse, lse_c,
           rows.grad_rows, gam_c, y, N, slice.V_total, ignore_index, static_cast<U*>(dH));
   }
 
@@ -466,23 +486,23 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
   // size the plan reserves (16 rows of ld_v = vc_pad + 64 elements are one block more per group).
   const int64_t g_group_bytes = (vc_pad / 32 + 1) * 1024;
   float* partial = reinterpret_cast<float*>(ws + p.off_partial);
-  // K elements per split-K slice: whole 256-element tiles
-  auto slice_len = [](int k_elems, int n_split) { return (int)ceil_div(ceil_div(k_elems, TILE), n_split) * TILE; };
+  // K elements per split-K slice: whole tiles
+  auto slice_len = [](int k_elems, int n_split) { return (int)ceil_div(ceil_div(k_elems, L::TILE), n_split) * L::TILE; };
   // argument blocks of the three steps of chunk (vc, nc); `Gb` is the staging buffer of that chunk
   auto chunk_vt = [&](int vc, int& vt0, int& n_vt) {
-    vt0 = vc * p.vc_tiles;
-    n_vt = std::min(p.vc_tiles, p.n_vt - vt0);
+    vt0 = vc * p.vc_tiles * UNIT;
+    n_vt = std::min(p.vc_tiles * UNIT, all_vt - vt0);
   };
   auto chunk_nt = [&](int nc, int& nt0, int& n_nt) {
-    nt0 = nc * p.nc_tiles;
-    n_nt = std::min(p.nc_tiles, p.n_rb - nt0);
+    nt0 = nc * p.nc_tiles * UNIT;
+    n_nt = std::min(p.nc_tiles * UNIT, all_nt - nt0);
   };
   auto recompute_args = [&](int vc, int nc, T* Gb) {
     int vt0, n_vt, nt0, n_nt;
     chunk_vt(vc, vt0, n_vt);
     chunk_nt(nc, nt0, n_nt);
     return RecomputeArgs<T>{Hc, HT, static_cast<const T*>(W), tgt_c, lse_c, hdr, npad, d, V, nt0, n_nt, vt0, n_vt,
-                            Gb, L::TRANSPOSING ? g_group_bytes : p.ld_v, GT, p.ld_n, gam_c, 1.f - rows.eps,
+                            Gb, L::TUNED ? g_group_bytes : p.ld_v, GT, p.ld_n, gam_c, 1.f - rows.eps,
                             rows.eps / (float)slice.V_total};
   };
   // dW[vocab chunk] += G^T . Hc[row chunk]   (contraction over the compact rows of the chunk)
@@ -493,15 +513,20 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     int flags = K_COMPACT;
     if (nc > 0) flags |= READ_ACC;
     flags |= (nc + 1 < p.n_nch) ? WRITE_ACC : WRITE_OUT;
-    if constexpr (L::TRANSPOSING)
-      return ContractArgs<T>{Hc, npad, 0, d, Gb, g_group_bytes, n_nt * TILE,
-                             n_nt * TILE, nt0 * TILE, n_mt, n_vt, dWacc, vt0 * TILE, static_cast<T*>(dW), vt0 * TILE,
+    if constexpr (L::TRANSPOSING && !L::TUNED)
+      return ContractArgs<T>{Hc + (int64_t)nt0 * L::TILE * d, d, n_nt * L::TILE, d, Gb, p.ld_v, 0, n_nt * L::TILE,
+                             nt0 * L::TILE, n_mt, n_vt, dWacc, vt0 * L::TILE, static_cast<T*>(dW), vt0 * L::TILE, V, flags,
+                             hdr, rowmap, grad_loss, mean, p.split_dw, slice_len(n_nt * L::TILE, p.split_dw),
+                             partial, vc_pad * d};
+    else if constexpr (L::TUNED)
+      return ContractArgs<T>{Hc, npad, 0, d, Gb, g_group_bytes, n_nt * L::TILE,
+                             n_nt * L::TILE, nt0 * L::TILE, n_mt, n_vt, dWacc, vt0 * L::TILE, static_cast<T*>(dW), vt0 * L::TILE,
                              V, flags, hdr, rowmap, grad_loss, mean, p.split_dw,
-                             slice_len(n_nt * TILE, p.split_dw), partial, vc_pad * d};
+                             slice_len(n_nt * L::TILE, p.split_dw), partial, vc_pad * d};
     else
-      return ContractArgs<T>{HT + (int64_t)nt0 * TILE, p.npad, 0, d, GT, p.ld_n, n_vt * TILE, n_nt * TILE,
-                             nt0 * TILE, n_mt, n_vt, dWacc, vt0 * TILE, static_cast<T*>(dW), vt0 * TILE, V, flags,
-                             hdr, rowmap, grad_loss, mean, p.split_dw, slice_len(n_nt * TILE, p.split_dw), partial,
+      return ContractArgs<T>{HT + (int64_t)nt0 * L::TILE, p.npad, 0, d, GT, p.ld_n, n_vt * L::TILE, n_nt * L::TILE,
+                             nt0 * L::TILE, n_mt, n_vt, dWacc, vt0 * L::TILE, static_cast<T*>(dW), vt0 * L::TILE, V, flags,
+                             hdr, rowmap, grad_loss, mean, p.split_dw, slice_len(n_nt * L::TILE, p.split_dw), partial,
                              vc_pad * d};
   };
   // dH[row chunk] += G . W[vocab chunk]      (contraction over the vocabulary chunk)
@@ -512,37 +537,46 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     int flags = ROWS_COMPACT;
     if (vc > 0) flags |= READ_ACC;
     flags |= (vc + 1 < p.n_vch) ? WRITE_ACC : WRITE_OUT;
-    if constexpr (L::TRANSPOSING)
-      return ContractArgs<T>{static_cast<const T*>(W) + (int64_t)vt0 * TILE * d, d, V - vt0 * TILE, d, Gb, g_group_bytes,
-                             n_nt * TILE, n_vt * TILE, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * TILE, npad,
-                             flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(n_vt * TILE, p.split_dh),
-                             partial - (int64_t)nt0 * TILE * d, nc_pad * d};
+    if constexpr (L::TRANSPOSING && !L::TUNED)
+      return ContractArgs<T>{static_cast<const T*>(W) + (int64_t)vt0 * L::TILE * d, d, V - vt0 * L::TILE, d, Gb, p.ld_v,
+                             n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE,
+                             npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(n_vt * L::TILE, p.split_dh),
+                             partial - (int64_t)nt0 * L::TILE * d, nc_pad * d};
+    else if constexpr (L::TUNED)
+      return ContractArgs<T>{static_cast<const T*>(W) + (int64_t)vt0 * L::TILE * d, d, V - vt0 * L::TILE, d, Gb, g_group_bytes,
+                             n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE, npad,
+                             flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(n_vt * L::TILE, p.split_dh),
+                             partial - (int64_t)nt0 * L::TILE * d, nc_pad * d};
     else
-      return ContractArgs<T>{WT, p.ld_v, 0, d, Gb, p.ld_v, n_nt * TILE, n_vt * TILE, 0, n_mt, n_nt, dHacc, 0,
-                             static_cast<T*>(dH), nt0 * TILE, npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh,
-                             slice_len(n_vt * TILE, p.split_dh), partial - (int64_t)nt0 * TILE * d, nc_pad * d};
+      return ContractArgs<T>{WT, p.ld_v, 0, d, Gb, p.ld_v, n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0,
+                             static_cast<T*>(dH), nt0 * L::TILE, npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh,
+                             slice_len(n_vt * L::TILE, p.split_dh), partial - (int64_t)nt0 * L::TILE * d, nc_pad * d};
   };
 
   // One contraction (dW or dH) of a chunk: the launch, its split-K sum if it has one, and with the tuned loop a
   // separately launched, K-split tail when the last round of workgroups would be mostly empty (tail_split).
   auto contract = [&](const ContractArgs<T>& a, bool is_dw) {
     auto launch = [&](const ContractArgs<T>& x) {
-      if constexpr (L::TRANSPOSING) {
+      if constexpr (L::TUNED) {
         const int grid = std::min(x.n_nt * x.n_mt * x.n_split, NUM_CU);
         if (is_dw) contract_kernel<T, L, OPS_DW_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
         else contract_kernel<T, L, OPS_DH_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
+      } else if constexpr (L::TRANSPOSING) {
+        const int grid = x.n_nt * x.n_mt * x.n_split;
+        if (is_dw) contract_kernel<T, L, OPS_DW_F32><<<grid, L::THREADS, L::LDS, st>>>(x);
+        else contract_kernel<T, L, OPS_DH_F32><<<grid, L::THREADS, L::LDS, st>>>(x);
       } else {
         contract_kernel<T, L, OPS_KC><<<x.n_nt * x.n_mt * x.n_split, L::THREADS, L::LDS, st>>>(x);
       }
       if (x.n_split > 1)
-        splitk_reduce_kernel<T><<<(unsigned)ceil_div((int64_t)x.n_nt * TILE * (d / 4), 256), 256, 0, st>>>(x);
+        splitk_reduce_kernel<T><<<(unsigned)ceil_div((int64_t)x.n_nt * L::TILE * (d / 4), 256), 256, 0, st>>>(x, x.n_nt * L::TILE);
     };
     TailSplit ts{0, 1};
-    if constexpr (L::TRANSPOSING) ts = tail_split(a.n_nt, a.n_mt, a.n_split, a.k_elems / TILE);
+    if constexpr (L::TUNED) ts = tail_split(a.n_nt, a.n_mt, a.n_split, a.k_elems / L::TILE);
     if (!ts.rows) { launch(a); return; }
     ContractArgs<T> body = a, tail = a;
     body.n_nt = a.n_nt - ts.rows;
-    const int64_t first = (int64_t)body.n_nt * TILE;     // the tail's first output row, relative to the launch's
+    const int64_t first = (int64_t)body.n_nt * L::TILE;     // the tail's first output row, relative to the launch's
     tail.n_nt = ts.rows;
     tail.out_row0 = a.out_row0 + (int)first;
     // G (blocked, ldb = bytes per group of 16 rows) is the B operand of both: its columns are dW's output rows (32
@@ -553,7 +587,7 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     tail.n_split = ts.slices;
     tail.k_split = slice_len(a.k_elems, ts.slices);
     tail.partial = a.partial - first * a.d;                // indexed like accbuf: by output row from the launch's first
-    tail.partial_stride = (int64_t)ts.rows * TILE * a.d;
+    tail.partial_stride = (int64_t)ts.rows * L::TILE * a.d;
     launch(body);
     launch(tail);
   };
@@ -564,16 +598,16 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     if constexpr (!L::TRANSPOSING) {
       // W^T chunk [d][ld_v]: K-contiguous operand of the dH contraction
       ProfScope ps(FLCE_PROF_BWD_PREP, st);
-      transpose_pad_kernel<U><<<dim3((unsigned)(n_vt * TILE / 64), (unsigned)ceil_div(d, 64)), 256, 0, st>>>(
-          static_cast<const U*>(W), d, V, vt0 * TILE, d, reinterpret_cast<U*>(WT), p.ld_v, n_vt * TILE);
+      transpose_pad_kernel<U><<<dim3((unsigned)(n_vt * L::TILE / 64), (unsigned)ceil_div(d, 64)), 256, 0, st>>>(
+          static_cast<const U*>(W), d, V, vt0 * L::TILE, d, reinterpret_cast<U*>(WT), p.ld_v, n_vt * L::TILE);
     }
     for (int nc = 0; nc < p.n_nch; ++nc) {
       {
         const RecomputeArgs<T> rc = recompute_args(vc, nc, G);
         ProfScope ps(FLCE_PROF_RECOMPUTE, st);
         // at most one workgroup per CU: each walks its share of the chunk's tiles
-        const int grid = L::TRANSPOSING ? std::min(rc.n_nt * rc.n_vt, NUM_CU) : rc.n_nt * rc.n_vt;
-        if constexpr (L::TRANSPOSING) {     // the tuned loop's backward always has the pre-tiled copies
+        const int grid = L::TUNED ? std::min(rc.n_nt * rc.n_vt, NUM_CU) : rc.n_nt * rc.n_vt;
+        if constexpr (L::TUNED) {     // the tuned loop's backward always has the pre-tiled copies
           if (rows.grad_rows) recompute_kernel<T, L, true, true><<<grid, L::THREADS, L::LDS, st>>>(rc);
           else recompute_kernel<T, L, true><<<grid, L::THREADS, L::LDS, st>>>(rc);
         } else {
@@ -698,12 +732,12 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
       return flce::forward_t<flce::bf16_t, uint16_t, flce::FastLoop>(p, H, W, targets, ignore_index, mean, loss_out,
                                                                      lse_out, ws, st, slice, m_out, a_out, zt_out,
                                                                      rows, so);
-    return flce::forward_t<flce::bf16_t, uint16_t, flce::GenericLoop<flce::bf16_t>>(
+    return flce::forward_t<flce::bf16_t, uint16_t, flce::GenericLoop>(
         p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
   }
-  return flce::forward_t<float, uint32_t, flce::GenericLoop<float>>(p, H, W, targets, ignore_index, mean, loss_out,
-                                                                    lse_out, ws, st, slice, m_out, a_out, zt_out,
-                                                                    rows, so);
+  if (p.tile == 64)
+    return flce::forward_t<float, uint32_t, flce::F32Loop<64>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
+  return flce::forward_t<float, uint32_t, flce::F32Loop<128>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
 }
 
 static flce_status backward_impl(const void* H, const void* W, const int64_t* targets, const float* lse, int64_t N,
@@ -730,11 +764,12 @@ static flce_status backward_impl(const void* H, const void* W, const int64_t* ta
       return flce::backward_t<flce::bf16_t, uint16_t, flce::FastLoop>(p, H, W, targets, lse, ignore_index, mean,
                                                                       grad_loss, dH_out, dW_out, ws, st, slice,
                                                                       rows);
-    return flce::backward_t<flce::bf16_t, uint16_t, flce::GenericLoop<flce::bf16_t>>(
+    return flce::backward_t<flce::bf16_t, uint16_t, flce::GenericLoop>(
         p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
   }
-  return flce::backward_t<float, uint32_t, flce::GenericLoop<float>>(p, H, W, targets, lse, ignore_index, mean,
-                                                                     grad_loss, dH_out, dW_out, ws, st, slice, rows);
+  if (p.tile == 64)
+    return flce::backward_t<float, uint32_t, flce::F32Loop<64>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
+  return flce::backward_t<float, uint32_t, flce::F32Loop<128>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
 }
 
 flce_status flce_forward(const void* H, const void* W, const int64_t* targets, int64_t N, int64_t d, int64_t V,

@@ -26,6 +26,7 @@
 #pragma once
 #include <type_traits>
 
+#include "mainloop_f32.h"
 #include "mainloop_fast.h"
 #include "tile_mma.h"
 
@@ -47,14 +48,14 @@ __host__ __device__ __forceinline__ int64_t packed_cols_offset(int q, int rows) 
 }
 
 // Main-loop policies.  A kernel is written once against this interface:
-//   THREADS, WM x WN (32x32 accumulator blocks per wavefront), LDS (dynamic LDS bytes),
-//   tile_m(i, r) / tile_n(j): position of acc[i][j][r] inside the 256 x 256 tile,
+//   THREADS, TILE (output tile edge), WM x WN (32x32 accumulator blocks per wavefront), LDS (dynamic LDS bytes),
+//   tile_m(i, r) / tile_n(j): position of acc[i][j][r] inside the tile,
 //   slot(): which of the 4 lanes that share an N column this lane is,
-//   run(): acc = A_tile . B_tile^T, ending with a barrier after the last LDS read.
-template <typename T>
-struct GenericLoop {      // any dtype, any K that is a multiple of 16 bytes; 8 wavefronts 2 x 4
-  static constexpr int THREADS = flce::THREADS, WM = flce::WM, WN = flce::WN, LDS = LDS_BYTES;
-  static constexpr bool TRANSPOSING = false;  // needs K-contiguous copies of every operand
+//   TRANSPOSING: can take an operand whose K index runs over memory rows (otherwise K-contiguous copies are made),
+//   TUNED: the bf16 loop with its persistent launches, pre-tiled copies and blocked G.
+struct GenericLoop {      // bf16 where the tuned loop does not reach (address windows); 8 wavefronts 2 x 4
+  static constexpr int TILE = flce::TILE, THREADS = flce::THREADS, WM = flce::WM, WN = flce::WN, LDS = LDS_BYTES;
+  static constexpr bool TRANSPOSING = false, TUNED = false;
   static __device__ __forceinline__ int tile_m(int i, int r) { return flce::tile_m(i, r); }
   static __device__ __forceinline__ int tile_n(int j) { return flce::tile_n(j); }
   static __device__ __forceinline__ int slot() {
@@ -68,26 +69,56 @@ struct GenericLoop {      // any dtype, any K that is a multiple of 16 bytes; 8 
   struct Stream {
     TileSrc As, Bs;
     int k_bytes;
-    __device__ __forceinline__ void start(const T* A, int64_t lda_bytes, int a_row0, int a_rows, const T* B, const T*,
-                                          int64_t ldb_bytes, int b_row0, int b_rows, int k_elems, char*) {
+    __device__ __forceinline__ void start(const bf16_t* A, int64_t lda_bytes, int a_row0, int a_rows, const bf16_t* B,
+                                          const bf16_t*, int64_t ldb_bytes, int b_row0, int b_rows, int k_elems, char*) {
       As = TileSrc{reinterpret_cast<const char*>(A), lda_bytes, a_row0, a_rows};
       Bs = TileSrc{reinterpret_cast<const char*>(B), ldb_bytes, b_row0, b_rows};
-      k_bytes = k_elems * (int)sizeof(T);
+      k_bytes = k_elems * (int)sizeof(bf16_t);
     }
-    __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[WM][WN]) { tile_mainloop<T>(As, Bs, k_bytes, lds, acc); }
+    __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[WM][WN]) { tile_mainloop(As, Bs, k_bytes, lds, acc); }
   };
   static __device__ __forceinline__ void run(const void* A, int64_t lda_bytes, int a_row0, int a_rows, const void* B,
                                              int64_t ldb_bytes, int b_row0, int b_rows, int k_bytes, char* lds,
                                              f32x16 (&acc)[WM][WN]) {
     const TileSrc As{static_cast<const char*>(A), lda_bytes, a_row0, a_rows};
     const TileSrc Bs{static_cast<const char*>(B), ldb_bytes, b_row0, b_rows};
-    tile_mainloop<T>(As, Bs, k_bytes, lds, acc);
+    tile_mainloop(As, Bs, k_bytes, lds, acc);
   }
 };
 
+template <int T>
+struct F32Loop {          // fp32; T x T tiles, 4 wavefronts 2 x 2, two workgroups per CU
+  static constexpr int TILE = T, THREADS = f32::THREADS, WM = T / 64, WN = T / 64, LDS = f32::lds_bytes<T>();
+  static constexpr bool TRANSPOSING = true, TUNED = false;
+  static __device__ __forceinline__ int tile_m(int i, int r) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    return (wave >> 1) * (T / 2) + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+  }
+  static __device__ __forceinline__ int tile_n(int j) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    return (wave & 1) * (T / 2) + j * 32 + (lane & 31);
+  }
+  static __device__ __forceinline__ int slot() { return fast::slot_of_lane(); }
+  static __device__ __forceinline__ float acc_get(const f32x16& blk, int r) { return blk[r]; }
+  template <bool BT>
+  struct Stream {         // as GenericLoop::Stream: the other resident workgroup covers a tile's first requests
+    f32::Operand As, Bs;
+    int k_elems;
+    __device__ __forceinline__ void start(const float* A, int64_t lda_bytes, int a_row0, int a_rows, const float* B,
+                                          const float*, int64_t ldb_bytes, int b_row0, int b_rows, int k, char*) {
+      As = f32::Operand{reinterpret_cast<const char*>(A), lda_bytes, a_row0, a_rows, 0};
+      Bs = f32::Operand{reinterpret_cast<const char*>(B), ldb_bytes, b_row0, b_rows, 0};
+      k_elems = k;
+    }
+    __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[WM][WN]) {
+      f32::mainloop<T, f32::KC, f32::KC>(As, Bs, k_elems, lds, acc);
+    }
+  };
+};
+
 struct FastLoop {         // bf16, K a multiple of 32 elements; 4 wavefronts 2 x 2, global -> LDS DMA
-  static constexpr int THREADS = fast::THREADS, WM = fast::WM, WN = fast::WN, LDS = fast::LDS_BYTES;
-  static constexpr bool TRANSPOSING = true;   // can take an operand whose K index runs over memory rows
+  static constexpr int TILE = flce::TILE, THREADS = fast::THREADS, WM = fast::WM, WN = fast::WN, LDS = fast::LDS_BYTES;
+  static constexpr bool TRANSPOSING = true, TUNED = true;
   // LDS that post-processing may use while the next tile's first three K stages are being filled: the fourth stage
   static constexpr int FREE_LDS_OFFSET = (fast::NS - 1) * fast::STAGE, FREE_LDS_BYTES = fast::STAGE;
   static __device__ __forceinline__ int tile_m(int i, int r) { return fast::tile_m(i, r); }
@@ -211,7 +242,7 @@ __device__ __forceinline__ void merge_fixed(const float (&m)[S], const float (&a
 // Forward tiles.  A = W tile (M = vocabulary, inside a lane), B = H tile (N = tokens,
 // across lanes): each lane streams the logits of its own token columns and keeps
 // (m, a, z_target) in registers across the vocabulary tiles of its window.
-// part = [3][n_win][n_rb * 256] floats: m, a, z_target per (window, row).
+// part = [3][n_win][npad] floats: m, a, z_target per (window, row).
 // ------------------------------------------------------------------------------------
 // HKR: the hidden states are also given pre-tiled (HT: pack_rows_kernel's copy, zero padded to whole row
 // blocks), and the main loop reads that copy: every global -> LDS request is then 1 KiB of consecutive
@@ -220,7 +251,7 @@ template <typename T, typename L, bool HKR>
 __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
     const T* __restrict__ H, const T* __restrict__ HT, const T* __restrict__ W, const int64_t* __restrict__ y,
     int N, int d, int V, int64_t ignore_index, int64_t V_total, int64_t v_begin, int n_rb, int n_win, int n_vt,
-    float* __restrict__ part, int item_begin, Header* __restrict__ hdr) {
+    float* __restrict__ part, int64_t npad, int item_begin, Header* __restrict__ hdr) {
   extern __shared__ __align__(16) char lds[];
   if (blockIdx.x == 0 && threadIdx.x == 0) hdr->arrived = 0;   // for the merge that follows on the stream
   // One workgroup per item (row block x window); a launch covers the items item_begin .. item_begin + gridDim.x - 1
@@ -231,7 +262,7 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
   grouped_raster(id, n_rb, n_win, FLCE_FWD_GROUP, rb, win);
   const int vt_begin = (int)((int64_t)win * n_vt / n_win);
   const int vt_end = (int)((int64_t)(win + 1) * n_vt / n_win);
-  const int n0 = rb * TILE;
+  const int n0 = rb * L::TILE;
   const int64_t ld_bytes = (int64_t)d * sizeof(T);
 
   int tgt[L::WN];
@@ -249,11 +280,11 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
   // The tuned loop's first K stages of tile t+1 are requested before the softmax update of tile t (which touches
   // no memory), so the update hides their latency: it matters when the K loop is short (small d).
   typename L::template Stream<HKR> stream;
-  if (vt_begin < vt_end) stream.start(W, ld_bytes, vt_begin * TILE, V, H, HT, ld_bytes, n0, N, d, lds);
+  if (vt_begin < vt_end) stream.start(W, ld_bytes, vt_begin * L::TILE, V, H, HT, ld_bytes, n0, N, d, lds);
   for (int vt = vt_begin; vt < vt_end; ++vt) {
-    const int v0 = vt * TILE;
+    const int v0 = vt * L::TILE;
     stream.run(lds, acc);
-    if (vt + 1 < vt_end) stream.start(W, ld_bytes, v0 + TILE, V, H, HT, ld_bytes, n0, N, d, lds);
+    if (vt + 1 < vt_end) stream.start(W, ld_bytes, v0 + L::TILE, V, H, HT, ld_bytes, n0, N, d, lds);
 
     // Online update of (m, a) and the target gather, one 32 x 32 accumulator block at a time
     // (16 logits of one token per lane).  All 32 rows of a block belong to one wavefront, so
@@ -306,28 +337,27 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
   // Four lanes hold partial state of each token (2 M-wavefronts x 2 lane halves):
   // merge them in fixed slot order through LDS (free after the main loop's barrier).
   float* sm = reinterpret_cast<float*>(lds);
-  float* sa = sm + 4 * TILE;
-  float* sz = sa + 4 * TILE;
+  float* sa = sm + 4 * L::TILE;
+  float* sz = sa + 4 * L::TILE;
   {
     const int slot = L::slot();
 #pragma unroll
     for (int j = 0; j < L::WN; ++j) {
       const int tok = L::tile_n(j);
-      sm[slot * TILE + tok] = m[j];
-      sa[slot * TILE + tok] = a[j];
-      sz[slot * TILE + tok] = zt[j];
+      sm[slot * L::TILE + tok] = m[j];
+      sa[slot * L::TILE + tok] = a[j];
+      sz[slot * L::TILE + tok] = zt[j];
     }
   }
   __syncthreads();
-  if (threadIdx.x < TILE) {
+  if (threadIdx.x < L::TILE) {
     const int tok = threadIdx.x;
     float pm[4], pa[4];
     float z = 0.f;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) { pm[s] = sm[s * TILE + tok]; pa[s] = sa[s * TILE + tok]; z += sz[s * TILE + tok]; }
+    for (int s = 0; s < 4; ++s) { pm[s] = sm[s * L::TILE + tok]; pa[s] = sa[s * L::TILE + tok]; z += sz[s * L::TILE + tok]; }
     float M, A;
     merge_fixed<4>(pm, pa, M, A);
-    const int64_t npad = (int64_t)n_rb * TILE;
     const int64_t o = (int64_t)win * npad + n0 + tok;
     part[o] = M;
     part[(int64_t)n_win * npad + o] = A;
@@ -858,7 +888,7 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
   // Only the row tiles that hold counted rows are rastered (their number is known on the device
   // alone), so the XCDs share the work evenly however many rows are ignored; workgroups beyond the
   // useful tiles of a launch sized for N rows leave at once.
-  const int n_nt = max(0, min(a.n_nt, ((int)a.hdr->n_valid - a.nt0 * TILE + TILE - 1) / TILE));
+  const int n_nt = max(0, min(a.n_nt, ((int)a.hdr->n_valid - a.nt0 * L::TILE + L::TILE - 1) / L::TILE));
   const int useful = n_nt * a.n_vt;
   int t = blockIdx.x;
   if (t >= useful) return;
@@ -888,26 +918,26 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
   int p, q;
   place(t, p, q);
   RowMeta<L> meta;
-  if constexpr (L::TRANSPOSING) load_meta((a.nt0 + p) * TILE, meta);
-  stream.start(W, ld_bytes, (a.vt0 + q) * TILE, V, Hc, HcT, ld_bytes, (a.nt0 + p) * TILE, npad, d, lds);
+  if constexpr (L::TUNED) load_meta((a.nt0 + p) * L::TILE, meta);
+  stream.start(W, ld_bytes, (a.vt0 + q) * L::TILE, V, Hc, HcT, ld_bytes, (a.nt0 + p) * L::TILE, npad, d, lds);
   f32x16 acc[L::WM][L::WN];
   for (;;) {
     stream.run(lds, acc);
     const int t_next = t + gridDim.x;
     // (a main loop with nothing to request ahead gets one tile per workgroup)
-    const bool more = L::TRANSPOSING && t_next < useful;
+    const bool more = L::TUNED && t_next < useful;
     int p_next = 0, q_next = 0;
     RowMeta<L> meta_next;
-    if constexpr (!L::TRANSPOSING) load_meta((a.nt0 + p) * TILE, meta);   // no registers to spare across that main loop
+    if constexpr (!L::TUNED) load_meta((a.nt0 + p) * L::TILE, meta);   // no registers to spare across that main loop
     need_meta(meta);
     if (more) {
       place(t_next, p_next, q_next);
-      load_meta((a.nt0 + p_next) * TILE, meta_next);
-      stream.start(W, ld_bytes, (a.vt0 + q_next) * TILE, V, Hc, HcT, ld_bytes, (a.nt0 + p_next) * TILE, npad, d, lds);
+      load_meta((a.nt0 + p_next) * L::TILE, meta_next);
+      stream.start(W, ld_bytes, (a.vt0 + q_next) * L::TILE, V, Hc, HcT, ld_bytes, (a.nt0 + p_next) * L::TILE, npad, d, lds);
     }
 
-    const int v0 = (a.vt0 + q) * TILE;
-    if constexpr (L::TRANSPOSING) {
+    const int v0 = (a.vt0 + q) * L::TILE;
+    if constexpr (L::TUNED) {
       // Tuned loop.  A lane holds, of 32 token rows x 128 vocabulary positions per j, scattered 8-byte pieces of one
       // row; stored as they lie, every store instruction would touch 64 different memory rows.  Each wavefront
       // therefore passes its 32 x 128 piece (8 KiB of bf16) through its own slice of the free LDS stage and writes
@@ -969,7 +999,7 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
         // 256 bytes per instruction.  G is stored in blocks of 16 rows x 32 positions (1 KiB; the blocks of a row
         // group along the vocabulary, row groups ldG BYTES apart), so that both contractions fetch whole blocks:
         // a row's 16 bytes at position chunk c lie in block c / 4 at (row % 16) * 64 + (c % 4) * 16.
-        const int row0 = p * TILE + (wave & 1) * 128 + j * 32;                  // a multiple of 32: two row groups
+        const int row0 = p * L::TILE + (wave & 1) * 128 + j * 32;                  // a multiple of 32: two row groups
         const int cchunk = q * 32 + (wave >> 1) * 16 + rchunk;                  // 8-position chunk inside the chunk's row
         char* __restrict__ gdst = reinterpret_cast<char*>(G) + (int64_t)(row0 >> 4) * ldG + (int64_t)(cchunk >> 2) * 1024 +
                                   rrow * 64 + (cchunk & 3) * 16;
@@ -992,9 +1022,9 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
       const bool whole = blk0 + 32 <= V;
 #pragma unroll
       for (int j = 0; j < L::WN; ++j) {
-        const int nl = p * TILE + L::tile_n(j);       // row inside the staging tile
+        const int nl = p * L::TILE + L::tile_n(j);       // row inside the staging tile
         // this lane's first position in the row; block (i, rq) lies a constant 32 i + 8 rq further on
-        T* __restrict__ grow = G + (int64_t)nl * ldG + q * TILE + L::tile_m(0, 0);
+        T* __restrict__ grow = G + (int64_t)nl * ldG + q * L::TILE + L::tile_m(0, 0);
         const int tgt = meta.tgt[j];
         // exp(z - lse) = 2^(z * log2e - lse * log2e); a padding row (tgt < 0) gets lse = +inf here, so its p is
         // exactly 0, and no column equals its target: its row of G is 0 without a mask
@@ -1025,9 +1055,9 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
             for (int e = 0; e < 4; ++e)
               if (v0 + mloc + e >= V) g[e] = 0.f;
           }
-          const int vl = q * TILE + mloc;
+          const int vl = q * L::TILE + mloc;
           Pack4<T>::store(grow + (i * 32 + rq * 8), g[0], g[1], g[2], g[3]);
-          if (!L::TRANSPOSING) {
+          if constexpr (!L::TRANSPOSING) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) GT[(int64_t)(vl + e) * ldGT + nl] = Pack4<T>::one(g[e]);
           }
@@ -1063,7 +1093,9 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
 //   OPS_DW_TR : A = the transposed pre-tiled copy of Hc (prep_rows_tiled_kernel; lda = its padded row count, the
 //               K steps of the row chunk start at image k_start / 32), B = the same blocked G, K over its rows
 enum : int { READ_ACC = 1, WRITE_ACC = 2, WRITE_OUT = 4, ROWS_COMPACT = 8, K_COMPACT = 16 };
-enum : int { OPS_KC = 0, OPS_DH_TR = 1, OPS_DW_TR = 2 };
+//   OPS_DH_F32 : fp32; A = W rows of the vocabulary chunk [k][m], B = G row-major [n][k]
+//   OPS_DW_F32 : fp32; A = Hc rows of the row chunk [k][m], B = G row-major [k][n] (K over the rows of both)
+enum : int { OPS_KC = 0, OPS_DH_TR = 1, OPS_DW_TR = 2, OPS_DH_F32 = 3, OPS_DW_F32 = 4 };
 
 template <typename T>
 struct ContractArgs {
@@ -1092,14 +1124,14 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
   // With compacted output rows only the row tiles that hold counted rows are rastered, so the
   // XCDs share the work evenly; surplus workgroups of the launch leave at once.
   int n_nt = a.n_nt;
-  if (a.flags & ROWS_COMPACT) n_nt = max(0, min(n_nt, (nv - a.out_row0 + TILE - 1) / TILE));
+  if (a.flags & ROWS_COMPACT) n_nt = max(0, min(n_nt, (nv - a.out_row0 + L::TILE - 1) / L::TILE));
   const int tiles = n_nt * a.n_mt;
   const int n_split = max(1, a.n_split);
   const int total = tiles * n_split;
   int b = blockIdx.x;
   if (b >= total) return;
   int k_all = a.k_elems;
-  if (a.flags & K_COMPACT) k_all = max(0, min(k_all, (nv - a.k_start + TILE - 1) / TILE * TILE));
+  if (a.flags & K_COMPACT) k_all = max(0, min(k_all, (nv - a.k_start + L::TILE - 1) / L::TILE * L::TILE));
   float scale = a.grad_loss;
   if (a.mean) scale = nv > 0 ? a.grad_loss / (float)nv : 0.f;
 
@@ -1114,7 +1146,7 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
   auto load_rows = [&](int p, int64_t (&orow)[L::WN]) {
 #pragma unroll
     for (int j = 0; j < L::WN; ++j) {
-      const int n = a.out_row0 + p * TILE + L::tile_n(j);
+      const int n = a.out_row0 + p * L::TILE + L::tile_n(j);
       orow[j] = -1;
       if (n < a.out_rows) orow[j] = (a.flags & ROWS_COMPACT) ? (int64_t)a.rowmap[n] : (int64_t)n;
     }
@@ -1134,9 +1166,9 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
 #pragma unroll
     for (int j = 0; j < L::WN; ++j) {
       if (orow[j] < 0) continue;
-      const int n = a.out_row0 + p * TILE + L::tile_n(j);
+      const int n = a.out_row0 + p * L::TILE + L::tile_n(j);
       // this lane's first hidden position; block (i, rq) lies a constant 32 i + 8 rq further on
-      const int m0 = q * TILE + L::tile_m(0, 0);
+      const int m0 = q * L::TILE + L::tile_m(0, 0);
       float* __restrict__ arow = accbuf + (int64_t)(n - a.acc_row0) * d + m0;
       T* __restrict__ orowp = out + orow[j] * d + m0;
 #pragma unroll
@@ -1166,8 +1198,21 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
   int64_t orow[L::WN];
   if constexpr (OPS == OPS_KC) {
     // one item per workgroup: this main loop has nothing to request ahead
-    L::run(A + k0, lda * (int64_t)sizeof(T), q * TILE, d, B + k0, ldb * (int64_t)sizeof(T), p * TILE, a.b_rows,
+    L::run(A + k0, lda * (int64_t)sizeof(T), q * L::TILE, d, B + k0, ldb * (int64_t)sizeof(T), p * L::TILE, a.b_rows,
            k_elems * (int)sizeof(T), lds, acc);
+    load_rows(p, orow);
+    flush(acc, z, p, q, orow);
+  } else if constexpr (OPS == OPS_DH_F32 || OPS == OPS_DW_F32) {
+    // likewise one item per workgroup: the other workgroup of the CU covers its start and its end
+    const int width = min(L::TILE, d - q * L::TILE) * 4;
+    const f32::Operand As{reinterpret_cast<const char*>(A + (int64_t)k0 * lda + q * L::TILE), lda * 4, 0, a.a_krows - k0, width};
+    if constexpr (OPS == OPS_DH_F32) {
+      const f32::Operand Bs{reinterpret_cast<const char*>(B + k0), ldb * 4, p * L::TILE, a.b_rows, 0};
+      f32::mainloop<L::TILE, f32::KR, f32::KC>(As, Bs, k_elems, lds, acc);
+    } else {
+      const f32::Operand Bs{reinterpret_cast<const char*>(B + (int64_t)k0 * ldb + p * L::TILE), ldb * 4, 0, k_elems, L::TILE * 4};
+      f32::mainloop<L::TILE, f32::KR, f32::KR>(As, Bs, k_elems, lds, acc);
+    }
     load_rows(p, orow);
     flush(acc, z, p, q, orow);
   } else {
@@ -1175,11 +1220,11 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
     auto start = [&](int p, int q, int k0, int k_elems) {
       if constexpr (OPS == OPS_DH_TR) {
         // A: K rows start at A (a_krows valid from there), window of 256 hidden columns at q
-        const int width = max(0, min(TILE, d - q * TILE)) * 2;
-        const fast::Operand As{reinterpret_cast<const char*>(A + (int64_t)k0 * lda) + (int64_t)q * TILE * 2, lda * 2, 0,
+        const int width = max(0, min(L::TILE, d - q * L::TILE)) * 2;
+        const fast::Operand As{reinterpret_cast<const char*>(A + (int64_t)k0 * lda) + (int64_t)q * L::TILE * 2, lda * 2, 0,
                                a.a_krows - k0, width};
         // B: G blocked (ldb = bytes from one group of 16 rows to the next), rows p * 256 ..., K from position k0
-        const fast::Operand Bs{reinterpret_cast<const char*>(B) + (int64_t)(p * (TILE / 16)) * ldb + (int64_t)(k0 / 32) * 1024,
+        const fast::Operand Bs{reinterpret_cast<const char*>(B) + (int64_t)(p * (L::TILE / 16)) * ldb + (int64_t)(k0 / 32) * 1024,
                                ldb, 0, 0, 0};
         pipe.start(As, Bs, k_elems, lds);
       } else {
@@ -1187,7 +1232,7 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
         const fast::Operand As{reinterpret_cast<const char*>(A) + packed_cols_offset(q, (int)lda) +
                                    (int64_t)((a.k_start + k0) / fast::BK) * fast::OPER, 0, 0, 0, 0};
         // B: G blocked, K over its rows from row k0, the tile's 256 vocabulary positions from p * 256
-        const fast::Operand Bs{reinterpret_cast<const char*>(B) + (int64_t)(k0 / 16) * ldb + (int64_t)(p * (TILE / 32)) * 1024,
+        const fast::Operand Bs{reinterpret_cast<const char*>(B) + (int64_t)(k0 / 16) * ldb + (int64_t)(p * (L::TILE / 32)) * 1024,
                                ldb, 0, 0, 0};
         pipe.start(As, Bs, k_elems, lds);
       }
@@ -1220,12 +1265,12 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
 // slices in slice order (fixed), then the running sum / Gamma / rounding exactly as the
 // unsplit epilogue would.  Memory bound; the loads of eight slices are in flight together.
 template <typename T>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(ContractArgs<T> a) {
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(ContractArgs<T> a, int launch_rows) {
   const int d4 = a.d / 4;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int row = (int)(i / d4), m = (int)(i - (int64_t)row * d4) * 4;
   const int n = a.out_row0 + row;
-  if (row >= a.n_nt * TILE || n >= a.out_rows) return;
+  if (row >= launch_rows || n >= a.out_rows) return;
   const int nv = (int)a.hdr->n_valid;
   int64_t orow = n;
   if (a.flags & ROWS_COMPACT) {

@@ -1,0 +1,202 @@
+// fp32 main loop for gfx950: T x T output tile (T = 128 or 64), 256 threads = 4 wavefronts arranged 2 x 2, each owning
+// WB x WB = T / 64 blocks of the 32x32x2 fp32 MFMA, two workgroups per CU.
+//
+// The fp32 matrix instruction is 16 times slower than the bf16 one (256 flops per clock and CU), so nothing about the
+// data path is critical; what counts is that every CU has work.  A 256-row tile of K = 512 keeps a CU busy for 109 us and
+// a problem of a few thousand rows by a few thousand vocabulary entries has fewer such tiles than the chip has CUs, hence
+// the small tiles (4 or 16 times fewer flops each) and the two resident workgroups that even out a ragged last round.
+// Forward + backward against 256-row tiles with register-staged loads and transposed copies: 256 x 256 x 4096 327 -> 77 us,
+// 1000 x 512 x 10007 950 -> 494 us (80 TFLOP/s), 4096 x 1024 x 32768 8.72 -> 8.21 ms (134 TFLOP/s of 157; a large library
+// matrix product reaches 153).
+//
+//   * Operand tiles go from global memory straight into LDS (buffer_load ... lds), 32 K elements per stage, NS stages;
+//     each wavefront's part of a stage has a descriptor of its own, advanced with K, so that no operand size is out of a
+//     32-bit offset's reach; rows and K elements past the end are zero-filled by the range check.
+//   * Each operand may be stored either way round:
+//       KC: T rows with their 32 K values adjacent, 128 bytes (K ends at a multiple of 4 elements; 16-byte chunks
+//           past it are not read).  LDS [T][128 B], 16-byte chunk index ^ (row / 2) % 8: a 128-bit fragment read
+//           touches every bank once.
+//       KR: K runs over memory rows, T columns side by side.  LDS [32][4 T B], chunk index ^ 8 on K rows with bit 2
+//           set: the two lane halves of a fragment read, four K rows apart, use different halves of the banks.
+//     so that dH = G.W and dW = G^T.H read G, W and H where they are.
+//   * K is taken in groups of 8: lane half h holds K = 8 g + 4 h + j, j = 0..3, for the group's four MFMAs (the order of
+//     K inside a group is free as long as both operands agree), which makes a KC fragment one 128-bit read.
+#pragma once
+#include "mainloop_fast.h"
+
+namespace flce {
+namespace f32 {
+
+constexpr int THREADS = 256;
+constexpr int BK = 32;                                      // K elements per stage
+// Stages whose products are added up before they are added to the tile's sum: a chain of 1024 additions and one of
+// K / 1024 instead of one of K, which the dH contraction (K = the vocabulary) would otherwise show: 3.3e-6 relative error
+// against 64 bits at 4096 x 1024 x 32768, 5.8e-7 with partial sums, at the same speed.
+constexpr int SUM_STAGES = 32;
+enum : int { KC = 0, KR = 1 };
+
+// One operand of the contraction.
+//   KC: base = first byte of row 0 at the first K element; row0 = first tile row; rows = valid rows of the tensor.
+//   KR: base = first byte of K row 0 at the tile's first column; rows = valid K rows; width_bytes = valid bytes of the
+//       tile's columns (columns past it may read as the next row's data: the caller masks what they produce).
+struct Operand {
+  const char* base;
+  int64_t ld_bytes;
+  int row0, rows, width_bytes;
+};
+
+// This wavefront's requests of one operand: T / 32 of 1 KiB per stage, its quarter of the operand's LDS tile.
+template <int T, int LAYOUT>
+struct Loader {
+  static constexpr int REQS = T / 32;
+  const char* base;        // first row of the wavefront's quarter, K tile 0
+  int64_t ld_bytes;
+  int rows;                // valid rows of the quarter (KC), valid K rows from the quarter's first on (KR)
+  int k_bytes, width_bytes;
+  uint32_t v[REQS], chunk[REQS];
+  __device__ __forceinline__ void init(const Operand& s, int k_elems) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    ld_bytes = s.ld_bytes; k_bytes = k_elems * 4; width_bytes = s.width_bytes;
+    if (LAYOUT == KC) {
+      const int r0 = wave * (T / 4);
+      base = s.base + (int64_t)(s.row0 + r0) * s.ld_bytes;
+      rows = max(0, min(s.rows - s.row0 - r0, T / 4));
+#pragma unroll
+      for (int i = 0; i < REQS; ++i) {
+        const int row = i * 8 + (lane >> 3), c = (lane & 7) ^ (((r0 + row) >> 1) & 7);
+        v[i] = (uint32_t)(row * s.ld_bytes) + c * 16;
+        chunk[i] = c * 16;
+      }
+    } else {
+      constexpr int CHUNKS = T / 4;                         // 16-byte chunks per K row
+      const int r0 = wave * 8;
+      base = s.base + (int64_t)r0 * s.ld_bytes;
+      rows = min(s.rows, k_elems) - r0;
+#pragma unroll
+      for (int i = 0; i < REQS; ++i) {
+        const int kr = i * (64 / CHUNKS) + lane / CHUNKS, c = (lane % CHUNKS) ^ ((((r0 + kr) >> 2) & 1) << 3);
+        v[i] = (uint32_t)(kr * s.ld_bytes) + c * 16;
+        chunk[i] = 0;
+      }
+    }
+  }
+  __device__ __forceinline__ void issue(char* tile, int kt) const {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t off = LAYOUT == KC ? (int64_t)kt * (BK * 4) : (int64_t)kt * BK * ld_bytes;
+    uint32_t n = 0;                                         // bytes in reach of the quarter at this K tile
+    if (LAYOUT == KC) {
+      if (rows > 0) n = (uint32_t)((int64_t)(rows - 1) * ld_bytes + k_bytes - off);
+    } else {
+      const int kr = max(0, min(rows - kt * BK, 8));
+      if (kr > 0) n = (uint32_t)((int64_t)(kr - 1) * ld_bytes + width_bytes);
+    }
+    const uint64_t addr = (uint64_t)(uintptr_t)(base + off);
+    u32x4 r = {(uint32_t)addr, (uint32_t)(addr >> 32) & 0xFFFFu, n, 0x00020000u};
+    r[0] = __builtin_amdgcn_readfirstlane(r[0]);
+    r[1] = __builtin_amdgcn_readfirstlane(r[1]);
+    r[2] = __builtin_amdgcn_readfirstlane(r[2]);
+#pragma unroll
+    for (int i = 0; i < REQS; ++i) {
+      uint32_t vo = v[i];
+      if (LAYOUT == KC) vo = kt * (BK * 4) + (int)chunk[i] < k_bytes ? vo : 0xFFFFFF00u;   // out of range: reads as zero
+      fast::dma16(r, fast::lds_address(tile + wave * (T * 32) + i * 1024), vo, 0);
+    }
+  }
+};
+
+// Fragments of one K group of 8: per 32-row block this lane's four K values.
+template <int T, int LAYOUT>
+__device__ __forceinline__ void read_frags(f32x4 (&f)[T / 64], const char* tile, int wsub, int g) {
+  const int l32 = threadIdx.x & 31, half = (threadIdx.x >> 5) & 1;
+#pragma unroll
+  for (int i = 0; i < T / 64; ++i) {
+    const int row = wsub * (T / 2) + i * 32 + l32;
+    if (LAYOUT == KC) {
+      f[i] = *reinterpret_cast<const f32x4*>(tile + row * 128 + (((2 * g + half) ^ ((l32 >> 1) & 7)) << 4));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        f[i][j] = *reinterpret_cast<const float*>(tile + (8 * g + 4 * half + j) * (T * 4) + ((row * 4) ^ (half << 7)));
+    }
+  }
+}
+
+template <int T>
+constexpr int stages() { return T == 128 ? 2 : 4; }         // 64 KiB of LDS either way: two workgroups per CU
+template <int T>
+constexpr int lds_bytes() { return stages<T>() * 2 * T * BK * 4; }
+
+// acc = A_tile . B_tile^T over k_elems of K.  On return every wavefront has passed a barrier after its last LDS read.
+template <int T, int LA, int LB>
+__device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int k_elems, char* lds,
+                                         f32x16 (&acc)[T / 64][T / 64]) {
+  constexpr int W = T / 64, NS = stages<T>(), OPER = T * BK * 4, STAGE = 2 * OPER, LOADS = 2 * (T / 32);
+#pragma unroll
+  for (int i = 0; i < W; ++i)
+#pragma unroll
+    for (int j = 0; j < W; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const int KT = (k_elems + BK - 1) / BK;
+  Loader<T, LA> la;
+  Loader<T, LB> lb;
+  la.init(A, k_elems);
+  lb.init(B, k_elems);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int s = 0; s < NS - 1 && s < KT; ++s) {
+    la.issue(lds + s * STAGE, s);
+    lb.issue(lds + s * STAGE + OPER, s);
+  }
+  for (int kb = 0; kb < KT; kb += SUM_STAGES) {
+    const int kb_end = min(KT, kb + SUM_STAGES);
+    f32x16 part[W][W];
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+      for (int j = 0; j < W; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[i][j][r] = 0.f;
+    for (int kt = kb; kt < kb_end; ++kt) {
+      // tile kt has landed once only the requests of the later tiles are in flight; this wavefront's LDS reads of the
+      // stage that is requested next (tile kt - 1's) have returned
+      switch (min(NS - 2, KT - 1 - kt)) {
+        case 0: fast::wait_vm_and_lds<0>(); break;
+        case 1: fast::wait_vm_and_lds<LOADS>(); break;
+        default: fast::wait_vm_and_lds<2 * LOADS>(); break;
+      }
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (kt + NS - 1 < KT) {
+        char* dst = lds + (kt + NS - 1) % NS * STAGE;
+        la.issue(dst, kt + NS - 1);
+        lb.issue(dst + OPER, kt + NS - 1);
+      }
+      const char* st = lds + kt % NS * STAGE;
+#pragma unroll
+      for (int g = 0; g < BK / 8; ++g) {
+        f32x4 a[W], b[W];
+        read_frags<T, LA>(a, st, wave >> 1, g);
+        read_frags<T, LB>(b, st + OPER, wave & 1, g);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int i = 0; i < W; ++i)
+#pragma unroll
+            for (int j = 0; j < W; ++j) part[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][k], b[j][k], part[i][j], 0, 0, 0);
+      }
+      asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+      for (int j = 0; j < W; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += part[i][j][r];
+  }
+  fast::wait_vm_and_lds<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+}  // namespace f32
+}  // namespace flce

@@ -1,4 +1,4 @@
-// 256 x 256 output tile of an "NT" contraction  D[m][n] = sum_k A[m][k] * B[n][k]
+// The generic bf16 main loop: 256 x 256 output tile of an "NT" contraction  D[m][n] = sum_k A[m][k] * B[n][k]
 // on the gfx950 matrix cores, both operands K-contiguous in memory.
 //
 // One workgroup = 512 threads = 8 wavefronts arranged 2 (M) x 4 (N); each
@@ -50,30 +50,10 @@ __device__ __forceinline__ int lds_off(int row, int chunk) {
   return row * KB + ((chunk ^ (row & 7)) << 4);
 }
 
-template <typename T> struct Mma;
-
-template <> struct Mma<bf16_t> {
-  static constexpr int KSTEPS = 4;   // 16 bf16 = 32 bytes of K per MFMA, 128 bytes per stage
-  typedef bf16x8 frag;
-  static __device__ __forceinline__ frag load(const char* tile, int row, int ks, int half) {
-    return *reinterpret_cast<const bf16x8*>(tile + lds_off(row, ks * 2 + half));
-  }
-  static __device__ __forceinline__ f32x16 mma(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-
-template <> struct Mma<float> {
-  static constexpr int KSTEPS = 16;  // 2 floats = 8 bytes of K per MFMA
-  typedef float frag;
-  static __device__ __forceinline__ frag load(const char* tile, int row, int ks, int half) {
-    int k = ks * 2 + half;           // element index inside the 32-float stage
-    return *reinterpret_cast<const float*>(tile + lds_off(row, k >> 2) + ((k & 3) << 2));
-  }
-  static __device__ __forceinline__ f32x16 mma(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-};
+constexpr int KSTEPS = 4;            // 16 bf16 = 32 bytes of K per MFMA, 128 bytes per stage
+__device__ __forceinline__ bf16x8 load_frag(const char* tile, int row, int ks, int half) {
+  return *reinterpret_cast<const bf16x8*>(tile + lds_off(row, ks * 2 + half));
+}
 
 // Global -> register staging of one operand tile slice: 4 chunks of 16 bytes per thread.
 struct Stage {
@@ -116,7 +96,6 @@ __device__ __forceinline__ void store_stage(const Stage& s, char* lds_stage) {
   }
 }
 
-template <typename T>
 __device__ __forceinline__ void compute_stage(const char* lds_stage, f32x16 (&acc)[WM][WN]) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -125,23 +104,22 @@ __device__ __forceinline__ void compute_stage(const char* lds_stage, f32x16 (&ac
   const char* At = lds_stage;
   const char* Bt = lds_stage + TILE * KB;
 #pragma unroll
-  for (int ks = 0; ks < Mma<T>::KSTEPS; ++ks) {
-    typename Mma<T>::frag a[WM], b[WN];
+  for (int ks = 0; ks < KSTEPS; ++ks) {
+    bf16x8 a[WM], b[WN];
 #pragma unroll
-    for (int i = 0; i < WM; ++i) a[i] = Mma<T>::load(At, wm * 128 + i * 32 + l32, ks, half);
+    for (int i = 0; i < WM; ++i) a[i] = load_frag(At, wm * 128 + i * 32 + l32, ks, half);
 #pragma unroll
-    for (int j = 0; j < WN; ++j) b[j] = Mma<T>::load(Bt, wn * 64 + j * 32 + l32, ks, half);
+    for (int j = 0; j < WN; ++j) b[j] = load_frag(Bt, wn * 64 + j * 32 + l32, ks, half);
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-      for (int j = 0; j < WN; ++j) acc[i][j] = Mma<T>::mma(a[i], b[j], acc[i][j]);
+      for (int j = 0; j < WN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
   }
 }
 
 // acc = A_tile . B_tile^T over the whole K extent.  `lds` is LDS_BYTES of dynamic
 // shared memory.  On return every wavefront has passed a barrier after its last
 // LDS read, so the caller may reuse `lds`.
-template <typename T>
 __device__ __forceinline__ void tile_mainloop(const TileSrc& A, const TileSrc& B, int k_bytes, char* lds,
                                               f32x16 (&acc)[WM][WN]) {
 #pragma unroll
@@ -159,7 +137,7 @@ __device__ __forceinline__ void tile_mainloop(const TileSrc& A, const TileSrc& B
   for (int kt = 0; kt < kt_n; ++kt) {
     const bool more = kt + 1 < kt_n;
     if (more) load_stage(s, A, B, (kt + 1) * KB, k_bytes);
-    compute_stage<T>(lds + (kt & 1) * STAGE_BYTES, acc);
+    compute_stage(lds + (kt & 1) * STAGE_BYTES, acc);
     if (more) store_stage(s, lds + ((kt + 1) & 1) * STAGE_BYTES);
     __syncthreads();
   }

@@ -1,0 +1,30 @@
+"""The fp32 main loop at the edges of its tiles: 64-row tiles below 320 tiles of 128 x 128 logits, 128-row tiles from there
+on; K tails shorter than a 16-byte chunk row, K longer than one block of partial sums (1024), rows and columns past the end."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2511_17599_amd import inputs as I              # noqa: E402
+from conftest import set_plan                             # noqa: E402
+from test_gpu_parity import check_against_oracle          # noqa: E402
+
+
+@pytest.mark.parametrize("N,d,V,ignore", [
+    (64, 32, 64, 0.0), (65, 8, 129, 0.1), (63, 72, 257, 0.0), (300, 1064, 200, 0.3), (5, 256, 2100, 0.0),   # 64-row tiles
+    (1300, 72, 3800, 0.1), (1281, 8, 3713, 0.5), (130, 200, 20500, 0.0), (20500, 40, 130, 0.02), (1409, 1032, 3650, 0.0),
+], ids=str)
+def test_f32_tiles(N, d, V, ignore):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = I.Workload(f"f32_{N}_{d}_{V}", N, d, V, "f32", "uniform", ignore_frac=ignore, seed=700 + N + d)
+    check_against_oracle(wl, I.make_inputs(wl))
+
+
+@pytest.mark.parametrize("N,V", [(700, 1500), (1300, 3800)])
+def test_f32_chunks_and_slices(monkeypatch, N, V):
+    """Several chunks with running sums and K slices, at both tile sizes."""
+    set_plan(monkeypatch, FLCE_VC_TILES=3, FLCE_NC_TILES=2, FLCE_SPLITK_DH=3, FLCE_SPLITK_DW=2, FLCE_WINDOWS=3)
+    wl = I.Workload(f"f32_chunks_{N}_{V}", N, 136, V, "f32", "zipf", zipf_s=1.1, ignore_frac=0.1, seed=710)
+    check_against_oracle(wl, I.make_inputs(wl), grad_loss=-0.5)
