@@ -55,7 +55,7 @@
  * Defaults suit MI355X; results stay within the tolerances for any setting but their
  * rounding, and the bit pattern, depend on it:
  *   FLCE_WINDOWS    vocabulary windows of the forward (Section 3.2.1); 0 / unset = automatic
- *                   (at least 4, enough row block x window workgroups to cover 256 CUs).
+ *                   (at least 4 where V allows, row blocks x windows filling whole rounds of 256 workgroups).
  *   FLCE_VC_TILES   largest vocabulary chunk of the backward, in 256-row tiles; 0 / unset = automatic
  *                   (128; up to 512 when there are fewer than 32 token tiles, same staging bytes).
  *   FLCE_NC_TILES   largest token chunk of the backward, in 256-row tiles (default 128).

@@ -139,10 +139,30 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   // At least 4, so that the 32 workgroups resident on one XCD are 8 row blocks x 4 windows and
   // share both operands through that XCD's L2 (one window would stream every H block from HBM).
   const Tuning tn = tuning();
-  int win = tn.windows;
-  if (win == 0) win = (int)std::max<int64_t>(4, ceil_div(NUM_CU, p.n_rb));
-  if (win > p.n_vt) win = p.n_vt;
-  p.n_win = win;
+  const int cover = (int)std::min<int64_t>(std::max<int64_t>(4, ceil_div(NUM_CU, p.n_rb)), p.n_vt);
+  p.n_win = cover;
+  int part_windows = cover;                 // what the partials are sized for
+  if (tn.windows) {
+    p.n_win = part_windows = std::min(tn.windows, p.n_vt);
+  } else {
+    // Among the window counts that fill up to 8 rounds of workgroups, the one with the least work in sequence.  bf16
+    // (one workgroup per CU): rounds x (tiles of the longest window + `fill`, the start and end of an item, 8 us against
+    // 24 ns per K element and tile).  fp32 (two per CU): a CU with two items takes them side by side at half the speed,
+    // one alone leaves about a fifth of it unused.  One more than a round is what this avoids: 13 row blocks x 20 windows
+    // were 260 items, the last 4 of them a launch as long as the first 256 (3300 x 2048 x 65536 forward: 1187 us, with 19
+    // windows 743).  The callers that cannot pass a workspace, and fp32, keep to the partials of `cover` windows.
+    const int64_t rb = ceil_div(N, p.tile), vt = ceil_div(V, p.tile);
+    auto cost = [&](int64_t win) {
+      const int64_t items = rb * win, longest = ceil_div(vt, win);
+      if (p.tile == TILE) return (double)ceil_div(items, NUM_CU) * ((double)longest + 8.0 / (0.0242 * (double)d));
+      return items <= NUM_CU ? 1.2 * (double)longest : 2.0 * (double)(ceil_div(items, 2 * NUM_CU) * longest);
+    };
+    const int64_t most = allow_h_copy && p.tile == TILE ? std::min<int64_t>(p.n_vt, std::max<int64_t>(cover, 8 * NUM_CU / rb)) : cover;
+    for (int64_t win = std::min<int64_t>(4, cover); win <= most; ++win)
+      if (cost(win) < 0.99 * cost(p.n_win)) p.n_win = (int)win;
+    part_windows = std::max(cover, p.n_win);
+  }
+  const int win = part_windows;
   int64_t o = ALIGN;                                  // header
   p.off_part = o;       o = align_up(o + 3ll * win * p.npad * 4, ALIGN);
   p.off_blk_loss = o;   o = align_up(o + (int64_t)p.n_rb * 4, ALIGN);

@@ -1,0 +1,47 @@
+"""Host-only: the forward's vocabulary windows fill whole rounds of 256 workgroups, and the callers that cannot pass a
+workspace are accepted at the same sizes as with ceil(256 / row blocks) windows."""
+import random
+
+import pytest
+
+from paper_2511_17599_amd import binding as B
+
+
+def _windows(N, d, V, dt=B.FLCE_DTYPE_BF16):
+    f = dict(kv.split("=") for kv in B.flce_plan_describe(N, d, V, dt).split()[2:])
+    return int(f["windows"]), int(f["fwd_ws"])
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_no_more_work_in_sequence_than_before(seed):
+    r = random.Random(seed)
+    for _ in range(200):
+        N, V, d = r.randint(1, 60000), r.randint(1, 200000), 32 * r.randint(1, 128)
+        win, ws = _windows(N, d, V)
+        rb, vt = -(-N // 256), -(-V // 256)
+        old = min(max(4, -(-256 // rb)), vt)
+        seq = lambda w: -(-rb * w // 256) * (-(-vt // w) + 8.0 / (0.0242 * d))
+        assert 1 <= win <= vt and seq(win) <= seq(old)
+        assert rb * win <= max(8 * 256, rb * old)            # partials: bounded by 8 rounds of items
+    # one more than a round is what it avoids: 5 row blocks
+    assert _windows(1030, 256, 20011)[0] * 5 <= 256
+
+
+def test_static_scratch_takes_the_same_shapes():
+    """4 N + 12 * windows * Npad + 4 * ceil(V / 1024) * d bytes and the 256-byte aligned rest, windows = ceil(256 / row
+    blocks), against the 16 MiB array: one row on either side of the limit (fake addresses: a call that is accepted
+    would launch, so only the refusal is called)."""
+    up = lambda x: -(-x // 256) * 256
+
+    def need(N, d, V):
+        rb, vt = -(-N // 256), -(-V // 256)
+        win = min(max(4, -(-256 // rb)), vt)
+        return (256 + up(12 * win * rb * 256) + 3 * up(4 * rb) + up(-(-V // 1024) * d * 4) + up(4 * d) + up(4 * N))
+    for d, V in ((4096, 128256), (768, 50257), (256, 600)):
+        lo, hi = 1, 1 << 22
+        while lo + 1 < hi:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if need(mid, d, V) <= B.FLCE_STATIC_SCRATCH_BYTES else (lo, mid)
+        p = 4096
+        call = lambda N: B.flce_forward_static(p, p, p, N, d, V, -100, B.FLCE_REDUCE_MEAN, B.FLCE_DTYPE_BF16, p, p)
+        assert call(hi) == B.FLCE_ERR_WORKSPACE
