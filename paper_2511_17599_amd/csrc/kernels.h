@@ -1143,34 +1143,34 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
     if (a.n_split > 1) { k0 = z * a.k_split; k_elems = max(0, min(a.k_split, k_all - k0)); }
   };
   // output rows of the lane's token columns: the original row of a compact row, -1 = nothing to write
-  auto load_rows = [&](int p, int64_t (&orow)[L::WN]) {
+  auto load_rows = [&](int p, int (&orow)[L::WN]) {
 #pragma unroll
     for (int j = 0; j < L::WN; ++j) {
       const int n = a.out_row0 + p * L::TILE + L::tile_n(j);
       orow[j] = -1;
-      if (n < a.out_rows) orow[j] = (a.flags & ROWS_COMPACT) ? (int64_t)a.rowmap[n] : (int64_t)n;
+      if (n < a.out_rows) orow[j] = (a.flags & ROWS_COMPACT) ? a.rowmap[n] : n;
     }
   };
-  auto need_rows = [&](int64_t (&orow)[L::WN]) {     // the compiler's wait for the loads above lands here
+  auto need_rows = [&](int (&orow)[L::WN]) {     // the compiler's wait for the loads above lands here
 #pragma unroll
     for (int j = 0; j < L::WN; ++j) asm volatile("" : "+v"(orow[j]));
   };
   // Running sum / Gamma / rounding of one finished tile.
-  auto flush = [&](f32x16 (&acc)[L::WM][L::WN], int z, int p, int q, const int64_t (&orow)[L::WN]) {
+  auto flush = [&](f32x16 (&acc)[L::WM][L::WN], int z, int p, int q, const int (&orow)[L::WN]) {
     int flags = a.flags;
     float* __restrict__ accbuf = a.accbuf;
     if (a.n_split > 1) {
       accbuf = a.partial + (int64_t)z * a.partial_stride;
       flags = (flags & ROWS_COMPACT) | WRITE_ACC;
     }
-#pragma unroll
-    for (int j = 0; j < L::WN; ++j) {
-      if (orow[j] < 0) continue;
+    // one 32-row column of blocks straight from the accumulator layout
+    auto direct = [&](f32x16 (&acc)[L::WM][L::WN], int j) {
+      if (orow[j] < 0) return;
       const int n = a.out_row0 + p * L::TILE + L::tile_n(j);
       // this lane's first hidden position; block (i, rq) lies a constant 32 i + 8 rq further on
       const int m0 = q * L::TILE + L::tile_m(0, 0);
       float* __restrict__ arow = accbuf + (int64_t)(n - a.acc_row0) * d + m0;
-      T* __restrict__ orowp = out + orow[j] * d + m0;
+      T* __restrict__ orowp = out + (int64_t)orow[j] * d + m0;
 #pragma unroll
       for (int i = 0; i < L::WM; ++i)
 #pragma unroll
@@ -1184,18 +1184,73 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
           if (flags & WRITE_ACC) *reinterpret_cast<f32x4*>(ap) = v;
           if (flags & WRITE_OUT) {
             // "+ 0.f" turns a -0 product into +0
-            Pack4<T>::store(orowp + c, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f,
-                            v[3] * scale + 0.f);
+            Pack4<T>::store(orowp + c, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f, v[3] * scale + 0.f);
           }
           if (rq == 3) __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
         }
+    };
+    if constexpr (L::TUNED) {
+      // The rounded output: in the accumulator layout a store instruction would touch 32 output rows with 16 bytes each.
+      // As in the recompute step, each wavefront passes 32 rows x 256 bytes at a time through its slice of the free LDS
+      // stage (8-byte slots XOR-ed with the row: conflict-free) and writes whole 256-byte runs, 4 rows per instruction.
+      // It matters where the K loop is short: dW at 500 tokens x 4096 x 128256 807 -> 750 us (the K loops alone take 479),
+      // the step at 1000 x 2048 x 100000 1616 -> 1528 us; at 8192 tokens it changes nothing.  The fp32 sums gain nothing
+      // from the detour (32 bytes per row as they lie; 4096 x 128 x 32000 363 us against 357) and go out directly.
+      static_assert(sizeof(T) == 2 && L::WM == 4 && L::WN == 4, "laid out for bf16 128 x 128 wave tiles");
+      const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      char* stage = lds + L::FREE_LDS_OFFSET + wave * 8192;
+      const int wrow = lane & 31, whalf = lane >> 5;              // writer: output row of the piece, lane half
+      const int rrow = lane >> 4, rchunk = lane & 15;             // reader: row within a group of 4, 16-byte chunk
+      const int mw = q * L::TILE + (wave >> 1) * 128;             // first hidden position of the wavefront's columns
+      // output row of piece row r: rows of dW follow each other, rows of dH go where the compact rows came from
+      auto row_of = [&](int j, int r) -> int {
+        if constexpr (OPS == OPS_DH_TR) return __shfl(orow[j], r, 64);
+        const int n = a.out_row0 + p * L::TILE + (wave & 1) * 128 + j * 32 + r;
+        return n < a.out_rows ? n : -1;
+      };
+      if (mw >= d) return;                                        // all of the wavefront's columns lie past the hidden size
+#pragma unroll
+      for (int j = 0; j < L::WN; ++j) {
+        if (!(flags & (READ_ACC | WRITE_ACC))) {
+          // Gamma applied, rounded, out: 32 rows x 128 positions of 2 bytes ("+ 0.f" turns a -0 product into +0)
+#pragma unroll
+          for (int i = 0; i < L::WM; ++i)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+              float v[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = L::acc_get(acc[i][j], rq * 4 + e) * scale + 0.f;
+              uint2 packed;
+              packed.x = f32x2_to_bf16x2_bits(v[0], v[1]);
+              packed.y = f32x2_to_bf16x2_bits(v[2], v[3]);
+              const int slot = ((i * 4 + rq) * 2 + whalf) ^ wrow;
+              *reinterpret_cast<uint2*>(stage + wrow * 256 + slot * 8) = packed;
+              if (rq == 3) __builtin_amdgcn_sched_barrier(0);     // one 32x32 block at a time in VGPRs
+            }
+          const int m = mw + rchunk * 8;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const int r = k * 4 + rrow;
+            u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * 256 + ((rchunk ^ (r >> 1)) * 16));
+            if (rrow & 1) v = u32x4{v[2], v[3], v[0], v[1]};      // r is odd exactly when rrow is
+            const int row = row_of(j, r);
+            if (row >= 0 && m < d) *reinterpret_cast<u32x4*>(out + (int64_t)row * d + m) = v;
+          }
+        } else {
+          // fp32 running sums and K slices go out as they lie, 16 bytes per lane
+          direct(acc, j);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < L::WN; ++j) direct(acc, j);
     }
   };
 
   f32x16 acc[L::WM][L::WN];
   int z, p, q, k0, k_elems;
   place(b, z, p, q, k0, k_elems);
-  int64_t orow[L::WN];
+  int orow[L::WN];
   if constexpr (OPS == OPS_KC) {
     // one item per workgroup: this main loop has nothing to request ahead
     L::run(A + k0, lda * (int64_t)sizeof(T), q * L::TILE, d, B + k0, ldb * (int64_t)sizeof(T), p * L::TILE, a.b_rows,
@@ -1244,7 +1299,7 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
       const int b_next = b + gridDim.x;
       const bool more = b_next < total;
       int z_next = 0, p_next = 0, q_next = 0, k0_next = 0, k_next = 0;
-      int64_t orow_next[L::WN];
+      int orow_next[L::WN];
       need_rows(orow);
       if (more) {
         place(b_next, z_next, p_next, q_next, k0_next, k_next);
