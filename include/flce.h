@@ -115,7 +115,7 @@ const char* flce_status_string(flce_status s);
  *             + fp32 running sums N * d (more than one vocabulary chunk) and Vc * d (more than one row chunk)
  *             + fp32 K-slice tiles when a contraction launch is split (small N or small d), or when the output-row
  *               tiles of its last, mostly empty round are launched on their own with K in slices (at most 64 MiB);
- *             the generic loop (bf16 with d % 32 != 0) adds transposed copies of a W chunk and of G; fp32 reads all three
+ *             the generic loop (bf16 beyond a descriptor's reach) adds transposed copies of a W chunk and of G; fp32 reads all three
  *             where they lie (one copy of the counted rows of H).
  *   Beyond the cap the size grows like c1 * (N + V) * d + c2 * N + c3: no N * V term.  flce_plan_describe
  *   prints the staging bytes of a shape.

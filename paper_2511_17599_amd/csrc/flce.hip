@@ -83,6 +83,7 @@ struct Plan {
   int64_t ld_v, ld_n;      // elements per row of the buffers whose rows run over a vocabulary / row chunk: the
                            // chunk's extent plus 64, so that rows never lie a power of two apart
   bool fast;               // tuned bf16 loop: W, Hc and G read in place by the contractions
+  bool ragged;             // its form for hidden sizes that are no multiple of a K step's 32 elements
   bool hkr;                // forward / recompute read a pre-tiled copy of H (tuned loop, unless the caller rules the copy out)
   int split_dh, split_dw;  // K slices of the dH / dW contraction launches (1 = unsplit)
   int64_t off_Hc, off_rowmap, off_tgt, off_lsec, off_gamc, off_HT, off_WT, off_G, off_GT, off_dHacc, off_dWacc, off_partial, bwd_bytes;
@@ -107,8 +108,7 @@ TailSplit tail_split(int64_t out_row_tiles, int64_t n_mt, int n_split, int64_t k
   return {(int)rows, (int)slices};
 }
 
-// The tuned bf16 loop needs K extents that are multiples of 32 elements and every tile's address
-// window within reach of a buffer descriptor: offsets and the record count are unsigned 32-bit, and
+// The tuned bf16 loop needs every tile's address window within reach of a buffer descriptor: offsets and the record count are unsigned 32-bit, and
 // the zero-filled overshoot of a last K stage (up to 32 rows) must not wrap 2^32.
 // The `generic` knob forces the generic loop everywhere.
 bool window_ok(int64_t k_rows, int64_t ld_bytes) { return (k_rows + 32) * ld_bytes < ((int64_t)1 << 32); }
@@ -116,7 +116,7 @@ bool fast_loop_ok(const Plan& p, const Tuning& tn) {
   if (p.esize != 2 || tn.generic) return false;
   const int64_t vc = (int64_t)p.vc_tiles * TILE, nc = (int64_t)p.nc_tiles * TILE;
   const int64_t ld_hw = p.d * 2, ld_g = p.ld_v * 2;
-  return p.d % 32 == 0 && window_ok(257, ld_hw) && window_ok(257, ld_g) &&      // K-contiguous tiles
+  return window_ok(257, ld_hw) && window_ok(257, ld_g) &&      // K-contiguous tiles
          window_ok(vc, ld_hw) && window_ok(nc, ld_hw) && window_ok(nc, ld_g);   // K over memory rows
 }
 
@@ -200,6 +200,7 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.ld_v = vc_pad + 64;
   p.ld_n = nc_pad + 64;
   p.fast = fast_loop_ok(p, tn);
+  p.ragged = p.fast && d % 32 != 0;
   p.hkr = allow_h_copy && p.fast;
   p.fwd_bytes = fwd_fixed + (p.hkr ? align_up(packed_block_offset(p.n_rb, (int)d), ALIGN) : 0);
   o = ALIGN;
@@ -312,8 +313,8 @@ hipError_t set_lds_allowances() {
     if ((e = allow_big_lds(fwd_tiles_kernel<T, L, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, true, true>, L::LDS)) != hipSuccess) return e;
-    if ((e = allow_big_lds(contract_kernel<T, L, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
-    if ((e = allow_big_lds(contract_kernel<T, L, OPS_DW_TR>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(contract_kernel<T, FastLoop<false>, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(contract_kernel<T, FastLoop<false>, OPS_DW_TR>, L::LDS)) != hipSuccess) return e;
   } else {
     if ((e = allow_big_lds(recompute_kernel<T, L, false>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, false, true>, L::LDS)) != hipSuccess) return e;
@@ -579,8 +580,8 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     auto launch = [&](const ContractArgs<T>& x) {
       if constexpr (L::TUNED) {
         const int grid = std::min(x.n_nt * x.n_mt * x.n_split, NUM_CU);
-        if (is_dw) contract_kernel<T, L, OPS_DW_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
-        else contract_kernel<T, L, OPS_DH_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
+        if (is_dw) contract_kernel<T, FastLoop<false>, OPS_DW_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
+        else contract_kernel<T, FastLoop<false>, OPS_DH_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
       } else if constexpr (L::TRANSPOSING) {
         const int grid = x.n_nt * x.n_mt * x.n_split;
         if (is_dw) contract_kernel<T, L, OPS_DW_F32><<<grid, L::THREADS, L::LDS, st>>>(x);
@@ -748,10 +749,10 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
   const int mean = reduction == FLCE_REDUCE_MEAN;
   char* ws = static_cast<char*>(workspace);
   if (dt == FLCE_DTYPE_BF16) {
+    if (p.ragged)
+      return flce::forward_t<flce::bf16_t, uint16_t, flce::FastLoop<true>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
     if (p.fast)
-      return flce::forward_t<flce::bf16_t, uint16_t, flce::FastLoop>(p, H, W, targets, ignore_index, mean, loss_out,
-                                                                     lse_out, ws, st, slice, m_out, a_out, zt_out,
-                                                                     rows, so);
+      return flce::forward_t<flce::bf16_t, uint16_t, flce::FastLoop<false>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
     return flce::forward_t<flce::bf16_t, uint16_t, flce::GenericLoop>(
         p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
   }
@@ -780,10 +781,10 @@ static flce_status backward_impl(const void* H, const void* W, const int64_t* ta
   const int mean = reduction == FLCE_REDUCE_MEAN;
   char* ws = static_cast<char*>(workspace);
   if (dt == FLCE_DTYPE_BF16) {
+    if (p.ragged)
+      return flce::backward_t<flce::bf16_t, uint16_t, flce::FastLoop<true>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
     if (p.fast)
-      return flce::backward_t<flce::bf16_t, uint16_t, flce::FastLoop>(p, H, W, targets, lse, ignore_index, mean,
-                                                                      grad_loss, dH_out, dW_out, ws, st, slice,
-                                                                      rows);
+      return flce::backward_t<flce::bf16_t, uint16_t, flce::FastLoop<false>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
     return flce::backward_t<flce::bf16_t, uint16_t, flce::GenericLoop>(
         p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
   }

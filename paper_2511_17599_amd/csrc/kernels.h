@@ -32,14 +32,14 @@
 
 namespace flce {
 
-// Byte offset of row block rb in a pre-tiled copy of a matrix with d columns: the block's d / 32 images of 16 KiB
+// Byte offset of row block rb in a pre-tiled copy of a matrix with d columns: the block's ceil(d / 32) images of 16 KiB
 // plus a skew, so that the blocks do not start a power of two apart (the workgroups resident at one time stream
 // several dozen blocks side by side, and blocks exactly 2^k bytes apart land on the same DRAM banks).
 #ifndef FLCE_PACK_SKEW
 #define FLCE_PACK_SKEW 17408
 #endif
 __host__ __device__ __forceinline__ int64_t packed_block_offset(int rb, int d) {
-  return (int64_t)rb * ((int64_t)d * (TILE * 2) + FLCE_PACK_SKEW);
+  return (int64_t)rb * ((int64_t)((d + 31) / 32 * 32) * (TILE * 2) + FLCE_PACK_SKEW);
 }
 // The same for the transposed pre-tiled copy of a matrix with `rows` rows (a multiple of 256): byte offset of the
 // block of column tile q (256 columns), which holds rows / 32 images.
@@ -116,7 +116,10 @@ struct F32Loop {          // fp32; T x T tiles, 4 wavefronts 2 x 2, two workgrou
   };
 };
 
-struct FastLoop {         // bf16, K a multiple of 32 elements; 4 wavefronts 2 x 2, global -> LDS DMA
+// RAGGED: the hidden size is a multiple of 8 but not of 32 (the K extent of the forward and the recompute; the
+// contractions' K extents are whole tiles, they always run with the plain form).
+template <bool RAGGED>
+struct FastLoop {         // bf16; 4 wavefronts 2 x 2, global -> LDS DMA
   static constexpr int TILE = flce::TILE, THREADS = fast::THREADS, WM = fast::WM, WN = fast::WN, LDS = fast::LDS_BYTES;
   static constexpr bool TRANSPOSING = true, TUNED = true;
   // LDS that post-processing may use while the next tile's first three K stages are being filled: the fourth stage
@@ -132,7 +135,7 @@ struct FastLoop {         // bf16, K a multiple of 32 elements; 4 wavefronts 2 x
   // per 256-row block and K step the 16 KiB image of its LDS tile, see pack_rows_kernel), and that copy is read.
   template <bool BP>
   struct Stream {
-    fast::Pipe<fast::KC, BP ? fast::PK : fast::KC> pipe;
+    fast::Pipe<fast::KC, BP ? fast::PK : fast::KC, true, fast::WM, fast::NS, RAGGED> pipe;
     __device__ __forceinline__ void start(const bf16_t* A, int64_t lda_bytes, int a_row0, int a_rows, const bf16_t* B,
                                           const bf16_t* Bp, int64_t ldb_bytes, int b_row0, int b_rows, int k_elems,
                                           char* lds) {
@@ -727,11 +730,11 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const U* __restrict__ H,
   }
 }
 
-// The pre-tiled copy of a row-major bf16 matrix X[rows][d] (d a multiple of 32) that the tuned main loop reads as
+// The pre-tiled copy of a row-major bf16 matrix X[rows][d] (d a multiple of 8) that the tuned main loop reads as
 // its B operand: for every block of 256 rows and every K step of 32 elements, the 16 KiB image of that step's LDS
 // tile, images of one row block following each other in K order:
 //   P[(rb * d / 32 + kt) * 16 KiB + r * 64 + 16 * pos] = the 16 bytes X[rb * 256 + r][kt * 32 + 8 * (pos ^ (r / 4) % 4) ...]
-// (the main loop's K-contiguous LDS tile, 256 rows of 64 bytes with its chunk swizzle), rows past the end as zeros.
+// (the main loop's K-contiguous LDS tile, 256 rows of 64 bytes with its chunk swizzle), rows and columns past the end as zeros.
 // pack_rows_store: one thread's part, the 64 bytes of row r of row block rb at K step kt.
 __device__ __forceinline__ void pack_rows_store(const u32x4 (&chunk)[4], char* __restrict__ P, int rb, int kt, int d, int r) {
   u32x4* dst = reinterpret_cast<u32x4*>(P + packed_block_offset(rb, d) + (int64_t)kt * fast::OPER + r * 64);
@@ -745,15 +748,15 @@ __device__ __forceinline__ void pack_rows_store(const u32x4 (&chunk)[4], char* _
 __global__ __launch_bounds__(256) void pack_rows_kernel(const char* __restrict__ X, int rows, int d,
                                                         char* __restrict__ P) {
   const int row = blockIdx.x * 64 + (threadIdx.x >> 2), kt = blockIdx.y * 4 + (threadIdx.x & 3);
-  const int KT = d / fast::BK;
-  if (kt >= KT) return;
+  if (kt * fast::BK >= d) return;
   u32x4 chunk[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) chunk[c] = u32x4{0u, 0u, 0u, 0u};
   if (row < rows) {
     const u32x4* src = reinterpret_cast<const u32x4*>(X + ((int64_t)row * d + kt * fast::BK) * 2);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) chunk[c] = src[c];
+    for (int c = 0; c < 4; ++c)
+      if (kt * fast::BK + c * 8 < d) chunk[c] = src[c];
   }
   pack_rows_store(chunk, P, row / TILE, kt, d, row % TILE);
 }
@@ -788,18 +791,20 @@ __global__ __launch_bounds__(256) void prep_rows_tiled_kernel(const char* __rest
   u32x4 chunk[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) chunk[i] = u32x4{0u, 0u, 0u, 0u};
-  if (col0 < d) {                                           // d is a multiple of 32: a group is inside or outside
+  if (col0 < d) {                                           // d is a multiple of 8: a 16-byte chunk is inside or outside
     if (n >= 0) {
       const u32x4* src = reinterpret_cast<const u32x4*>(H + ((int64_t)n * d + col0) * 2);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) chunk[i] = src[i];
+      for (int i = 0; i < 4; ++i)
+        if (col0 + i * 8 < d) chunk[i] = src[i];
     }
     if (HcP) pack_rows_store(chunk, HcP, c / TILE, col0 / fast::BK, d, c % TILE);
     bool oor;
     if (c < N && !target_counts(y[c], ignore_index, V_total, oor)) {
       u32x4* z = reinterpret_cast<u32x4*>(dH + ((int64_t)c * d + col0) * 2);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) z[i] = u32x4{0u, 0u, 0u, 0u};
+      for (int i = 0; i < 4; ++i)
+        if (col0 + i * 8 < d) z[i] = u32x4{0u, 0u, 0u, 0u};
     }
   }
 #pragma unroll

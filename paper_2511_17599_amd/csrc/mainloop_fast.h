@@ -33,7 +33,7 @@
 //     with one wavefront per SIMD a burst of memory instructions stalls the MFMA
 //     stream.
 //
-// Requires the K extent to be a multiple of 32 elements and offsets inside one tile's
+// Requires the K extent to be a multiple of 32 elements (of 8 in the RAGGED form) and offsets inside one tile's
 // address window within 2^32 bytes (unsigned 32-bit buffer offsets); the generic loop in tile_mma.h covers everything else.
 #pragma once
 #include <type_traits>
@@ -106,7 +106,7 @@ __device__ __forceinline__ u32x4 make_rsrc(const Operand& s, int k_elems) {
   uint32_t n = 0;
   const char* b = s.base;
   if (LAYOUT == PK) {
-    n = (uint32_t)(k_elems / BK) * OPER;
+    n = (uint32_t)((k_elems + BK - 1) / BK) * OPER;
   } else if (LAYOUT == KB) {         // 16 row groups, the last one up to the end of the K extent
     n = (uint32_t)(15 * s.ld_bytes + (int64_t)(k_elems / BK) * 1024);
   } else if (LAYOUT == RB) {         // k_elems / 16 row groups, 8 blocks of the last one
@@ -151,12 +151,18 @@ __device__ __forceinline__ void wait_vm_and_lds() {
 
 // Global -> LDS requests of one operand: REQS per wavefront per stage (4 for a 256-row tile; a K-contiguous tile
 // may also be 128 rows high: 2), 1 KiB each, written linearly into this wavefront's slice of the operand tile.
-template <int LAYOUT, int REQS = 4>
+// RAGGED (K-contiguous layout): K need not be a multiple of a stage's 32 elements, only of 8; the 16-byte chunks of the
+// last stage past the end of K are requested out of the descriptor's range and land as zeros.  (Such shapes ran on the
+// generic loop, with transposed copies of H, W and G: 20597 x 168 x 179711 13.46 -> 9.25 ms per step, 3716 x 136 x 84702
+// 1027 -> 713 us, 500 x 1000 x 30000 271 -> 207 us, same bits.)
+template <int LAYOUT, int REQS = 4, bool RAGGED = false>
 struct Loader {
   static_assert(REQS == 4 || (LAYOUT == KC && REQS == 2), "a half-height tile exists in the K-contiguous layout only");
   u32x4 rs;
   uint32_t v[REQS];       // per-lane byte offsets of the requests (K tile 0); unsigned: a window may reach 2^32 bytes
   uint32_t k_step;        // KC: bytes of K per stage (scalar offset); KR: bytes of 32 K rows (added per lane)
+  int last_kt;            // RAGGED: the last K tile, and whether this lane's chunk of it lies past the end of K (every
+  bool past_end;          // request of a lane takes the same chunk: request rows are a multiple of 16 apart)
   __device__ __forceinline__ void init(const Operand& s, int k_elems) {
     rs = make_rsrc<LAYOUT, 64 * REQS>(s, k_elems);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -180,12 +186,19 @@ struct Loader {
         v[i] = (uint32_t)(krow * s.ld_bytes) + off;
       }
     }
+    if (LAYOUT == KC && RAGGED) {
+      const int chunk = (lane & 3) ^ ((lane >> 4) & 3);
+      last_kt = (k_elems + BK - 1) / BK - 1;
+      past_end = last_kt * BK + chunk * 8 >= k_elems;
+    }
     k_step = LAYOUT == PK ? OPER : LAYOUT == KC ? BK * 2 : LAYOUT == KB ? 1024 : LAYOUT == RB ? (uint32_t)(2 * s.ld_bytes)
                                                                                       : (uint32_t)(BK * s.ld_bytes);
   }
   // request i of K tile kt into `dst` (this wavefront's slice of the operand tile of some stage)
   __device__ __forceinline__ void issue(int i, char* dst, int kt) const {
-    if (kc_like(LAYOUT))
+    if (LAYOUT == KC && RAGGED)   // the whole offset goes through the range check
+      dma16(rs, lds_address(dst + i * 1024), kt == last_kt && past_end ? 0xFFFFFFF0u : v[i] + (uint32_t)kt * k_step, 0);
+    else if (kc_like(LAYOUT))
       dma16(rs, lds_address(dst + i * 1024), v[i], (uint32_t)kt * k_step);
     else   // the K advance moves to other rows: keep it in the per-lane offset, which the range check covers
       dma16(rs, lds_address(dst + i * 1024), v[i] + (uint32_t)kt * k_step, 0);
@@ -252,7 +265,10 @@ __device__ __forceinline__ void read_frag(bf16x8 (&f)[4], const FragAddr<LAYOUT,
 // AM = 32-row blocks of A per wavefront: 4 is the 256 x 256 tile above; 2 halves the A tile (128 rows, K-contiguous
 // only), i.e. a 128 x 256 tile with 128 accumulators per lane, which lets two workgroups share a CU (with NSTAGES = 3
 // a workgroup then needs 72 KiB of LDS).  `acc` has AM x 4 blocks.
-template <int LA, int LB, bool WITH_MFMA = true, int AM = WM, int NSTAGES = NS>
+//
+// RAGGED: K is a multiple of 8 elements, K-contiguous operands have it as their extent and a pre-tiled operand is padded
+// with zeros to whole stages.
+template <int LA, int LB, bool WITH_MFMA = true, int AM = WM, int NSTAGES = NS, bool RAGGED = false>
 struct Pipe {
   static_assert(AM == 4 || (AM == 2 && LA == KC), "a half-height A tile exists in the K-contiguous layout only");
   static constexpr int REQS_A = AM;                    // requests per wavefront per stage, A (1 KiB each)
@@ -261,14 +277,14 @@ struct Pipe {
   static constexpr int LDS_TOTAL = NSTAGES * STAGE_BYTES;
   static constexpr int LOADS = REQS_A + 4;             // requests per wavefront per K tile
   static constexpr int NM = AM * WN;                   // MFMAs per half step
-  Loader<LA, REQS_A> la;
-  Loader<LB> lb;
+  Loader<LA, REQS_A, RAGGED> la;
+  Loader<LB, 4, RAGGED> lb;
   FragAddr<LA, AM> fa;
   FragAddr<LB> fb;
   int KT, lds_wave;
 
   __device__ __forceinline__ void start(const Operand& A, const Operand& B, int k_elems, char* lds) {
-    KT = k_elems / BK;
+    KT = RAGGED ? (k_elems + BK - 1) / BK : k_elems / BK;
     la.init(A, k_elems);
     lb.init(B, k_elems);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
