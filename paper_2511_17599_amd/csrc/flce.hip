@@ -85,6 +85,7 @@ struct Plan {
   bool fast;               // tuned bf16 loop: W, Hc and G read in place by the contractions
   bool ragged;             // its form for hidden sizes that are no multiple of a K step's 32 elements
   bool hkr;                // forward / recompute read a pre-tiled copy of H (tuned loop, unless the caller rules the copy out)
+  bool fwd_copy;           // the forward makes that copy (long enough for it to pay)
   int split_dh, split_dw;  // K slices of the dH / dW contraction launches (1 = unsplit)
   int64_t off_Hc, off_rowmap, off_tgt, off_lsec, off_gamc, off_HT, off_WT, off_G, off_GT, off_dHacc, off_dWacc, off_partial, bwd_bytes;
 };
@@ -202,7 +203,11 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.fast = fast_loop_ok(p, tn);
   p.ragged = p.fast && d % 32 != 0;
   p.hkr = allow_h_copy && p.fast;
-  p.fwd_bytes = fwd_fixed + (p.hkr ? align_up(packed_block_offset(p.n_rb, (int)d), ALIGN) : 0);
+  // The copy takes a launch (5 us) and one pass over H (4 N d bytes at 4 TB/s), and saves the loop about 7 % (2 N d V flops
+  // at 1.3 PFLOP/s): below this it costs more than it gives (585 x 384 x 20040 forward 27.9 us
+  // with it, 25.7 without; 614 x 2496 x 512 step 159 / 152; 2048 x 1024 x 32000, just above the line, level).
+  p.fwd_copy = p.hkr && (double)N * (double)d * (double)V >= 4.6e10 + 9300.0 * (double)N * (double)d;
+  p.fwd_bytes = fwd_fixed + (p.fwd_copy ? align_up(packed_block_offset(p.n_rb, (int)d), ALIGN) : 0);
   o = ALIGN;
   // the counted rows of H: as they are (generic loop), or pre-tiled for the dW contraction (tuned loop)
   p.off_Hc = o;     o = align_up(o + (p.fast ? packed_cols_offset((int)ceil_div(d, TILE), (int)p.npad) : d * p.npad * p.esize), ALIGN);
@@ -398,7 +403,7 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
   const int items = n_rb * p.n_win;
   const int per_launch = L::TUNED ? NUM_CU : items;
   bool hkr = false;
-  if constexpr (L::TUNED) hkr = p.hkr;
+  if constexpr (L::TUNED) hkr = p.fwd_copy;
   T* HT = nullptr;
   if (hkr) {
     if constexpr (L::TUNED) {
