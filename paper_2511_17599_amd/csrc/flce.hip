@@ -87,7 +87,8 @@ struct Plan {
   bool hkr;                // forward / recompute read a pre-tiled copy of H (tuned loop, unless the caller rules the copy out)
   bool fwd_copy;           // the forward makes that copy (long enough for it to pay)
   int split_dh, split_dw;  // K slices of the dH / dW contraction launches (1 = unsplit)
-  int64_t off_Hc, off_rowmap, off_tgt, off_lsec, off_gamc, off_HT, off_WT, off_G, off_GT, off_dHacc, off_dWacc, off_partial, bwd_bytes;
+  bool pair;               // dW and dH of the only chunk go out as one launch
+  int64_t off_Hc, off_rowmap, off_tgt, off_lsec, off_gamc, off_HT, off_WT, off_G, off_GT, off_dHacc, off_dWacc, off_partial, off_partial_dh, bwd_bytes;
 };
 
 // A contraction launch of more than one round of workgroups whose last round would be mostly empty: the output-row
@@ -227,34 +228,55 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   // Split-K for launches with too few output tiles to occupy the CUs (small N or small d): the K
   // extent is cut into slices whose fp32 tiles are summed in slice order by a second kernel.
   const int64_t n_mt = ceil_div(d, p.tile), unit = TILE / p.tile;
-  auto auto_split = [&](int64_t tiles, int64_t k_tiles) -> int {
-    // Time of the launch in units of one K tile of the main loop (K elements = tile edge): rounds of workgroups times
-    // (K tiles of a slice + `ends` for filling the pipeline and writing the tile out), plus, for a split, the launch that
-    // adds the slices and the fp32 tiles written and read back; a split has to win by 5 %.  A K tile takes 6.2 us in
-    // bf16, and at fp32 (two workgroups share a CU) 6.8 us per CU with 128-tiles, 0.85 with 64-tiles.
-    const double ends = p.tile == 64 ? 3.5 : 1.2, launch = p.tile == 64 ? 6.0 : 0.8,
-                 per_tile = p.tile == TILE ? 0.02 : p.tile == 128 ? 0.005 : 0.01;
+  // Time of a contraction launch in units of one K tile of the main loop (K elements = tile edge): rounds of workgroups
+  // times (K tiles of a slice + `ends` for filling the pipeline and writing the tile out), plus, for a split, the launch
+  // that adds the slices and the fp32 tiles written and read back.  A K tile takes 6.2 us in bf16, and at fp32 (two
+  // workgroups share a CU) 6.8 us per CU with 128-tiles, 0.85 with 64-tiles.
+  const double ends = p.tile == 64 ? 3.5 : 1.2, launch = p.tile == 64 ? 6.0 : 0.8,
+               per_tile = p.tile == TILE ? 0.02 : p.tile == 128 ? 0.005 : 0.01;
+  auto split_cost = [&](int64_t tiles, int64_t k_tiles, int sp) {
+    return (double)ceil_div(tiles * sp, NUM_CU) * ((double)ceil_div(k_tiles, sp) + ends) +
+           (sp > 1 ? launch + per_tile * (double)(tiles * sp) : 0.0);
+  };
+  auto auto_split = [&](int64_t tiles, int64_t k_tiles) -> int {     // a split has to win by 5 %
     int best = 1;
-    double best_cost = 0.0;
-    for (int sp = 1; sp <= MAX_SPLIT && sp <= k_tiles; ++sp) {
-      const double cost = (double)ceil_div(tiles * sp, NUM_CU) * ((double)ceil_div(k_tiles, sp) + ends) +
-                          (sp > 1 ? launch + per_tile * (double)(tiles * sp) : 0.0);
-      if (sp == 1 || cost < best_cost * (best == 1 ? 0.95 : 1.0)) { best_cost = cost; best = sp; }
-    }
+    for (int sp = 2; sp <= MAX_SPLIT && sp <= k_tiles; ++sp)
+      if (split_cost(tiles, k_tiles, sp) < split_cost(tiles, k_tiles, best) * (best == 1 ? 0.95 : 1.0)) best = sp;
     return best;
   };
   p.split_dh = tn.splitk_dh;
   p.split_dw = tn.splitk_dw;
-  if (p.split_dh == 0) p.split_dh = auto_split(p.nc_tiles * unit * n_mt, p.vc_tiles * unit);
-  if (p.split_dw == 0) p.split_dw = auto_split(p.vc_tiles * unit * n_mt, p.nc_tiles * unit);
-  p.split_dh = (int)std::min<int64_t>(p.split_dh, p.vc_tiles * unit);
-  p.split_dw = (int)std::min<int64_t>(p.split_dw, p.nc_tiles * unit);
+  const int64_t tiles_dh = p.nc_tiles * unit * n_mt, k_dh = p.vc_tiles * unit;
+  const int64_t tiles_dw = p.vc_tiles * unit * n_mt, k_dw = p.nc_tiles * unit;
+  if (p.split_dh == 0) p.split_dh = auto_split(tiles_dh, k_dh);
+  if (p.split_dw == 0) p.split_dw = auto_split(tiles_dw, k_dw);
+  p.split_dh = (int)std::min<int64_t>(p.split_dh, k_dh);
+  p.split_dw = (int)std::min<int64_t>(p.split_dw, k_dw);
+  // One launch for both: K is cut so that no slice of either is longer than `len` K tiles and all of them together are at
+  // most two rounds of workgroups; taken where that beats one launch after the other, and only while the uncut tiles of
+  // both fit one round (742 x 384 x 4845 102 -> 82 us, 2048 x 512 x 8000 149 -> 126, fp32 849 x 216 x 1732 89 -> 80, the
+  // row preparation without its own scan launch included).
+  p.pair = false;
+  if (p.n_vch == 1 && p.n_nch == 1 && (p.fast || p.tile != TILE) && tn.splitk_dh == 0 && tn.splitk_dw == 0 &&
+      tiles_dh + tiles_dw <= NUM_CU) {
+    double best = 0.97 * (split_cost(tiles_dh, k_dh, p.split_dh) + split_cost(tiles_dw, k_dw, p.split_dw) + launch);
+    for (int64_t len = std::max(k_dh, k_dw); len >= 1; --len) {
+      const int64_t sh = ceil_div(k_dh, len), sw = ceil_div(k_dw, len);
+      const int64_t wgs = tiles_dh * sh + tiles_dw * sw;
+      if (sh > MAX_SPLIT || sw > MAX_SPLIT || wgs > 2 * NUM_CU) break;
+      const double cost = (double)ceil_div(wgs, NUM_CU) * ((double)len + ends) + (sh > 1 || sw > 1 ? launch : 0.0) +
+                          per_tile * (double)((sh > 1 ? tiles_dh * sh : 0) + (sw > 1 ? tiles_dw * sw : 0));
+      if (cost < best) { best = cost; p.pair = true; p.split_dh = (int)sh; p.split_dw = (int)sw; }
+    }
+  }
   p.off_partial = o;
   {
-    int64_t bytes = 0;
-    if (p.split_dh > 1) bytes = std::max(bytes, (int64_t)p.split_dh * nc_pad * d * 4);
-    if (p.split_dw > 1) bytes = std::max(bytes, (int64_t)p.split_dw * vc_pad * d * 4);
-    if (p.fast) {
+    const int64_t dh_bytes = p.split_dh > 1 ? align_up((int64_t)p.split_dh * nc_pad * d * 4, ALIGN) : 0;
+    int64_t bytes = p.split_dw > 1 ? align_up((int64_t)p.split_dw * vc_pad * d * 4, ALIGN) : 0;
+    // one after the other they share the buffer, side by side they do not
+    p.off_partial_dh = p.pair ? o + bytes : o;
+    bytes = p.pair ? bytes + dh_bytes : std::max(bytes, dh_bytes);
+    if (p.fast && !p.pair) {
       // tails of the launches that occur: full chunks and the last (shorter) chunk of either direction
       const int64_t v_last = p.n_vt - (int64_t)(p.n_vch - 1) * p.vc_tiles, n_last = p.n_rb - (int64_t)(p.n_nch - 1) * p.nc_tiles;
       for (const int64_t vt : {(int64_t)p.vc_tiles, v_last})
@@ -320,12 +342,14 @@ hipError_t set_lds_allowances() {
     if ((e = allow_big_lds(recompute_kernel<T, L, true, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(contract_kernel<T, FastLoop<false>, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(contract_kernel<T, FastLoop<false>, OPS_DW_TR>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(contract_pair_kernel<T, FastLoop<false>, OPS_DW_TR, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
   } else {
     if ((e = allow_big_lds(recompute_kernel<T, L, false>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, false, true>, L::LDS)) != hipSuccess) return e;
     if constexpr (L::TRANSPOSING) {
       if ((e = allow_big_lds(contract_kernel<T, L, OPS_DH_F32>, L::LDS)) != hipSuccess) return e;
       if ((e = allow_big_lds(contract_kernel<T, L, OPS_DW_F32>, L::LDS)) != hipSuccess) return e;
+      if ((e = allow_big_lds(contract_pair_kernel<T, L, OPS_DW_F32, OPS_DH_F32>, L::LDS)) != hipSuccess) return e;
     } else {
       if ((e = allow_big_lds(contract_kernel<T, L, OPS_KC>, L::LDS)) != hipSuccess) return e;
     }
@@ -491,20 +515,33 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
 
   {
     ProfScope ps(FLCE_PROF_BWD_PREP, st);
-    compact_targets_kernel<<<1, 1024, 0, st>>>(y, N, V, slice.V_total, slice.v_begin, ignore_index, npad, rowmap,
-                                               tgt_c, hdr);
-    // lse and Gamma per compact row, zero rows of dH, and the counted rows of H packed together, twice: with the
-    // generic loop as they are (Hc) and transposed [d][npad] (the dW contraction's K-contiguous operand); with the
-    // tuned loop pre-tiled for the recompute (in HT's place) and pre-tiled the other way round for dW (in Hc's place)
-    if constexpr (L::TUNED)
-      prep_rows_tiled_kernel<<<dim3((unsigned)(p.npad / 32), (unsigned)n_mt), 256, 0, st>>>(
-          static_cast<const char*>(H), d, rowmap, npad, reinterpret_cast<char*>(HT), reinterpret_cast<char*>(Hc), lse,
-          lse_c, rows.grad_rows, gam_c, y, N, slice.V_total, ignore_index, static_cast<char*>(dH));
-    else
-      prep_rows_kernel<U><<<dim3((unsigned)(p.npad / 64), (unsigned)ceil_div(d, 64)), 256, 0, st>>>(
-          static_cast<const U*>(H), d, rowmap, reinterpret_cast<U*>(Hc),
-          L::TRANSPOSING ? nullptr : reinterpret_cast<U*>(HT), p.npad, lse, lse_c,
-          rows.grad_rows, gam_c, y, N, slice.V_total, ignore_index, static_cast<U*>(dH));
+    const CompactArgs ca{y, N, V, slice.V_total, slice.v_begin, ignore_index, rowmap, tgt_c, hdr};
+    const bool scan = N <= COMPACT_HERE;
+    if (!scan)
+      compact_targets_kernel<<<1, 1024, 0, st>>>(y, N, V, slice.V_total, slice.v_begin, ignore_index, npad, rowmap, tgt_c,
+                                                 hdr);
+    // lse and Gamma per compact row, zero rows of dH, and the counted rows of H packed together: with the tuned loop
+    // pre-tiled for the recompute (in HT's place) and pre-tiled the other way round for dW (in Hc's place); otherwise as
+    // they are (Hc), and with the generic loop also transposed [d][npad] (the dW contraction's K-contiguous operand)
+    if constexpr (L::TUNED) {
+      const dim3 grid((unsigned)(p.npad / 32), (unsigned)n_mt);
+      auto prep = [&](auto kernel) {
+        kernel<<<grid, 256, 0, st>>>(static_cast<const char*>(H), d, npad, reinterpret_cast<char*>(HT),
+                                     reinterpret_cast<char*>(Hc), lse, lse_c, rows.grad_rows, gam_c, ca,
+                                     static_cast<char*>(dH));
+      };
+      if (scan) prep(prep_rows_tiled_kernel<true>);
+      else prep(prep_rows_tiled_kernel<false>);
+    } else {
+      const dim3 grid((unsigned)(p.npad / 64), (unsigned)ceil_div(d, 64));
+      auto prep = [&](auto kernel) {
+        kernel<<<grid, 256, 0, st>>>(static_cast<const U*>(H), d, reinterpret_cast<U*>(Hc),
+                                     L::TRANSPOSING ? nullptr : reinterpret_cast<U*>(HT), p.npad, lse, lse_c,
+                                     rows.grad_rows, gam_c, ca, static_cast<U*>(dH));
+      };
+      if (scan) prep(prep_rows_kernel<U, true>);
+      else prep(prep_rows_kernel<U, false>);
+    }
   }
 
   // With the tuned loop G is staged in blocks of 16 rows x 32 positions (1 KiB), the blocks of a row group one after
@@ -512,6 +549,7 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
   // size the plan reserves (16 rows of ld_v = vc_pad + 64 elements are one block more per group).
   const int64_t g_group_bytes = (vc_pad / 32 + 1) * 1024;
   float* partial = reinterpret_cast<float*>(ws + p.off_partial);
+  float* partial_dh = reinterpret_cast<float*>(ws + p.off_partial_dh);
   // K elements per split-K slice: whole tiles
   auto slice_len = [](int k_elems, int n_split) { return (int)ceil_div(ceil_div(k_elems, L::TILE), n_split) * L::TILE; };
   // argument blocks of the three steps of chunk (vc, nc); `Gb` is the staging buffer of that chunk
@@ -567,16 +605,16 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
       return ContractArgs<T>{static_cast<const T*>(W) + (int64_t)vt0 * L::TILE * d, d, V - vt0 * L::TILE, d, Gb, p.ld_v,
                              n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE,
                              npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(n_vt * L::TILE, p.split_dh),
-                             partial - (int64_t)nt0 * L::TILE * d, nc_pad * d};
+                             partial_dh - (int64_t)nt0 * L::TILE * d, nc_pad * d};
     else if constexpr (L::TUNED)
       return ContractArgs<T>{static_cast<const T*>(W) + (int64_t)vt0 * L::TILE * d, d, V - vt0 * L::TILE, d, Gb, g_group_bytes,
                              n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE, npad,
                              flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(n_vt * L::TILE, p.split_dh),
-                             partial - (int64_t)nt0 * L::TILE * d, nc_pad * d};
+                             partial_dh - (int64_t)nt0 * L::TILE * d, nc_pad * d};
     else
       return ContractArgs<T>{WT, p.ld_v, 0, d, Gb, p.ld_v, n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0,
                              static_cast<T*>(dH), nt0 * L::TILE, npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh,
-                             slice_len(n_vt * L::TILE, p.split_dh), partial - (int64_t)nt0 * L::TILE * d, nc_pad * d};
+                             slice_len(n_vt * L::TILE, p.split_dh), partial_dh - (int64_t)nt0 * L::TILE * d, nc_pad * d};
   };
 
   // One contraction (dW or dH) of a chunk: the launch, its split-K sum if it has one, and with the tuned loop a
@@ -618,6 +656,21 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     launch(tail);
   };
 
+  // dW and dH of the only chunk in one launch, and the slice sums of whichever is cut in another.
+  auto contract_pair = [&](const ContractArgs<T>& w, const ContractArgs<T>& h) {
+    const int wg_w = w.n_nt * w.n_mt * w.n_split, wg_h = h.n_nt * h.n_mt * h.n_split;
+    if constexpr (L::TUNED)
+      contract_pair_kernel<T, FastLoop<false>, OPS_DW_TR, OPS_DH_TR><<<wg_w + wg_h, L::THREADS, L::LDS, st>>>(w, h, wg_w);
+    else if constexpr (L::TRANSPOSING)
+      contract_pair_kernel<T, L, OPS_DW_F32, OPS_DH_F32><<<wg_w + wg_h, L::THREADS, L::LDS, st>>>(w, h, wg_w);
+    auto blocks = [&](const ContractArgs<T>& x) {
+      return x.n_split > 1 ? (int)ceil_div((int64_t)x.n_nt * L::TILE * (d / 4), 256) : 0;
+    };
+    const int bw = blocks(w), bh = blocks(h);
+    if (bw + bh > 0)
+      splitk_reduce_pair_kernel<T><<<bw + bh, 256, 0, st>>>(w, w.n_nt * L::TILE, bw, h, h.n_nt * L::TILE);
+  };
+
   for (int vc = 0; vc < p.n_vch; ++vc) {
     int vt0, n_vt;
     chunk_vt(vc, vt0, n_vt);
@@ -640,6 +693,11 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
           if (rows.grad_rows) recompute_kernel<T, L, false, true><<<grid, L::THREADS, L::LDS, st>>>(rc);
           else recompute_kernel<T, L, false><<<grid, L::THREADS, L::LDS, st>>>(rc);
         }
+      }
+      if (p.pair) {
+        ProfScope ps(FLCE_PROF_CONTRACT_DW, st);       // (both: one launch)
+        contract_pair(dw_args(vc, nc, G), dh_args(vc, nc, G));
+        continue;
       }
       {
         ProfScope ps(FLCE_PROF_CONTRACT_DW, st);
@@ -712,15 +770,15 @@ int flce_plan_describe(int64_t N, int64_t d, int64_t V, flce_dtype dt, char* buf
   // K-split tails of the contraction launches of a full chunk (output-row tiles x slices; 0x1 = none)
   const int64_t n_mt = (d + flce::TILE - 1) / flce::TILE;
   flce::TailSplit th{0, 1}, tw{0, 1};
-  if (p.fast) {
+  if (p.fast && !p.pair) {
     th = flce::tail_split(p.nc_tiles, n_mt, p.split_dh, p.vc_tiles);
     tw = flce::tail_split(p.vc_tiles, n_mt, p.split_dw, p.nc_tiles);
   }
   return std::snprintf(buf, buf_bytes,
                        "flce %s loop=%s h_copy=%d windows=%d vocab_chunks=%dx%d row_chunks=%dx%d splitk_dH=%d splitk_dW=%d "
-                       "tail_dH=%dx%d tail_dW=%dx%d staging_bytes=%lld fwd_ws=%lld bwd_ws=%lld",
+                       "tail_dH=%dx%d tail_dW=%dx%d pair=%d staging_bytes=%lld fwd_ws=%lld bwd_ws=%lld",
                        flce_version(), p.fast ? "tuned" : "generic", p.hkr ? 1 : 0, p.n_win, p.n_vch, p.vc_tiles, p.n_nch,
-                       p.nc_tiles, p.split_dh, p.split_dw, th.rows, th.slices, tw.rows, tw.slices,
+                       p.nc_tiles, p.split_dh, p.split_dw, th.rows, th.slices, tw.rows, tw.slices, p.pair ? 1 : 0,
                        (long long)((int64_t)p.nc_tiles * flce::TILE * p.ld_v * p.esize), (long long)p.fwd_bytes,
                        (long long)p.bwd_bytes);
 }

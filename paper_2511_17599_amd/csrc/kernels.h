@@ -702,30 +702,80 @@ __global__ __launch_bounds__(1024) void compact_targets_kernel(const int64_t* __
   }
 }
 
+// The same scan inside a block of the row preparation (256 threads, N <= COMPACT_HERE rows): every block reads all targets
+// (16 KiB at most, from the L2) and keeps what concerns its own ROWS compact rows c0 .. c0 + ROWS - 1, which saves the
+// launch of compact_targets_kernel (4.5 us).  The blocks named by `owner` also store the map for the kernels that
+// follow, one of them (`first`) the header.
+constexpr int COMPACT_HERE = 2048;
+struct CompactArgs {
+  const int64_t* y; int N, V; int64_t V_total, v_begin, ignore_index;
+  int* rowmap; int* tgt_c; Header* hdr;
+};
+template <int ROWS>
+__device__ __forceinline__ void compact_here(const CompactArgs& a, int c0, bool owner, bool first, int (&row)[ROWS]) {
+  constexpr int U = COMPACT_HERE / 256;
+  __shared__ int cnt[U * 4], bad[U * 4], tgt[ROWS];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int64_t v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) v[u] = a.y[min(u * 256 + t, a.N - 1)];
+  if (t < ROWS) { row[t] = -1; tgt[t] = -1; }
+  int tg[U];
+  uint64_t m[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    bool oor = false;
+    tg[u] = u * 256 + t < a.N ? classify_target_in_slice(v[u], a.ignore_index, a.V_total, a.v_begin, a.V, 0x7FFFFFFF, oor) : -1;
+    m[u] = __ballot(tg[u] >= 0);
+    const bool any = __ballot(oor) != 0ull;
+    if (lane == 0) { cnt[u * 4 + wave] = __popcll(m[u]); bad[u * 4 + wave] = any; }
+  }
+  __syncthreads();
+  int pos = 0, total = 0, any = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    int mine = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) { if (w == wave) mine = total; total += cnt[u * 4 + w]; any |= bad[u * 4 + w]; }
+    pos = mine + __popcll(m[u] & ((1ull << lane) - 1)) - c0;
+    if (tg[u] >= 0 && pos >= 0 && pos < ROWS) { row[pos] = u * 256 + t; tgt[pos] = tg[u]; }
+  }
+  __syncthreads();
+  if (owner && t < ROWS) { a.rowmap[c0 + t] = row[t]; a.tgt_c[c0 + t] = tgt[t]; }
+  if (first && t == 0) {
+    a.hdr->status = any ? 4 : 0;
+    a.hdr->pad0 = 0;
+    a.hdr->n_valid = total;
+    a.hdr->loss_sum = 0.f;
+    a.hdr->arrived = 0;
+  }
+}
+
 // The backward's row preparation, one launch, 64 compact rows x 64 hidden positions per block:
 //   Hc[c][:]  = H[rowmap[c]][:], zero for the padding rows behind the last counted row;
 //   HcT[:][c] = the same transposed, when a main loop reads that copy (HcT != nullptr; ld_t elements per row);
 //   lse_c[c], gam_c[c] = the row's log-sum-exp and (per-row variant) upstream gradient, 0 for padding rows;
 //   dH[n][:]  = exactly +0 for every token n that does not count (the contractions write the counted rows only).
 // U is an unsigned integer type of the element's width (pure data movement).
-template <typename U>
-__global__ __launch_bounds__(256) void prep_rows_kernel(const U* __restrict__ H, int d, const int* __restrict__ rowmap,
-                                                        U* __restrict__ Hc, U* __restrict__ HcT, int64_t ld_t,
+// SCAN: the blocks find their rows themselves (compact_here) instead of reading rowmap.
+template <typename U, bool SCAN>
+__global__ __launch_bounds__(256) void prep_rows_kernel(const U* __restrict__ H, int d, U* __restrict__ Hc,
+                                                        U* __restrict__ HcT, int64_t ld_t,
                                                         const float* __restrict__ lse, float* __restrict__ lse_c,
                                                         const float* __restrict__ grad_rows, float* __restrict__ gam_c,
-                                                        const int64_t* __restrict__ y, int N, int64_t V_total,
-                                                        int64_t ignore_index, U* __restrict__ dH) {
+                                                        CompactArgs ca, U* __restrict__ dH) {
   __shared__ U tile[64][65];
   __shared__ int src_row[64];
   __shared__ int dead[64];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int rb = blockIdx.x * 64, cb = blockIdx.y * 64;
+  if constexpr (SCAN) compact_here(ca, rb, blockIdx.y == 0, blockIdx.x == 0 && blockIdx.y == 0, src_row);
   if (threadIdx.x < 64) {
     const int r = rb + (int)threadIdx.x;               // a compact row, and also token r of the original order
-    const int n = rowmap[r];
+    const int n = SCAN ? src_row[threadIdx.x] : ca.rowmap[r];
     src_row[threadIdx.x] = n;
     bool oor;
-    dead[threadIdx.x] = (r < N && !target_counts(y[r], ignore_index, V_total, oor)) ? 1 : 0;
+    dead[threadIdx.x] = (r < ca.N && !target_counts(ca.y[r], ca.ignore_index, ca.V_total, oor)) ? 1 : 0;
     if (blockIdx.y == 0) {
       lse_c[r] = (n >= 0) ? lse[n] : 0.f;
       if (grad_rows) gam_c[r] = (n >= 0) ? grad_rows[n] : 0.f;
@@ -793,20 +843,27 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const char* __restrict__
 //          the images of one q following each other, block q at packed_cols_offset(q, rows_pad); hidden positions
 //          past d are zeros;
 //   lse_c / gam_c gathered likewise; dH rows of tokens that do not count set to exactly +0.
-__global__ __launch_bounds__(256) void prep_rows_tiled_kernel(const char* __restrict__ H, int d,
-                                                              const int* __restrict__ rowmap, int rows_pad,
+// SCAN: the blocks find their rows themselves (compact_here) instead of reading rowmap.
+template <bool SCAN>
+__global__ __launch_bounds__(256) void prep_rows_tiled_kernel(const char* __restrict__ H, int d, int rows_pad,
                                                               char* __restrict__ HcP, char* __restrict__ HcTP,
                                                               const float* __restrict__ lse, float* __restrict__ lse_c,
                                                               const float* __restrict__ grad_rows,
-                                                              float* __restrict__ gam_c,
-                                                              const int64_t* __restrict__ y, int N, int64_t V_total,
-                                                              int64_t ignore_index, char* __restrict__ dH) {
+                                                              float* __restrict__ gam_c, CompactArgs ca,
+                                                              char* __restrict__ dH) {
   __shared__ __align__(16) uint16_t tile[32][TILE + 8];     // 528-byte rows: a column read touches every bank once
   const int kt = blockIdx.x, q = blockIdx.y;
   const int rr = threadIdx.x >> 3, g = threadIdx.x & 7;    // row of the K step, group of 32 hidden positions
   const int c = kt * 32 + rr;                               // compact row c, and also token c of the original order
   const int col0 = q * TILE + g * 32;
-  const int n = rowmap[c];
+  int n;
+  if constexpr (SCAN) {
+    __shared__ int src_row[32];
+    compact_here(ca, kt * 32, q == 0, kt == 0 && q == 0, src_row);
+    n = src_row[rr];
+  } else {
+    n = ca.rowmap[c];
+  }
   if (q == 0 && g == 0) {
     lse_c[c] = (n >= 0) ? lse[n] : 0.f;
     if (grad_rows) gam_c[c] = (n >= 0) ? grad_rows[n] : 0.f;
@@ -823,7 +880,7 @@ __global__ __launch_bounds__(256) void prep_rows_tiled_kernel(const char* __rest
     }
     if (HcP) pack_rows_store(chunk, HcP, c / TILE, col0 / fast::BK, d, c % TILE);
     bool oor;
-    if (c < N && !target_counts(y[c], ignore_index, V_total, oor)) {
+    if (c < ca.N && !target_counts(ca.y[c], ca.ignore_index, ca.V_total, oor)) {
       u32x4* z = reinterpret_cast<u32x4*>(dH + ((int64_t)c * d + col0) * 2);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -1138,12 +1195,12 @@ struct ContractArgs {
   int n_split, k_split; float* partial; int64_t partial_stride;
 };
 
-// With the tuned loop a launch has at most 256 workgroups; workgroup b takes work items b, b + gridDim.x, ... (an
+// With the tuned loop a launch has at most 256 workgroups; workgroup b takes work items b, b + n_wg, ... (an
 // item = one output tile of one K slice) and requests the first K stages of its next item before it writes out the
 // current one, as the recompute step does.
-template <typename T, typename L, int OPS>
-__global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a) {
-  extern __shared__ __align__(16) char lds[];
+// ONE: there are as many workgroups as items.
+template <typename T, typename L, int OPS, bool ONE = false>
+__device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n_wg, char* lds) {
   const T* __restrict__ A = a.A; const T* __restrict__ B = a.B;
   const int64_t lda = a.lda, ldb = a.ldb;
   const int d = a.d;
@@ -1156,7 +1213,7 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
   const int tiles = n_nt * a.n_mt;
   const int n_split = max(1, a.n_split);
   const int total = tiles * n_split;
-  int b = blockIdx.x;
+  int b = wg;
   if (b >= total) return;
   int k_all = a.k_elems;
   if (a.flags & K_COMPACT) k_all = max(0, min(k_all, (nv - a.k_start + L::TILE - 1) / L::TILE * L::TILE));
@@ -1324,7 +1381,12 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
     start(p, q, k0, k_elems);
     for (;;) {
       pipe.run(lds, acc);
-      const int b_next = b + gridDim.x;
+      if constexpr (ONE) {
+        need_rows(orow);
+        flush(acc, z, p, q, orow);
+        return;
+      }
+      const int b_next = b + n_wg;
       const bool more = b_next < total;
       int z_next = 0, p_next = 0, q_next = 0, k0_next = 0, k_next = 0;
       int orow_next[L::WN];
@@ -1344,13 +1406,28 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
   }
 }
 
+template <typename T, typename L, int OPS>
+__global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a) {
+  extern __shared__ __align__(16) char lds[];
+  contract<T, L, OPS>(a, blockIdx.x, gridDim.x, lds);
+}
+
+// dW and dH of one chunk side by side: the first wg_w workgroups take dW's items, the others dH's.  For problems whose
+// output tiles (K slices included) fit the chip together: see pair_splits on the host side.
+template <typename T, typename L, int OPS_W, int OPS_H>
+__global__ __launch_bounds__(L::THREADS) void contract_pair_kernel(ContractArgs<T> w, ContractArgs<T> h, int wg_w) {
+  extern __shared__ __align__(16) char lds[];
+  if ((int)blockIdx.x < wg_w) contract<T, L, OPS_W, true>(w, blockIdx.x, wg_w, lds);
+  else contract<T, L, OPS_H, true>(h, (int)blockIdx.x - wg_w, (int)gridDim.x - wg_w, lds);
+}
+
 // Second half of a split-K contraction: one thread per four output elements; adds the K
 // slices in slice order (fixed), then the running sum / Gamma / rounding exactly as the
 // unsplit epilogue would.  Memory bound; the loads of eight slices are in flight together.
 template <typename T>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(ContractArgs<T> a, int launch_rows) {
+__device__ __forceinline__ void splitk_reduce(const ContractArgs<T>& a, int launch_rows, int block) {
   const int d4 = a.d / 4;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = (int64_t)block * 256 + threadIdx.x;
   const int row = (int)(i / d4), m = (int)(i - (int64_t)row * d4) * 4;
   const int n = a.out_row0 + row;
   if (row >= launch_rows || n >= a.out_rows) return;
@@ -1381,6 +1458,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(ContractArgs<T> a, i
   if (a.flags & WRITE_OUT)
     Pack4<T>::store(a.out + orow * a.d + m, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f,
                     v[3] * scale + 0.f);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(ContractArgs<T> a, int launch_rows) {
+  splitk_reduce(a, launch_rows, blockIdx.x);
+}
+// The slice sums of dW (the first blocks_w blocks) and dH in one launch.
+template <typename T>
+__global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(ContractArgs<T> w, int rows_w, int blocks_w,
+                                                                 ContractArgs<T> h, int rows_h) {
+  if ((int)blockIdx.x < blocks_w) splitk_reduce(w, rows_w, blockIdx.x);
+  else splitk_reduce(h, rows_h, (int)blockIdx.x - blocks_w);
 }
 
 // Alg. 4, scalar branch: out = Gamma * in, elementwise, Gamma from the header's n_valid.
