@@ -72,7 +72,7 @@ struct Plan {
   int64_t N, d, V;
   int esize;
   int n_rb, n_vt;          // 256-row tiles of tokens / vocabulary
-  int tile;                // output tile edge of the main loop (fp32: 128 or 64)
+  int tile, fwd_tile;      // output tile edge of the main loop, backward and forward (bf16: 256 or 128, fp32: 128 or 64)
   int64_t npad;
   // forward
   int n_win;
@@ -126,6 +126,7 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   if (N <= 0 || d <= 0 || V <= 0 || (d % 8) != 0) return false;
   if (N > 0x7FFFFF00ll || V > 0x7FFFFF00ll || d > (1 << 24)) return false;
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return false;
+  const Tuning tn = tuning();
   p.N = N; p.d = d; p.V = V;
   p.esize = dt == FLCE_DTYPE_BF16 ? 2 : 4;
   p.n_rb = (int)ceil_div(N, TILE);
@@ -135,12 +136,29 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   // 64 tiles of 128: 77 us with 64-row tiles against 118; 1024 x 512 x 4096, 256 tiles: 211 / 220; 1000 x 256 x 6400, 400
   // tiles: 190 / 185; 2048 x 256 x 16000, 2000 tiles: 715 / 586).
   if (dt == FLCE_DTYPE_F32) p.tile = ceil_div(N, 128) * ceil_div(V, 128) < 320 ? 64 : 128;
+  p.fwd_tile = p.tile;
+  const bool f32 = dt == FLCE_DTYPE_F32;
+  // bf16: 256-row tiles are the faster loop (1.4 PFLOP/s against 0.8 with 128-row ones, which move twice the bytes per
+  // flop), but one of them keeps a CU busy for K / 32 x 0.78 us + the work at its end, and where there are too few of them,
+  // or K is short, the 128-row ones with two workgroups per CU are done earlier.  Times in us, fitted over 29 shapes from
+  // 256 x 1024 x 2048 to 9588 x 128 x 16317; `ends` is what a tile costs beyond its K steps, and very long K loops of
+  // several rounds fall back a little further (331 x 3136 x 102294).  Forward + backward with 256- and by this rule:
+  // 614 x 2496 x 512 135 -> 65 us, 742 x 384 x 4845 79 / 52, 357 x 1408 x 10140 139 / 98, 4730 x 320 x 4151 137 / 106,
+  // 5435 x 104 x 18745 263 / 203, 18786 x 128 x 76178 3074 / 2755; 59 random shapes 1.13x and 1.11x, at worst 0.99x.
+  const double steps = (double)ceil_div(d, 32);
+  auto small_waves = [](int64_t tiles) {        // tiles of 128 in sequence on a CU; one alone is slower than half of two
+    return tiles <= NUM_CU ? 1.3 : 2.0 * (double)ceil_div(tiles, 2 * NUM_CU);
+  };
+  const int64_t t256 = ceil_div(N, 256) * ceil_div(V, 256), t128 = ceil_div(N, 128) * ceil_div(V, 128);
+  auto logits_us = [&](int tile, double ends256, double ends128) {
+    return tile == TILE ? (double)ceil_div(t256, NUM_CU) * (0.775 * steps + ends256) : small_waves(t128) * (0.28 * steps + 0.12 * std::max(0.0, steps - 64.0) + ends128);
+  };
+  if (!f32 && !tn.generic && logits_us(128, 6.5, 0.9) < 0.95 * logits_us(TILE, 6.5, 0.9)) p.fwd_tile = 128;
   p.npad = (int64_t)p.n_rb * TILE;
 
   // Windows (Section 3.2.1): enough (row block, window) workgroups to cover the CUs.
   // At least 4, so that the 32 workgroups resident on one XCD are 8 row blocks x 4 windows and
   // share both operands through that XCD's L2 (one window would stream every H block from HBM).
-  const Tuning tn = tuning();
   const int cover = (int)std::min<int64_t>(std::max<int64_t>(4, ceil_div(NUM_CU, p.n_rb)), p.n_vt);
   p.n_win = cover;
   int part_windows = cover;                 // what the partials are sized for
@@ -153,13 +171,15 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
     // one alone leaves about a fifth of it unused.  One more than a round is what this avoids: 13 row blocks x 20 windows
     // were 260 items, the last 4 of them a launch as long as the first 256 (3300 x 2048 x 65536 forward: 1187 us, with 19
     // windows 743).  The callers that cannot pass a workspace, and fp32, keep to the partials of `cover` windows.
-    const int64_t rb = ceil_div(N, p.tile), vt = ceil_div(V, p.tile);
+    const int64_t rb = ceil_div(N, p.fwd_tile), vt = ceil_div(V, p.fwd_tile);
+    const double fill = 8.0 / (0.0242 * (double)d);
     auto cost = [&](int64_t win) {
       const int64_t items = rb * win, longest = ceil_div(vt, win);
-      if (p.tile == TILE) return (double)ceil_div(items, NUM_CU) * ((double)longest + 8.0 / (0.0242 * (double)d));
-      return items <= NUM_CU ? 1.2 * (double)longest : 2.0 * (double)(ceil_div(items, 2 * NUM_CU) * longest);
+      if (p.fwd_tile == TILE) return (double)ceil_div(items, NUM_CU) * ((double)longest + fill);
+      const double start = f32 ? 0.0 : 1.5 / (0.28 * steps + 0.9), alone = f32 ? 1.2 : 1.3;
+      return (items <= NUM_CU ? alone : 2.0 * (double)ceil_div(items, 2 * NUM_CU)) * ((double)longest + start);
     };
-    const int64_t most = allow_h_copy && p.tile == TILE ? std::min<int64_t>(p.n_vt, std::max<int64_t>(cover, 8 * NUM_CU / rb)) : cover;
+    const int64_t most = allow_h_copy && !f32 ? std::min<int64_t>(vt, std::max<int64_t>(cover, 8 * NUM_CU / rb)) : cover;
     for (int64_t win = std::min<int64_t>(4, cover); win <= most; ++win)
       if (cost(win) < 0.99 * cost(p.n_win)) p.n_win = (int)win;
     part_windows = std::max(cover, p.n_win);
@@ -227,48 +247,62 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.off_dWacc = o;  if (p.n_nch > 1) o = align_up(o + vc_pad * d * 4, ALIGN);
   // Split-K for launches with too few output tiles to occupy the CUs (small N or small d): the K
   // extent is cut into slices whose fp32 tiles are summed in slice order by a second kernel.
-  const int64_t n_mt = ceil_div(d, p.tile), unit = TILE / p.tile;
-  // Time of a contraction launch in units of one K tile of the main loop (K elements = tile edge): rounds of workgroups
-  // times (K tiles of a slice + `ends` for filling the pipeline and writing the tile out), plus, for a split, the launch
-  // that adds the slices and the fp32 tiles written and read back.  A K tile takes 6.2 us in bf16, and at fp32 (two
-  // workgroups share a CU) 6.8 us per CU with 128-tiles, 0.85 with 64-tiles.
-  const double ends = p.tile == 64 ? 3.5 : 1.2, launch = p.tile == 64 ? 6.0 : 0.8,
-               per_tile = p.tile == TILE ? 0.02 : p.tile == 128 ? 0.005 : 0.01;
-  auto split_cost = [&](int64_t tiles, int64_t k_tiles, int sp) {
-    return (double)ceil_div(tiles * sp, NUM_CU) * ((double)ceil_div(k_tiles, sp) + ends) +
-           (sp > 1 ? launch + per_tile * (double)(tiles * sp) : 0.0);
-  };
-  auto auto_split = [&](int64_t tiles, int64_t k_tiles) -> int {     // a split has to win by 5 %
-    int best = 1;
-    for (int sp = 2; sp <= MAX_SPLIT && sp <= k_tiles; ++sp)
-      if (split_cost(tiles, k_tiles, sp) < split_cost(tiles, k_tiles, best) * (best == 1 ? 0.95 : 1.0)) best = sp;
-    return best;
-  };
-  p.split_dh = tn.splitk_dh;
-  p.split_dw = tn.splitk_dw;
-  const int64_t tiles_dh = p.nc_tiles * unit * n_mt, k_dh = p.vc_tiles * unit;
-  const int64_t tiles_dw = p.vc_tiles * unit * n_mt, k_dw = p.nc_tiles * unit;
-  if (p.split_dh == 0) p.split_dh = auto_split(tiles_dh, k_dh);
-  if (p.split_dw == 0) p.split_dw = auto_split(tiles_dw, k_dw);
-  p.split_dh = (int)std::min<int64_t>(p.split_dh, k_dh);
-  p.split_dw = (int)std::min<int64_t>(p.split_dw, k_dw);
-  // One launch for both: K is cut so that no slice of either is longer than `len` K tiles and all of them together are at
-  // most two rounds of workgroups; taken where that beats one launch after the other, and only while the uncut tiles of
-  // both fit one round (742 x 384 x 4845 102 -> 82 us, 2048 x 512 x 8000 149 -> 126, fp32 849 x 216 x 1732 89 -> 80, the
-  // row preparation without its own scan launch included).
-  p.pair = false;
-  if (p.n_vch == 1 && p.n_nch == 1 && (p.fast || p.tile != TILE) && tn.splitk_dh == 0 && tn.splitk_dw == 0 &&
-      tiles_dh + tiles_dw <= NUM_CU) {
-    double best = 0.97 * (split_cost(tiles_dh, k_dh, p.split_dh) + split_cost(tiles_dw, k_dw, p.split_dw) + launch);
-    for (int64_t len = std::max(k_dh, k_dw); len >= 1; --len) {
-      const int64_t sh = ceil_div(k_dh, len), sw = ceil_div(k_dw, len);
-      const int64_t wgs = tiles_dh * sh + tiles_dw * sw;
-      if (sh > MAX_SPLIT || sw > MAX_SPLIT || wgs > 2 * NUM_CU) break;
-      const double cost = (double)ceil_div(wgs, NUM_CU) * ((double)len + ends) + (sh > 1 || sw > 1 ? launch : 0.0) +
-                          per_tile * (double)((sh > 1 ? tiles_dh * sh : 0) + (sw > 1 ? tiles_dw * sw : 0));
-      if (cost < best) { best = cost; p.pair = true; p.split_dh = (int)sh; p.split_dw = (int)sw; }
+  // The contractions of a full chunk with tiles of a given edge: K slices of each, whether both go out as one launch, and
+  // the time in us.  A launch takes rounds of workgroups times (K tiles of a slice + `ends` for filling the pipeline and
+  // writing the tile out), plus, for a split, the launch that adds the slices and the fp32 tiles written and read back.
+  // A K tile (K elements = tile edge) takes 6.2 us in bf16 with 256-tiles and 1.12 with 128-tiles (two workgroups per
+  // CU), and at fp32 (likewise two) 6.8 us per CU with 128-tiles, 0.85 with 64-tiles.
+  struct Contractions { int split_dh, split_dw; bool pair; double us; };
+  auto contractions = [&](int tile) {
+    Contractions c{tn.splitk_dh, tn.splitk_dw, false, 0.0};
+    const int64_t n_mt = ceil_div(d, tile), unit = TILE / tile;
+    const bool small = !f32 && tile != TILE;
+    const double k_us = small ? 1.12 : !f32 ? 6.2 : tile == 128 ? 6.8 : 0.85, ends = tile == 64 ? 3.5 : small ? 2.0 : 1.2,
+                 tile_us = !f32 && !small ? 0.124 : tile == 64 ? 0.0085 : 0.034, launch = 5.0;
+    auto rounds = [&](int64_t wgs) { return small ? small_waves(wgs) : (double)ceil_div(wgs, NUM_CU); };
+    auto split_cost = [&](int64_t tiles, int64_t k_tiles, int sp) {
+      return rounds(tiles * sp) * ((double)ceil_div(k_tiles, sp) + ends) * k_us +
+             (sp > 1 ? launch + tile_us * (double)(tiles * sp) : 0.0);
+    };
+    auto auto_split = [&](int64_t tiles, int64_t k_tiles) -> int {     // a split has to win by 5 %
+      int best = 1;
+      for (int sp = 2; sp <= MAX_SPLIT && sp <= k_tiles; ++sp)
+        if (split_cost(tiles, k_tiles, sp) < split_cost(tiles, k_tiles, best) * (best == 1 ? 0.95 : 1.0)) best = sp;
+      return best;
+    };
+    const int64_t tiles_dh = p.nc_tiles * unit * n_mt, k_dh = p.vc_tiles * unit;
+    const int64_t tiles_dw = p.vc_tiles * unit * n_mt, k_dw = p.nc_tiles * unit;
+    if (c.split_dh == 0) c.split_dh = auto_split(tiles_dh, k_dh);
+    if (c.split_dw == 0) c.split_dw = auto_split(tiles_dw, k_dw);
+    c.split_dh = (int)std::min<int64_t>(c.split_dh, k_dh);
+    c.split_dw = (int)std::min<int64_t>(c.split_dw, k_dw);
+    c.us = split_cost(tiles_dh, k_dh, c.split_dh) + split_cost(tiles_dw, k_dw, c.split_dw) + launch;
+    // One launch for both: K is cut so that no slice of either is longer than `len` K tiles and all of them together are
+    // at most two rounds of workgroups; taken where that beats one launch after the other, and only while the uncut tiles
+    // of both are resident together (742 x 384 x 4845 102 -> 82 us, 2048 x 512 x 8000 149 -> 126, fp32 849 x 216 x 1732
+    // 89 -> 80, the row preparation without its own scan launch included).
+    if (p.n_vch == 1 && p.n_nch == 1 && (p.fast || f32) && tn.splitk_dh == 0 && tn.splitk_dw == 0 &&
+        tiles_dh + tiles_dw <= (tile != TILE ? 2 : 1) * NUM_CU) {
+      double best = 0.97 * c.us;
+      for (int64_t len = std::max(k_dh, k_dw); len >= 1; --len) {
+        const int64_t sh = ceil_div(k_dh, len), sw = ceil_div(k_dw, len);
+        const int64_t wgs = tiles_dh * sh + tiles_dw * sw;
+        if (sh > MAX_SPLIT || sw > MAX_SPLIT || wgs > 2 * NUM_CU) break;
+        const double cost = rounds(wgs) * ((double)len + ends) * k_us + (sh > 1 || sw > 1 ? launch : 0.0) +
+                            tile_us * (double)((sh > 1 ? tiles_dh * sh : 0) + (sw > 1 ? tiles_dw * sw : 0));
+        if (cost < best) { best = c.us = cost; c.pair = true; c.split_dh = (int)sh; c.split_dw = (int)sw; }
+      }
     }
+    return c;
+  };
+  Contractions con = contractions(p.tile);
+  if (p.fast) {
+    const Contractions small = contractions(128);
+    const double chunks = (double)p.n_vch * p.n_nch;
+    if (logits_us(128, 8.0, 1.6) + chunks * small.us < 0.97 * (logits_us(TILE, 8.0, 1.6) + chunks * con.us)) { p.tile = 128; con = small; }
   }
+  p.split_dh = con.split_dh; p.split_dw = con.split_dw; p.pair = con.pair;
+  const int64_t n_mt = ceil_div(d, p.tile);
   p.off_partial = o;
   {
     const int64_t dh_bytes = p.split_dh > 1 ? align_up((int64_t)p.split_dh * nc_pad * d * 4, ALIGN) : 0;
@@ -276,7 +310,7 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
     // one after the other they share the buffer, side by side they do not
     p.off_partial_dh = p.pair ? o + bytes : o;
     bytes = p.pair ? bytes + dh_bytes : std::max(bytes, dh_bytes);
-    if (p.fast && !p.pair) {
+    if (p.fast && !p.pair && p.tile == TILE) {
       // tails of the launches that occur: full chunks and the last (shorter) chunk of either direction
       const int64_t v_last = p.n_vt - (int64_t)(p.n_vch - 1) * p.vc_tiles, n_last = p.n_rb - (int64_t)(p.n_nch - 1) * p.nc_tiles;
       for (const int64_t vt : {(int64_t)p.vc_tiles, v_last})
@@ -340,9 +374,9 @@ hipError_t set_lds_allowances() {
     if ((e = allow_big_lds(fwd_tiles_kernel<T, L, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, true>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, true, true>, L::LDS)) != hipSuccess) return e;
-    if ((e = allow_big_lds(contract_kernel<T, FastLoop<false>, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
-    if ((e = allow_big_lds(contract_kernel<T, FastLoop<false>, OPS_DW_TR>, L::LDS)) != hipSuccess) return e;
-    if ((e = allow_big_lds(contract_pair_kernel<T, FastLoop<false>, OPS_DW_TR, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(contract_kernel<T, typename L::Even, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(contract_kernel<T, typename L::Even, OPS_DW_TR>, L::LDS)) != hipSuccess) return e;
+    if ((e = allow_big_lds(contract_pair_kernel<T, typename L::Even, OPS_DW_TR, OPS_DH_TR>, L::LDS)) != hipSuccess) return e;
   } else {
     if ((e = allow_big_lds(recompute_kernel<T, L, false>, L::LDS)) != hipSuccess) return e;
     if ((e = allow_big_lds(recompute_kernel<T, L, false, true>, L::LDS)) != hipSuccess) return e;
@@ -425,7 +459,7 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
   // 361 GB of fabric traffic per forward against 192 GB that the raster should need).
   const int n_rb = (int)ceil_div(p.N, L::TILE), n_vt = (int)ceil_div(p.V, L::TILE);
   const int items = n_rb * p.n_win;
-  const int per_launch = L::TUNED ? NUM_CU : items;
+  const int per_launch = [&] { if constexpr (L::TUNED) return NUM_CU * L::PER_CU; return items; }();
   bool hkr = false;
   if constexpr (L::TUNED) hkr = p.fwd_copy;
   T* HT = nullptr;
@@ -524,7 +558,7 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     // pre-tiled for the recompute (in HT's place) and pre-tiled the other way round for dW (in Hc's place); otherwise as
     // they are (Hc), and with the generic loop also transposed [d][npad] (the dW contraction's K-contiguous operand)
     if constexpr (L::TUNED) {
-      const dim3 grid((unsigned)(p.npad / 32), (unsigned)n_mt);
+      const dim3 grid((unsigned)(p.npad / 32), (unsigned)ceil_div(d, TILE));
       auto prep = [&](auto kernel) {
         kernel<<<grid, 256, 0, st>>>(static_cast<const char*>(H), d, npad, reinterpret_cast<char*>(HT),
                                      reinterpret_cast<char*>(Hc), lse, lse_c, rows.grad_rows, gam_c, ca,
@@ -622,9 +656,9 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
   auto contract = [&](const ContractArgs<T>& a, bool is_dw) {
     auto launch = [&](const ContractArgs<T>& x) {
       if constexpr (L::TUNED) {
-        const int grid = std::min(x.n_nt * x.n_mt * x.n_split, NUM_CU);
-        if (is_dw) contract_kernel<T, FastLoop<false>, OPS_DW_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
-        else contract_kernel<T, FastLoop<false>, OPS_DH_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
+        const int grid = std::min(x.n_nt * x.n_mt * x.n_split, NUM_CU * L::PER_CU);
+        if (is_dw) contract_kernel<T, typename L::Even, OPS_DW_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
+        else contract_kernel<T, typename L::Even, OPS_DH_TR><<<grid, L::THREADS, L::LDS, st>>>(x);
       } else if constexpr (L::TRANSPOSING) {
         const int grid = x.n_nt * x.n_mt * x.n_split;
         if (is_dw) contract_kernel<T, L, OPS_DW_F32><<<grid, L::THREADS, L::LDS, st>>>(x);
@@ -636,7 +670,7 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
         splitk_reduce_kernel<T><<<(unsigned)ceil_div((int64_t)x.n_nt * L::TILE * (d / 4), 256), 256, 0, st>>>(x, x.n_nt * L::TILE);
     };
     TailSplit ts{0, 1};
-    if constexpr (L::TUNED) ts = tail_split(a.n_nt, a.n_mt, a.n_split, a.k_elems / L::TILE);
+    if constexpr (L::TUNED && L::TILE == TILE) ts = tail_split(a.n_nt, a.n_mt, a.n_split, a.k_elems / L::TILE);
     if (!ts.rows) { launch(a); return; }
     ContractArgs<T> body = a, tail = a;
     body.n_nt = a.n_nt - ts.rows;
@@ -660,7 +694,7 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
   auto contract_pair = [&](const ContractArgs<T>& w, const ContractArgs<T>& h) {
     const int wg_w = w.n_nt * w.n_mt * w.n_split, wg_h = h.n_nt * h.n_mt * h.n_split;
     if constexpr (L::TUNED)
-      contract_pair_kernel<T, FastLoop<false>, OPS_DW_TR, OPS_DH_TR><<<wg_w + wg_h, L::THREADS, L::LDS, st>>>(w, h, wg_w);
+      contract_pair_kernel<T, typename L::Even, OPS_DW_TR, OPS_DH_TR><<<wg_w + wg_h, L::THREADS, L::LDS, st>>>(w, h, wg_w);
     else if constexpr (L::TRANSPOSING)
       contract_pair_kernel<T, L, OPS_DW_F32, OPS_DH_F32><<<wg_w + wg_h, L::THREADS, L::LDS, st>>>(w, h, wg_w);
     auto blocks = [&](const ContractArgs<T>& x) {
@@ -684,8 +718,9 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
       {
         const RecomputeArgs<T> rc = recompute_args(vc, nc, G);
         ProfScope ps(FLCE_PROF_RECOMPUTE, st);
-        // at most one workgroup per CU: each walks its share of the chunk's tiles
-        const int grid = L::TUNED ? std::min(rc.n_nt * rc.n_vt, NUM_CU) : rc.n_nt * rc.n_vt;
+        // at most as many workgroups as fit the chip: each walks its share of the chunk's tiles
+        int grid = rc.n_nt * rc.n_vt;
+        if constexpr (L::TUNED) grid = std::min(grid, NUM_CU * L::PER_CU);
         if constexpr (L::TUNED) {     // the tuned loop's backward always has the pre-tiled copies
           if (rows.grad_rows) recompute_kernel<T, L, true, true><<<grid, L::THREADS, L::LDS, st>>>(rc);
           else recompute_kernel<T, L, true><<<grid, L::THREADS, L::LDS, st>>>(rc);
@@ -770,15 +805,15 @@ int flce_plan_describe(int64_t N, int64_t d, int64_t V, flce_dtype dt, char* buf
   // K-split tails of the contraction launches of a full chunk (output-row tiles x slices; 0x1 = none)
   const int64_t n_mt = (d + flce::TILE - 1) / flce::TILE;
   flce::TailSplit th{0, 1}, tw{0, 1};
-  if (p.fast && !p.pair) {
+  if (p.fast && !p.pair && p.tile == flce::TILE) {
     th = flce::tail_split(p.nc_tiles, n_mt, p.split_dh, p.vc_tiles);
     tw = flce::tail_split(p.vc_tiles, n_mt, p.split_dw, p.nc_tiles);
   }
   return std::snprintf(buf, buf_bytes,
                        "flce %s loop=%s h_copy=%d windows=%d vocab_chunks=%dx%d row_chunks=%dx%d splitk_dH=%d splitk_dW=%d "
-                       "tail_dH=%dx%d tail_dW=%dx%d pair=%d staging_bytes=%lld fwd_ws=%lld bwd_ws=%lld",
+                       "tail_dH=%dx%d tail_dW=%dx%d pair=%d tiles=%d/%d staging_bytes=%lld fwd_ws=%lld bwd_ws=%lld",
                        flce_version(), p.fast ? "tuned" : "generic", p.hkr ? 1 : 0, p.n_win, p.n_vch, p.vc_tiles, p.n_nch,
-                       p.nc_tiles, p.split_dh, p.split_dw, th.rows, th.slices, tw.rows, tw.slices, p.pair ? 1 : 0,
+                       p.nc_tiles, p.split_dh, p.split_dw, th.rows, th.slices, tw.rows, tw.slices, p.pair ? 1 : 0, p.fwd_tile, p.tile,
                        (long long)((int64_t)p.nc_tiles * flce::TILE * p.ld_v * p.esize), (long long)p.fwd_bytes,
                        (long long)p.bwd_bytes);
 }
@@ -812,8 +847,12 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
   const int mean = reduction == FLCE_REDUCE_MEAN;
   char* ws = static_cast<char*>(workspace);
   if (dt == FLCE_DTYPE_BF16) {
+    if (p.ragged && p.fwd_tile == 128)
+      return flce::forward_t<flce::bf16_t, uint16_t, flce::SmallLoop<true>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
     if (p.ragged)
       return flce::forward_t<flce::bf16_t, uint16_t, flce::FastLoop<true>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
+    if (p.fast && p.fwd_tile == 128)
+      return flce::forward_t<flce::bf16_t, uint16_t, flce::SmallLoop<false>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
     if (p.fast)
       return flce::forward_t<flce::bf16_t, uint16_t, flce::FastLoop<false>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
     return flce::forward_t<flce::bf16_t, uint16_t, flce::GenericLoop>(
@@ -844,8 +883,12 @@ static flce_status backward_impl(const void* H, const void* W, const int64_t* ta
   const int mean = reduction == FLCE_REDUCE_MEAN;
   char* ws = static_cast<char*>(workspace);
   if (dt == FLCE_DTYPE_BF16) {
+    if (p.ragged && p.tile == 128)
+      return flce::backward_t<flce::bf16_t, uint16_t, flce::SmallLoop<true>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
     if (p.ragged)
       return flce::backward_t<flce::bf16_t, uint16_t, flce::FastLoop<true>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
+    if (p.fast && p.tile == 128)
+      return flce::backward_t<flce::bf16_t, uint16_t, flce::SmallLoop<false>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
     if (p.fast)
       return flce::backward_t<flce::bf16_t, uint16_t, flce::FastLoop<false>>(p, H, W, targets, lse, ignore_index, mean, grad_loss, dH_out, dW_out, ws, st, slice, rows);
     return flce::backward_t<flce::bf16_t, uint16_t, flce::GenericLoop>(

@@ -116,54 +116,72 @@ struct F32Loop {          // fp32; T x T tiles, 4 wavefronts 2 x 2, two workgrou
   };
 };
 
+// The tuned bf16 loop; 4 wavefronts 2 x 2 of B x B accumulator blocks, global -> LDS DMA.
 // RAGGED: the hidden size is a multiple of 8 but not of 32 (the K extent of the forward and the recompute; the
 // contractions' K extents are whole tiles, they always run with the plain form).
-template <bool RAGGED>
-struct FastLoop {         // bf16; 4 wavefronts 2 x 2, global -> LDS DMA
-  static constexpr int TILE = flce::TILE, THREADS = fast::THREADS, WM = fast::WM, WN = fast::WN, LDS = fast::LDS_BYTES;
+template <bool RAGGED, int B>
+struct TunedLoop {
+  static constexpr int TILE = 64 * B, THREADS = fast::THREADS, WM = B, WN = B;
   static constexpr bool TRANSPOSING = true, TUNED = true;
-  // LDS that post-processing may use while the next tile's first three K stages are being filled: the fourth stage
-  static constexpr int FREE_LDS_OFFSET = (fast::NS - 1) * fast::STAGE, FREE_LDS_BYTES = fast::STAGE;
-  static __device__ __forceinline__ int tile_m(int i, int r) { return fast::tile_m(i, r); }
-  static __device__ __forceinline__ int tile_n(int j) { return fast::tile_n(j); }
+  // 256-row tiles: one workgroup per CU, 4 stages of 32 KiB; 128-row tiles: two, 5 stages of 16 KiB each
+  static constexpr int PER_CU = B == 4 ? 1 : 2, STAGES = B == 4 ? fast::NS : 5, STAGE = B * 8192, LDS = STAGES * STAGE;
+  template <int LA, int LB, bool RG = false> using Pipe = fast::Pipe<LA, LB, true, B, STAGES, RG, B>;
+  // LDS that post-processing may use while the next tile's first K stages are being filled: the last stage
+  static constexpr int FREE_LDS_OFFSET = (STAGES - 1) * STAGE;
+  static __device__ __forceinline__ int tile_m(int i, int r) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    return (wave >> 1) * (B * 32) + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+  }
+  static __device__ __forceinline__ int tile_n(int j) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    return (wave & 1) * (B * 32) + j * 32 + (lane & 31);
+  }
   static __device__ __forceinline__ int slot() { return fast::slot_of_lane(); }
-  // The 256 accumulators of a wavefront live in the accumulation registers.  Post-processing reads them one
-  // block at a time where it uses them; left to itself the compiler copies most of a tile into vector
-  // registers in one sweep at the end of the main loop, which overflows the register file into scratch memory.
   // A sequence of tiles with the same B operand: start() requests the first K stages of a tile (all LDS stages must
   // be free: every wavefront is past the previous run()), run() computes it.  BP: B is also given pre-tiled (Bp:
   // per 256-row block and K step the 16 KiB image of its LDS tile, see pack_rows_kernel), and that copy is read.
   template <bool BP>
   struct Stream {
-    fast::Pipe<fast::KC, BP ? fast::PK : fast::KC, true, fast::WM, fast::NS, RAGGED> pipe;
-    __device__ __forceinline__ void start(const bf16_t* A, int64_t lda_bytes, int a_row0, int a_rows, const bf16_t* B,
+    Pipe<fast::KC, BP ? fast::PK : fast::KC, RAGGED> pipe;
+    __device__ __forceinline__ void start(const bf16_t* A, int64_t lda_bytes, int a_row0, int a_rows, const bf16_t* Bm,
                                           const bf16_t* Bp, int64_t ldb_bytes, int b_row0, int b_rows, int k_elems,
                                           char* lds) {
       const fast::Operand As{reinterpret_cast<const char*>(A), lda_bytes, a_row0, a_rows, 0};
       if constexpr (BP) {
-        // b_row0 is a multiple of 256: the block's images follow each other, one per K step
-        const fast::Operand Bs{reinterpret_cast<const char*>(Bp) + packed_block_offset(b_row0 / TILE, k_elems), 0, 0, 0, 0};
+        // the block's images follow each other, one per K step, 64 bytes per row
+        const fast::Operand Bs{reinterpret_cast<const char*>(Bp) + packed_block_offset(b_row0 / flce::TILE, k_elems) +
+                                   b_row0 % flce::TILE * 64, 0, 0, 0, 0};
         pipe.start(As, Bs, k_elems, lds);
       } else {
-        const fast::Operand Bs{reinterpret_cast<const char*>(B), ldb_bytes, b_row0, b_rows, 0};
+        const fast::Operand Bs{reinterpret_cast<const char*>(Bm), ldb_bytes, b_row0, b_rows, 0};
         pipe.start(As, Bs, k_elems, lds);
       }
     }
     __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[WM][WN]) { pipe.run(lds, acc); }
   };
+  // The accumulators of a wavefront live in the accumulation registers.  Post-processing reads them one
+  // block at a time where it uses them; left to itself the compiler copies most of a tile into vector
+  // registers in one sweep at the end of the main loop, which overflows the register file into scratch memory.
   static __device__ __forceinline__ float acc_get(const f32x16& blk, int r) {   // r: a constant after unrolling
     float v;
     asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(blk[r]));
     return v;
   }
-  static __device__ __forceinline__ void run(const void* A, int64_t lda_bytes, int a_row0, int a_rows, const void* B,
-                                             int64_t ldb_bytes, int b_row0, int b_rows, int k_bytes, char* lds,
-                                             f32x16 (&acc)[WM][WN]) {
-    const fast::Operand As{static_cast<const char*>(A), lda_bytes, a_row0, a_rows, 0};
-    const fast::Operand Bs{static_cast<const char*>(B), ldb_bytes, b_row0, b_rows, 0};
-    fast::mainloop<fast::KC, fast::KC>(As, Bs, k_bytes / 2, lds, acc);
+  // A wavefront's pieces of 32 rows x (32 B) columns of bf16 on their way through its slice of the free stage (rows of
+  // ROW_BYTES in 8-byte slots, the slot number XOR-ed so that the 32 rows one write instruction touches lie in different
+  // banks): where the 4 columns of lane half `half`, block i, quarter rq of row r are written, and where 16-byte chunk c
+  // of row r is read (its two slots side by side, in swapped order where `swapped`).
+  static constexpr int ROW_BYTES = 64 * B, CHUNKS = ROW_BYTES / 16, ROWS_PER_STORE = 64 / CHUNKS;
+  static __device__ __forceinline__ int piece_slot(int r, int i, int rq, int half) {
+    return r * ROW_BYTES + ((((i * 4 + rq) * 2 + half) ^ (B == 4 ? r : r >> 1)) << 3);
   }
+  static __device__ __forceinline__ int piece_chunk(int r, int c) {
+    return r * ROW_BYTES + ((c ^ (B == 4 ? r >> 1 : r >> 2)) << 4);
+  }
+  static __device__ __forceinline__ bool swapped(int r) { return (B == 4 ? r : r >> 1) & 1; }
 };
+template <bool RAGGED> struct FastLoop : TunedLoop<RAGGED, 4> { using Even = FastLoop<false>; };
+template <bool RAGGED> struct SmallLoop : TunedLoop<RAGGED, 2> { using Even = SmallLoop<false>; };
 
 #ifndef FLCE_FWD_GROUP
 #define FLCE_FWD_GROUP 8     // row blocks per raster patch of the forward (x 32 / this many windows per XCD)
@@ -1023,19 +1041,17 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
 
     const int v0 = (a.vt0 + q) * L::TILE;
     if constexpr (L::TUNED) {
-      // Tuned loop.  A lane holds, of 32 token rows x 128 vocabulary positions per j, scattered 8-byte pieces of one
+      // Tuned loop.  A lane holds, of 32 token rows x (32 WM) vocabulary positions per j, scattered 8-byte pieces of one
       // row; stored as they lie, every store instruction would touch 64 different memory rows.  Each wavefront
-      // therefore passes its 32 x 128 piece (8 KiB of bf16) through its own slice of the free LDS stage and writes
-      // whole 256-byte runs: 16 lanes per row, 4 rows per instruction.  LDS row = 256 bytes = 32 slots of 8 bytes,
-      // slot index XOR-ed with the row number: the 32 rows that one 8-byte write instruction touches land in 32
-      // different slots (all 64 banks once), and a 16-byte read finds its two slots side by side, in swapped order
-      // on odd rows.
-      static_assert(sizeof(T) == 2 && L::WM == 4 && L::WN == 4, "tuned epilogue is laid out for bf16 128 x 128 wave tiles");
+      // therefore passes its piece (8 KiB of bf16 with 256-row tiles) through its own slice of the free LDS stage and
+      // writes whole runs of 256 (128) bytes: 16 (8) lanes per row, 4 (8) rows per instruction.
+      static_assert(sizeof(T) == 2, "the tuned epilogue is laid out for bf16");
+      constexpr int RPS = L::ROWS_PER_STORE;
       const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-      char* stage = lds + L::FREE_LDS_OFFSET + wave * 8192;
+      char* stage = lds + L::FREE_LDS_OFFSET + wave * (32 * L::ROW_BYTES);
       const int wrow = lane & 31, whalf = lane >> 5;              // writer: token row of the piece, lane half
-      const int rrow = lane >> 4, rchunk = lane & 15;             // reader: row within a group of 4, 16-byte chunk
-      const int vbase = v0 + (wave >> 1) * 128;                   // first vocabulary position of the piece
+      const int rrow = lane / L::CHUNKS, rchunk = lane % L::CHUNKS;   // reader: row within a store, 16-byte chunk
+      const int vbase = v0 + (wave >> 1) * (L::WM * 32);          // first vocabulary position of the piece
 #pragma unroll
       for (int j = 0; j < L::WN; ++j) {
         const int tgt = meta.tgt[j];
@@ -1075,25 +1091,24 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
             uint2 packed;
             packed.x = f32x2_to_bf16x2_bits(g[0], g[1]);
             packed.y = f32x2_to_bf16x2_bits(g[2], g[3]);
-            const int slot = ((i * 4 + rq) * 2 + whalf) ^ wrow;
-            *reinterpret_cast<uint2*>(stage + wrow * 256 + slot * 8) = packed;
+            *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
           }
           __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
         }
-        // the piece is complete in LDS (a wavefront's LDS operations complete in order): write it out, four rows of
-        // 256 bytes per instruction.  G is stored in blocks of 16 rows x 32 positions (1 KiB; the blocks of a row
+        // the piece is complete in LDS (a wavefront's LDS operations complete in order): write it out, whole rows at a
+        // time.  G is stored in blocks of 16 rows x 32 positions (1 KiB; the blocks of a row
         // group along the vocabulary, row groups ldG BYTES apart), so that both contractions fetch whole blocks:
         // a row's 16 bytes at position chunk c lie in block c / 4 at (row % 16) * 64 + (c % 4) * 16.
-        const int row0 = p * L::TILE + (wave & 1) * 128 + j * 32;                  // a multiple of 32: two row groups
-        const int cchunk = q * 32 + (wave >> 1) * 16 + rchunk;                  // 8-position chunk inside the chunk's row
+        const int row0 = p * L::TILE + (wave & 1) * (L::WN * 32) + j * 32;          // a multiple of 32: two row groups
+        const int cchunk = q * (L::TILE / 8) + (wave >> 1) * (L::WM * 4) + rchunk;  // 8-position chunk inside the chunk's row
         char* __restrict__ gdst = reinterpret_cast<char*>(G) + (int64_t)(row0 >> 4) * ldG + (int64_t)(cchunk >> 2) * 1024 +
                                   rrow * 64 + (cchunk & 3) * 16;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int r = k * 4 + rrow;
-          u32x4 vq = *reinterpret_cast<const u32x4*>(stage + r * 256 + ((rchunk ^ (r >> 1)) * 16));
-          if (rrow & 1) vq = u32x4{vq[2], vq[3], vq[0], vq[1]};      // r is odd exactly when rrow is
-          *reinterpret_cast<u32x4*>(gdst + (int64_t)(k >> 2) * ldG + (k & 3) * 256) = vq;
+        for (int k = 0; k < 32 / RPS; ++k) {
+          const int r = k * RPS + rrow;
+          u32x4 vq = *reinterpret_cast<const u32x4*>(stage + L::piece_chunk(r, rchunk));
+          if (L::swapped(rrow)) vq = u32x4{vq[2], vq[3], vq[0], vq[1]};      // (r and rrow agree in those bits)
+          *reinterpret_cast<u32x4*>(gdst + (int64_t)(k * RPS / 16) * ldG + k * RPS % 16 * 64) = vq;
         }
       }
     } else {
@@ -1281,23 +1296,24 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
       // It matters where the K loop is short: dW at 500 tokens x 4096 x 128256 807 -> 750 us (the K loops alone take 479),
       // the step at 1000 x 2048 x 100000 1616 -> 1528 us; at 8192 tokens it changes nothing.  The fp32 sums gain nothing
       // from the detour (32 bytes per row as they lie; 4096 x 128 x 32000 363 us against 357) and go out directly.
-      static_assert(sizeof(T) == 2 && L::WM == 4 && L::WN == 4, "laid out for bf16 128 x 128 wave tiles");
+      static_assert(sizeof(T) == 2, "laid out for bf16");
+      constexpr int RPS = L::ROWS_PER_STORE;
       const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-      char* stage = lds + L::FREE_LDS_OFFSET + wave * 8192;
+      char* stage = lds + L::FREE_LDS_OFFSET + wave * (32 * L::ROW_BYTES);
       const int wrow = lane & 31, whalf = lane >> 5;              // writer: output row of the piece, lane half
-      const int rrow = lane >> 4, rchunk = lane & 15;             // reader: row within a group of 4, 16-byte chunk
-      const int mw = q * L::TILE + (wave >> 1) * 128;             // first hidden position of the wavefront's columns
+      const int rrow = lane / L::CHUNKS, rchunk = lane % L::CHUNKS;   // reader: row within a store, 16-byte chunk
+      const int mw = q * L::TILE + (wave >> 1) * (L::WM * 32);    // first hidden position of the wavefront's columns
       // output row of piece row r: rows of dW follow each other, rows of dH go where the compact rows came from
       auto row_of = [&](int j, int r) -> int {
         if constexpr (OPS == OPS_DH_TR) return __shfl(orow[j], r, 64);
-        const int n = a.out_row0 + p * L::TILE + (wave & 1) * 128 + j * 32 + r;
+        const int n = a.out_row0 + p * L::TILE + (wave & 1) * (L::WN * 32) + j * 32 + r;
         return n < a.out_rows ? n : -1;
       };
       if (mw >= d) return;                                        // all of the wavefront's columns lie past the hidden size
 #pragma unroll
       for (int j = 0; j < L::WN; ++j) {
         if (!(flags & (READ_ACC | WRITE_ACC))) {
-          // Gamma applied, rounded, out: 32 rows x 128 positions of 2 bytes ("+ 0.f" turns a -0 product into +0)
+          // Gamma applied, rounded, out: 32 rows x (32 WM) positions of 2 bytes ("+ 0.f" turns a -0 product into +0)
 #pragma unroll
           for (int i = 0; i < L::WM; ++i)
 #pragma unroll
@@ -1308,16 +1324,15 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
               uint2 packed;
               packed.x = f32x2_to_bf16x2_bits(v[0], v[1]);
               packed.y = f32x2_to_bf16x2_bits(v[2], v[3]);
-              const int slot = ((i * 4 + rq) * 2 + whalf) ^ wrow;
-              *reinterpret_cast<uint2*>(stage + wrow * 256 + slot * 8) = packed;
+              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
               if (rq == 3) __builtin_amdgcn_sched_barrier(0);     // one 32x32 block at a time in VGPRs
             }
           const int m = mw + rchunk * 8;
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int r = k * 4 + rrow;
-            u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * 256 + ((rchunk ^ (r >> 1)) * 16));
-            if (rrow & 1) v = u32x4{v[2], v[3], v[0], v[1]};      // r is odd exactly when rrow is
+          for (int k = 0; k < 32 / RPS; ++k) {
+            const int r = k * RPS + rrow;
+            u32x4 v = *reinterpret_cast<const u32x4*>(stage + L::piece_chunk(r, rchunk));
+            if (L::swapped(rrow)) v = u32x4{v[2], v[3], v[0], v[1]};         // (r and rrow agree in those bits)
             const int row = row_of(j, r);
             if (row >= 0 && m < d) *reinterpret_cast<u32x4*>(out + (int64_t)row * d + m) = v;
           }
@@ -1356,22 +1371,22 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
     load_rows(p, orow);
     flush(acc, z, p, q, orow);
   } else {
-    fast::Pipe<OPS == OPS_DH_TR ? fast::KR : fast::PK, OPS == OPS_DH_TR ? fast::KB : fast::RB> pipe;
+    typename L::template Pipe<OPS == OPS_DH_TR ? fast::KR : fast::PK, OPS == OPS_DH_TR ? fast::KB : fast::RB> pipe;
     auto start = [&](int p, int q, int k0, int k_elems) {
       if constexpr (OPS == OPS_DH_TR) {
-        // A: K rows start at A (a_krows valid from there), window of 256 hidden columns at q
+        // A: K rows start at A (a_krows valid from there), window of the tile's hidden columns at q
         const int width = max(0, min(L::TILE, d - q * L::TILE)) * 2;
         const fast::Operand As{reinterpret_cast<const char*>(A + (int64_t)k0 * lda) + (int64_t)q * L::TILE * 2, lda * 2, 0,
                                a.a_krows - k0, width};
-        // B: G blocked (ldb = bytes from one group of 16 rows to the next), rows p * 256 ..., K from position k0
+        // B: G blocked (ldb = bytes from one group of 16 rows to the next), rows p * TILE ..., K from position k0
         const fast::Operand Bs{reinterpret_cast<const char*>(B) + (int64_t)(p * (L::TILE / 16)) * ldb + (int64_t)(k0 / 32) * 1024,
                                ldb, 0, 0, 0};
         pipe.start(As, Bs, k_elems, lds);
       } else {
         // A: the images of hidden tile q, from K step (k_start + k0) / 32 on
-        const fast::Operand As{reinterpret_cast<const char*>(A) + packed_cols_offset(q, (int)lda) +
+        const fast::Operand As{reinterpret_cast<const char*>(A) + packed_cols_offset(q * L::TILE / flce::TILE, (int)lda) + q * L::TILE % flce::TILE * 64 +
                                    (int64_t)((a.k_start + k0) / fast::BK) * fast::OPER, 0, 0, 0, 0};
-        // B: G blocked, K over its rows from row k0, the tile's 256 vocabulary positions from p * 256
+        // B: G blocked, K over its rows from row k0, the tile's vocabulary positions from p * TILE
         const fast::Operand Bs{reinterpret_cast<const char*>(B) + (int64_t)(k0 / 16) * ldb + (int64_t)(p * (L::TILE / 32)) * 1024,
                                ldb, 0, 0, 0};
         pipe.start(As, Bs, k_elems, lds);

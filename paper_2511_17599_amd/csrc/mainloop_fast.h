@@ -101,18 +101,19 @@ __device__ __forceinline__ uint32_t lds_address(const char* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
 }
 
-template <int LAYOUT, int TILE_ROWS = TILE>
+template <int LAYOUT, int REQS>
 __device__ __forceinline__ u32x4 make_rsrc(const Operand& s, int k_elems) {
   uint32_t n = 0;
   const char* b = s.base;
   if (LAYOUT == PK) {
-    n = (uint32_t)((k_elems + BK - 1) / BK) * OPER;
-  } else if (LAYOUT == KB) {         // 16 row groups, the last one up to the end of the K extent
-    n = (uint32_t)(15 * s.ld_bytes + (int64_t)(k_elems / BK) * 1024);
-  } else if (LAYOUT == RB) {         // k_elems / 16 row groups, 8 blocks of the last one
-    if (k_elems > 0) n = (uint32_t)((int64_t)(k_elems / 16 - 1) * s.ld_bytes + 8 * 1024);
+    const int kt = (k_elems + BK - 1) / BK;   // images of 256 rows; a 128-row tile is one half of each
+    if (kt > 0) n = (uint32_t)(kt - 1) * OPER + REQS * 4096;
+  } else if (LAYOUT == KB) {         // a row group per request of the workgroup, the last one up to the end of the K extent
+    n = (uint32_t)((4 * REQS - 1) * s.ld_bytes + (int64_t)(k_elems / BK) * 1024);
+  } else if (LAYOUT == RB) {         // k_elems / 16 row groups, the tile's blocks of the last one
+    if (k_elems > 0) n = (uint32_t)((int64_t)(k_elems / 16 - 1) * s.ld_bytes + 2 * REQS * 1024);
   } else if (LAYOUT == KC) {
-    int vr = min(TILE_ROWS, s.rows - s.row0);
+    int vr = min(64 * REQS, s.rows - s.row0);
     if (vr > 0) n = (uint32_t)((int64_t)(vr - 1) * s.ld_bytes + k_elems * 2);
     b += (int64_t)s.row0 * s.ld_bytes;
   } else {
@@ -149,40 +150,40 @@ __device__ __forceinline__ void wait_vm_and_lds() {
   __builtin_amdgcn_s_waitcnt((hi << 14) | (0x0 << 8) | (0x7 << 4) | lo);
 }
 
-// Global -> LDS requests of one operand: REQS per wavefront per stage (4 for a 256-row tile; a K-contiguous tile
-// may also be 128 rows high: 2), 1 KiB each, written linearly into this wavefront's slice of the operand tile.
+// Global -> LDS requests of one operand: REQS per wavefront per stage (4 for a 256-row tile, 2 for a 128-row one), 1 KiB each, written linearly into this wavefront's slice of the operand tile.
 // RAGGED (K-contiguous layout): K need not be a multiple of a stage's 32 elements, only of 8; the 16-byte chunks of the
 // last stage past the end of K are requested out of the descriptor's range and land as zeros.  (Such shapes ran on the
 // generic loop, with transposed copies of H, W and G: 20597 x 168 x 179711 13.46 -> 9.25 ms per step, 3716 x 136 x 84702
 // 1027 -> 713 us, 500 x 1000 x 30000 271 -> 207 us, same bits.)
 template <int LAYOUT, int REQS = 4, bool RAGGED = false>
 struct Loader {
-  static_assert(REQS == 4 || (LAYOUT == KC && REQS == 2), "a half-height tile exists in the K-contiguous layout only");
+  static_assert(REQS == 4 || REQS == 2, "256 or 128 tile rows");
   u32x4 rs;
   uint32_t v[REQS];       // per-lane byte offsets of the requests (K tile 0); unsigned: a window may reach 2^32 bytes
   uint32_t k_step;        // KC: bytes of K per stage (scalar offset); KR: bytes of 32 K rows (added per lane)
   int last_kt;            // RAGGED: the last K tile, and whether this lane's chunk of it lies past the end of K (every
   bool past_end;          // request of a lane takes the same chunk: request rows are a multiple of 16 apart)
   __device__ __forceinline__ void init(const Operand& s, int k_elems) {
-    rs = make_rsrc<LAYOUT, 64 * REQS>(s, k_elems);
+    rs = make_rsrc<LAYOUT, REQS>(s, k_elems);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < REQS; ++i) {
       if (LAYOUT == PK) {
-        v[i] = (uint32_t)(wave * 4096 + i * 1024 + lane * 16);
-      } else if (LAYOUT == KB) {     // request = row group wave * 4 + i of the tile: one block, KC's chunk order
+        v[i] = (uint32_t)(wave * (REQS * 1024) + i * 1024 + lane * 16);
+      } else if (LAYOUT == KB) {     // request = row group wave * REQS + i of the tile: one block, KC's chunk order
         const int chunk = (lane & 3) ^ ((lane >> 4) & 3);
-        v[i] = (uint32_t)((wave * 4 + i) * s.ld_bytes) + (lane >> 2) * 64 + chunk * 16;
-      } else if (LAYOUT == RB) {     // request = block (row group, column block) = ((wave * 4 + i) / 8, % 8), as it is
-        const int b = wave * 4 + i;
-        v[i] = (uint32_t)((b >> 3) * s.ld_bytes) + (b & 7) * 1024 + lane * 16;
+        v[i] = (uint32_t)((wave * REQS + i) * s.ld_bytes) + (lane >> 2) * 64 + chunk * 16;
+      } else if (LAYOUT == RB) {     // request = block (row group, column block) of the 2 x (2 REQS) of a K step, as it is
+        const int b = wave * REQS + i;
+        v[i] = (uint32_t)(b / (2 * REQS) * s.ld_bytes) + b % (2 * REQS) * 1024 + lane * 16;
       } else if (LAYOUT == KC) {
         const int row = wave * (16 * REQS) + i * 16 + (lane >> 2);
         const int chunk = (lane & 3) ^ ((row >> 2) & 3);
         v[i] = (uint32_t)(row * s.ld_bytes) + chunk * 16;
       } else {
-        const int krow = wave * 8 + i * 2 + (lane >> 5);
-        const int off = ((lane & 31) * 16) ^ ((krow & 3) << 6);
+        constexpr int LANES = 8 * REQS;        // of 16 bytes per K row
+        const int krow = wave * 8 + i * (64 / LANES) + lane / LANES;
+        const int off = ((lane % LANES) * 16) ^ ((krow & 3) << 6);
         v[i] = (uint32_t)(krow * s.ld_bytes) + off;
       }
     }
@@ -209,7 +210,7 @@ struct Loader {
 // wavefront works on (BLOCKS 32-row blocks each: 4 for a 256-row tile, 2 for a 128-row one).
 template <int LAYOUT, int BLOCKS = 4>
 struct FragAddr {
-  static_assert(BLOCKS == 4 || (LAYOUT == KC && BLOCKS == 2), "a half-height tile exists in the K-contiguous layout only");
+  static_assert(BLOCKS == 4 || BLOCKS == 2, "256 or 128 tile rows");
   int o[4];   // KC: o[ks] for the two MFMA K steps (o[2], o[3] unused); KR: o[i] for the 4 blocks
   __device__ __forceinline__ void init(int wsub) {
     const int lane = threadIdx.x & 63;
@@ -221,12 +222,12 @@ struct FragAddr {
     } else {
       const int e = (lane >> 2) & 3, q = lane & 3, mg = (lane >> 4) & 1, kh = lane >> 5;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        o[i] = LAYOUT == RB ? (wsub * 4 + i) * 1024 + (8 * kh + e) * 64 + 32 * mg + 8 * q
-                            : (8 * kh + e) * 512 + wsub * 256 + 64 * (i ^ e) + 32 * mg + 8 * q;
+      for (int i = 0; i < BLOCKS; ++i)
+        o[i] = LAYOUT == RB ? (wsub * BLOCKS + i) * 1024 + (8 * kh + e) * 64 + 32 * mg + 8 * q
+                            : (8 * kh + e) * (128 * BLOCKS) + 64 * ((wsub * BLOCKS + i) ^ e) + 32 * mg + 8 * q;
     }
   }
-  static constexpr int READS = kc_like(LAYOUT) ? BLOCKS : 8;   // LDS reads per MFMA K step
+  static constexpr int READS = kc_like(LAYOUT) ? BLOCKS : 2 * BLOCKS;   // LDS reads per MFMA K step
 };
 
 struct Frags {
@@ -240,9 +241,9 @@ __device__ __forceinline__ void read_frag(bf16x8 (&f)[4], const FragAddr<LAYOUT,
     f[t] = *reinterpret_cast<const bf16x8*>(tile + fa.o[ks] + t * 32 * 64);
   } else {
     const int i = t >> 1, r = t & 1;
-    // K rows 16 ks + 4 r + (0..3, +8 for the upper lanes): KR has them 512 bytes apart; RB has the 16 rows of MFMA
-    // K step ks in row group ks of the tile (8 blocks of 1 KiB), 64 bytes apart
-    const int koff = LAYOUT == RB ? ks * 8192 + r * 256 : (16 * ks + 4 * r) * 512;
+    // K rows 16 ks + 4 r + (0..3, +8 for the upper lanes): KR has them one tile row apart; RB has the 16 rows of MFMA
+    // K step ks in row group ks of the tile (2 BLOCKS blocks of 1 KiB), 64 bytes apart
+    const int koff = LAYOUT == RB ? ks * (BLOCKS * 2048) + r * 256 : (16 * ks + 4 * r) * (128 * BLOCKS);
     const s16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + fa.o[i] + koff));
     const bf16x4 hb = __builtin_bit_cast(bf16x4, h);
     if (r == 0) { f[i][0] = hb[0]; f[i][1] = hb[1]; f[i][2] = hb[2]; f[i][3] = hb[3]; }
@@ -262,25 +263,24 @@ __device__ __forceinline__ void read_frag(bf16x8 (&f)[4], const FragAddr<LAYOUT,
 // WITH_MFMA = false leaves the matrix instructions out (everything else, i.e. the global -> LDS requests, the LDS
 // fragment reads, the waits and barriers, stays): only the measurement probe uses it, to time the data path alone.
 //
-// AM = 32-row blocks of A per wavefront: 4 is the 256 x 256 tile above; 2 halves the A tile (128 rows, K-contiguous
-// only), i.e. a 128 x 256 tile with 128 accumulators per lane, which lets two workgroups share a CU (with NSTAGES = 3
-// a workgroup then needs 72 KiB of LDS).  `acc` has AM x 4 blocks.
+// AM, AN = 32-row blocks of A and B per wavefront: 4 x 4 is the 256 x 256 tile above.  2 x 2 is a 128 x 128 tile (64
+// accumulators per lane, two workgroups per CU) for problems with too few 256-row tiles; 2 x 4 serves the probe.
 //
 // RAGGED: K is a multiple of 8 elements, K-contiguous operands have it as their extent and a pre-tiled operand is padded
 // with zeros to whole stages.
-template <int LA, int LB, bool WITH_MFMA = true, int AM = WM, int NSTAGES = NS, bool RAGGED = false>
+template <int LA, int LB, bool WITH_MFMA = true, int AM = WM, int NSTAGES = NS, bool RAGGED = false,
+          int AN = WN>
 struct Pipe {
-  static_assert(AM == 4 || (AM == 2 && LA == KC), "a half-height A tile exists in the K-contiguous layout only");
-  static constexpr int REQS_A = AM;                    // requests per wavefront per stage, A (1 KiB each)
+  static constexpr int REQS_A = AM, REQS_B = AN;       // requests per wavefront per stage (1 KiB each)
   static constexpr int OPER_A = AM * 4096;             // bytes of the A tile of one stage
-  static constexpr int STAGE_BYTES = OPER_A + OPER;    // A tile, then B tile
+  static constexpr int STAGE_BYTES = OPER_A + AN * 4096;   // A tile, then B tile
   static constexpr int LDS_TOTAL = NSTAGES * STAGE_BYTES;
-  static constexpr int LOADS = REQS_A + 4;             // requests per wavefront per K tile
-  static constexpr int NM = AM * WN;                   // MFMAs per half step
+  static constexpr int LOADS = REQS_A + REQS_B;        // requests per wavefront per K tile
+  static constexpr int NM = AM * AN;                   // MFMAs per half step
   Loader<LA, REQS_A, RAGGED> la;
-  Loader<LB, 4, RAGGED> lb;
+  Loader<LB, REQS_B, RAGGED> lb;
   FragAddr<LA, AM> fa;
-  FragAddr<LB> fb;
+  FragAddr<LB, AN> fb;
   int KT, lds_wave;
 
   __device__ __forceinline__ void start(const Operand& A, const Operand& B, int k_elems, char* lds) {
@@ -290,7 +290,7 @@ struct Pipe {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     fa.init(wave >> 1);
     fb.init(wave & 1);
-    lds_wave = wave * 4096;      // this wavefront's slice of a 256-row operand tile (of a shorter A tile: pro rata)
+    lds_wave = wave * 1024;      // this wavefront's slice of an operand tile, per request
     // Opaque to the optimiser: in a kernel that walks several tiles these two are loop invariant, and everything
     // derived from them (a dozen comparisons of the K count, the LDS address of every request of every stage)
     // would be precomputed once and kept alive in scalar registers across the whole tile loop, which overflows them.
@@ -299,9 +299,9 @@ struct Pipe {
     for (int s = 0; s < NSTAGES - 1; ++s)
       if (s < KT) {
 #pragma unroll
-        for (int i = 0; i < REQS_A; ++i) la.issue(i, lds + s * STAGE_BYTES + lds_wave * REQS_A / 4, s);
+        for (int i = 0; i < REQS_A; ++i) la.issue(i, lds + s * STAGE_BYTES + lds_wave * REQS_A, s);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lb.issue(i, lds + s * STAGE_BYTES + OPER_A + lds_wave, s);
+        for (int i = 0; i < REQS_B; ++i) lb.issue(i, lds + s * STAGE_BYTES + OPER_A + lds_wave * REQS_B, s);
       }
   }
 
@@ -317,13 +317,13 @@ struct Pipe {
     }
   }
 
-  __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[AM][WN]) {
-    constexpr int RA = FragAddr<LA, AM>::READS, RB = FragAddr<LB>::READS, RT = RA + RB;
+  __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[AM][AN]) {
+    constexpr int RA = FragAddr<LA, AM>::READS, RB = FragAddr<LB, AN>::READS, RT = RA + RB;
     if (KT <= 0) {          // an empty K extent (no counted row, or a K slice past the end): the tile is zero
 #pragma unroll
       for (int i = 0; i < AM; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j)
+        for (int j = 0; j < AN; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
       __builtin_amdgcn_s_barrier();
@@ -372,12 +372,12 @@ struct Pipe {
             else read_frag<LB>(FR.b, fb, st + OPER_A, ks, t - RA);
           }
         // the requests of one operand, evenly spread too: one in the middle of every NM / requests slots
-        constexpr int PER_A = NM / REQS_A, PER_B = NM / 4;
+        constexpr int PER_A = NM / REQS_A, PER_B = NM / REQS_B;
         if (load_kt >= 0) {
           if (which == 0) {
-            if (s % PER_A == PER_A / 2) la.issue(s / PER_A, lst + lds_wave * REQS_A / 4, load_kt);
+            if (s % PER_A == PER_A / 2) la.issue(s / PER_A, lst + lds_wave * REQS_A, load_kt);
           } else {
-            if (s % PER_B == PER_B / 2) lb.issue(s / PER_B, lst + OPER_A + lds_wave, load_kt);
+            if (s % PER_B == PER_B / 2) lb.issue(s / PER_B, lst + OPER_A + lds_wave * REQS_B, load_kt);
           }
         }
         __builtin_amdgcn_sched_barrier(0);

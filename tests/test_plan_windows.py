@@ -9,7 +9,7 @@ from paper_2511_17599_amd import binding as B
 
 def _windows(N, d, V, dt=B.FLCE_DTYPE_BF16):
     f = dict(kv.split("=") for kv in B.flce_plan_describe(N, d, V, dt).split()[2:])
-    return int(f["windows"]), int(f["fwd_ws"])
+    return int(f["windows"]), int(f["tiles"].split("/")[0])
 
 
 @pytest.mark.parametrize("seed", range(4))
@@ -17,14 +17,19 @@ def test_no_more_work_in_sequence_than_before(seed):
     r = random.Random(seed)
     for _ in range(200):
         N, V, d = r.randint(1, 60000), r.randint(1, 200000), 32 * r.randint(1, 128)
-        win, ws = _windows(N, d, V)
-        rb, vt = -(-N // 256), -(-V // 256)
-        old = min(max(4, -(-256 // rb)), vt)
-        seq = lambda w: -(-rb * w // 256) * (-(-vt // w) + 8.0 / (0.0242 * d))
+        win, tile = _windows(N, d, V)
+        rb, vt = -(-N // tile), -(-V // tile)
+        old = min(max(4, -(-256 // -(-N // 256))), -(-V // 256))   # (of the 256-row plan)
+        if tile == 256:                                      # one workgroup per CU
+            seq = lambda w: -(-rb * w // 256) * (-(-vt // w) + 8.0 / (0.0242 * d))
+        else:                                                # two
+            end = 1.5 / (0.28 * -(-d // 32) + 0.9)
+            seq = lambda w: (1.3 if rb * w <= 256 else 2 * -(-rb * w // 512)) * (-(-vt // w) + end)
         assert 1 <= win <= vt and seq(win) <= seq(old)
         assert rb * win <= max(8 * 256, rb * old)            # partials: bounded by 8 rounds of items
     # one more than a round is what it avoids: 5 row blocks
-    assert _windows(1030, 256, 20011)[0] * 5 <= 256
+    win, tile = _windows(1030, 2048, 20011)
+    assert tile == 256 and win * 5 <= 256
 
 
 def test_static_scratch_takes_the_same_shapes():
