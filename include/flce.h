@@ -164,6 +164,16 @@ flce_status flce_backward(const void* H, const void* W, const int64_t* targets, 
                           void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /*
+ * flce_backward with the upstream gradient of the scalar loss in device memory (one float, read by the kernels on the
+ * stream), for callers that have it there and would have to wait for the stream to hand it over as a host value.
+ */
+flce_status flce_backward_device_grad(const void* H, const void* W, const int64_t* targets, const float* lse,
+                                      int64_t N, int64_t d, int64_t V, int64_t ignore_index,
+                                      flce_reduction reduction, flce_dtype dt, const float* grad_loss,
+                                      void* dH_out, void* dW_out,
+                                      void* workspace, size_t workspace_bytes, void* hip_stream);
+
+/*
  * flce_forward for callers that cannot allocate device memory or pass a workspace (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc).  Same computation and outputs as
  * flce_forward; the scratch (per-window softmax partials, per-block sums, status header) lives in a device

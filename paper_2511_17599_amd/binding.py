@@ -19,7 +19,7 @@ FLCE_DTYPE_BF16, FLCE_DTYPE_F32 = 0, 1
 FLCE_REDUCE_MEAN, FLCE_REDUCE_SUM = 0, 1
 FLCE_STATIC_SCRATCH_BYTES = 16 << 20
 
-EXPORTS = ("flce_version", "flce_tuning_reload", "flce_status_string", "flce_workspace_bytes", "flce_plan_describe", "flce_forward", "flce_backward", "flce_forward_static",
+EXPORTS = ("flce_version", "flce_tuning_reload", "flce_status_string", "flce_workspace_bytes", "flce_plan_describe", "flce_forward", "flce_backward", "flce_backward_device_grad", "flce_forward_static",
            "flce_forward_with_grads", "flce_scale", "flce_forward_rows", "flce_backward_rows", "flce_forward_partial", "flce_merge_workspace_bytes",
            "flce_merge_partials", "flce_backward_partial", "flce_last_device_status", "flce_profile_enable",
            "flce_profile_collect", "flce_probe")
@@ -57,6 +57,10 @@ def lib():
         L.flce_backward.argtypes = [c.c_void_p, c.c_void_p, c.c_void_p, c.c_void_p, c.c_int64, c.c_int64, c.c_int64,
                                     c.c_int64, c.c_int, c.c_int, c.c_float, c.c_void_p, c.c_void_p, c.c_void_p,
                                     c.c_size_t, c.c_void_p]
+        L.flce_backward_device_grad.restype = c.c_int
+        L.flce_backward_device_grad.argtypes = [c.c_void_p, c.c_void_p, c.c_void_p, c.c_void_p, c.c_int64, c.c_int64,
+                                                c.c_int64, c.c_int64, c.c_int, c.c_int, c.c_void_p, c.c_void_p, c.c_void_p,
+                                                c.c_void_p, c.c_size_t, c.c_void_p]
         L.flce_forward_with_grads.restype = c.c_int
         L.flce_forward_with_grads.argtypes = [c.c_void_p, c.c_void_p, c.c_void_p, c.c_int64, c.c_int64, c.c_int64,
                                               c.c_int64, c.c_int, c.c_int, c.c_void_p, c.c_void_p, c.c_void_p,
@@ -157,6 +161,13 @@ def flce_backward(H, W, targets, lse, N, d, V, ignore_index, reduction, dt, grad
     return lib().flce_backward(_ptr(H), _ptr(W), _ptr(targets), _ptr(lse), N, d, V, ignore_index, reduction, dt,
                                float(grad_loss), _ptr(dH_out), _ptr(dW_out), _ptr(workspace), workspace_bytes,
                                _stream(hip_stream))
+
+
+def flce_backward_device_grad(H, W, targets, lse, N, d, V, ignore_index, reduction, dt, grad_loss, dH_out, dW_out,
+                              workspace, workspace_bytes, hip_stream=None):
+    return lib().flce_backward_device_grad(_ptr(H), _ptr(W), _ptr(targets), _ptr(lse), N, d, V, ignore_index, reduction,
+                                           dt, _ptr(grad_loss), _ptr(dH_out), _ptr(dW_out), _ptr(workspace),
+                                           workspace_bytes, _stream(hip_stream))
 
 
 def flce_forward_with_grads(H, W, targets, N, d, V, ignore_index, reduction, dt, loss_out, lse_out, dH_partial,

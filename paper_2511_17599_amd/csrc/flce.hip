@@ -180,8 +180,11 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
       return (items <= NUM_CU ? alone : 2.0 * (double)ceil_div(items, 2 * NUM_CU)) * ((double)longest + start);
     };
     const int64_t most = allow_h_copy && !f32 ? std::min<int64_t>(vt, std::max<int64_t>(cover, 8 * NUM_CU / rb)) : cover;
-    for (int64_t win = std::min<int64_t>(4, cover); win <= most; ++win)
+    for (int r = 1; r <= 8; ++r) {          // per number of rounds the most windows that fit, and of those as few as
+      const int64_t fit = std::max<int64_t>(1, std::min<int64_t>(most, r * NUM_CU / rb));      // make the longest no longer
+      const int64_t win = std::min(most, std::max<int64_t>(std::min<int64_t>(4, cover), ceil_div(vt, ceil_div(vt, fit))));
       if (cost(win) < 0.99 * cost(p.n_win)) p.n_win = (int)win;
+    }
     part_windows = std::max(cover, p.n_win);
   }
   const int win = part_windows;
@@ -284,13 +287,17 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
     if (p.n_vch == 1 && p.n_nch == 1 && (p.fast || f32) && tn.splitk_dh == 0 && tn.splitk_dw == 0 &&
         tiles_dh + tiles_dw <= (tile != TILE ? 2 : 1) * NUM_CU) {
       double best = 0.97 * c.us;
-      for (int64_t len = std::max(k_dh, k_dw); len >= 1; --len) {
+      auto consider = [&](int64_t len) {
         const int64_t sh = ceil_div(k_dh, len), sw = ceil_div(k_dw, len);
         const int64_t wgs = tiles_dh * sh + tiles_dw * sw;
-        if (sh > MAX_SPLIT || sw > MAX_SPLIT || wgs > 2 * NUM_CU) break;
+        if (sh > MAX_SPLIT || sw > MAX_SPLIT || wgs > 2 * NUM_CU) return;
         const double cost = rounds(wgs) * ((double)len + ends) * k_us + (sh > 1 || sw > 1 ? launch : 0.0) +
                             tile_us * (double)((sh > 1 ? tiles_dh * sh : 0) + (sw > 1 ? tiles_dw * sw : 0));
         if (cost < best) { best = c.us = cost; c.pair = true; c.split_dh = (int)sh; c.split_dw = (int)sw; }
+      };
+      for (int sp = 1; sp <= MAX_SPLIT; ++sp) {       // the slice lengths at which one of the two numbers of slices changes
+        consider(ceil_div(k_dh, sp));
+        consider(ceil_div(k_dw, sp));
       }
     }
     return c;
@@ -523,7 +530,7 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
 
 template <typename T, typename U, typename L>
 flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_t* y, const float* lse,
-                       int64_t ignore_index, int mean, float grad_loss, void* dH, void* dW, char* ws,
+                       int64_t ignore_index, int mean, GradLoss grad_loss, void* dH, void* dW, char* ws,
                        hipStream_t st, Slice slice, PerRow rows = PerRow{nullptr, nullptr, 0.f}) {
   if (prepare_kernels<T, L>() != hipSuccess) return FLCE_ERR_HIP;
   if (L::TUNED && !p.hkr) return FLCE_ERR_UNSUPPORTED;   // (no caller plans a backward without the copies of H)
@@ -865,8 +872,8 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
 
 static flce_status backward_impl(const void* H, const void* W, const int64_t* targets, const float* lse, int64_t N,
                                  int64_t d, int64_t V, int64_t ignore_index, flce_reduction reduction, flce_dtype dt,
-                                 float grad_loss, void* dH_out, void* dW_out, void* workspace, size_t workspace_bytes,
-                                 void* hip_stream, flce::Slice slice,
+                                 flce::GradLoss grad_loss, void* dH_out, void* dW_out, void* workspace,
+                                 size_t workspace_bytes, void* hip_stream, flce::Slice slice,
                                  flce::PerRow rows = flce::PerRow{nullptr, nullptr, 0.f}) {
   if (!H || !W || !targets || !lse || !dH_out || !dW_out) return FLCE_ERR_BAD_ARG;
   if (!(rows.eps >= 0.f && rows.eps < 1.f)) return FLCE_ERR_BAD_ARG;
@@ -910,8 +917,17 @@ flce_status flce_backward(const void* H, const void* W, const int64_t* targets, 
                           int64_t d, int64_t V, int64_t ignore_index, flce_reduction reduction, flce_dtype dt,
                           float grad_loss, void* dH_out, void* dW_out, void* workspace, size_t workspace_bytes,
                           void* hip_stream) {
-  return backward_impl(H, W, targets, lse, N, d, V, ignore_index, reduction, dt, grad_loss, dH_out, dW_out,
-                       workspace, workspace_bytes, hip_stream, flce::Slice{V, 0});
+  return backward_impl(H, W, targets, lse, N, d, V, ignore_index, reduction, dt, flce::GradLoss{grad_loss, nullptr}, dH_out,
+                       dW_out, workspace, workspace_bytes, hip_stream, flce::Slice{V, 0});
+}
+
+flce_status flce_backward_device_grad(const void* H, const void* W, const int64_t* targets, const float* lse, int64_t N,
+                                      int64_t d, int64_t V, int64_t ignore_index, flce_reduction reduction, flce_dtype dt,
+                                      const float* grad_loss, void* dH_out, void* dW_out, void* workspace,
+                                      size_t workspace_bytes, void* hip_stream) {
+  if (!grad_loss) return FLCE_ERR_BAD_ARG;
+  return backward_impl(H, W, targets, lse, N, d, V, ignore_index, reduction, dt, flce::GradLoss{0.f, grad_loss}, dH_out,
+                       dW_out, workspace, workspace_bytes, hip_stream, flce::Slice{V, 0});
 }
 
 flce_status flce_forward_static(const void* H, const void* W, const int64_t* targets, int64_t N, int64_t d, int64_t V,
@@ -947,7 +963,7 @@ flce_status flce_backward_rows(const void* H, const void* W, const int64_t* targ
                                float label_smoothing, flce_dtype dt, void* dH_out, void* dW_out, void* workspace,
                                size_t workspace_bytes, void* hip_stream) {
   if (!grad_rows) return FLCE_ERR_BAD_ARG;
-  return backward_impl(H, W, targets, lse, N, d, V, ignore_index, FLCE_REDUCE_SUM, dt, 1.0f, dH_out, dW_out,
+  return backward_impl(H, W, targets, lse, N, d, V, ignore_index, FLCE_REDUCE_SUM, dt, flce::GradLoss{1.0f, nullptr}, dH_out, dW_out,
                        workspace, workspace_bytes, hip_stream, flce::Slice{V, 0},
                        flce::PerRow{nullptr, grad_rows, label_smoothing});
 }
@@ -999,8 +1015,8 @@ flce_status flce_backward_partial(const void* H, const void* W_slice, const int6
                                   int64_t ignore_index, flce_reduction reduction, flce_dtype dt, float grad_loss,
                                   void* dH_partial_out, void* dW_slice_out, void* workspace,
                                   size_t workspace_bytes, void* hip_stream) {
-  return backward_impl(H, W_slice, targets, lse, N, d, V_slice, ignore_index, reduction, dt, grad_loss,
-                       dH_partial_out, dW_slice_out, workspace, workspace_bytes, hip_stream,
+  return backward_impl(H, W_slice, targets, lse, N, d, V_slice, ignore_index, reduction, dt,
+                       flce::GradLoss{grad_loss, nullptr}, dH_partial_out, dW_slice_out, workspace, workspace_bytes, hip_stream,
                        flce::Slice{V_total, v_begin});
 }
 

@@ -1197,13 +1197,19 @@ enum : int { READ_ACC = 1, WRITE_ACC = 2, WRITE_OUT = 4, ROWS_COMPACT = 8, K_COM
 //   OPS_DW_F32 : fp32; A = Hc rows of the row chunk [k][m], B = G row-major [k][n] (K over the rows of both)
 enum : int { OPS_KC = 0, OPS_DH_TR = 1, OPS_DW_TR = 2, OPS_DH_F32 = 3, OPS_DW_F32 = 4 };
 
+// Upstream gradient of the scalar loss: a device word if there is one, a host value otherwise.
+struct GradLoss {
+  float value; const float* word;
+  __device__ __forceinline__ float get() const { return word ? *word : value; }
+};
+
 template <typename T>
 struct ContractArgs {
   const T* A; int64_t lda; int a_krows, d;
   const T* B; int64_t ldb; int b_rows, k_elems, k_start, n_mt, n_nt;
   float* accbuf; int acc_row0;
   T* out; int out_row0, out_rows, flags;
-  const Header* hdr; const int* rowmap; float grad_loss; int mean;
+  const Header* hdr; const int* rowmap; GradLoss grad_loss; int mean;
   // split-K (n_split > 1): the launch has n_split x tiles workgroups; slice z contracts K elements
   // [z * k_split, (z + 1) * k_split) and stores its fp32 tile into partial + z * partial_stride (indexed like
   // accbuf); splitk_reduce_kernel then adds the slices in slice order and does the READ/WRITE part of `flags`.
@@ -1232,8 +1238,8 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
   if (b >= total) return;
   int k_all = a.k_elems;
   if (a.flags & K_COMPACT) k_all = max(0, min(k_all, (nv - a.k_start + L::TILE - 1) / L::TILE * L::TILE));
-  float scale = a.grad_loss;
-  if (a.mean) scale = nv > 0 ? a.grad_loss / (float)nv : 0.f;
+  float scale = a.grad_loss.get();
+  if (a.mean) scale = nv > 0 ? scale / (float)nv : 0.f;
 
   // item -> K slice z, output-row tile p, hidden tile q; K range [k0, k0 + k_elems) of the slice
   auto place = [&](int item, int& z, int& p, int& q, int& k0, int& k_elems) {
@@ -1453,8 +1459,8 @@ __device__ __forceinline__ void splitk_reduce(const ContractArgs<T>& a, int laun
     orow = a.rowmap[n];
     if (orow < 0) return;
   }
-  float scale = a.grad_loss;
-  if (a.mean) scale = nv > 0 ? a.grad_loss / (float)nv : 0.f;
+  float scale = a.grad_loss.get();
+  if (a.mean) scale = nv > 0 ? scale / (float)nv : 0.f;
   const int64_t off = (int64_t)(n - a.acc_row0) * a.d + m;
   f32x4 v = *reinterpret_cast<const f32x4*>(a.partial + off);
   constexpr int U = 8;

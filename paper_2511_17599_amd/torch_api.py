@@ -19,6 +19,14 @@ _DT = {torch.bfloat16: B.FLCE_DTYPE_BF16, torch.float32: B.FLCE_DTYPE_F32}
 _RED = {"mean": B.FLCE_REDUCE_MEAN, "sum": B.FLCE_REDUCE_SUM}
 
 
+# the current stream's handle, without a Stream object around it where torch offers that
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(device):
+    return _raw_stream(device.index) if _raw_stream else torch.cuda.current_stream(device).cuda_stream
+
+
 def _check(rc):
     if rc != B.FLCE_OK:
         raise RuntimeError(f"libflce: {B.flce_status_string(rc)}")
@@ -53,7 +61,7 @@ class _ScalarLoss(torch.autograd.Function):
         N, d = H2.shape
         V = W2.shape[0]
         dt = _DT[H2.dtype]
-        st = torch.cuda.current_stream(H2.device)
+        st = _stream(H2.device)
         loss = torch.empty(1, dtype=torch.float32, device=H2.device)
         lse = torch.empty(N, dtype=torch.float32, device=H2.device)
         ws, nb = _workspace(N, d, V, dt, 0, H2.device)
@@ -69,13 +77,15 @@ class _ScalarLoss(torch.autograd.Function):
         N, d = H2.shape
         V = W2.shape[0]
         dt = _DT[H2.dtype]
-        st = torch.cuda.current_stream(H2.device)
+        st = _stream(H2.device)
         dH = torch.empty_like(H2)
         dW = torch.empty_like(W2)
         ws, nb = _workspace(N, d, V, dt, 1, H2.device)
-        # the library takes the upstream gradient as a host scalar: reading it waits for the stream
-        g = float(grad_out)
-        _check(B.flce_backward(H2, W2, y, lse, N, d, V, ignore_index, _RED[reduction], dt, g, dH, dW, ws, nb, st))
+        # The kernels read the upstream gradient where it is: no wait for the stream between forward and backward.  (The
+        # autograd engine runs this on the forward's stream and keeps gradients made on another one alive for it.)
+        g = grad_out.to(device=H2.device, dtype=torch.float32)
+        _check(B.flce_backward_device_grad(H2, W2, y, lse, N, d, V, ignore_index, _RED[reduction], dt, g, dH, dW, ws, nb,
+                                           st))
         return dH.reshape(shape), dW, None, None, None
 
 
@@ -88,7 +98,7 @@ class _RowLosses(torch.autograd.Function):
         N, d = H2.shape
         V = W2.shape[0]
         dt = _DT[H2.dtype]
-        st = torch.cuda.current_stream(H2.device)
+        st = _stream(H2.device)
         rows = torch.empty(N, dtype=torch.float32, device=H2.device)
         lse = torch.empty(N, dtype=torch.float32, device=H2.device)
         ws, nb = _workspace(N, d, V, dt, 0, H2.device)
@@ -104,7 +114,7 @@ class _RowLosses(torch.autograd.Function):
         N, d = H2.shape
         V = W2.shape[0]
         dt = _DT[H2.dtype]
-        st = torch.cuda.current_stream(H2.device)
+        st = _stream(H2.device)
         dH = torch.empty_like(H2)
         dW = torch.empty_like(W2)
         gr = grad_rows.reshape(-1).to(torch.float32).contiguous()
