@@ -1054,12 +1054,10 @@ flce_status flce_scale(const void* dH_partial, const void* dW_partial, int64_t N
     using T = decltype(tag);
     flce::ProfScope ps(FLCE_PROF_SCALE, st);
     const int64_t nh = N * d / 4, nw = V * d / 4;
-    const unsigned gh = (unsigned)std::min<int64_t>(flce::ceil_div(nh, 256), 16384);
-    const unsigned gw = (unsigned)std::min<int64_t>(flce::ceil_div(nw, 256), 16384);
-    flce::scale_kernel<T><<<gh, 256, 0, st>>>(static_cast<const T*>(dH_partial), static_cast<T*>(dH_out), nh, hdr,
-                                              grad_loss, mean);
-    flce::scale_kernel<T><<<gw, 256, 0, st>>>(static_cast<const T*>(dW_partial), static_cast<T*>(dW_out), nw, hdr,
-                                              grad_loss, mean);
+    const unsigned grid = (unsigned)std::min<int64_t>(flce::ceil_div(nh + nw, 256), 16384);
+    flce::scale_kernel<T><<<grid, 256, 0, st>>>(static_cast<const T*>(dH_partial), static_cast<T*>(dH_out), nh,
+                                                static_cast<const T*>(dW_partial), static_cast<T*>(dW_out), nw, hdr,
+                                                grad_loss, mean);
   };
   if (dt == FLCE_DTYPE_BF16) run(flce::bf16_t{});
   else run(float{});

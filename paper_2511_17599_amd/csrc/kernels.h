@@ -1493,17 +1493,22 @@ __global__ __launch_bounds__(256) void splitk_reduce_pair_kernel(ContractArgs<T>
   else splitk_reduce(h, rows_h, (int)blockIdx.x - blocks_w);
 }
 
-// Alg. 4, scalar branch: out = Gamma * in, elementwise, Gamma from the header's n_valid.
+// Alg. 4, scalar branch: out = Gamma * in, elementwise, Gamma from the header's n_valid.  Both gradients in one launch, one
+// after the other in 8-byte or 16-byte groups of four; bound by memory.
 template <typename T>
-__global__ __launch_bounds__(256) void scale_kernel(const T* __restrict__ in, T* __restrict__ out, int64_t n4,
+__global__ __launch_bounds__(256) void scale_kernel(const T* __restrict__ in_h, T* __restrict__ out_h, int64_t n4_h,
+                                                    const T* __restrict__ in_w, T* __restrict__ out_w, int64_t n4_w,
                                                     const Header* __restrict__ hdr, float grad_loss, int mean) {
   const int nv = (int)hdr->n_valid;
   float scale = grad_loss;
   if (mean) scale = nv > 0 ? grad_loss / (float)nv : 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4_h + n4_w; i += (int64_t)gridDim.x * 256) {
+    const bool h = i < n4_h;
+    const T* in = h ? in_h + i * 4 : in_w + (i - n4_h) * 4;
+    T* out = h ? out_h + i * 4 : out_w + (i - n4_h) * 4;
     float v[4];
-    Pack4<T>::load(in + i * 4, v);
-    Pack4<T>::store(out + i * 4, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f, v[3] * scale + 0.f);
+    Pack4<T>::load(in, v);
+    Pack4<T>::store(out, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f, v[3] * scale + 0.f);
   }
 }
 
