@@ -182,7 +182,8 @@ flce_status flce_backward_device_grad(const void* H, const void* W, const int64_
  * array's address once per device, then only launches kernels on `hip_stream`.
  *   Limit    : shapes whose forward scratch exceeds the array return FLCE_ERR_WORKSPACE and launch nothing.
  *              The scratch is 12 * windows * ceil(N/256)*256 + 4 * ceil(V/1024) * d + 4 * N bytes + ~2 KiB
- *              (windows = max(4, ceil(256 / ceil(N/256))) unless FLCE_WINDOWS says otherwise): N up to about
+ *              (windows = max(4, ceil(256 / ceil(N/256))) unless FLCE_WINDOWS says otherwise; more are used where the
+ *              array has room for them, which does not change what is accepted): N up to about
  *              250 000 rows at d = 4096, V = 128256.  H is read in place (flce_forward's pre-tiled copy of
  *              H is what does not fit a fixed array), which costs up to a tenth of the forward's speed.
  *   status_out, n_valid_out : device, one int32 / one int64, either may be NULL: the range flag (0 or

@@ -122,7 +122,9 @@ bool fast_loop_ok(const Plan& p, const Tuning& tn) {
          window_ok(vc, ld_hw) && window_ok(nc, ld_hw) && window_ok(nc, ld_g);   // K over memory rows
 }
 
-bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool allow_h_copy = true) {
+// allow_h_copy: the caller has a workspace for the pre-tiled copy of H.  wide: ... and for the partials of more windows than
+// cover the CUs.
+bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool allow_h_copy = true, bool wide = true) {
   if (N <= 0 || d <= 0 || V <= 0 || (d % 8) != 0) return false;
   if (N > 0x7FFFFF00ll || V > 0x7FFFFF00ll || d > (1 << 24)) return false;
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return false;
@@ -170,16 +172,20 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
     // 24 ns per K element and tile).  fp32 (two per CU): a CU with two items takes them side by side at half the speed,
     // one alone leaves about a fifth of it unused.  One more than a round is what this avoids: 13 row blocks x 20 windows
     // were 260 items, the last 4 of them a launch as long as the first 256 (3300 x 2048 x 65536 forward: 1187 us, with 19
-    // windows 743).  The callers that cannot pass a workspace, and fp32, keep to the partials of `cover` windows.
+    // windows 743).  Callers without a workspace may have room for the partials of `cover` windows only (100 x 2112 x 22439
+    // without one: 57 us with 88 windows, 36 with 176), and fp32 keeps to them too.
     const int64_t rb = ceil_div(N, p.fwd_tile), vt = ceil_div(V, p.fwd_tile);
     const double fill = 8.0 / (0.0242 * (double)d);
+    const double tile_us = p.fwd_tile == TILE ? 0.775 * steps : 0.28 * steps + 0.9;
     auto cost = [&](int64_t win) {
       const int64_t items = rb * win, longest = ceil_div(vt, win);
-      if (p.fwd_tile == TILE) return (double)ceil_div(items, NUM_CU) * ((double)longest + fill);
+      // the merge takes 16 threads x 16 windows at a time, 4 us each
+      const double merge = f32 ? 0.0 : 4.0 * (double)(ceil_div(win, 256) - 1) / tile_us;
+      if (p.fwd_tile == TILE) return (double)ceil_div(items, NUM_CU) * ((double)longest + fill) + merge;
       const double start = f32 ? 0.0 : 1.5 / (0.28 * steps + 0.9), alone = f32 ? 1.2 : 1.3;
-      return (items <= NUM_CU ? alone : 2.0 * (double)ceil_div(items, 2 * NUM_CU)) * ((double)longest + start);
+      return (items <= NUM_CU ? alone : 2.0 * (double)ceil_div(items, 2 * NUM_CU)) * ((double)longest + start) + merge;
     };
-    const int64_t most = allow_h_copy && !f32 ? std::min<int64_t>(vt, std::max<int64_t>(cover, 8 * NUM_CU / rb)) : cover;
+    const int64_t most = wide && !f32 ? std::min<int64_t>(vt, std::max<int64_t>(cover, 8 * NUM_CU / rb)) : cover;
     for (int r = 1; r <= 8; ++r) {          // per number of rounds the most windows that fit, and of those as few as
       const int64_t fit = std::max<int64_t>(1, std::min<int64_t>(most, r * NUM_CU / rb));      // make the longest no longer
       const int64_t win = std::min(most, std::max<int64_t>(std::min<int64_t>(4, cover), ceil_div(vt, ceil_div(vt, fit))));
@@ -836,7 +842,7 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
                                 float* loss_out, float* lse_out, void* workspace, size_t workspace_bytes,
                                 void* hip_stream, flce::Slice slice, float* m_out, float* a_out, float* zt_out,
                                 flce::PerRow rows = flce::PerRow{nullptr, nullptr, 0.f}, bool allow_h_copy = true,
-                                flce::StatusOut so = flce::StatusOut{nullptr, nullptr}) {
+                                bool wide = true, flce::StatusOut so = flce::StatusOut{nullptr, nullptr}) {
   const bool partial = m_out || a_out || zt_out;
   if (!H || !W || !targets) return FLCE_ERR_BAD_ARG;
   if (partial ? (!m_out || !a_out || !zt_out) : ((!loss_out && !rows.loss_rows_out) || !lse_out))
@@ -845,7 +851,7 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
   if (reduction != FLCE_REDUCE_MEAN && reduction != FLCE_REDUCE_SUM) return FLCE_ERR_BAD_ARG;
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return FLCE_ERR_BAD_ARG;
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p, allow_h_copy)) return FLCE_ERR_BAD_SHAPE;
+  if (!flce::make_plan(N, d, V, dt, p, allow_h_copy, wide)) return FLCE_ERR_BAD_SHAPE;
   if (slice.v_begin < 0 || slice.v_begin + V > slice.V_total) return FLCE_ERR_BAD_SHAPE;
   if (!flce::aligned16(H) || !flce::aligned16(W)) return FLCE_ERR_BAD_ARG;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < (size_t)p.fwd_bytes)
@@ -938,14 +944,18 @@ flce_status flce_forward_static(const void* H, const void* W, const int64_t* tar
   if (!H || !W || !targets || !loss_out || !lse_out) return FLCE_ERR_BAD_ARG;
   if (reduction != FLCE_REDUCE_MEAN && reduction != FLCE_REDUCE_SUM) return FLCE_ERR_BAD_ARG;
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return FLCE_ERR_BAD_ARG;
+  // More windows than cover the CUs are used where their partials fit too; what fits is decided without them.
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p, /*allow_h_copy=*/false)) return FLCE_ERR_BAD_SHAPE;
+  if (!flce::make_plan(N, d, V, dt, p, /*allow_h_copy=*/false, /*wide=*/false)) return FLCE_ERR_BAD_SHAPE;
   if ((size_t)p.fwd_bytes > flce::STATIC_SCRATCH_BYTES) return FLCE_ERR_WORKSPACE;
+  flce::Plan w;
+  const bool wide = flce::make_plan(N, d, V, dt, w, /*allow_h_copy=*/false, /*wide=*/true) &&
+                    (size_t)w.fwd_bytes <= flce::STATIC_SCRATCH_BYTES;
   void* ws = nullptr;
   if (flce::static_scratch(&ws) != hipSuccess) return FLCE_ERR_HIP;
   return forward_impl(H, W, targets, N, d, V, ignore_index, reduction, dt, loss_out, lse_out, ws,
                       flce::STATIC_SCRATCH_BYTES, hip_stream, flce::Slice{V, 0}, nullptr, nullptr, nullptr,
-                      flce::PerRow{nullptr, nullptr, 0.f}, /*allow_h_copy=*/false,
+                      flce::PerRow{nullptr, nullptr, 0.f}, /*allow_h_copy=*/false, wide,
                       flce::StatusOut{status_out, n_valid_out});
 }
 
