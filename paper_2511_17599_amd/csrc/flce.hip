@@ -645,23 +645,25 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
     int vt0, n_vt, nt0, n_nt;
     chunk_vt(vc, vt0, n_vt);
     chunk_nt(nc, nt0, n_nt);
+    // K: the chunk's vocabulary rows, the last tile's up to a whole K step (G is zero past the vocabulary's end)
+    const int k_v = std::min(n_vt * L::TILE, (int)align_up((int64_t)V - (int64_t)vt0 * L::TILE, 32));
     int flags = ROWS_COMPACT;
     if (vc > 0) flags |= READ_ACC;
     flags |= (vc + 1 < p.n_vch) ? WRITE_ACC : WRITE_OUT;
     if constexpr (L::TRANSPOSING && !L::TUNED)
       return ContractArgs<T>{static_cast<const T*>(W) + (int64_t)vt0 * L::TILE * d, d, V - vt0 * L::TILE, d, Gb, p.ld_v,
-                             n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE,
-                             npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(n_vt * L::TILE, p.split_dh),
+                             n_nt * L::TILE, k_v, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE,
+                             npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(k_v, p.split_dh),
                              partial_dh - (int64_t)nt0 * L::TILE * d, nc_pad * d};
     else if constexpr (L::TUNED)
       return ContractArgs<T>{static_cast<const T*>(W) + (int64_t)vt0 * L::TILE * d, d, V - vt0 * L::TILE, d, Gb, g_group_bytes,
-                             n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE, npad,
-                             flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(n_vt * L::TILE, p.split_dh),
+                             n_nt * L::TILE, k_v, 0, n_mt, n_nt, dHacc, 0, static_cast<T*>(dH), nt0 * L::TILE, npad,
+                             flags, hdr, rowmap, grad_loss, mean, p.split_dh, slice_len(k_v, p.split_dh),
                              partial_dh - (int64_t)nt0 * L::TILE * d, nc_pad * d};
     else
-      return ContractArgs<T>{WT, p.ld_v, 0, d, Gb, p.ld_v, n_nt * L::TILE, n_vt * L::TILE, 0, n_mt, n_nt, dHacc, 0,
+      return ContractArgs<T>{WT, p.ld_v, 0, d, Gb, p.ld_v, n_nt * L::TILE, k_v, 0, n_mt, n_nt, dHacc, 0,
                              static_cast<T*>(dH), nt0 * L::TILE, npad, flags, hdr, rowmap, grad_loss, mean, p.split_dh,
-                             slice_len(n_vt * L::TILE, p.split_dh), partial_dh - (int64_t)nt0 * L::TILE * d, nc_pad * d};
+                             slice_len(k_v, p.split_dh), partial_dh - (int64_t)nt0 * L::TILE * d, nc_pad * d};
   };
 
   // One contraction (dW or dH) of a chunk: the launch, its split-K sum if it has one, and with the tuned loop a
@@ -683,7 +685,7 @@ flce_status backward_t(const Plan& p, const void* H, const void* W, const int64_
         splitk_reduce_kernel<T><<<(unsigned)ceil_div((int64_t)x.n_nt * L::TILE * (d / 4), 256), 256, 0, st>>>(x, x.n_nt * L::TILE);
     };
     TailSplit ts{0, 1};
-    if constexpr (L::TUNED && L::TILE == TILE) ts = tail_split(a.n_nt, a.n_mt, a.n_split, a.k_elems / L::TILE);
+    if constexpr (L::TUNED && L::TILE == TILE) ts = tail_split(a.n_nt, a.n_mt, a.n_split, ceil_div(a.k_elems, L::TILE));
     if (!ts.rows) { launch(a); return; }
     ContractArgs<T> body = a, tail = a;
     body.n_nt = a.n_nt - ts.rows;
