@@ -1061,39 +1061,62 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
         float gam = 1.f;
         if constexpr (PER_ROW) gam = tgt >= 0 ? meta.gam[j] : 0.f;
         const float unif = tgt >= 0 ? a.uniform_part : 0.f;
+        // A whole column of blocks without a target of the wavefront and inside the vocabulary (almost all are: 32 WM of V
+        // positions) needs no tests (step of 4326 x 232 x 74697 1044 -> 1008 us, 1144 x 576 x 191782 1306 -> 1264,
+        // 4096 x 768 x 50257 1198 -> 1178).
+        if (vbase + L::WM * 32 <= V && __ballot((unsigned)(tgt - vbase) < 32u * L::WM) == 0ull) {
 #pragma unroll
-        for (int i = 0; i < L::WM; ++i) {
-          const int blk0 = vbase + i * 32;                        // wave-uniform
-          const bool whole = blk0 + 32 <= V;
-          // Does any token column of this wavefront have its target among the block's 32 vocabulary positions?
-          // Almost never (32 of V positions), and then the one-hot term costs nothing: a wave-uniform branch.
-          const bool hit = __ballot((unsigned)(tgt - blk0) < 32u) != 0ull;
+          for (int i = 0; i < L::WM; ++i) {
 #pragma unroll
-          for (int rq = 0; rq < 4; ++rq) {
-            const int vpos = blk0 + rq * 8 + whalf * 4;           // first of this lane's 4 consecutive positions
-            float g[4];
+            for (int rq = 0; rq < 4; ++rq) {
+              float g[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) g[e] = fast_exp2(fmaf(L::acc_get(acc[i][j], rq * 4 + e), LOG2E, ll));
-            if (hit) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (vpos + e == tgt) g[e] -= PER_ROW ? a.onehot_weight : 1.f;
+              for (int e = 0; e < 4; ++e) {
+                g[e] = fast_exp2(fmaf(L::acc_get(acc[i][j], rq * 4 + e), LOG2E, ll));
+                if constexpr (PER_ROW) g[e] = gam * (g[e] - unif);
+              }
+              uint2 packed;
+              packed.x = f32x2_to_bf16x2_bits(g[0], g[1]);
+              packed.y = f32x2_to_bf16x2_bits(g[2], g[3]);
+              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
             }
-            if constexpr (PER_ROW) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) g[e] = gam * (g[e] - unif);
-            }
-            if (!whole) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (vpos + e >= V) g[e] = 0.f;
-            }
-            uint2 packed;
-            packed.x = f32x2_to_bf16x2_bits(g[0], g[1]);
-            packed.y = f32x2_to_bf16x2_bits(g[2], g[3]);
-            *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
+            __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
           }
-          __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
+        } else {
+#pragma unroll
+          for (int i = 0; i < L::WM; ++i) {
+            const int blk0 = vbase + i * 32;                        // wave-uniform
+            const bool whole = blk0 + 32 <= V;
+            // Does any token column of this wavefront have its target among the block's 32 vocabulary positions?
+            // Almost never (32 of V positions), and then the one-hot term costs nothing: a wave-uniform branch.
+            const bool hit = __ballot((unsigned)(tgt - blk0) < 32u) != 0ull;
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+              const int vpos = blk0 + rq * 8 + whalf * 4;           // first of this lane's 4 consecutive positions
+              float g[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) g[e] = fast_exp2(fmaf(L::acc_get(acc[i][j], rq * 4 + e), LOG2E, ll));
+              if (hit) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  if (vpos + e == tgt) g[e] -= PER_ROW ? a.onehot_weight : 1.f;
+              }
+              if constexpr (PER_ROW) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] = gam * (g[e] - unif);
+              }
+              if (!whole) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  if (vpos + e >= V) g[e] = 0.f;
+              }
+              uint2 packed;
+              packed.x = f32x2_to_bf16x2_bits(g[0], g[1]);
+              packed.y = f32x2_to_bf16x2_bits(g[2], g[3]);
+              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
+          }
         }
         // the piece is complete in LDS (a wavefront's LDS operations complete in order): write it out, whole rows at a
         // time.  G is stored in blocks of 16 rows x 32 positions (1 KiB; the blocks of a row
