@@ -55,7 +55,7 @@
  * Defaults suit MI355X; results stay within the tolerances for any setting but their
  * rounding, and the bit pattern, depend on it:
  *   FLCE_WINDOWS    vocabulary windows of the forward (Section 3.2.1); 0 / unset = automatic
- *                   (at least 4 where V allows, row blocks x windows filling whole rounds of 256 workgroups).
+ *                   (at least 4 where V allows, row blocks x windows filling whole rounds of workgroups).
  *   FLCE_VC_TILES   largest vocabulary chunk of the backward, in 256-row tiles; 0 / unset = automatic
  *                   (128; up to 512 when there are fewer than 32 token tiles, same staging bytes).
  *   FLCE_NC_TILES   largest token chunk of the backward, in 256-row tiles (default 128).
@@ -105,7 +105,7 @@ const char* flce_status_string(flce_status s);
  * flce_backward (for_backward != 0) at this shape.  Returns 0 for an invalid
  * shape or dtype.  Host call, touches no device.
  *   forward : 12 * windows * Npad + 4 * ceil(V/1024) * d + 4 * N + O(N/256) bytes, plus Npad * d elements (and 17 KiB
- *             per 256 rows) for the pre-tiled copy of H that the tuned bf16 loop reads.  Npad = N rounded up to 256.
+ *             per 256 rows) for the pre-tiled copy of H, where the tuned bf16 loop reads one.  Npad = N rounded up to 256.
  *   backward: 2 * Npad * d elements (the counted rows of H packed together, in two copies: pre-tiled for the two
  *             kernels that read them, or plain and transposed with the generic loop; d rounded up to 256 in one) + 16 * Npad bytes
  *             + the staging tile for G: Nc x (Vc + 64) elements with Nc = min(Npad, 32768) and
@@ -125,7 +125,8 @@ size_t flce_workspace_bytes(int64_t N, int64_t d, int64_t V, flce_dtype dt, int 
 /*
  * Writes a one-line description of the launch plan at this shape (library version, main loop, windows,
  * chunk counts x largest chunk in 256-row tiles, K slices, K-split tails of a full chunk's dH / dW launch as
- * output-row tiles x slices, staging and workspace bytes) into `buf`; returns
+ * output-row tiles x slices, whether both contractions go out as one launch, tile edges of the
+ * forward and the backward, staging and workspace bytes) into `buf`; returns
  * the length it needs (as snprintf) or -1 for an invalid shape.  Reports and profile summaries carry it, so
  * that a measurement can be matched to the plan it was taken on.  Host call.
  */

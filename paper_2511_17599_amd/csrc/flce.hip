@@ -239,7 +239,7 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.fwd_copy = p.hkr && (double)N * (double)d * (double)V >= 4.6e10 + 9300.0 * (double)N * (double)d;
   p.fwd_bytes = fwd_fixed + (p.fwd_copy ? align_up(packed_block_offset(p.n_rb, (int)d), ALIGN) : 0);
   o = ALIGN;
-  // the counted rows of H: as they are (generic loop), or pre-tiled for the dW contraction (tuned loop)
+  // the counted rows of H: as they are (fp32, generic loop), or pre-tiled for the dW contraction (tuned loop)
   p.off_Hc = o;     o = align_up(o + (p.fast ? packed_cols_offset((int)ceil_div(d, TILE), (int)p.npad) : d * p.npad * p.esize), ALIGN);
   p.off_rowmap = o; o = align_up(o + p.npad * 4, ALIGN);
   p.off_tgt = o;    o = align_up(o + p.npad * 4, ALIGN);

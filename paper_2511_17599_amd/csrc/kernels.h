@@ -4,19 +4,23 @@
 //             gather per lane: Alg. 1 in tile form; one workgroup per row block x
 //             vocabulary window: Section 3.2.1)
 //             merge_rows_kernel (the merging epilogue of Section 3.2.1, lse = m + ln a,
-//             per-row loss, fixed-order sums; finalize_loss_kernel for a merge on its own)
-//   backward: compact_targets_kernel + prep_rows_kernel (n_valid, range flag, and the
-//             rows that count packed together: ignored rows have a zero row of G; a second
-//             copy of them transposed (generic loop) or pre-tiled (tuned loop))
-//             pack_rows_kernel (the forward's pre-tiled copy of H for the tuned loop);
-//             transpose_pad_kernel (generic loop: the K-contiguous copy of W that the dH
-//             contraction needs)
+//             per-row loss; its last block adds the blocks' sums in fixed order;
+//             finalize_loss_kernel does that for flce_merge_partials)
+//   backward: compact_targets_kernel (n_valid, range flag, the rows that count; up to 2048
+//             rows the row preparation does its scan itself) and prep_rows_tiled_kernel /
+//             prep_rows_kernel (the rows that count packed together, since ignored rows have a
+//             zero row of G: pre-tiled, twice, for the tuned loop; as they are for fp32;
+//             as they are and transposed for the generic loop)
+//             pack_rows_kernel (the forward's pre-tiled copy of H for the tuned loop, where
+//             it pays); transpose_pad_kernel (generic loop: the K-contiguous copy of W that the
+//             dH contraction needs)
 //             recompute_kernel (Alg. 2: z recomputed, g = p - onehot, staged once in a
 //             fixed-size buffer; the generic loop also stages the transpose)
 //             contract_kernel (Eq. 4 and Eq. 5 as output-stationary MFMA
-//             contractions with a fixed chunk order; Gamma applied at the flush)
-//             splitk_reduce_kernel (fixed-order sum of K slices when a contraction
-//             launch would otherwise leave most CUs idle)
+//             contractions with a fixed chunk order; Gamma applied at the flush);
+//             contract_pair_kernel (both in one launch, small problems)
+//             splitk_reduce_kernel / splitk_reduce_pair_kernel (fixed-order sum of K slices
+//             when a contraction launch would otherwise leave most CUs idle)
 //   Alg. 3/4: the forward and the backward above with Gamma = 1, then scale_kernel
 //   per row : merge_rows_kernel writes one loss per row (label smoothing: colsum_* and
 //             mean_logit_kernel give mean_v Z_iv), recompute_kernel<.., PER_ROW> scales each

@@ -1,9 +1,10 @@
 // bf16 main loop tuned for gfx950: 256 x 256 tile, 256 threads = 4 wavefronts (one per
 // SIMD) arranged 2 x 2, each owning a 128 x 128 sub-tile (4 x 4 blocks of the
-// 32x32x16 MFMA, 256 fp32 accumulators per lane).
+// 32x32x16 MFMA, 256 fp32 accumulators per lane); or, with 2 x 2 blocks per wavefront, a 128 x 128
+// tile of which two workgroups fit on a CU, for problems with few tiles or a short K.
 //
 //   * Operand tiles go from global memory straight into LDS (buffer_load ... lds,
-//     16 bytes per lane), four stages of 32 bf16 of K deep, so a tile is requested
+//     16 bytes per lane), four stages (128-row tiles: five) of 32 bf16 of K deep, so a tile is requested
 //     two to three K steps before it is read.  Rows past the end of a tensor are
 //     zero-filled by the buffer's range check.
 //   * Each operand may be stored either way round in memory:
