@@ -29,10 +29,11 @@ namespace f32 {
 
 constexpr int THREADS = 256;
 constexpr int BK = 32;                                      // K elements per stage
-// Stages whose products are added up before they are added to the tile's sum: a chain of 1024 additions and one of
-// K / 1024 instead of one of K, which the dH contraction (K = the vocabulary) would otherwise show: 3.3e-6 relative error
-// against 64 bits at 4096 x 1024 x 32768, 5.8e-7 with partial sums, at the same speed.
-constexpr int SUM_STAGES = 32;
+// Stages whose products are added up before they are added to the tile's sum: a chain of 512 additions and one of
+// K / 512 instead of one of K, which the contractions (K = the vocabulary, the rows) would otherwise show.  Relative error of
+// dH and dW against 64 bits at 4096 x 1024 x 16384: about 3e-6 with one chain, 5.8e-7 and 5.8e-7 with 1024, 4.2e-7 and 4.1e-7
+// with 512 (8215 -> 8248 us per step at twice the vocabulary), 3.2e-7 and 3.0e-7 with 256 (8360 us).
+constexpr int SUM_STAGES = 16;
 enum : int { KC = 0, KR = 1 };
 
 // One operand of the contraction.
