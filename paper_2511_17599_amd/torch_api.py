@@ -84,6 +84,8 @@ class _ScalarLoss(torch.autograd.Function):
         # The kernels read the upstream gradient where it is: no wait for the stream between forward and backward.  (The
         # autograd engine runs this on the forward's stream and keeps gradients made on another one alive for it.)
         g = grad_out.to(device=H2.device, dtype=torch.float32)
+        if g.is_neg() or g._is_zerotensor():     # marked, not stored: the word in memory is not the value, or there is none
+            g = g.clone().resolve_neg()
         _check(B.flce_backward_device_grad(H2, W2, y, lse, N, d, V, ignore_index, _RED[reduction], dt, g, dH, dW, ws, nb,
                                            st))
         return dH.reshape(shape), dW, None, None, None
