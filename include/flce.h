@@ -105,7 +105,8 @@ const char* flce_status_string(flce_status s);
  * flce_backward (for_backward != 0) at this shape.  Returns 0 for an invalid
  * shape or dtype.  Host call, touches no device.
  *   forward : 12 * windows * Npad + 4 * ceil(V/1024) * d + 4 * N + O(N/256) bytes, plus Npad * d elements (and 17 KiB
- *             per 256 rows) for the pre-tiled copy of H, where the tuned bf16 loop reads one.  Npad = N rounded up to 256.
+ *             per 256 rows) for the pre-tiled copy of H, where the tuned bf16 loop reads one (with d % 32 != 0 only up
+ *             to 512 MiB: beyond, H is read in place).  Npad = N rounded up to 256.
  *   backward: 2 * Npad * d elements (the counted rows of H packed together, in two copies: pre-tiled for the two
  *             kernels that read them, or plain and transposed with the generic loop; d rounded up to 256 in one) + 16 * Npad bytes
  *             + the staging tile for G: Nc x (Vc + 64) elements with Nc = min(Npad, 32768) and

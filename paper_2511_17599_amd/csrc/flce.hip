@@ -28,6 +28,8 @@ constexpr int NUM_CU = 256;   // MI355X; the plan must not depend on a device qu
 // 256 rows, d = 128, V = 82194 has 321 K tiles; with 8 slices (8 busy CUs)
 // the whole step took 318 us, with 64 it takes 134 (200 x 1024 x 50257: 317 and 210).
 constexpr int MAX_SPLIT = 64;
+// Most bytes that a plan spends on the forward's copy of H at a ragged hidden size.
+constexpr int64_t BYTES_CAP = (int64_t)512 << 20;
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -236,8 +238,13 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   // The copy takes a launch (5 us) and one pass over H (4 N d bytes at 4 TB/s), and saves the loop about 7 % (2 N d V flops
   // at 1.3 PFLOP/s): below this it costs more than it gives (585 x 384 x 20040 forward 27.9 us
   // with it, 25.7 without; 614 x 2496 x 512 step 159 / 152; 2048 x 1024 x 32000, just above the line, level).
-  p.fwd_copy = p.hkr && (double)N * (double)d * (double)V >= 4.6e10 + 9300.0 * (double)N * (double)d;
-  p.fwd_bytes = fwd_fixed + (p.fwd_copy ? align_up(packed_block_offset(p.n_rb, (int)d), ALIGN) : 0);
+  // Hidden sizes that are no multiple of 32 take it up to a bounded size only: without it such a forward runs in O(N + d)
+  // words, and an evaluation sized by those has to fit whatever N and d (H read in place costs 6-20 %: 8192 x 4104 x 128256
+  // 7.09 -> 8.49 ms, 32768 x 1048 x 131072 8.44 -> 9.89, 16384 x 520 x 60000 1.07 -> 1.14; these are below the bound).
+  const int64_t copy_bytes = align_up(packed_block_offset(p.n_rb, (int)d), ALIGN);
+  p.fwd_copy = p.hkr && !(p.ragged && copy_bytes > BYTES_CAP) &&
+               (double)N * (double)d * (double)V >= 4.6e10 + 9300.0 * (double)N * (double)d;
+  p.fwd_bytes = fwd_fixed + (p.fwd_copy ? copy_bytes : 0);
   o = ALIGN;
   // the counted rows of H: as they are (fp32, generic loop), or pre-tiled for the dW contraction (tuned loop)
   p.off_Hc = o;     o = align_up(o + (p.fast ? packed_cols_offset((int)ceil_div(d, TILE), (int)p.npad) : d * p.npad * p.esize), ALIGN);
