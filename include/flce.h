@@ -114,8 +114,10 @@ const char* flce_status_string(flce_status s);
  *               Nc * Vc stays within 2^25 elements there): at most 2 GiB + 4 MiB in bf16 whatever N and V,
  *               512 MiB at N = 8192; below the cap this IS Npad x Vpad, the whole G in the storage type;
  *             + fp32 running sums N * d (more than one vocabulary chunk) and Vc * d (more than one row chunk)
- *             + fp32 K-slice tiles when a contraction launch is split (small N or small d), or when the output-row
- *               tiles of its last, mostly empty round are launched on their own with K in slices (at most 64 MiB);
+ *             + fp32 K-slice tiles when a contraction launch is split (small N or small d): slices x Nc x d words for dH,
+ *               slices x Vc x d for dW, 64 slices and 512 MiB at most (the larger of the two, or both together when they
+ *               go out as one launch, which never has more than 128 MiB); or, when the output-row tiles of its last,
+ *               mostly empty round are launched on their own with K in slices, the tiles of those (at most 64 MiB);
  *             the generic loop (bf16 beyond a descriptor's reach) adds transposed copies of a W chunk and of G; fp32 reads all three
  *             where they lie (one copy of the counted rows of H).
  *   Beyond the cap the size grows like c1 * (N + V) * d + c2 * N + c3: no N * V term.  flce_plan_describe

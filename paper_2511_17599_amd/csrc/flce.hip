@@ -28,7 +28,8 @@ constexpr int NUM_CU = 256;   // MI355X; the plan must not depend on a device qu
 // 256 rows, d = 128, V = 82194 has 321 K tiles; with 8 slices (8 busy CUs)
 // the whole step took 318 us, with 64 it takes 134 (200 x 1024 x 50257: 317 and 210).
 constexpr int MAX_SPLIT = 64;
-// Most bytes that a plan spends on the forward's copy of H at a ragged hidden size.
+// Most bytes that a plan spends on the forward's copy of H at a ragged hidden size, and on the fp32 tiles of the K slices of
+// one contraction launch (60000 random shapes up to 140000 x 8192 x 262144: five would take more, 617 MB at most).
 constexpr int64_t BYTES_CAP = (int64_t)512 << 20;
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
@@ -280,16 +281,17 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
       return rounds(tiles * sp) * ((double)ceil_div(k_tiles, sp) + ends) * k_us +
              (sp > 1 ? launch + tile_us * (double)(tiles * sp) : 0.0);
     };
-    auto auto_split = [&](int64_t tiles, int64_t k_tiles) -> int {     // a split has to win by 5 %
+    auto auto_split = [&](int64_t tiles, int64_t k_tiles, int64_t out_rows) -> int {     // a split has to win by 5 %
       int best = 1;
-      for (int sp = 2; sp <= MAX_SPLIT && sp <= k_tiles; ++sp)
+      const int64_t most = std::min<int64_t>(MAX_SPLIT, BYTES_CAP / (out_rows * d * 4));
+      for (int sp = 2; sp <= most && sp <= k_tiles; ++sp)
         if (split_cost(tiles, k_tiles, sp) < split_cost(tiles, k_tiles, best) * (best == 1 ? 0.95 : 1.0)) best = sp;
       return best;
     };
     const int64_t tiles_dh = p.nc_tiles * unit * n_mt, k_dh = p.vc_tiles * unit;
     const int64_t tiles_dw = p.vc_tiles * unit * n_mt, k_dw = p.nc_tiles * unit;
-    if (c.split_dh == 0) c.split_dh = auto_split(tiles_dh, k_dh);
-    if (c.split_dw == 0) c.split_dw = auto_split(tiles_dw, k_dw);
+    if (c.split_dh == 0) c.split_dh = auto_split(tiles_dh, k_dh, nc_pad);
+    if (c.split_dw == 0) c.split_dw = auto_split(tiles_dw, k_dw, vc_pad);
     c.split_dh = (int)std::min<int64_t>(c.split_dh, k_dh);
     c.split_dw = (int)std::min<int64_t>(c.split_dw, k_dw);
     c.us = split_cost(tiles_dh, k_dh, c.split_dh) + split_cost(tiles_dw, k_dw, c.split_dw) + launch;

@@ -16,3 +16,14 @@ def test_ragged_hidden_sizes_run_the_forward_in_words_per_row(N, d, V):
     assert B.flce_workspace_bytes(N, d, V, BF16, 0) <= words
     n = CAP // 2 // (2 * d)
     assert B.flce_workspace_bytes(n, d, V, BF16, 0) >= n * d * 2
+
+
+@pytest.mark.parametrize("N,d,V,dt", [(6232, 8040, 106136, BF16), (32116, 2064, 23705, BF16), (3830, 4880, 136110, B.FLCE_DTYPE_F32),
+                                      (1500, 16384, 60000, BF16), (2, 1024, 159101, BF16), (2682, 6080, 72653, BF16)])
+def test_k_slices_take_a_bounded_share_of_the_workspace(N, d, V, dt):
+    f = dict(kv.split("=") for kv in B.flce_plan_describe(N, d, V, dt).split()[2:])
+    rows = {k: 256 * int(f[k].split("x")[1]) for k in ("row_chunks", "vocab_chunks")}
+    print(f)
+    for slices, chunk in (("splitk_dH", "row_chunks"), ("splitk_dW", "vocab_chunks")):
+        n = int(f[slices])
+        assert n <= 64 and (n == 1 or n * rows[chunk] * d * 4 <= CAP)
