@@ -136,6 +136,36 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.esize = dt == FLCE_DTYPE_BF16 ? 2 : 4;
   p.n_rb = (int)ceil_div(N, TILE);
   p.n_vt = (int)ceil_div(V, TILE);
+  p.npad = (int64_t)p.n_rb * TILE;
+
+  // Backward staging: a fixed-size G tile of at most vc x nc 256-tiles.
+  const int nc_max = tn.nc_tiles;
+  // Automatic vocabulary chunk: 128 tiles; with few token rows the same staging bytes reach further along the
+  // vocabulary (at most 128 x 32 tiles of G, 512 MiB in bf16, up to 512 vocabulary tiles), which saves whole
+  // launches and the fp32 running sum of dH on short-sequence shapes.  Kept within a buffer descriptor's reach.
+  int vc_max = tn.vc_tiles;
+  if (vc_max == 0) {
+    const int64_t nct = std::min<int64_t>(p.n_rb, nc_max);
+    vc_max = (int)std::max<int64_t>(128, std::min<int64_t>(512, 4096 / nct));
+    const int64_t reach = (((int64_t)1 << 32) / (d * p.esize) - 64) / TILE;
+    if (vc_max > 128 && reach < vc_max) vc_max = (int)std::max<int64_t>(128, reach);
+  }
+  // Chunks of the full size plus a remainder, so that launches of full chunks come out in whole rounds of 256
+  // workgroups (128 tiles times any even tile count); an even split only when the remainder would be a sliver.
+  auto chunking = [](int tiles, int cmax, int& n_chunks, int& chunk) {
+    n_chunks = (int)ceil_div(tiles, cmax);
+    const int rem = tiles - (n_chunks - 1) * cmax;
+    chunk = (n_chunks == 1 || rem * 4 >= cmax) ? std::min(tiles, cmax) : (int)ceil_div(tiles, n_chunks);
+  };
+  chunking(p.n_vt, vc_max, p.n_vch, p.vc_tiles);
+  chunking(p.n_rb, nc_max, p.n_nch, p.nc_tiles);
+  const int64_t vc_pad = (int64_t)p.vc_tiles * TILE, nc_pad = (int64_t)p.nc_tiles * TILE;
+  p.ld_v = vc_pad + 64;
+  p.ld_n = nc_pad + 64;
+  p.fast = fast_loop_ok(p, tn);
+  p.ragged = p.fast && d % 32 != 0;
+  p.hkr = allow_h_copy && p.fast;
+
   p.tile = TILE;
   // fp32: 64-row tiles while there are too few 128-row ones to give every CU more than one (whole steps: 256 x 256 x 4096,
   // 64 tiles of 128: 77 us with 64-row tiles against 118; 1024 x 512 x 4096, 256 tiles: 211 / 220; 1000 x 256 x 6400, 400
@@ -158,8 +188,7 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   auto logits_us = [&](int tile, double ends256, double ends128) {
     return tile == TILE ? (double)ceil_div(t256, NUM_CU) * (0.775 * steps + ends256) : small_waves(t128) * (0.28 * steps + 0.12 * std::max(0.0, steps - 64.0) + ends128);
   };
-  if (!f32 && !tn.generic && logits_us(128, 6.5, 0.9) < 0.95 * logits_us(TILE, 6.5, 0.9)) p.fwd_tile = 128;
-  p.npad = (int64_t)p.n_rb * TILE;
+  if (p.fast && logits_us(128, 6.5, 0.9) < 0.95 * logits_us(TILE, 6.5, 0.9)) p.fwd_tile = 128;
 
   // Windows (Section 3.2.1): enough (row block, window) workgroups to cover the CUs.
   // At least 4, so that the 32 workgroups resident on one XCD are 8 row blocks x 4 windows and
@@ -209,33 +238,6 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.off_fHT = o;        // sized below, once the loop flavour is known
   const int64_t fwd_fixed = o;
 
-  // Backward staging: a fixed-size G tile of at most vc x nc 256-tiles.
-  const int nc_max = tn.nc_tiles;
-  // Automatic vocabulary chunk: 128 tiles; with few token rows the same staging bytes reach further along the
-  // vocabulary (at most 128 x 32 tiles of G, 512 MiB in bf16, up to 512 vocabulary tiles), which saves whole
-  // launches and the fp32 running sum of dH on short-sequence shapes.  Kept within a buffer descriptor's reach.
-  int vc_max = tn.vc_tiles;
-  if (vc_max == 0) {
-    const int64_t nct = std::min<int64_t>(p.n_rb, nc_max);
-    vc_max = (int)std::max<int64_t>(128, std::min<int64_t>(512, 4096 / nct));
-    const int64_t reach = (((int64_t)1 << 32) / (d * p.esize) - 64) / TILE;
-    if (vc_max > 128 && reach < vc_max) vc_max = (int)std::max<int64_t>(128, reach);
-  }
-  // Chunks of the full size plus a remainder, so that launches of full chunks come out in whole rounds of 256
-  // workgroups (128 tiles times any even tile count); an even split only when the remainder would be a sliver.
-  auto chunking = [](int tiles, int cmax, int& n_chunks, int& chunk) {
-    n_chunks = (int)ceil_div(tiles, cmax);
-    const int rem = tiles - (n_chunks - 1) * cmax;
-    chunk = (n_chunks == 1 || rem * 4 >= cmax) ? std::min(tiles, cmax) : (int)ceil_div(tiles, n_chunks);
-  };
-  chunking(p.n_vt, vc_max, p.n_vch, p.vc_tiles);
-  chunking(p.n_rb, nc_max, p.n_nch, p.nc_tiles);
-  const int64_t vc_pad = (int64_t)p.vc_tiles * TILE, nc_pad = (int64_t)p.nc_tiles * TILE;
-  p.ld_v = vc_pad + 64;
-  p.ld_n = nc_pad + 64;
-  p.fast = fast_loop_ok(p, tn);
-  p.ragged = p.fast && d % 32 != 0;
-  p.hkr = allow_h_copy && p.fast;
   // The copy takes a launch (5 us) and one pass over H (4 N d bytes at 4 TB/s), and saves the loop about 7 % (2 N d V flops
   // at 1.3 PFLOP/s): below this it costs more than it gives (585 x 384 x 20040 forward 27.9 us
   // with it, 25.7 without; 614 x 2496 x 512 step 159 / 152; 2048 x 1024 x 32000, just above the line, level).

@@ -5,6 +5,7 @@ import random
 import pytest
 
 from paper_2511_17599_amd import binding as B
+from conftest import set_plan
 
 
 def _windows(N, d, V, dt=B.FLCE_DTYPE_BF16):
@@ -50,3 +51,14 @@ def test_static_scratch_takes_the_same_shapes():
         p = 4096
         call = lambda N: B.flce_forward_static(p, p, p, N, d, V, -100, B.FLCE_REDUCE_MEAN, B.FLCE_DTYPE_BF16, p, p)
         assert call(hi) == B.FLCE_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("knobs,N,d,V", [({"FLCE_VC_TILES": 4096}, 100, 4096, 1050000), ({"FLCE_GENERIC": 1}, 300, 256, 5000),
+                                         ({}, 300, 131072, 50000)])
+def test_the_generic_loop_is_planned_with_its_own_tiles(monkeypatch, knobs, N, d, V):
+    """bf16 out of the tuned loop's reach (a vocabulary chunk beyond 4 GiB, a long row, the knob): 256-row tiles, and no more
+    windows than there are of those."""
+    set_plan(monkeypatch, **knobs)
+    assert "loop=generic" in B.flce_plan_describe(N, d, V, B.FLCE_DTYPE_BF16)
+    win, tile = _windows(N, d, V)
+    assert tile == 256 and win <= -(-V // 256)
