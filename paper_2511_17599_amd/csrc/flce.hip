@@ -125,13 +125,28 @@ bool fast_loop_ok(const Plan& p, const Tuning& tn) {
          window_ok(vc, ld_hw) && window_ok(nc, ld_hw) && window_ok(nc, ld_g);   // K over memory rows
 }
 
-// allow_h_copy: the caller has a workspace for the pre-tiled copy of H.  wide: ... and for the partials of more windows than
-// cover the CUs.
-bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool allow_h_copy = true, bool wide = true) {
+// The least number of slices above n whose longest slice is shorter than with n.
+int64_t next_slices(int64_t k_tiles, int64_t n) {
+  const int64_t len = ceil_div(k_tiles, n);
+  return len > 1 ? ceil_div(k_tiles, len - 1) : MAX_SPLIT + 1;
+}
+// Tiles of 128 in sequence on a CU; one alone is slower than half of two.
+double small_waves(int64_t tiles) { return tiles <= NUM_CU ? 1.3 : 2.0 * (double)ceil_div(tiles, 2 * NUM_CU); }
+// A pass over all logits with tiles of a given edge, in us (bf16; the rule that uses it is in plan_base).
+double logits_us(const Plan& p, int tile, double ends256, double ends128) {
+  const double steps = (double)ceil_div(p.d, 32);
+  const int64_t tiles = ceil_div(p.N, tile) * ceil_div(p.V, tile);
+  if (tile == TILE) return (double)ceil_div(tiles, NUM_CU) * (0.775 * steps + ends256);
+  return small_waves(tiles) * (0.28 * steps + 0.12 * std::max(0.0, steps - 64.0) + ends128);
+}
+
+// The plan in three parts: what both directions need, the forward's and the backward's.  A call plans its own direction only:
+// flce_workspace_bytes, mean of 150 random shapes on one core of the host, 2.4 us in either direction with everything planned
+// and every number of K slices tried, 0.7 forward and 1.1 backward as it is (0.7 without any search of slices or windows).
+bool plan_base(int64_t N, int64_t d, int64_t V, flce_dtype dt, const Tuning& tn, bool allow_h_copy, Plan& p) {
   if (N <= 0 || d <= 0 || V <= 0 || (d % 8) != 0) return false;
   if (N > 0x7FFFFF00ll || V > 0x7FFFFF00ll || d > (1 << 24)) return false;
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return false;
-  const Tuning tn = tuning();
   p.N = N; p.d = d; p.V = V;
   p.esize = dt == FLCE_DTYPE_BF16 ? 2 : 4;
   p.n_rb = (int)ceil_div(N, TILE);
@@ -172,7 +187,6 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   // tiles: 190 / 185; 2048 x 256 x 16000, 2000 tiles: 715 / 586).
   if (dt == FLCE_DTYPE_F32) p.tile = ceil_div(N, 128) * ceil_div(V, 128) < 320 ? 64 : 128;
   p.fwd_tile = p.tile;
-  const bool f32 = dt == FLCE_DTYPE_F32;
   // bf16: 256-row tiles are the faster loop (1.4 PFLOP/s against 0.8 with 128-row ones, which move twice the bytes per
   // flop), but one of them keeps a CU busy for K / 32 x 0.78 us + the work at its end, and where there are too few of them,
   // or K is short, the 128-row ones with two workgroups per CU are done earlier.  Times in us, fitted over 29 shapes from
@@ -180,15 +194,15 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   // several rounds fall back a little further (331 x 3136 x 102294).  Forward + backward with 256- and by this rule:
   // 614 x 2496 x 512 135 -> 65 us, 742 x 384 x 4845 79 / 52, 357 x 1408 x 10140 139 / 98, 4730 x 320 x 4151 137 / 106,
   // 5435 x 104 x 18745 263 / 203, 18786 x 128 x 76178 3074 / 2755; 59 random shapes 1.13x and 1.11x, at worst 0.99x.
+  if (p.fast && logits_us(p, 128, 6.5, 0.9) < 0.95 * logits_us(p, TILE, 6.5, 0.9)) p.fwd_tile = 128;
+  return true;
+}
+
+// wide: the caller has a workspace for the partials of more windows than cover the CUs.
+void plan_forward(const Tuning& tn, bool wide, Plan& p) {
+  const int64_t N = p.N, d = p.d, V = p.V;
+  const bool f32 = p.esize == 4;
   const double steps = (double)ceil_div(d, 32);
-  auto small_waves = [](int64_t tiles) {        // tiles of 128 in sequence on a CU; one alone is slower than half of two
-    return tiles <= NUM_CU ? 1.3 : 2.0 * (double)ceil_div(tiles, 2 * NUM_CU);
-  };
-  const int64_t t256 = ceil_div(N, 256) * ceil_div(V, 256), t128 = ceil_div(N, 128) * ceil_div(V, 128);
-  auto logits_us = [&](int tile, double ends256, double ends128) {
-    return tile == TILE ? (double)ceil_div(t256, NUM_CU) * (0.775 * steps + ends256) : small_waves(t128) * (0.28 * steps + 0.12 * std::max(0.0, steps - 64.0) + ends128);
-  };
-  if (p.fast && logits_us(128, 6.5, 0.9) < 0.95 * logits_us(TILE, 6.5, 0.9)) p.fwd_tile = 128;
 
   // Windows (Section 3.2.1): enough (row block, window) workgroups to cover the CUs.
   // At least 4, so that the 32 workgroups resident on one XCD are 8 row blocks x 4 windows and
@@ -218,10 +232,15 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
       return (items <= NUM_CU ? alone : 2.0 * (double)ceil_div(items, 2 * NUM_CU)) * ((double)longest + start) + merge;
     };
     const int64_t most = wide && !f32 ? std::min<int64_t>(vt, std::max<int64_t>(cover, 8 * NUM_CU / rb)) : cover;
+    double least = cost(p.n_win);
+    int64_t last = p.n_win;
     for (int r = 1; r <= 8; ++r) {          // per number of rounds the most windows that fit, and of those as few as
       const int64_t fit = std::max<int64_t>(1, std::min<int64_t>(most, r * NUM_CU / rb));      // make the longest no longer
       const int64_t win = std::min(most, std::max<int64_t>(std::min<int64_t>(4, cover), ceil_div(vt, ceil_div(vt, fit))));
-      if (cost(win) < 0.99 * cost(p.n_win)) p.n_win = (int)win;
+      if (win == last) continue;
+      last = win;
+      const double c = cost(win);
+      if (c < 0.99 * least) { p.n_win = (int)win; least = c; }
     }
     part_windows = std::max(cover, p.n_win);
   }
@@ -248,7 +267,13 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.fwd_copy = p.hkr && !(p.ragged && copy_bytes > BYTES_CAP) &&
                (double)N * (double)d * (double)V >= 4.6e10 + 9300.0 * (double)N * (double)d;
   p.fwd_bytes = fwd_fixed + (p.fwd_copy ? copy_bytes : 0);
-  o = ALIGN;
+}
+
+void plan_backward(const Tuning& tn, Plan& p) {
+  const int64_t N = p.N, d = p.d;
+  const bool f32 = p.esize == 4;
+  const int64_t vc_pad = (int64_t)p.vc_tiles * TILE, nc_pad = (int64_t)p.nc_tiles * TILE;
+  int64_t o = ALIGN;
   // the counted rows of H: as they are (fp32, generic loop), or pre-tiled for the dW contraction (tuned loop)
   p.off_Hc = o;     o = align_up(o + (p.fast ? packed_cols_offset((int)ceil_div(d, TILE), (int)p.npad) : d * p.npad * p.esize), ALIGN);
   p.off_rowmap = o; o = align_up(o + p.npad * 4, ALIGN);
@@ -257,7 +282,7 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
   p.off_gamc = o;   o = align_up(o + p.npad * 4, ALIGN);
   p.off_G = o;      o = align_up(o + nc_pad * p.ld_v * p.esize, ALIGN);
   // K-contiguous copies, only for the main loop that cannot read an operand across memory rows
-  const bool copies = dt == FLCE_DTYPE_BF16 && !p.fast;
+  const bool copies = !f32 && !p.fast;
   p.off_HT = o;     if (copies) o = align_up(o + d * p.npad * p.esize, ALIGN);
                     else if (p.hkr) o = align_up(o + packed_block_offset(p.n_rb, (int)d), ALIGN);
   p.off_WT = o;     if (copies) o = align_up(o + d * p.ld_v * p.esize, ALIGN);
@@ -285,9 +310,16 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
     };
     auto auto_split = [&](int64_t tiles, int64_t k_tiles, int64_t out_rows) -> int {     // a split has to win by 5 %
       int best = 1;
-      const int64_t most = std::min<int64_t>(MAX_SPLIT, BYTES_CAP / (out_rows * d * 4));
-      for (int sp = 2; sp <= most && sp <= k_tiles; ++sp)
-        if (split_cost(tiles, k_tiles, sp) < split_cost(tiles, k_tiles, best) * (best == 1 ? 0.95 : 1.0)) best = sp;
+      const int64_t most = std::min(std::min<int64_t>(MAX_SPLIT, BYTES_CAP / (out_rows * d * 4)), k_tiles);
+      double least = 0.95 * split_cost(tiles, k_tiles, 1);
+      // Of the numbers of slices with the same longest slice the first costs least, and no cut does better than all CUs
+      // sharing the K tiles, the ends of every slice and its sums evenly.
+      const double even = launch + (double)(tiles * k_tiles) * k_us / NUM_CU;
+      for (int64_t sp = 2; sp <= most; sp = next_slices(k_tiles, sp)) {
+        if (even + (double)(tiles * sp) * (k_us * ends / NUM_CU + tile_us) >= least) break;
+        const double cost = split_cost(tiles, k_tiles, (int)sp);
+        if (cost < least) { least = cost; best = (int)sp; }
+      }
       return best;
     };
     const int64_t tiles_dh = p.nc_tiles * unit * n_mt, k_dh = p.vc_tiles * unit;
@@ -304,26 +336,31 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
     if (p.n_vch == 1 && p.n_nch == 1 && (p.fast || f32) && tn.splitk_dh == 0 && tn.splitk_dw == 0 &&
         tiles_dh + tiles_dw <= (tile != TILE ? 2 : 1) * NUM_CU) {
       double best = 0.97 * c.us;
-      auto consider = [&](int64_t len) {
+      auto consider = [&](int64_t len) {              // false: too many slices, and more of them with any shorter `len`
         const int64_t sh = ceil_div(k_dh, len), sw = ceil_div(k_dw, len);
         const int64_t wgs = tiles_dh * sh + tiles_dw * sw;
-        if (sh > MAX_SPLIT || sw > MAX_SPLIT || wgs > 2 * NUM_CU) return;
+        if (sh > MAX_SPLIT || sw > MAX_SPLIT || wgs > 2 * NUM_CU) return false;
         const double cost = rounds(wgs) * ((double)len + ends) * k_us + (sh > 1 || sw > 1 ? launch : 0.0) +
                             tile_us * (double)((sh > 1 ? tiles_dh * sh : 0) + (sw > 1 ? tiles_dw * sw : 0));
         if (cost < best) { best = c.us = cost; c.pair = true; c.split_dh = (int)sh; c.split_dw = (int)sw; }
+        return true;
       };
-      for (int sp = 1; sp <= MAX_SPLIT; ++sp) {       // the slice lengths at which one of the two numbers of slices changes
-        consider(ceil_div(k_dh, sp));
-        consider(ceil_div(k_dw, sp));
+      int64_t next_dh = 1, next_dw = 1;               // the slice lengths at which one of the two numbers of slices changes
+      for (int64_t sp = 1; sp <= MAX_SPLIT; sp = std::min(next_dh, next_dw)) {
+        if (sp == next_dh) next_dh = consider(ceil_div(k_dh, sp)) ? next_slices(k_dh, sp) : MAX_SPLIT + 1;
+        if (sp == next_dw) next_dw = consider(ceil_div(k_dw, sp)) ? next_slices(k_dw, sp) : MAX_SPLIT + 1;
       }
     }
     return c;
   };
   Contractions con = contractions(p.tile);
   if (p.fast) {
-    const Contractions small = contractions(128);
     const double chunks = (double)p.n_vch * p.n_nch;
-    if (logits_us(128, 8.0, 1.6) + chunks * small.us < 0.97 * (logits_us(TILE, 8.0, 1.6) + chunks * con.us)) { p.tile = 128; con = small; }
+    const double recompute = logits_us(p, 128, 8.0, 1.6), big = 0.97 * (logits_us(p, TILE, 8.0, 1.6) + chunks * con.us);
+    if (recompute < big) {
+      const Contractions small = contractions(128);
+      if (recompute + chunks * small.us < big) { p.tile = 128; con = small; }
+    }
   }
   p.split_dh = con.split_dh; p.split_dw = con.split_dw; p.pair = con.pair;
   const int64_t n_mt = ceil_div(d, p.tile);
@@ -347,6 +384,15 @@ bool make_plan(int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool all
     o = align_up(o + bytes, ALIGN);
   }
   p.bwd_bytes = o;
+}
+
+enum : int { PLAN_FORWARD = 1, PLAN_BACKWARD = 2, PLAN_BOTH = 3 };   // 0: the shape's check only
+// allow_h_copy: the caller has a workspace for the pre-tiled copy of H.
+bool make_plan(int parts, int64_t N, int64_t d, int64_t V, flce_dtype dt, Plan& p, bool allow_h_copy = true, bool wide = true) {
+  const Tuning tn = tuning();
+  if (!plan_base(N, d, V, dt, tn, allow_h_copy, p)) return false;
+  if (parts & PLAN_FORWARD) plan_forward(tn, wide, p);
+  if (parts & PLAN_BACKWARD) plan_backward(tn, p);
   return true;
 }
 
@@ -827,7 +873,7 @@ const char* flce_status_string(flce_status s) {
 
 int flce_plan_describe(int64_t N, int64_t d, int64_t V, flce_dtype dt, char* buf, size_t buf_bytes) {
   flce::Plan p;
-  if (!buf || buf_bytes == 0 || !flce::make_plan(N, d, V, dt, p)) return -1;
+  if (!buf || buf_bytes == 0 || !flce::make_plan(flce::PLAN_BOTH, N, d, V, dt, p)) return -1;
   // K-split tails of the contraction launches of a full chunk (output-row tiles x slices; 0x1 = none)
   const int64_t n_mt = (d + flce::TILE - 1) / flce::TILE;
   flce::TailSplit th{0, 1}, tw{0, 1};
@@ -846,7 +892,7 @@ int flce_plan_describe(int64_t N, int64_t d, int64_t V, flce_dtype dt, char* buf
 
 size_t flce_workspace_bytes(int64_t N, int64_t d, int64_t V, flce_dtype dt, int for_backward) {
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p)) return 0;
+  if (!flce::make_plan(for_backward ? flce::PLAN_BACKWARD : flce::PLAN_FORWARD, N, d, V, dt, p)) return 0;
   return (size_t)(for_backward ? p.bwd_bytes : p.fwd_bytes);
 }
 
@@ -864,7 +910,7 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
   if (reduction != FLCE_REDUCE_MEAN && reduction != FLCE_REDUCE_SUM) return FLCE_ERR_BAD_ARG;
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return FLCE_ERR_BAD_ARG;
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p, allow_h_copy, wide)) return FLCE_ERR_BAD_SHAPE;
+  if (!flce::make_plan(flce::PLAN_FORWARD, N, d, V, dt, p, allow_h_copy, wide)) return FLCE_ERR_BAD_SHAPE;
   if (slice.v_begin < 0 || slice.v_begin + V > slice.V_total) return FLCE_ERR_BAD_SHAPE;
   if (!flce::aligned16(H) || !flce::aligned16(W)) return FLCE_ERR_BAD_ARG;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < (size_t)p.fwd_bytes)
@@ -899,7 +945,7 @@ static flce_status backward_impl(const void* H, const void* W, const int64_t* ta
   if (reduction != FLCE_REDUCE_MEAN && reduction != FLCE_REDUCE_SUM) return FLCE_ERR_BAD_ARG;
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return FLCE_ERR_BAD_ARG;
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p)) return FLCE_ERR_BAD_SHAPE;
+  if (!flce::make_plan(flce::PLAN_BACKWARD, N, d, V, dt, p)) return FLCE_ERR_BAD_SHAPE;
   if (slice.v_begin < 0 || slice.v_begin + V > slice.V_total) return FLCE_ERR_BAD_SHAPE;
   if (!flce::aligned16(H) || !flce::aligned16(W) || !flce::aligned16(dH_out) || !flce::aligned16(dW_out))
     return FLCE_ERR_BAD_ARG;
@@ -959,10 +1005,10 @@ flce_status flce_forward_static(const void* H, const void* W, const int64_t* tar
   if (dt != FLCE_DTYPE_BF16 && dt != FLCE_DTYPE_F32) return FLCE_ERR_BAD_ARG;
   // More windows than cover the CUs are used where their partials fit too; what fits is decided without them.
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p, /*allow_h_copy=*/false, /*wide=*/false)) return FLCE_ERR_BAD_SHAPE;
+  if (!flce::make_plan(flce::PLAN_FORWARD, N, d, V, dt, p, /*allow_h_copy=*/false, /*wide=*/false)) return FLCE_ERR_BAD_SHAPE;
   if ((size_t)p.fwd_bytes > flce::STATIC_SCRATCH_BYTES) return FLCE_ERR_WORKSPACE;
   flce::Plan w;
-  const bool wide = flce::make_plan(N, d, V, dt, w, /*allow_h_copy=*/false, /*wide=*/true) &&
+  const bool wide = flce::make_plan(flce::PLAN_FORWARD, N, d, V, dt, w, /*allow_h_copy=*/false, /*wide=*/true) &&
                     (size_t)w.fwd_bytes <= flce::STATIC_SCRATCH_BYTES;
   void* ws = nullptr;
   if (flce::static_scratch(&ws) != hipSuccess) return FLCE_ERR_HIP;
@@ -1050,7 +1096,7 @@ flce_status flce_forward_with_grads(const void* H, const void* W, const int64_t*
   // Alg. 3 = Alg. 1 followed by the gradient sweep with the upstream gradient left out: the forward,
   // then the backward with Gamma = 1 (sum semantics, grad_loss 1), on the same stream and workspace.
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p)) return FLCE_ERR_BAD_SHAPE;
+  if (!flce::make_plan(flce::PLAN_BOTH, N, d, V, dt, p)) return FLCE_ERR_BAD_SHAPE;
   if (workspace_bytes < (size_t)std::max(p.fwd_bytes, p.bwd_bytes)) return FLCE_ERR_WORKSPACE;
   if (!dH_partial || !dW_partial) return FLCE_ERR_BAD_ARG;
   const flce_status st = flce_forward(H, W, targets, N, d, V, ignore_index, reduction, dt, loss_out, lse_out,
@@ -1066,7 +1112,7 @@ flce_status flce_scale(const void* dH_partial, const void* dW_partial, int64_t N
   if (!dH_partial || !dW_partial || !dH_out || !dW_out || !workspace) return FLCE_ERR_BAD_ARG;
   if (reduction != FLCE_REDUCE_MEAN && reduction != FLCE_REDUCE_SUM) return FLCE_ERR_BAD_ARG;
   flce::Plan p;
-  if (!flce::make_plan(N, d, V, dt, p)) return FLCE_ERR_BAD_SHAPE;
+  if (!flce::make_plan(0, N, d, V, dt, p)) return FLCE_ERR_BAD_SHAPE;
   if (!flce::aligned16(dH_partial) || !flce::aligned16(dW_partial) || !flce::aligned16(dH_out) ||
       !flce::aligned16(dW_out))
     return FLCE_ERR_BAD_ARG;
