@@ -61,8 +61,8 @@
  *   FLCE_NC_TILES   largest token chunk of the backward, in 256-row tiles (default 128).
  *                   The staging buffer for G holds one chunk pair: at most VC x NC tiles.
  *   FLCE_SPLITK_DH, FLCE_SPLITK_DW
- *                   K slices of the dH / dW contraction launches; 0 / unset = automatic
- *                   (split only when a launch has too few output tiles for the CUs).
+ *                   K slices of the dH / dW contraction launches, up to 64 (and one per K tile); 0 / unset =
+ *                   automatic (split only when a launch has too few output tiles for the CUs).
  *   FLCE_GENERIC    1 = bf16: use the generic main loop also where the tuned one applies.
  */
 #ifndef FLCE_H_

@@ -59,8 +59,8 @@ Tuning read_tuning_from_env() {
   t.windows = env_int("FLCE_WINDOWS", 0, 0, 1 << 16);
   t.vc_tiles = env_int("FLCE_VC_TILES", 0, 0, 4096);
   t.nc_tiles = env_int("FLCE_NC_TILES", 128, 1, 4096);
-  t.splitk_dh = env_int("FLCE_SPLITK_DH", 0, 0, 16);
-  t.splitk_dw = env_int("FLCE_SPLITK_DW", 0, 0, 16);
+  t.splitk_dh = env_int("FLCE_SPLITK_DH", 0, 0, MAX_SPLIT);
+  t.splitk_dw = env_int("FLCE_SPLITK_DW", 0, 0, MAX_SPLIT);
   t.generic = env_int("FLCE_GENERIC", 0, 0, 1);
   return t;
 }

@@ -2,6 +2,7 @@
 import pytest
 
 from paper_2511_17599_amd import binding as B
+from conftest import set_plan
 
 CAP = 512 << 20
 BF16 = B.FLCE_DTYPE_BF16
@@ -27,3 +28,10 @@ def test_k_slices_take_a_bounded_share_of_the_workspace(N, d, V, dt):
     for slices, chunk in (("splitk_dH", "row_chunks"), ("splitk_dW", "vocab_chunks")):
         n = int(f[slices])
         assert n <= 64 and (n == 1 or n * rows[chunk] * d * 4 <= CAP)
+
+
+@pytest.mark.parametrize("slices", [1, 17, 64])
+def test_every_number_of_slices_the_plan_takes_can_be_asked_for(monkeypatch, slices):
+    set_plan(monkeypatch, FLCE_SPLITK_DH=slices, FLCE_SPLITK_DW=slices)
+    line = B.flce_plan_describe(20000, 64, 20000, BF16)
+    assert f"splitk_dH={slices} splitk_dW={slices} " in line
