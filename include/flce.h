@@ -63,6 +63,8 @@
  *   FLCE_SPLITK_DH, FLCE_SPLITK_DW
  *                   K slices of the dH / dW contraction launches, up to 64 (and one per K tile); 0 / unset =
  *                   automatic (split only when a launch has too few output tiles for the CUs).
+ *   FLCE_TILE       bf16, tuned loop: output tile edge of both directions, 128 or 256; 0 / unset / else = automatic
+ *                   (256 unless there are few such tiles or the hidden size is short).
  *   FLCE_GENERIC    1 = bf16: use the generic main loop also where the tuned one applies.
  */
 #ifndef FLCE_H_
@@ -126,11 +128,12 @@ const char* flce_status_string(flce_status s);
 size_t flce_workspace_bytes(int64_t N, int64_t d, int64_t V, flce_dtype dt, int for_backward);
 
 /*
- * Writes a one-line description of the launch plan at this shape (library version, main loop, windows,
- * chunk counts x largest chunk in 256-row tiles, K slices, K-split tails of a full chunk's dH / dW launch as
- * output-row tiles x slices, whether both contractions go out as one launch, tile edges of the
- * forward and the backward, staging and workspace bytes) into `buf`; returns
- * the length it needs (as snprintf) or -1 for an invalid shape.  Reports and profile summaries carry it, so
+ * Writes a one-line description of the launch plan at this shape (library version; main loop: `tuned` for the bf16
+ * loop with its pre-tiled copies, `generic` for all that does without, the generic bf16 loop and the fp32 one; whether
+ * the forward / the backward reads a pre-tiled copy of H; windows; chunk counts x largest chunk in 256-row tiles; K
+ * slices; K-split tails of a full chunk's dH / dW launch as output-row tiles x slices; whether both contractions go out as
+ * one launch; tile edges of the forward / the backward; staging and workspace bytes) into `buf`; returns the length it
+ * needs (as snprintf) or -1 for an invalid shape.  Reports and profile summaries carry it, so
  * that a measurement can be matched to the plan it was taken on.  Host call.
  */
 int flce_plan_describe(int64_t N, int64_t d, int64_t V, flce_dtype dt, char* buf, size_t buf_bytes);

@@ -48,7 +48,7 @@ int env_int(const char* name, int dflt, int lo, int hi) {
 // fixed for the process from then on (flce_tuning_reload reads them again): a plan never changes between the
 // sizing of a workspace and its use, and no call touches the environment afterwards.
 struct Tuning {
-  int windows, vc_tiles, nc_tiles, splitk_dh, splitk_dw, generic;
+  int windows, vc_tiles, nc_tiles, splitk_dh, splitk_dw, generic, tile;
 };
 std::mutex g_tuning_mu;
 bool g_tuning_loaded = false;
@@ -62,6 +62,8 @@ Tuning read_tuning_from_env() {
   t.splitk_dh = env_int("FLCE_SPLITK_DH", 0, 0, MAX_SPLIT);
   t.splitk_dw = env_int("FLCE_SPLITK_DW", 0, 0, MAX_SPLIT);
   t.generic = env_int("FLCE_GENERIC", 0, 0, 1);
+  t.tile = env_int("FLCE_TILE", 0, 0, TILE);
+  if (t.tile != TILE && t.tile != 128) t.tile = 0;
   return t;
 }
 
@@ -194,7 +196,7 @@ bool plan_base(int64_t N, int64_t d, int64_t V, flce_dtype dt, const Tuning& tn,
   // several rounds fall back a little further (331 x 3136 x 102294).  Forward + backward with 256- and by this rule:
   // 614 x 2496 x 512 135 -> 65 us, 742 x 384 x 4845 79 / 52, 357 x 1408 x 10140 139 / 98, 4730 x 320 x 4151 137 / 106,
   // 5435 x 104 x 18745 263 / 203, 18786 x 128 x 76178 3074 / 2755; 59 random shapes 1.13x and 1.11x, at worst 0.99x.
-  if (p.fast && logits_us(p, 128, 6.5, 0.9) < 0.95 * logits_us(p, TILE, 6.5, 0.9)) p.fwd_tile = 128;
+  if (p.fast && (tn.tile ? tn.tile == 128 : logits_us(p, 128, 6.5, 0.9) < 0.95 * logits_us(p, TILE, 6.5, 0.9))) p.fwd_tile = 128;
   return true;
 }
 
@@ -354,7 +356,10 @@ void plan_backward(const Tuning& tn, Plan& p) {
     return c;
   };
   Contractions con = contractions(p.tile);
-  if (p.fast) {
+  if (p.fast && tn.tile == 128) {
+    p.tile = 128;
+    con = contractions(128);
+  } else if (p.fast && tn.tile == 0) {
     const double chunks = (double)p.n_vch * p.n_nch;
     const double recompute = logits_us(p, 128, 8.0, 1.6), big = 0.97 * (logits_us(p, TILE, 8.0, 1.6) + chunks * con.us);
     if (recompute < big) {
@@ -882,9 +887,9 @@ int flce_plan_describe(int64_t N, int64_t d, int64_t V, flce_dtype dt, char* buf
     tw = flce::tail_split(p.vc_tiles, n_mt, p.split_dw, p.nc_tiles);
   }
   return std::snprintf(buf, buf_bytes,
-                       "flce %s loop=%s h_copy=%d windows=%d vocab_chunks=%dx%d row_chunks=%dx%d splitk_dH=%d splitk_dW=%d "
+                       "flce %s loop=%s h_copy=%d/%d windows=%d vocab_chunks=%dx%d row_chunks=%dx%d splitk_dH=%d splitk_dW=%d "
                        "tail_dH=%dx%d tail_dW=%dx%d pair=%d tiles=%d/%d staging_bytes=%lld fwd_ws=%lld bwd_ws=%lld",
-                       flce_version(), p.fast ? "tuned" : "generic", p.hkr ? 1 : 0, p.n_win, p.n_vch, p.vc_tiles, p.n_nch,
+                       flce_version(), p.fast ? "tuned" : "generic", p.fwd_copy ? 1 : 0, p.hkr ? 1 : 0, p.n_win, p.n_vch, p.vc_tiles, p.n_nch,
                        p.nc_tiles, p.split_dh, p.split_dw, th.rows, th.slices, tw.rows, tw.slices, p.pair ? 1 : 0, p.fwd_tile, p.tile,
                        (long long)((int64_t)p.nc_tiles * flce::TILE * p.ld_v * p.esize), (long long)p.fwd_bytes,
                        (long long)p.bwd_bytes);

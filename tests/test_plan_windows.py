@@ -62,3 +62,14 @@ def test_the_generic_loop_is_planned_with_its_own_tiles(monkeypatch, knobs, N, d
     assert "loop=generic" in B.flce_plan_describe(N, d, V, B.FLCE_DTYPE_BF16)
     win, tile = _windows(N, d, V)
     assert tile == 256 and win <= -(-V // 256)
+
+
+@pytest.mark.parametrize("tile", [128, 256])
+def test_the_tile_edge_can_be_asked_for(monkeypatch, tile):
+    """Both directions of a tuned bf16 call, whatever the rule would take; the generic and the fp32 loop have their own."""
+    set_plan(monkeypatch, FLCE_TILE=tile)
+    for N, d, V in ((300, 200, 2100), (8192, 4096, 128256), (2048, 1024, 32000)):
+        assert f" tiles={tile}/{tile} " in B.flce_plan_describe(N, d, V, B.FLCE_DTYPE_BF16)
+        assert f" tiles={tile}/" not in B.flce_plan_describe(N, d, V, B.FLCE_DTYPE_F32) or tile == 128
+    set_plan(monkeypatch, FLCE_GENERIC=1)
+    assert " tiles=256/256 " in B.flce_plan_describe(300, 200, 2100, B.FLCE_DTYPE_BF16)
