@@ -25,6 +25,15 @@ def set_plan(monkeypatch, **knobs):
     B.flce_tuning_reload()
 
 
+def tile_edges(N, d, V, dtype="bf16"):
+    """Tile edges of the forward and the backward in the plan that holds now, as the plan line gives them."""
+    from paper_2511_17599_amd import binding as B
+    dt = {"bf16": B.FLCE_DTYPE_BF16, "f32": B.FLCE_DTYPE_F32}[dtype]
+    line = B.flce_plan_describe(N, d, V, dt)
+    print(line, flush=True)
+    return tuple(int(e) for e in line.split(" tiles=")[1].split()[0].split("/"))
+
+
 @pytest.fixture(autouse=True)
 def _default_plan(monkeypatch):
     """Every test starts from the default launch plan, whatever the previous test or the caller's shell set."""
