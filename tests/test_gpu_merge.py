@@ -1,5 +1,6 @@
-"""The window merge at the edges of its dispatch: up to 8 parts per row one thread merges them, beyond that four do, with
-the loss of the call summed by the merge itself (forward) or by a second launch (merge of slices handed over)."""
+"""The window merge at the edges of its dispatch: up to 8 parts per row one thread merges them; beyond that 16 threads do up
+to 4096 rows (64 blocks of 64 rows) and 4 from there on; with the loss of the call summed by the merge itself (forward) or by
+a second launch (merge of slices handed over)."""
 import numpy as np
 import pytest
 
@@ -22,7 +23,8 @@ def _need_gpu():
 
 @pytest.mark.parametrize("N,windows", [(1, 8), (257, 9), (300, 64), (77, 70), (2305, 65), (4096, 20), (4097, 20)])
 def test_forward_with_many_windows(monkeypatch, N, windows):
-    """One and several 256-row blocks; the last group of windows full, partly filled and (65 = 4 x 17 - 3) ragged."""
+    """One and several blocks of rows; the windows of a thread full (64 = 16 x 4), partly filled (65 = 13 x 5, three threads
+    without any) and one fewer than there are threads for (9)."""
     set_plan(monkeypatch, FLCE_WINDOWS=windows)
     wl = I.Workload(f"merge_{N}_{windows}", N, 32, 70 * 256 - 3, "bf16", "uniform", ignore_frac=0.2, seed=300 + N)
     x = I.make_inputs(wl)

@@ -45,3 +45,10 @@ def test_no_kernel_spills_or_uses_scratch(tmp_path):
     # one wavefront per SIMD in the tuned kernels: the whole accumulation register file holds the 256 x 256 tile
     for n in tuned:
         assert usage[n]["agprs"] == 256 and usage[n]["occupancy"] == 1, (n, usage[n])
+    # the loops of which two workgroups (one wavefront per SIMD each) share a CU have the registers for it
+    shared = [n for n in usage if "SmallLoop" in n or "F32Loop" in n]
+    for piece in ("SmallLoop", "F32LoopILi64E", "F32LoopILi128E"):
+        for kernel in ("fwd_tiles_kernel", "recompute_kernel", "contract_kernel", "contract_pair_kernel"):
+            assert any(piece in n and kernel in n for n in shared), (piece, kernel)
+    for n in shared:
+        assert usage[n]["occupancy"] >= 2, (n, usage[n])
