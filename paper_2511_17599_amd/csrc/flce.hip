@@ -529,7 +529,7 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
   int* blk_cnt = reinterpret_cast<int*>(ws + p.off_blk_cnt);
   int* blk_oor = reinterpret_cast<int*>(ws + p.off_blk_oor);
   // One workgroup per item (row block x window).  With the tuned loop a launch takes at most one round of workgroups
-  // (256 items, whole raster groups of 8 row blocks when the window count divides 32): a larger grid's later rounds
+  // (256 items, 512 of 128-row tiles; whole raster groups of 8 row blocks when the window count divides 32): a larger grid's later rounds
   // drift apart over the ~100 tiles of an item and stop sharing their operands in the L2 (measured at 512 row blocks:
   // 361 GB of fabric traffic per forward against 192 GB that the raster should need).
   const int n_rb = (int)ceil_div(p.N, L::TILE), n_vt = (int)ceil_div(p.V, L::TILE);

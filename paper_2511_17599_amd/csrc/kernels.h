@@ -403,7 +403,7 @@ __device__ __forceinline__ V wave_sum(V v) {
 // parts, U of them at a time with all their loads in flight together (a part past the end re-reads the last one and is
 // not used), and the groups' results are merged through LDS in group order: every sum has a fixed order.
 // What bounds it is memory latency: the parts of one row lie in different memory rows, and where there are many parts
-// there are few rows (windows = max(4, 256 / row blocks)): a thread per row took 45 us for 77 rows of 197 windows and
+// there are few rows (row blocks x windows are a few rounds of workgroups): a thread per row took 45 us for 77 rows of 197 windows and
 // 40 us for 500 rows of 128 windows, 16 threads per row with 16 loads each take 7.9 and 9.8 us (the loss included).
 // Returns with the row's (M, A, z) valid in the threads of group 0.
 template <int ROWS, int GROUPS, int U>
@@ -979,8 +979,9 @@ struct RowMeta {
   float gam[L::WN];     // per-row variant only
 };
 
-// The recompute step.  The launch has min(tiles, 256) workgroups; workgroup b takes tiles b, b + gridDim.x, ... of
-// the chunk.  With the tuned loop the first K stages of a workgroup's next tile (and that tile's per-row inputs) are
+// The recompute step.  With the tuned loop the launch has at most one round of workgroups (NUM_CU * L::PER_CU: 256 with
+// 256-row tiles, 512 with 128-row ones) and workgroup b takes tiles b, b + gridDim.x, ... of the chunk; with the other loops
+// it has one per tile.  With the tuned loop the first K stages of a workgroup's next tile (and that tile's per-row inputs) are
 // requested before the current tile's G is formed and stored, so the latency of a tile's first operands hides behind
 // the previous tile's post-processing: it matters when the K loop is short (small d).
 // PER_ROW: g = Gamma_row * (p - (1 - eps) [v == y_row] - eps / V), the upstream gradient applied here because
@@ -1244,7 +1245,7 @@ struct ContractArgs {
   int n_split, k_split; float* partial; int64_t partial_stride;
 };
 
-// With the tuned loop a launch has at most 256 workgroups; workgroup b takes work items b, b + n_wg, ... (an
+// With the tuned loop a launch has at most one round of workgroups (NUM_CU * L::PER_CU); workgroup b takes work items b, b + n_wg, ... (an
 // item = one output tile of one K slice) and requests the first K stages of its next item before it writes out the
 // current one, as the recompute step does.
 // ONE: there are as many workgroups as items.
@@ -1462,7 +1463,7 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
 }
 
 // dW and dH of one chunk side by side: the first wg_w workgroups take dW's items, the others dH's.  For problems whose
-// output tiles (K slices included) fit the chip together: see pair_splits on the host side.
+// output tiles fit the chip together, at most two rounds of them K slices included: `contractions` in plan_backward.
 template <typename T, typename L, int OPS_W, int OPS_H>
 __global__ __launch_bounds__(L::THREADS) void contract_pair_kernel(ContractArgs<T> w, ContractArgs<T> h, int wg_w) {
   extern __shared__ __align__(16) char lds[];

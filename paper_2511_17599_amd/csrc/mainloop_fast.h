@@ -255,8 +255,9 @@ __device__ __forceinline__ void read_frag(bf16x8 (&f)[4], const FragAddr<LAYOUT,
 // The contraction of one tile, split in two calls so that a kernel that works on several
 // tiles can request the first stages of the next tile before it post-processes the
 // accumulators of the current one:
-//   start(A, B, k_elems, lds): requests K tiles 0..2 into stages 0..2 (all stages must be free:
-//                              every wavefront has passed the final barrier of the previous run);
+//   start(A, B, k_elems, lds): requests K tiles 0 .. NSTAGES - 2 into the stages of the same numbers, which must be
+//                              free: every wavefront has passed the final barrier of the previous run (the last
+//                              stage stays empty until run(): post-processing may use it);
 //   run(lds, acc):             acc = A_tile . B_tile^T over k_elems of K (a multiple of 32).  On
 //                              return all wavefronts have passed a barrier after their last LDS
 //                              read, so the caller may reuse `lds` or call start() again.
@@ -401,7 +402,7 @@ struct Pipe {
       __builtin_amdgcn_s_barrier();
       half_step(LATER, f1, f0, stage_at(after(sc)), 0, 1, kt + NSTAGES - 1, lst);
     };
-    // Drain: the last (up to NS-1) tiles, nothing left to request.
+    // Drain: the last (up to NSTAGES - 1) tiles, nothing left to request.
     auto drain_step = [&](auto first, int kt, int sc) {
       half_step(first, f0, f1, stage_at(sc), 1, 0, -1, nullptr);
       wait_tiles_in_flight(max(0, KT - kt - 2));            // tile kt+1 landed; the later ones may be in flight

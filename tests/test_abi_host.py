@@ -56,7 +56,7 @@ def test_workspace_beyond_the_staging_cap_has_no_NV_term():
 def test_workspace_below_the_staging_cap_is_what_the_header_says():
     """A problem smaller than the staging cap stages its whole G (storage type): that part does grow like N x V,
     everything else like (N + V) d.  Checked at a shape under the cap, at the same shape doubled, and at the tiny
-    fp32 benchmark shape (generic loop: transposed copies on top)."""
+    fp32 benchmark shape (which stages G as fp32)."""
     dt, e = B.FLCE_DTYPE_BF16, 2
 
     def parts(N, d, V):
@@ -74,7 +74,7 @@ def test_workspace_below_the_staging_cap_is_what_the_header_says():
         assert rest <= 2 * N * d * e + 16 * N + 4 * N * d + 4 * V * d + 8 * 4 * max(N, V) * d + (1 << 20)
     # the bf16 staging is half the fp32 logits it replaces; with the other buffers the backward stays below them
     assert B.flce_workspace_bytes(4096, 768, 50257, dt, 1) < 0.62 * 4096 * 50257 * 4
-    # tiny fp32 shape (generic loop): G, its transpose, a transposed W chunk and 8 K-slice tiles of dH
+    # tiny fp32 shape: G, the counted rows of H and the K-slice tiles of dH
     text, f = plan_fields(256, 256, 4096, B.FLCE_DTYPE_F32)
     assert "loop=generic" in text
     tiny = int(f["bwd_ws"])
