@@ -264,7 +264,8 @@ void plan_forward(const Tuning& tn, bool wide, Plan& p) {
   // with it, 25.7 without; 614 x 2496 x 512 step 159 / 152; 2048 x 1024 x 32000, just above the line, level).
   // Hidden sizes that are no multiple of 32 take it up to a bounded size only: without it such a forward runs in O(N + d)
   // words, and an evaluation sized by those has to fit whatever N and d (H read in place costs 6-20 %: 8192 x 4104 x 128256
-  // 7.09 -> 8.49 ms, 32768 x 1048 x 131072 8.44 -> 9.89, 16384 x 520 x 60000 1.07 -> 1.14; these are below the bound).
+  // 7.09 -> 8.49 ms, 32768 x 1048 x 131072 8.44 -> 9.89, 16384 x 520 x 60000 1.07 -> 1.14, below the bound; beyond it
+  // 103047 x 7824 x 22916 takes 36.2 ms in 7 MB, 31.2 with the copy in 1.6 GB, 49.0 on the generic loop; same bits).
   const int64_t copy_bytes = align_up(packed_block_offset(p.n_rb, (int)d), ALIGN);
   p.fwd_copy = p.hkr && !(p.ragged && copy_bytes > BYTES_CAP) &&
                (double)N * (double)d * (double)V >= 4.6e10 + 9300.0 * (double)N * (double)d;
