@@ -52,23 +52,31 @@ __host__ __device__ __forceinline__ int64_t packed_cols_offset(int q, int rows) 
 }
 
 // Main-loop policies.  A kernel is written once against this interface:
-//   THREADS, TILE (output tile edge), WM x WN (32x32 accumulator blocks per wavefront), LDS (dynamic LDS bytes),
-//   tile_m(i, r) / tile_n(j): position of acc[i][j][r] inside the tile,
-//   slot(): which of the 4 lanes that share an N column this lane is,
+//   THREADS, TILE (output tile edge), LDS (dynamic LDS bytes), WM x WN (accumulator blocks per wavefront, 16 values of a
+//   lane in one N column of ROWS rows each), Acc: a finished tile's accumulators, get(i, j, r) element r of block (i, j)
+//   (i, j, r constants after unrolling), tile_m(i, r) / tile_n(j): its position inside the tile; inside its block it is row
+//   (r / 4) QUAD + lane_row() + r % 4,
+//   slot(): which of the SLOTS lanes that share an N column this lane is,
 //   TRANSPOSING: can take an operand whose K index runs over memory rows (otherwise K-contiguous copies are made),
 //   TUNED: the bf16 loop with its persistent launches, pre-tiled copies and blocked G.
+template <int WM, int WN>
+struct VectorAcc {        // of the loops that leave the accumulators to the compiler
+  f32x16 v[WM][WN];
+  __device__ __forceinline__ float get(int i, int j, int r) const { return v[i][j][r]; }
+};
 struct GenericLoop {      // bf16 where the tuned loop does not reach (address windows); 8 wavefronts 2 x 4
   static constexpr int TILE = flce::TILE, THREADS = flce::THREADS, WM = flce::WM, WN = flce::WN, LDS = LDS_BYTES;
   static constexpr bool TRANSPOSING = false, TUNED = false;
+  static constexpr int ROWS = 32, QUAD = 8, SLOTS = 4;
+  using Acc = VectorAcc<WM, WN>;
+  static __device__ __forceinline__ int lane_row() { return (threadIdx.x & 32) >> 3; }
   static __device__ __forceinline__ int tile_m(int i, int r) { return flce::tile_m(i, r); }
   static __device__ __forceinline__ int tile_n(int j) { return flce::tile_n(j); }
   static __device__ __forceinline__ int slot() {
     return ((threadIdx.x >> 6) >> 2) * 2 + ((threadIdx.x & 63) >> 5);
   }
-  // element r of an accumulator block, for the code that post-processes a finished tile
-  static __device__ __forceinline__ float acc_get(const f32x16& blk, int r) { return blk[r]; }
   // A sequence of tiles A[a_row0 ..][:] x B[b_row0 ..][:] over K = k_elems; start() names the next tile, run() computes
-  // it.  This loop has nothing to request ahead: start() only records the operands.
+  // it and calls `released` when the next start() may come.  This loop has nothing to request ahead: start() only records the operands.
   template <bool BT>
   struct Stream {
     TileSrc As, Bs;
@@ -79,14 +87,18 @@ struct GenericLoop {      // bf16 where the tuned loop does not reach (address w
       Bs = TileSrc{reinterpret_cast<const char*>(B), ldb_bytes, b_row0, b_rows};
       k_bytes = k_elems * (int)sizeof(bf16_t);
     }
-    __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[WM][WN]) { tile_mainloop(As, Bs, k_bytes, lds, acc); }
+    template <typename F>
+    __device__ __forceinline__ void run(char* lds, Acc& acc, F released) {
+      tile_mainloop(As, Bs, k_bytes, lds, acc.v);
+      released();
+    }
   };
   static __device__ __forceinline__ void run(const void* A, int64_t lda_bytes, int a_row0, int a_rows, const void* B,
                                              int64_t ldb_bytes, int b_row0, int b_rows, int k_bytes, char* lds,
-                                             f32x16 (&acc)[WM][WN]) {
+                                             Acc& acc) {
     const TileSrc As{static_cast<const char*>(A), lda_bytes, a_row0, a_rows};
     const TileSrc Bs{static_cast<const char*>(B), ldb_bytes, b_row0, b_rows};
-    tile_mainloop(As, Bs, k_bytes, lds, acc);
+    tile_mainloop(As, Bs, k_bytes, lds, acc.v);
   }
 };
 
@@ -94,6 +106,9 @@ template <int T>
 struct F32Loop {          // fp32; T x T tiles, 4 wavefronts 2 x 2, two workgroups per CU
   static constexpr int TILE = T, THREADS = f32::THREADS, WM = T / 64, WN = T / 64, LDS = f32::lds_bytes<T>();
   static constexpr bool TRANSPOSING = true, TUNED = false;
+  static constexpr int ROWS = 32, QUAD = 8, SLOTS = 4;
+  using Acc = VectorAcc<WM, WN>;
+  static __device__ __forceinline__ int lane_row() { return (threadIdx.x & 32) >> 3; }
   static __device__ __forceinline__ int tile_m(int i, int r) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     return (wave >> 1) * (T / 2) + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
@@ -103,7 +118,6 @@ struct F32Loop {          // fp32; T x T tiles, 4 wavefronts 2 x 2, two workgrou
     return (wave & 1) * (T / 2) + j * 32 + (lane & 31);
   }
   static __device__ __forceinline__ int slot() { return fast::slot_of_lane(); }
-  static __device__ __forceinline__ float acc_get(const f32x16& blk, int r) { return blk[r]; }
   template <bool BT>
   struct Stream {         // as GenericLoop::Stream: the other resident workgroup covers a tile's first requests
     f32::Operand As, Bs;
@@ -114,33 +128,38 @@ struct F32Loop {          // fp32; T x T tiles, 4 wavefronts 2 x 2, two workgrou
       Bs = f32::Operand{reinterpret_cast<const char*>(B), ldb_bytes, b_row0, b_rows, 0};
       k_elems = k;
     }
-    __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[WM][WN]) {
-      f32::mainloop<T, f32::KC, f32::KC>(As, Bs, k_elems, lds, acc);
+    template <typename F>
+    __device__ __forceinline__ void run(char* lds, Acc& acc, F released) {
+      f32::mainloop<T, f32::KC, f32::KC>(As, Bs, k_elems, lds, acc.v);
+      released();
     }
   };
 };
 
-// The tuned bf16 loop; 4 wavefronts 2 x 2 of B x B accumulator blocks, global -> LDS DMA.
+// The tuned bf16 loop; 4 wavefronts 2 x 2 of 32 B rows x 32 B columns, global -> LDS DMA.
 // RAGGED: the hidden size is a multiple of 8 but not of 32 (the K extent of the forward and the recompute; the
 // contractions' K extents are whole tiles, they always run with the plain form).
 template <bool RAGGED, int B>
 struct TunedLoop {
-  static constexpr int TILE = 64 * B, THREADS = fast::THREADS, WM = B, WN = B;
+  static constexpr int TILE = 64 * B, THREADS = fast::THREADS, WM = B / 2, WN = 2 * B;
   static constexpr bool TRANSPOSING = true, TUNED = true;
+  static constexpr int ROWS = 64, QUAD = 16, SLOTS = 8;
+  using Acc = fast::Acc<2 * B, 2 * B>;
   // 256-row tiles: one workgroup per CU, 4 stages of 32 KiB; 128-row tiles: two, 5 stages of 16 KiB each
   static constexpr int PER_CU = B == 4 ? 1 : 2, STAGES = B == 4 ? fast::NS : 5, STAGE = B * 8192, LDS = STAGES * STAGE;
   template <int LA, int LB, bool RG = false> using Pipe = fast::Pipe<LA, LB, true, B, STAGES, RG, B>;
   // LDS that post-processing may use while the next tile's first K stages are being filled: the last stage
   static constexpr int FREE_LDS_OFFSET = (STAGES - 1) * STAGE;
+  static __device__ __forceinline__ int lane_row() { return (threadIdx.x & 48) >> 2; }
   static __device__ __forceinline__ int tile_m(int i, int r) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    return (wave >> 1) * (B * 32) + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+    const int wave = threadIdx.x >> 6;
+    return (wave >> 1) * (B * 32) + i * ROWS + (r >> 2) * QUAD + lane_row() + (r & 3);
   }
   static __device__ __forceinline__ int tile_n(int j) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    return (wave & 1) * (B * 32) + j * 32 + (lane & 31);
+    const int wave = threadIdx.x >> 6;
+    return (wave & 1) * (B * 32) + j * 16 + (threadIdx.x & 15);
   }
-  static __device__ __forceinline__ int slot() { return fast::slot_of_lane(); }
+  static __device__ __forceinline__ int slot() { return (threadIdx.x >> 7) * 4 + ((threadIdx.x & 63) >> 4); }
   // A sequence of tiles with the same B operand: start() requests the first K stages of a tile (all LDS stages must
   // be free: every wavefront is past the previous run()), run() computes it.  BP: B is also given pre-tiled (Bp:
   // per 256-row block and K step the 16 KiB image of its LDS tile, see pack_rows_kernel), and that copy is read.
@@ -161,28 +180,23 @@ struct TunedLoop {
         pipe.start(As, Bs, k_elems, lds);
       }
     }
-    __device__ __forceinline__ void run(char* lds, f32x16 (&acc)[WM][WN]) { pipe.run(lds, acc); }
+    template <typename F>
+    __device__ __forceinline__ void run(char* lds, Acc& acc, F released) { pipe.run(lds, released); }
   };
-  // The accumulators of a wavefront live in the accumulation registers.  Post-processing reads them one
-  // block at a time where it uses them; left to itself the compiler copies most of a tile into vector
-  // registers in one sweep at the end of the main loop, which overflows the register file into scratch memory.
-  static __device__ __forceinline__ float acc_get(const f32x16& blk, int r) {   // r: a constant after unrolling
-    float v;
-    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(blk[r]));
-    return v;
-  }
-  // A wavefront's pieces of 32 rows x (32 B) columns of bf16 on their way through its slice of the free stage (rows of
-  // ROW_BYTES in 8-byte slots, the slot number XOR-ed so that the 32 rows one write instruction touches lie in different
-  // banks): where the 4 columns of lane half `half`, block i, quarter rq of row r are written, and where 16-byte chunk c
-  // of row r is read (its two slots side by side, in swapped order where `swapped`).
+  // A wavefront's pieces of 16 rows x (32 B) columns of bf16 on their way through its slice of the free stage, rows of
+  // ROW_BYTES in 16-byte chunks whose number is XOR-ed with mix(row), so that the 16 rows (x 2 neighbouring 8-byte halves)
+  // one write cycle touches lie in different banks, and likewise the four rows x four neighbouring chunks of a read
+  // cycle (blocks of G; output rows are read in the order of the places, and the store takes the chunks as they come).
+  // piece_slot: where a lane writes its 4 columns of quad rq of block i in row r; piece_chunk: where chunk c of row r is read.
   static constexpr int ROW_BYTES = 64 * B, CHUNKS = ROW_BYTES / 16, ROWS_PER_STORE = 64 / CHUNKS;
-  static __device__ __forceinline__ int piece_slot(int r, int i, int rq, int half) {
-    return r * ROW_BYTES + ((((i * 4 + rq) * 2 + half) ^ (B == 4 ? r : r >> 1)) << 3);
+  static __device__ __forceinline__ int mix(int r) {
+    return B == 4 ? ((r & 3) << 2 | r >> 2) : ((r >> 1 & 1) << 2 | r >> 2);
   }
-  static __device__ __forceinline__ int piece_chunk(int r, int c) {
-    return r * ROW_BYTES + ((c ^ (B == 4 ? r >> 1 : r >> 2)) << 4);
+  static __device__ __forceinline__ int piece_slot(int r, int i, int rq) {      // chunk i * 8 + rq * 2 + (lane / 32), half (lane / 16) % 2
+    const int quarter = (threadIdx.x & 63) >> 4;
+    return r * ROW_BYTES + (((i * 8 + rq * 2 + (quarter >> 1)) ^ mix(r)) << 4) + ((quarter & 1) << 3);
   }
-  static __device__ __forceinline__ bool swapped(int r) { return (B == 4 ? r : r >> 1) & 1; }
+  static __device__ __forceinline__ int piece_chunk(int r, int c) { return r * ROW_BYTES + ((c ^ mix(r)) << 4); }
 };
 template <bool RAGGED> struct FastLoop : TunedLoop<RAGGED, 4> { using Even = FastLoop<false>; };
 template <bool RAGGED> struct SmallLoop : TunedLoop<RAGGED, 2> { using Even = SmallLoop<false>; };
@@ -290,48 +304,62 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
   const int n0 = rb * L::TILE;
   const int64_t ld_bytes = (int64_t)d * sizeof(T);
 
+  int64_t yj[L::WN];
   int tgt[L::WN];
   float m[L::WN], a[L::WN], zt[L::WN];
 #pragma unroll
   for (int j = 0; j < L::WN; ++j) {
-    const int n = n0 + L::tile_n(j);
-    bool oor;
-    // W holds the V vocabulary rows [v_begin, v_begin + V) of V_total; a target in another slice matches no column
-    tgt[j] = (n < N) ? classify_target_in_slice(y[n], ignore_index, V_total, v_begin, V, -1, oor) : -1;
+    yj[j] = y[min(n0 + L::tile_n(j), N - 1)];
     m[j] = NEG_INF; a[j] = 0.f; zt[j] = 0.f;
   }
+  // Small tuned tiles look at the targets near the end of the first tile: a wait for them here comes before the first operands
+  // are requested (334 x 320 x 2142, one tile per workgroup, 8.15 -> 7.8 us).  The others walk many tiles and have no
+  // scalar registers for it.
+  constexpr bool LATE = L::TUNED && L::TILE < TILE;
+  auto classify = [&] {
+#pragma unroll
+    for (int j = 0; j < L::WN; ++j) {
+      asm volatile("" : "+v"(yj[j]));
+      bool oor;
+      // W holds the V vocabulary rows [v_begin, v_begin + V) of V_total; a target in another slice matches no column
+      tgt[j] = n0 + L::tile_n(j) < N ? classify_target_in_slice(yj[j], ignore_index, V_total, v_begin, V, -1, oor) : -1;
+    }
+  };
 
-  f32x16 acc[L::WM][L::WN];
+  if constexpr (!LATE) classify();
+  typename L::Acc acc;
   // The tuned loop's first K stages of tile t+1 are requested before the softmax update of tile t (which touches
   // no memory), so the update hides their latency: it matters when the K loop is short (small d).
   typename L::template Stream<HKR> stream;
   if (vt_begin < vt_end) stream.start(W, ld_bytes, vt_begin * L::TILE, V, H, HT, ld_bytes, n0, N, d, lds);
   for (int vt = vt_begin; vt < vt_end; ++vt) {
     const int v0 = vt * L::TILE;
-    stream.run(lds, acc);
-    if (vt + 1 < vt_end) stream.start(W, ld_bytes, v0 + L::TILE, V, H, HT, ld_bytes, n0, N, d, lds);
+    stream.run(lds, acc, [&] {
+      if constexpr (LATE) { if (vt == vt_begin) classify(); }
+      if (vt + 1 < vt_end) stream.start(W, ld_bytes, v0 + L::TILE, V, H, HT, ld_bytes, n0, N, d, lds);
+    });
 
-    // Online update of (m, a) and the target gather, one 32 x 32 accumulator block at a time
-    // (16 logits of one token per lane).  All 32 rows of a block belong to one wavefront, so
+    // Online update of (m, a) and the target gather, one accumulator block at a time
+    // (16 logits of one token per lane).  All rows of a block belong to one wavefront, so
     // "entirely behind the vocabulary's end" and "straddles the end" are wave-uniform tests;
     // padded rows count as logits of -inf.
 #pragma unroll
     for (int j = 0; j < L::WN; ++j) {
 #pragma unroll
       for (int i = 0; i < L::WM; ++i) {
-        const int blk0 = v0 + __builtin_amdgcn_readfirstlane(L::tile_m(i, 0) & ~31);   // first row of the block
+        const int blk0 = v0 + __builtin_amdgcn_readfirstlane(L::tile_m(i, 0) & ~(L::ROWS - 1));   // first row of the block
         if (blk0 >= V) continue;
         float z[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) z[r] = L::acc_get(acc[i][j], r);
-        // Row of register r inside its 32-row block: 8 * (r / 4) + (r % 4), a constant, plus 4 for the upper
-        // half of the lanes (the 32x32 MFMA's accumulator layout); comparisons are written against the constant.
-        const int half4 = L::tile_m(i, 0) & 4;
-        if (blk0 + 32 > V) {
-          const int live = V - blk0 - half4;                // rows of this block below the vocabulary's end, per lane half
+        for (int r = 0; r < 16; ++r) z[r] = acc.get(i, j, r);
+        // Row of register r inside its block: QUAD * (r / 4) + (r % 4), a constant, plus what the lane adds (the MFMA's
+        // accumulator layout); comparisons are written against the constant.
+        const int lrow = L::lane_row();
+        if (blk0 + L::ROWS > V) {
+          const int live = V - blk0 - lrow;                 // rows of this block below the vocabulary's end, for this lane
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            if ((r >> 2) * 8 + (r & 3) >= live) z[r] = NEG_INF;
+            if ((r >> 2) * L::QUAD + (r & 3) >= live) z[r] = NEG_INF;
         }
         float bmax = z[0];
 #pragma unroll
@@ -346,12 +374,12 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
         m[j] = mn;
 
         const int rel = tgt[j] - blk0;                    // target row inside this block, if any
-        const bool mine = (unsigned)rel < 32u && tgt[j] >= 0;
+        const bool mine = (unsigned)rel < (unsigned)L::ROWS && tgt[j] >= 0;
         if (__ballot(mine) != 0ull) {
-          const int relh = rel - half4;
+          const int rell = rel - lrow;
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            if (mine && (r >> 2) * 8 + (r & 3) == relh) zt[j] = z[r];
+            if (mine && (r >> 2) * L::QUAD + (r & 3) == rell) zt[j] = z[r];
         }
         // one block at a time in VGPRs
         __builtin_amdgcn_sched_barrier(0);
@@ -359,11 +387,12 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
     }
   }
 
-  // Four lanes hold partial state of each token (2 M-wavefronts x 2 lane halves):
-  // merge them in fixed slot order through LDS (free after the main loop's barrier).
+  // SLOTS lanes hold partial state of each token (2 M-wavefronts x the lanes of one that share a column):
+  // merge them in fixed slot order through LDS (free after the main loop's last barrier).
+  constexpr int S = L::SLOTS;
   float* sm = reinterpret_cast<float*>(lds);
-  float* sa = sm + 4 * L::TILE;
-  float* sz = sa + 4 * L::TILE;
+  float* sa = sm + S * L::TILE;
+  float* sz = sa + S * L::TILE;
   {
     const int slot = L::slot();
 #pragma unroll
@@ -377,12 +406,12 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
   __syncthreads();
   if (threadIdx.x < L::TILE) {
     const int tok = threadIdx.x;
-    float pm[4], pa[4];
+    float pm[S], pa[S];
     float z = 0.f;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) { pm[s] = sm[s * L::TILE + tok]; pa[s] = sa[s * L::TILE + tok]; z += sz[s * L::TILE + tok]; }
+    for (int s = 0; s < S; ++s) { pm[s] = sm[s * L::TILE + tok]; pa[s] = sa[s * L::TILE + tok]; z += sz[s * L::TILE + tok]; }
     float M, A;
-    merge_fixed<4>(pm, pa, M, A);
+    merge_fixed<S>(pm, pa, M, A);
     const int64_t o = (int64_t)win * npad + n0 + tok;
     part[o] = M;
     part[(int64_t)n_win * npad + o] = A;
@@ -828,12 +857,12 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const U* __restrict__ H,
 // The pre-tiled copy of a row-major bf16 matrix X[rows][d] (d a multiple of 8) that the tuned main loop reads as
 // its B operand: for every block of 256 rows and every K step of 32 elements, the 16 KiB image of that step's LDS
 // tile, images of one row block following each other in K order:
-//   P[(rb * d / 32 + kt) * 16 KiB + r * 64 + 16 * pos] = the 16 bytes X[rb * 256 + r][kt * 32 + 8 * (pos ^ (r / 4) % 4) ...]
+//   P[(rb * d / 32 + kt) * 16 KiB + r * 64 + 16 * pos] = the 16 bytes X[rb * 256 + r][kt * 32 + 8 * (pos ^ chunk_swizzle(r)) ...]
 // (the main loop's K-contiguous LDS tile, 256 rows of 64 bytes with its chunk swizzle), rows and columns past the end as zeros.
 // pack_rows_store: one thread's part, the 64 bytes of row r of row block rb at K step kt.
 __device__ __forceinline__ void pack_rows_store(const u32x4 (&chunk)[4], char* __restrict__ P, int rb, int kt, int d, int r) {
   u32x4* dst = reinterpret_cast<u32x4*>(P + packed_block_offset(rb, d) + (int64_t)kt * fast::OPER + r * 64);
-  const int sw = (r >> 2) & 3;
+  const int sw = fast::chunk_swizzle(r);
 #pragma unroll
   for (int c = 0; c < 4; ++c) dst[c ^ sw] = chunk[c];
 }
@@ -913,7 +942,7 @@ __global__ __launch_bounds__(256) void prep_rows_tiled_kernel(const char* __rest
   for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(&tile[rr][g * 32 + i * 8]) = chunk[i];
   __syncthreads();
   // thread m: the 32 rows' values at hidden position q * 256 + m, as the 64 bytes of row m of the image
-  const int m = threadIdx.x, sw = (m >> 2) & 3;
+  const int m = threadIdx.x, sw = fast::chunk_swizzle(m);
   u32x4* dst = reinterpret_cast<u32x4*>(HcTP + packed_cols_offset(q, rows_pad) + (int64_t)kt * fast::OPER + m * 64);
 #pragma unroll
   for (int ch = 0; ch < 4; ++ch) {
@@ -1028,35 +1057,36 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
   RowMeta<L> meta;
   if constexpr (L::TUNED) load_meta((a.nt0 + p) * L::TILE, meta);
   stream.start(W, ld_bytes, (a.vt0 + q) * L::TILE, V, Hc, HcT, ld_bytes, (a.nt0 + p) * L::TILE, npad, d, lds);
-  f32x16 acc[L::WM][L::WN];
+  typename L::Acc acc;
   for (;;) {
-    stream.run(lds, acc);
     const int t_next = t + gridDim.x;
     // (a main loop with nothing to request ahead gets one tile per workgroup)
     const bool more = L::TUNED && t_next < useful;
     int p_next = 0, q_next = 0;
     RowMeta<L> meta_next;
-    if constexpr (!L::TUNED) load_meta((a.nt0 + p) * L::TILE, meta);   // no registers to spare across that main loop
-    need_meta(meta);
-    if (more) {
-      place(t_next, p_next, q_next);
-      load_meta((a.nt0 + p_next) * L::TILE, meta_next);
-      stream.start(W, ld_bytes, (a.vt0 + q_next) * L::TILE, V, Hc, HcT, ld_bytes, (a.nt0 + p_next) * L::TILE, npad, d, lds);
-    }
+    stream.run(lds, acc, [&] {
+      if constexpr (!L::TUNED) load_meta((a.nt0 + p) * L::TILE, meta);   // no registers to spare across that main loop
+      need_meta(meta);
+      if (more) {
+        place(t_next, p_next, q_next);
+        load_meta((a.nt0 + p_next) * L::TILE, meta_next);
+        stream.start(W, ld_bytes, (a.vt0 + q_next) * L::TILE, V, Hc, HcT, ld_bytes, (a.nt0 + p_next) * L::TILE, npad, d, lds);
+      }
+    });
 
     const int v0 = (a.vt0 + q) * L::TILE;
     if constexpr (L::TUNED) {
-      // Tuned loop.  A lane holds, of 32 token rows x (32 WM) vocabulary positions per j, scattered 8-byte pieces of one
-      // row; stored as they lie, every store instruction would touch 64 different memory rows.  Each wavefront
-      // therefore passes its piece (8 KiB of bf16 with 256-row tiles) through its own slice of the free LDS stage and
-      // writes whole runs of 256 (128) bytes: 16 (8) lanes per row, 4 (8) rows per instruction.
+      // Tuned loop.  A lane holds, of 16 token rows x (32 B) vocabulary positions per j, scattered 8-byte pieces of one
+      // row; stored as they lie, every store instruction would touch 16 different memory rows in 32-byte pieces.  Each wavefront
+      // therefore passes its piece (4 KiB of bf16 with 256-row tiles) through its own slice of the free LDS stage and
+      // writes whole blocks of G, 1 KiB of consecutive bytes per instruction.
       static_assert(sizeof(T) == 2, "the tuned epilogue is laid out for bf16");
-      constexpr int RPS = L::ROWS_PER_STORE;
+      constexpr int POS = L::WM * L::ROWS;                        // vocabulary positions of a piece
       const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-      char* stage = lds + L::FREE_LDS_OFFSET + wave * (32 * L::ROW_BYTES);
-      const int wrow = lane & 31, whalf = lane >> 5;              // writer: token row of the piece, lane half
-      const int rrow = lane / L::CHUNKS, rchunk = lane % L::CHUNKS;   // reader: row within a store, 16-byte chunk
-      const int vbase = v0 + (wave >> 1) * (L::WM * 32);          // first vocabulary position of the piece
+      char* stage = lds + L::FREE_LDS_OFFSET + wave * (16 * L::ROW_BYTES);
+      const int wrow = lane & 15;                                 // writer: token row of the piece
+      const int rrow = lane >> 2, rchunk = lane & 3;              // reader: row and 16-byte chunk inside a block
+      const int vbase = v0 + (wave >> 1) * POS;                   // first vocabulary position of the piece
 #pragma unroll
       for (int j = 0; j < L::WN; ++j) {
         const int tgt = meta.tgt[j];
@@ -1066,10 +1096,10 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
         float gam = 1.f;
         if constexpr (PER_ROW) gam = tgt >= 0 ? meta.gam[j] : 0.f;
         const float unif = tgt >= 0 ? a.uniform_part : 0.f;
-        // A whole column of blocks without a target of the wavefront and inside the vocabulary (almost all are: 32 WM of V
+        // A whole column of blocks without a target of the wavefront and inside the vocabulary (almost all are: POS of V
         // positions) needs no tests (step of 4326 x 232 x 74697 1044 -> 1008 us, 1144 x 576 x 191782 1306 -> 1264,
         // 4096 x 768 x 50257 1198 -> 1178).
-        if (vbase + L::WM * 32 <= V && __ballot((unsigned)(tgt - vbase) < 32u * L::WM) == 0ull) {
+        if (vbase + POS <= V && __ballot((unsigned)(tgt - vbase) < (unsigned)POS) == 0ull) {
 #pragma unroll
           for (int i = 0; i < L::WM; ++i) {
 #pragma unroll
@@ -1077,30 +1107,30 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
               float g[4];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                g[e] = fast_exp2(fmaf(L::acc_get(acc[i][j], rq * 4 + e), LOG2E, ll));
+                g[e] = fast_exp2(fmaf(acc.get(i, j, rq * 4 + e), LOG2E, ll));
                 if constexpr (PER_ROW) g[e] = gam * (g[e] - unif);
               }
               uint2 packed;
               packed.x = f32x2_to_bf16x2_bits(g[0], g[1]);
               packed.y = f32x2_to_bf16x2_bits(g[2], g[3]);
-              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
+              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq)) = packed;
             }
-            __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
+            __builtin_amdgcn_sched_barrier(0);   // one accumulator block at a time in VGPRs
           }
         } else {
 #pragma unroll
           for (int i = 0; i < L::WM; ++i) {
-            const int blk0 = vbase + i * 32;                        // wave-uniform
-            const bool whole = blk0 + 32 <= V;
-            // Does any token column of this wavefront have its target among the block's 32 vocabulary positions?
-            // Almost never (32 of V positions), and then the one-hot term costs nothing: a wave-uniform branch.
-            const bool hit = __ballot((unsigned)(tgt - blk0) < 32u) != 0ull;
+            const int blk0 = vbase + i * L::ROWS;                   // wave-uniform
+            const bool whole = blk0 + L::ROWS <= V;
+            // Does any token column of this wavefront have its target among the block's vocabulary positions?
+            // Almost never, and then the one-hot term costs nothing: a wave-uniform branch.
+            const bool hit = __ballot((unsigned)(tgt - blk0) < (unsigned)L::ROWS) != 0ull;
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
-              const int vpos = blk0 + rq * 8 + whalf * 4;           // first of this lane's 4 consecutive positions
+              const int vpos = blk0 + rq * L::QUAD + L::lane_row();   // first of this lane's 4 consecutive positions
               float g[4];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) g[e] = fast_exp2(fmaf(L::acc_get(acc[i][j], rq * 4 + e), LOG2E, ll));
+              for (int e = 0; e < 4; ++e) g[e] = fast_exp2(fmaf(acc.get(i, j, rq * 4 + e), LOG2E, ll));
               if (hit) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -1118,26 +1148,20 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
               uint2 packed;
               packed.x = f32x2_to_bf16x2_bits(g[0], g[1]);
               packed.y = f32x2_to_bf16x2_bits(g[2], g[3]);
-              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
+              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq)) = packed;
             }
-            __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
+            __builtin_amdgcn_sched_barrier(0);   // one accumulator block at a time in VGPRs
           }
         }
-        // the piece is complete in LDS (a wavefront's LDS operations complete in order): write it out, whole rows at a
+        // the piece is complete in LDS (a wavefront's LDS operations complete in order): write it out, a block at a
         // time.  G is stored in blocks of 16 rows x 32 positions (1 KiB; the blocks of a row
-        // group along the vocabulary, row groups ldG BYTES apart), so that both contractions fetch whole blocks:
-        // a row's 16 bytes at position chunk c lie in block c / 4 at (row % 16) * 64 + (c % 4) * 16.
-        const int row0 = p * L::TILE + (wave & 1) * (L::WN * 32) + j * 32;          // a multiple of 32: two row groups
-        const int cchunk = q * (L::TILE / 8) + (wave >> 1) * (L::WM * 4) + rchunk;  // 8-position chunk inside the chunk's row
-        char* __restrict__ gdst = reinterpret_cast<char*>(G) + (int64_t)(row0 >> 4) * ldG + (int64_t)(cchunk >> 2) * 1024 +
-                                  rrow * 64 + (cchunk & 3) * 16;
+        // group along the vocabulary, row groups ldG BYTES apart), so that both contractions fetch whole blocks.
+        const int row0 = p * L::TILE + (wave & 1) * (L::WN * 16) + j * 16;          // a row group
+        char* __restrict__ gdst = reinterpret_cast<char*>(G) + (int64_t)(row0 >> 4) * ldG +
+                                  (int64_t)(q * (L::TILE / 32) + (wave >> 1) * (POS / 32)) * 1024 + lane * 16;
 #pragma unroll
-        for (int k = 0; k < 32 / RPS; ++k) {
-          const int r = k * RPS + rrow;
-          u32x4 vq = *reinterpret_cast<const u32x4*>(stage + L::piece_chunk(r, rchunk));
-          if (L::swapped(rrow)) vq = u32x4{vq[2], vq[3], vq[0], vq[1]};      // (r and rrow agree in those bits)
-          *reinterpret_cast<u32x4*>(gdst + (int64_t)(k * RPS / 16) * ldG + k * RPS % 16 * 64) = vq;
-        }
+        for (int k = 0; k < POS / 32; ++k)
+          *reinterpret_cast<u32x4*>(gdst + k * 1024) = *reinterpret_cast<const u32x4*>(stage + L::piece_chunk(rrow, k * 4 + rchunk));
       }
     } else {
     // Blocks in (i, j) order, i outermost: what depends on the vocabulary position only (the padding masks of a
@@ -1168,7 +1192,7 @@ __global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> 
           const int mloc = L::tile_m(i, rq * 4);    // first of 4 consecutive vocabulary positions
           float g[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) g[e] = fast_exp2(fmaf(L::acc_get(acc[i][j], rq * 4 + e), LOG2E, ll));
+          for (int e = 0; e < 4; ++e) g[e] = fast_exp2(fmaf(acc.get(i, j, rq * 4 + e), LOG2E, ll));
           if (hit) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -1272,8 +1296,10 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
 
   // item -> K slice z, output-row tile p, hidden tile q; K range [k0, k0 + k_elems) of the slice
   auto place = [&](int item, int& z, int& p, int& q, int& k0, int& k_elems) {
-    z = item / tiles;
-    grouped_raster(xcd_contiguous_id(item - z * tiles, tiles), n_nt, a.n_mt, 8, p, q);
+    // (opaque per tile: the divisions' constants would be kept in scalar registers, which the tuned loop is short of)
+    const int per_slice = fast::scalar(tiles), n_mt = fast::scalar(a.n_mt);
+    z = item / per_slice;
+    grouped_raster(xcd_contiguous_id(item - z * per_slice, per_slice), n_nt, n_mt, 8, p, q);
     k0 = 0; k_elems = k_all;
     if (a.n_split > 1) { k0 = z * a.k_split; k_elems = max(0, min(a.k_split, k_all - k0)); }
   };
@@ -1291,18 +1317,18 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
     for (int j = 0; j < L::WN; ++j) asm volatile("" : "+v"(orow[j]));
   };
   // Running sum / Gamma / rounding of one finished tile.
-  auto flush = [&](f32x16 (&acc)[L::WM][L::WN], int z, int p, int q, const int (&orow)[L::WN]) {
+  auto flush = [&](const typename L::Acc& acc, int z, int p, int q, const int (&orow)[L::WN]) {
     int flags = a.flags;
     float* __restrict__ accbuf = a.accbuf;
     if (a.n_split > 1) {
       accbuf = a.partial + (int64_t)z * a.partial_stride;
       flags = (flags & ROWS_COMPACT) | WRITE_ACC;
     }
-    // one 32-row column of blocks straight from the accumulator layout
-    auto direct = [&](f32x16 (&acc)[L::WM][L::WN], int j) {
+    // one column of blocks straight from the accumulator layout
+    auto direct = [&](const typename L::Acc& acc, int j) {
       if (orow[j] < 0) return;
       const int n = a.out_row0 + p * L::TILE + L::tile_n(j);
-      // this lane's first hidden position; block (i, rq) lies a constant 32 i + 8 rq further on
+      // this lane's first hidden position; quad (i, rq) lies a constant further on
       const int m0 = q * L::TILE + L::tile_m(0, 0);
       float* __restrict__ arow = accbuf + (int64_t)(n - a.acc_row0) * d + m0;
       T* __restrict__ orowp = out + (int64_t)orow[j] * d + m0;
@@ -1310,10 +1336,10 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
       for (int i = 0; i < L::WM; ++i)
 #pragma unroll
         for (int rq = 0; rq < 4; ++rq) {
-          const int c = i * 32 + rq * 8;
+          const int c = i * L::ROWS + rq * L::QUAD;
           if (m0 + c >= d) continue;
-          f32x4 v = {L::acc_get(acc[i][j], rq * 4), L::acc_get(acc[i][j], rq * 4 + 1), L::acc_get(acc[i][j], rq * 4 + 2),
-                     L::acc_get(acc[i][j], rq * 4 + 3)};
+          f32x4 v = {acc.get(i, j, rq * 4), acc.get(i, j, rq * 4 + 1), acc.get(i, j, rq * 4 + 2),
+                     acc.get(i, j, rq * 4 + 3)};
           float* ap = arow + c;
           if (flags & READ_ACC) v += *reinterpret_cast<const f32x4*>(ap);
           if (flags & WRITE_ACC) *reinterpret_cast<f32x4*>(ap) = v;
@@ -1321,53 +1347,51 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
             // "+ 0.f" turns a -0 product into +0
             Pack4<T>::store(orowp + c, v[0] * scale + 0.f, v[1] * scale + 0.f, v[2] * scale + 0.f, v[3] * scale + 0.f);
           }
-          if (rq == 3) __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time in VGPRs
+          if (rq == 3) __builtin_amdgcn_sched_barrier(0);   // one accumulator block at a time in VGPRs
         }
     };
     if constexpr (L::TUNED) {
-      // The rounded output: in the accumulator layout a store instruction would touch 32 output rows with 16 bytes each.
-      // As in the recompute step, each wavefront passes 32 rows x 256 bytes at a time through its slice of the free LDS
-      // stage (8-byte slots XOR-ed with the row: conflict-free) and writes whole 256-byte runs, 4 rows per instruction.
+      // The rounded output: in the accumulator layout a store instruction would touch 16 output rows with 32 bytes each.
+      // As in the recompute step, each wavefront passes 16 rows x 256 bytes at a time through its slice of the free LDS
+      // stage and writes whole 256-byte runs, 4 rows per instruction.
       // It matters where the K loop is short: dW at 500 tokens x 4096 x 128256 807 -> 750 us (the K loops alone take 479),
       // the step at 1000 x 2048 x 100000 1616 -> 1528 us; at 8192 tokens it changes nothing.  The fp32 sums gain nothing
-      // from the detour (32 bytes per row as they lie; 4096 x 128 x 32000 363 us against 357) and go out directly.
+      // from the detour (64 bytes per row as they lie) and go out directly.
       static_assert(sizeof(T) == 2, "laid out for bf16");
       constexpr int RPS = L::ROWS_PER_STORE;
       const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-      char* stage = lds + L::FREE_LDS_OFFSET + wave * (32 * L::ROW_BYTES);
-      const int wrow = lane & 31, whalf = lane >> 5;              // writer: output row of the piece, lane half
-      const int rrow = lane / L::CHUNKS, rchunk = lane % L::CHUNKS;   // reader: row within a store, 16-byte chunk
-      const int mw = q * L::TILE + (wave >> 1) * (L::WM * 32);    // first hidden position of the wavefront's columns
+      char* stage = lds + L::FREE_LDS_OFFSET + wave * (16 * L::ROW_BYTES);
+      const int wrow = lane & 15;                                 // writer: output row of the piece
+      const int rrow = lane / L::CHUNKS, rpos = lane % L::CHUNKS;   // reader: row within a store, place of a 16-byte chunk
+      const int mw = q * L::TILE + (wave >> 1) * (L::WM * L::ROWS);   // first hidden position of the wavefront's columns
       // output row of piece row r: rows of dW follow each other, rows of dH go where the compact rows came from
       auto row_of = [&](int j, int r) -> int {
         if constexpr (OPS == OPS_DH_TR) return __shfl(orow[j], r, 64);
-        const int n = a.out_row0 + p * L::TILE + (wave & 1) * (L::WN * 32) + j * 32 + r;
+        const int n = a.out_row0 + p * L::TILE + (wave & 1) * (L::WN * 16) + j * 16 + r;
         return n < a.out_rows ? n : -1;
       };
       if (mw >= d) return;                                        // all of the wavefront's columns lie past the hidden size
 #pragma unroll
       for (int j = 0; j < L::WN; ++j) {
         if (!(flags & (READ_ACC | WRITE_ACC))) {
-          // Gamma applied, rounded, out: 32 rows x (32 WM) positions of 2 bytes ("+ 0.f" turns a -0 product into +0)
+          // Gamma applied, rounded, out ("+ 0.f" turns a -0 product into +0)
 #pragma unroll
           for (int i = 0; i < L::WM; ++i)
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
               float v[4];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = L::acc_get(acc[i][j], rq * 4 + e) * scale + 0.f;
+              for (int e = 0; e < 4; ++e) v[e] = acc.get(i, j, rq * 4 + e) * scale + 0.f;
               uint2 packed;
               packed.x = f32x2_to_bf16x2_bits(v[0], v[1]);
               packed.y = f32x2_to_bf16x2_bits(v[2], v[3]);
-              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq, whalf)) = packed;
-              if (rq == 3) __builtin_amdgcn_sched_barrier(0);     // one 32x32 block at a time in VGPRs
+              *reinterpret_cast<uint2*>(stage + L::piece_slot(wrow, i, rq)) = packed;
+              if (rq == 3) __builtin_amdgcn_sched_barrier(0);     // one accumulator block at a time in VGPRs
             }
-          const int m = mw + rchunk * 8;
 #pragma unroll
-          for (int k = 0; k < 32 / RPS; ++k) {
-            const int r = k * RPS + rrow;
-            u32x4 v = *reinterpret_cast<const u32x4*>(stage + L::piece_chunk(r, rchunk));
-            if (L::swapped(rrow)) v = u32x4{v[2], v[3], v[0], v[1]};         // (r and rrow agree in those bits)
+          for (int k = 0; k < 16 / RPS; ++k) {
+            const int r = k * RPS + rrow, m = mw + (rpos ^ L::mix(r)) * 8;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * L::ROW_BYTES + rpos * 16);
             const int row = row_of(j, r);
             if (row >= 0 && m < d) *reinterpret_cast<u32x4*>(out + (int64_t)row * d + m) = v;
           }
@@ -1382,7 +1406,7 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
     }
   };
 
-  f32x16 acc[L::WM][L::WN];
+  typename L::Acc acc;
   int z, p, q, k0, k_elems;
   place(b, z, p, q, k0, k_elems);
   int orow[L::WN];
@@ -1398,10 +1422,10 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
     const f32::Operand As{reinterpret_cast<const char*>(A + (int64_t)k0 * lda + q * L::TILE), lda * 4, 0, a.a_krows - k0, width};
     if constexpr (OPS == OPS_DH_F32) {
       const f32::Operand Bs{reinterpret_cast<const char*>(B + k0), ldb * 4, p * L::TILE, a.b_rows, 0};
-      f32::mainloop<L::TILE, f32::KR, f32::KC>(As, Bs, k_elems, lds, acc);
+      f32::mainloop<L::TILE, f32::KR, f32::KC>(As, Bs, k_elems, lds, acc.v);
     } else {
       const f32::Operand Bs{reinterpret_cast<const char*>(B + (int64_t)k0 * ldb + p * L::TILE), ldb * 4, 0, k_elems, L::TILE * 4};
-      f32::mainloop<L::TILE, f32::KR, f32::KR>(As, Bs, k_elems, lds, acc);
+      f32::mainloop<L::TILE, f32::KR, f32::KR>(As, Bs, k_elems, lds, acc.v);
     }
     load_rows(p, orow);
     flush(acc, z, p, q, orow);
@@ -1430,9 +1454,8 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
     load_rows(p, orow);
     start(p, q, k0, k_elems);
     for (;;) {
-      pipe.run(lds, acc);
       if constexpr (ONE) {
-        need_rows(orow);
+        pipe.run(lds, [&] { need_rows(orow); });
         flush(acc, z, p, q, orow);
         return;
       }
@@ -1440,12 +1463,14 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
       const bool more = b_next < total;
       int z_next = 0, p_next = 0, q_next = 0, k0_next = 0, k_next = 0;
       int orow_next[L::WN];
-      need_rows(orow);
-      if (more) {
-        place(b_next, z_next, p_next, q_next, k0_next, k_next);
-        load_rows(p_next, orow_next);
-        start(p_next, q_next, k0_next, k_next);
-      }
+      pipe.run(lds, [&] {
+        need_rows(orow);
+        if (more) {
+          place(b_next, z_next, p_next, q_next, k0_next, k_next);
+          load_rows(p_next, orow_next);
+          start(p_next, q_next, k0_next, k_next);
+        }
+      });
       flush(acc, z, p, q, orow);
       if (!more) break;
       need_rows(orow_next);
