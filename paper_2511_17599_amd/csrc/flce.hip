@@ -184,11 +184,14 @@ bool plan_base(int64_t N, int64_t d, int64_t V, flce_dtype dt, const Tuning& tn,
   p.hkr = allow_h_copy && p.fast;
 
   p.tile = TILE;
-  // fp32: 64-row tiles while there are too few 128-row ones to give every CU more than one (whole steps: 256 x 256 x 4096,
-  // 64 tiles of 128: 77 us with 64-row tiles against 118; 1024 x 512 x 4096, 256 tiles: 211 / 220; 1000 x 256 x 6400, 400
-  // tiles: 190 / 185; 2048 x 256 x 16000, 2000 tiles: 715 / 586).
-  if (dt == FLCE_DTYPE_F32) p.tile = ceil_div(N, 128) * ceil_div(V, 128) < 320 ? 64 : 128;
-  p.fwd_tile = p.tile;
+  // fp32: 64-row tiles while there are too few 128-row ones to give every CU work.  The 128-row ones compute with bf16 parts of
+  // the operands, which is faster per flop, so the backward's line lies lower than the forward's, whose windows fit fewer
+  // of them.  Backward with 64 and with 128, us: 256 x 256 x 4096 (64 tiles of 128) 40 / 52, 400 x 256 x 4096 (128) 52 / 58,
+  // 512 x 512 x 4096 (128) 88 / 84, 1170 x 96 x 2500 (200) 62 / 50, 1024 x 512 x 4096 (256) 150 / 114; forward 1024 x 512 x 4096
+  // 61 / 70, 300 x 304 x 12000 (282) 43 / 49, 2000 x 1024 x 2400 (304) 131 / 125.
+  const int64_t tiles128 = ceil_div(N, 128) * ceil_div(V, 128);
+  if (dt == FLCE_DTYPE_F32) p.tile = tiles128 < 160 ? 64 : 128;
+  p.fwd_tile = dt == FLCE_DTYPE_F32 && tiles128 < 320 ? 64 : p.tile;
   // bf16: 256-row tiles are the faster loop (1.4 PFLOP/s against 0.8 with 128-row ones, which move twice the bytes per
   // flop), but one of them keeps a CU busy for K / 32 x 0.78 us + the work at its end, and where there are too few of them,
   // or K is short, the 128-row ones with two workgroups per CU are done earlier.  Times in us, fitted over 29 shapes from
@@ -298,13 +301,13 @@ void plan_backward(const Tuning& tn, Plan& p) {
   // the time in us.  A launch takes rounds of workgroups times (K tiles of a slice + `ends` for filling the pipeline and
   // writing the tile out), plus, for a split, the launch that adds the slices and the fp32 tiles written and read back.
   // A K tile (K elements = tile edge) takes 6.2 us in bf16 with 256-tiles and 1.12 with 128-tiles (two workgroups per
-  // CU), and at fp32 (likewise two) 6.8 us per CU with 128-tiles, 0.85 with 64-tiles.
+  // CU), and at fp32 (likewise two) 5.2 us per CU with 128-tiles, 0.85 with 64-tiles.
   struct Contractions { int split_dh, split_dw; bool pair; double us; };
   auto contractions = [&](int tile) {
     Contractions c{tn.splitk_dh, tn.splitk_dw, false, 0.0};
     const int64_t n_mt = ceil_div(d, tile), unit = TILE / tile;
     const bool small = !f32 && tile != TILE;
-    const double k_us = small ? 1.12 : !f32 ? 6.2 : tile == 128 ? 6.8 : 0.85, ends = tile == 64 ? 3.5 : small ? 2.0 : 1.2,
+    const double k_us = small ? 1.12 : !f32 ? 6.2 : tile == 128 ? 5.2 : 0.85, ends = tile == 64 ? 3.5 : small ? 2.0 : 1.2,
                  tile_us = !f32 && !small ? 0.124 : tile == 64 ? 0.0085 : 0.034, launch = 5.0;
     auto rounds = [&](int64_t wgs) { return small ? small_waves(wgs) : (double)ceil_div(wgs, NUM_CU); };
     auto split_cost = [&](int64_t tiles, int64_t k_tiles, int sp) {
@@ -936,7 +939,7 @@ static flce_status forward_impl(const void* H, const void* W, const int64_t* tar
     return flce::forward_t<flce::bf16_t, uint16_t, flce::GenericLoop>(
         p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
   }
-  if (p.tile == 64)
+  if (p.fwd_tile == 64)
     return flce::forward_t<float, uint32_t, flce::F32Loop<64>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
   return flce::forward_t<float, uint32_t, flce::F32Loop<128>>(p, H, W, targets, ignore_index, mean, loss_out, lse_out, ws, st, slice, m_out, a_out, zt_out, rows, so);
 }

@@ -1,13 +1,19 @@
 // fp32 main loop for gfx950: T x T output tile (T = 128 or 64), 256 threads = 4 wavefronts arranged 2 x 2, each owning
-// WB x WB = T / 64 blocks of the 32x32x2 fp32 MFMA, two workgroups per CU.
+// WB x WB = T / 64 blocks of a 32 x 32 MFMA, two workgroups per CU.
 //
-// The fp32 matrix instruction is 16 times slower than the bf16 one (256 flops per clock and CU), so nothing about the
-// data path is critical; what counts is that every CU has work.  A 256-row tile of K = 512 keeps a CU busy for 109 us and
+// The fp32 matrix instruction is 16 times slower than the bf16 one (256 flops per clock and CU).  128-row tiles therefore
+// write each operand value as the exact sum of three bf16 numbers, x = h + m + l (8 bits of mantissa each), and add up the six
+// products hh, hm, mh, mm, hl, lh in the bf16 instruction's fp32 accumulators; what is left out is below 2^-24 of a product.
+// Its sums round once per 16 products and part instead of once per 2 products, and the partial sums are kept
+// short (sum_stages), so the error against 64 bits is no larger: dH and dW 4.0e-7 -> 1.7e-7 (1000 x 512 x 10007), 4.2e-7 ->
+// 2.5e-7 and 4.1e-7 -> 1.8e-7 (4096 x 1024 x 16384), log-sum-exp level (its rounding to 32 bits dominates).  Forward + backward
+// 1000 x 512 x 10007 452 -> 360 us, 4096 x 1024 x 32768 8.50 -> 6.67 ms (both sides in turn).  What bounds it: the vector work of
+// taking the parts (44 instructions per eight values and block row) beside the 24 MFMAs of a K step of 16, of which two
+// wavefronts per SIMD overlap about two thirds.  64-row tiles serve problems too small to fill the chip, where one
+// wavefront per SIMD would do the two one after the other: they stay with the fp32 instruction (with parts 256 x 256 x 4096
+// forward 37.0 -> 39.2 us).  A 256-row tile of K = 512 keeps a CU busy for 109 us and
 // a problem of a few thousand rows by a few thousand vocabulary entries has fewer such tiles than the chip has CUs, hence
-// the small tiles (4 or 16 times fewer flops each) and the two resident workgroups that even out a ragged last round.
-// Forward + backward against 256-row tiles with register-staged loads and transposed copies: 256 x 256 x 4096 327 -> 77 us,
-// 1000 x 512 x 10007 950 -> 494 us (80 TFLOP/s), 4096 x 1024 x 32768 8.72 -> 8.21 ms (134 TFLOP/s of 157; a large library
-// matrix product reaches 153).
+// the small tiles and the two resident workgroups that even out a ragged last round.
 //
 //   * Operand tiles go from global memory straight into LDS (buffer_load ... lds), 32 K elements per stage, NS stages;
 //     each wavefront's part of a stage has a descriptor of its own, advanced with K, so that no operand size is out of a
@@ -29,11 +35,12 @@ namespace f32 {
 
 constexpr int THREADS = 256;
 constexpr int BK = 32;                                      // K elements per stage
-// Stages whose products are added up before they are added to the tile's sum: a chain of 512 additions and one of
-// K / 512 instead of one of K, which the contractions (K = the vocabulary, the rows) would otherwise show.  Relative error of
-// dH and dW against 64 bits at 4096 x 1024 x 16384: about 3e-6 with one chain, 5.8e-7 and 5.8e-7 with 1024, 4.2e-7 and 4.1e-7
-// with 512 (8215 -> 8248 us per step at twice the vocabulary), 3.2e-7 and 3.0e-7 with 256 (8360 us).
-constexpr int SUM_STAGES = 16;
+// Stages whose products are added up before they are added to the tile's sum: a chain of that many and one of the rest instead
+// of one of K, which the contractions (K = the vocabulary, the rows) would otherwise show.  Relative error of dH and dW against 64
+// bits at 4096 x 1024 x 16384 with the fp32 instruction: about 3e-6 with one chain, 4.2e-7 and 4.1e-7 with 512 elements;
+// with bf16 parts 2.8e-7 and 2.6e-7 with 512, 2.5e-7 and 1.8e-7 with 128, at the same speed.
+template <bool SPLIT>
+constexpr int sum_stages() { return SPLIT ? 4 : 16; }
 enum : int { KC = 0, KR = 1 };
 
 // One operand of the contraction.
@@ -127,9 +134,24 @@ constexpr int stages() { return T == 128 ? 2 : 4; }         // 64 KiB of LDS eit
 template <int T>
 constexpr int lds_bytes() { return stages<T>() * 2 * T * BK * 4; }
 
+// Eight fp32 values as three bf16 each, x = h + m + l exactly (8 bits of mantissa each, rounded to nearest).
+struct Split { bf16x8 h, m, l; };
+__device__ __forceinline__ Split split(const f32x4& x0, const f32x4& x1) {
+  union { bf16x8 v; uint32_t w[4]; } h, m, l;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const float a = p < 2 ? x0[2 * p] : x1[2 * p - 4], b = p < 2 ? x0[2 * p + 1] : x1[2 * p - 3];
+    h.w[p] = f32x2_to_bf16x2_bits(a, b);
+    const float ra = a - __uint_as_float(h.w[p] << 16), rb = b - __uint_as_float(h.w[p] & 0xFFFF0000u);
+    m.w[p] = f32x2_to_bf16x2_bits(ra, rb);
+    l.w[p] = f32x2_to_bf16x2_bits(ra - __uint_as_float(m.w[p] << 16), rb - __uint_as_float(m.w[p] & 0xFFFF0000u));
+  }
+  return Split{h.v, m.v, l.v};
+}
+
 // acc = A_tile . B_tile^T over k_elems of K.  On return every wavefront has passed a barrier after its last LDS read.
-template <int T, int LA, int LB>
-__device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int k_elems, char* lds,
+template <int T, int LA, int LB, bool SPLIT>
+__device__ __forceinline__ void mainloop_as(const Operand& A, const Operand& B, int k_elems, char* lds,
                                          f32x16 (&acc)[T / 64][T / 64]) {
   constexpr int W = T / 64, NS = stages<T>(), OPER = T * BK * 4, STAGE = 2 * OPER, LOADS = 2 * (T / 32);
 #pragma unroll
@@ -148,8 +170,8 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
     la.issue(lds + s * STAGE, s);
     lb.issue(lds + s * STAGE + OPER, s);
   }
-  for (int kb = 0; kb < KT; kb += SUM_STAGES) {
-    const int kb_end = min(KT, kb + SUM_STAGES);
+  for (int kb = 0; kb < KT; kb += sum_stages<SPLIT>()) {
+    const int kb_end = min(KT, kb + sum_stages<SPLIT>());
     f32x16 part[W][W];
 #pragma unroll
     for (int i = 0; i < W; ++i)
@@ -173,6 +195,33 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
         lb.issue(dst + OPER, kt + NS - 1);
       }
       const char* st = lds + kt % NS * STAGE;
+      if constexpr (SPLIT) {
+#pragma unroll
+        for (int g = 0; g < BK / 8; g += 2) {
+          f32x4 x[2][W];
+          Split a[W], b[W];
+          read_frags<T, LA>(x[0], st, wave >> 1, g);
+          read_frags<T, LA>(x[1], st, wave >> 1, g + 1);
+#pragma unroll
+          for (int i = 0; i < W; ++i) a[i] = split(x[0][i], x[1][i]);
+          read_frags<T, LB>(x[0], st + OPER, wave & 1, g);
+          read_frags<T, LB>(x[1], st + OPER, wave & 1, g + 1);
+#pragma unroll
+          for (int j = 0; j < W; ++j) b[j] = split(x[0][j], x[1][j]);
+          auto products = [&](auto pa, auto pb) {
+#pragma unroll
+            for (int i = 0; i < W; ++i)
+#pragma unroll
+              for (int j = 0; j < W; ++j) part[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i].*pa, b[j].*pb, part[i][j], 0, 0, 0);
+          };
+          products(&Split::l, &Split::h);
+          products(&Split::h, &Split::l);
+          products(&Split::m, &Split::m);
+          products(&Split::m, &Split::h);
+          products(&Split::h, &Split::m);
+          products(&Split::h, &Split::h);
+        }
+      } else
 #pragma unroll
       for (int g = 0; g < BK / 8; ++g) {
         f32x4 a[W], b[W];
@@ -197,6 +246,24 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
   fast::wait_vm_and_lds<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+
+template <int T, int LA, int LB>
+__device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int k_elems, char* lds,
+                                         f32x16 (&acc)[T / 64][T / 64]) {
+  mainloop_as<T, LA, LB, T == 128>(A, B, k_elems, lds, acc);
+  if constexpr (T == 128) {
+    // An infinity, a NaN or a value that rounds past bf16's largest has no such parts: its products are NaN.  The tile is
+    // then done again as it is.
+    float bad = 0.f;
+#pragma unroll
+    for (int i = 0; i < T / 64; ++i)
+#pragma unroll
+      for (int j = 0; j < T / 64; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bad = fmaf(acc[i][j][r], 0.f, bad);
+    if (__syncthreads_or(bad != bad)) mainloop_as<T, LA, LB, false>(A, B, k_elems, lds, acc);
+  }
 }
 
 }  // namespace f32
