@@ -3,7 +3,9 @@
     python -m paper_2511_17599_amd.build
 
 hipcc cross-compiles without a GPU.  The packed-fp32 target feature is switched
-off for all device code of this library.
+off for all device code of this library.  Launch arguments come preloaded in scalar
+registers (the first 16 words): a kernel's first loads otherwise wait for two of its
+argument segment, 0.3 to 0.4 us of a forward of 14 us (334 x 320 x 2142).
 """
 from __future__ import annotations
 
@@ -18,6 +20,7 @@ LIB = os.path.join(PKG, "libflce.so")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-command-line-argument",
 ]
 

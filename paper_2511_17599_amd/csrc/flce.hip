@@ -559,11 +559,11 @@ flce_status forward_t(const Plan& p, const void* H, const void* W, const int64_t
         if constexpr (L::TUNED)
           fwd_tiles_kernel<T, L, true><<<grid, L::THREADS, L::LDS, st>>>(
               static_cast<const T*>(H), HT, static_cast<const T*>(W), y, (int)p.N, (int)p.d, (int)p.V, ignore_index,
-              slice.V_total, slice.v_begin, n_rb, p.n_win, n_vt, part, p.npad, item0, hdr);
+              slice.V_total, slice.v_begin, n_rb, p.n_win, n_vt, (double)n_vt / p.n_win, part, p.npad, item0, hdr);
       } else {
         fwd_tiles_kernel<T, L, false><<<grid, L::THREADS, L::LDS, st>>>(
             static_cast<const T*>(H), nullptr, static_cast<const T*>(W), y, (int)p.N, (int)p.d, (int)p.V, ignore_index,
-            slice.V_total, slice.v_begin, n_rb, p.n_win, n_vt, part, p.npad, item0, hdr);
+            slice.V_total, slice.v_begin, n_rb, p.n_win, n_vt, (double)n_vt / p.n_win, part, p.npad, item0, hdr);
       }
     }
   }

@@ -290,7 +290,7 @@ template <typename T, typename L, bool HKR>
 __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
     const T* __restrict__ H, const T* __restrict__ HT, const T* __restrict__ W, const int64_t* __restrict__ y,
     int N, int d, int V, int64_t ignore_index, int64_t V_total, int64_t v_begin, int n_rb, int n_win, int n_vt,
-    float* __restrict__ part, int64_t npad, int item_begin, Header* __restrict__ hdr) {
+    double vt_per_win, float* __restrict__ part, int64_t npad, int item_begin, Header* __restrict__ hdr) {
   extern __shared__ __align__(16) char lds[];
   if (blockIdx.x == 0 && threadIdx.x == 0) hdr->arrived = 0;   // for the merge that follows on the stream
   // One workgroup per item (row block x window); a launch covers the items item_begin .. item_begin + gridDim.x - 1
@@ -299,8 +299,11 @@ __global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
   const int id = item_begin + xcd_contiguous_id(blockIdx.x, gridDim.x);
   int rb, win;
   grouped_raster(id, n_rb, n_win, FLCE_FWD_GROUP, rb, win);
-  const int vt_begin = (int)((int64_t)win * n_vt / n_win);
-  const int vt_end = (int)((int64_t)(win + 1) * n_vt / n_win);
+  // The tiles of window `win`, spread evenly; vt_per_win = n_vt / n_win, so that no division is on the way to the first load
+  // (two of 64 bits before; with the launch arguments in registers 334 x 320 x 2142 forward 14.4 -> 13.7 us, fp32
+  // 256 x 256 x 4096 36.8 -> 35.4).  Both sides of a boundary come from the same expression, the last one is n_vt.
+  const int vt_begin = __builtin_amdgcn_readfirstlane((int)(win * vt_per_win));
+  const int vt_end = win + 1 < n_win ? __builtin_amdgcn_readfirstlane((int)((win + 1) * vt_per_win)) : n_vt;
   const int n0 = rb * L::TILE;
   const int64_t ld_bytes = (int64_t)d * sizeof(T);
 
