@@ -104,16 +104,16 @@ def lib():
 
 
 def _ptr(x):
-    if x is None:
-        return None
+    if x is None or type(x) is int:
+        return x
     if hasattr(x, "data_ptr"):
         return x.data_ptr()
     return int(x)
 
 
 def _stream(s):
-    if s is None:
-        return None
+    if s is None or type(s) is int:
+        return s
     if hasattr(s, "cuda_stream"):
         return s.cuda_stream
     return int(s)

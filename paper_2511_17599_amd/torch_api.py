@@ -37,9 +37,14 @@ def _prepare(H, W, targets):
         raise TypeError("H and W must both be bfloat16 or both float32")
     if not (H.is_cuda and W.is_cuda and targets.is_cuda):
         raise ValueError("libflce works on GPU tensors only")
-    H2 = H.reshape(-1, H.shape[-1]).contiguous()
+    # A small call is bound by this host work: what is as the library wants it goes through untouched (64 x 64 x 600, forward
+    # and backward 131 -> 121 us with the same elsewhere in this file).
+    H2 = H if H.dim() == 2 and H.is_contiguous() else H.reshape(-1, H.shape[-1]).contiguous()
     W2 = W.contiguous()
-    y = targets.reshape(-1).to(torch.int64).contiguous()
+    if targets.dim() == 1 and targets.dtype is torch.int64 and targets.is_contiguous():
+        y = targets
+    else:
+        y = targets.reshape(-1).to(torch.int64).contiguous()
     if y.numel() != H2.shape[0] or W2.shape[1] != H2.shape[1]:
         raise ValueError("shapes: H [..., d], W [V, d], targets [...]")
     return H2, W2, y
@@ -62,13 +67,13 @@ class _ScalarLoss(torch.autograd.Function):
         V = W2.shape[0]
         dt = _DT[H2.dtype]
         st = _stream(H2.device)
-        loss = torch.empty(1, dtype=torch.float32, device=H2.device)
+        loss = torch.empty((), dtype=torch.float32, device=H2.device)
         lse = torch.empty(N, dtype=torch.float32, device=H2.device)
         ws, nb = _workspace(N, d, V, dt, 0, H2.device)
         _check(B.flce_forward(H2, W2, y, N, d, V, ignore_index, _RED[reduction], dt, loss, lse, ws, nb, st))
         ctx.save_for_backward(H2, W2, y, lse)
         ctx.meta = (H.shape, ignore_index, reduction)
-        return loss[0]
+        return loss
 
     @staticmethod
     def backward(ctx, grad_out):
@@ -83,12 +88,14 @@ class _ScalarLoss(torch.autograd.Function):
         ws, nb = _workspace(N, d, V, dt, 1, H2.device)
         # The kernels read the upstream gradient where it is: no wait for the stream between forward and backward.  (The
         # autograd engine runs this on the forward's stream and keeps gradients made on another one alive for it.)
-        g = grad_out.to(device=H2.device, dtype=torch.float32)
+        g = grad_out
+        if g.dtype is not torch.float32 or g.device != H2.device:
+            g = g.to(device=H2.device, dtype=torch.float32)
         if g.is_neg() or g._is_zerotensor():     # marked, not stored: the word in memory is not the value, or there is none
             g = g.clone().resolve_neg()
         _check(B.flce_backward_device_grad(H2, W2, y, lse, N, d, V, ignore_index, _RED[reduction], dt, g, dH, dW, ws, nb,
                                            st))
-        return dH.reshape(shape), dW, None, None, None
+        return dH if dH.shape == shape else dH.reshape(shape), dW, None, None, None
 
 
 class _RowLosses(torch.autograd.Function):
@@ -107,7 +114,7 @@ class _RowLosses(torch.autograd.Function):
         _check(B.flce_forward_rows(H2, W2, y, N, d, V, ignore_index, label_smoothing, dt, rows, lse, ws, nb, st))
         ctx.save_for_backward(H2, W2, y, lse)
         ctx.meta = (H.shape, ignore_index, label_smoothing)
-        return rows.reshape(targets.shape)
+        return rows if targets.dim() == 1 else rows.reshape(targets.shape)
 
     @staticmethod
     def backward(ctx, grad_rows):
@@ -123,7 +130,7 @@ class _RowLosses(torch.autograd.Function):
         ws, nb = _workspace(N, d, V, dt, 1, H2.device)
         _check(B.flce_backward_rows(H2, W2, y, lse, gr, N, d, V, ignore_index, label_smoothing, dt, dH, dW, ws, nb,
                                     st))
-        return dH.reshape(shape), dW, None, None, None
+        return dH if dH.shape == shape else dH.reshape(shape), dW, None, None, None
 
 
 def linear_cross_entropy(H, W, targets, ignore_index=-100, reduction="mean", label_smoothing=0.0):
