@@ -57,6 +57,7 @@ struct Operand {
 template <int T, int LAYOUT>
 struct Loader {
   static constexpr int REQS = T / 32;
+  static_assert(REQS == 4 || REQS == 2, "128 or 64 tile rows");
   const char* base;        // first row of the wavefront's quarter, K tile 0
   int64_t ld_bytes;
   int rows;                // valid rows of the quarter (KC), valid K rows from the quarter's first on (KR)
@@ -103,12 +104,24 @@ struct Loader {
     r[0] = __builtin_amdgcn_readfirstlane(r[0]);
     r[1] = __builtin_amdgcn_readfirstlane(r[1]);
     r[2] = __builtin_amdgcn_readfirstlane(r[2]);
+    uint32_t o[REQS];
 #pragma unroll
     for (int i = 0; i < REQS; ++i) {
-      uint32_t vo = v[i];
-      if (LAYOUT == KC) vo = kt * (BK * 4) + (int)chunk[i] < k_bytes ? vo : 0xFFFFFF00u;   // out of range: reads as zero
-      fast::dma16(r, fast::lds_address(tile + wave * (T * 32) + i * 1024), vo, 0);
+      o[i] = v[i];
+      if (LAYOUT == KC) o[i] = kt * (BK * 4) + (int)chunk[i] < k_bytes ? o[i] : 0xFFFFFF00u;   // out of range: reads as zero
     }
+    // One piece of assembly with the wait states that a descriptor made by vector instructions asks for (see mainloop_fast.h).
+    const uint32_t dst = fast::lds_address(tile + wave * (T * 32));
+    if constexpr (REQS == 4)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %5, 0 offen lds\n\t"
+                   "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %5, 0 offen lds\n\t"
+                   "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %5, 0 offen lds\n\t"
+                   "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %4, %5, 0 offen lds"
+                   :: "s"(dst), "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "s"(r) : "memory", "m0", "scc");
+    else
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
+                   "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds"
+                   :: "s"(dst), "v"(o[0]), "v"(o[1]), "s"(r) : "memory", "m0", "scc");
   }
 };
 

@@ -92,17 +92,13 @@ struct Operand {
   int width_bytes;
 };
 
-// The global -> LDS request is issued through inline assembly: as an intrinsic the compiler
-// treats it as a store that may alias every later LDS read it cannot disambiguate (the
+// Global -> LDS requests are issued through inline assembly: as an intrinsic the compiler
+// treats one as a store that may alias every later LDS read it cannot disambiguate (the
 // transposing reads among them) and waits for vmcnt(0) before each, which serialises the
 // pipeline.  Here the only consumers are separated from the DMA by the explicit vmcnt
-// wait + barrier of the main loop.  M0 carries the LDS destination of the wavefront.
-__device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t lds_addr, uint32_t voffset, uint32_t soffset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
-               : "memory", "m0");
-}
+// wait + barrier of the main loop.  M0 carries the LDS destination of the wavefront.  The descriptor may come fresh from
+// vector instructions (readfirstlane), whose scalar results a memory instruction may read five wait states later: the compiler
+// keeps that distance from its own instructions only, hence the s_nop 4 ahead of a group's first request.
 
 __device__ __forceinline__ uint32_t lds_address(const char* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
@@ -342,13 +338,13 @@ struct Loader {
   __device__ __forceinline__ void issue_all(uint32_t dst, int kt) {
     ragged_end(kt);
     if constexpr (REQS == 4)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
                    "buffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
                    "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\t"
                    "buffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
                    :: "s"(dst), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(rs), "s"(soff) : "memory", "m0");
     else
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
                    "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds"
                    :: "s"(dst), "v"(v[0]), "v"(v[1]), "s"(rs), "s"(soff) : "memory", "m0");
     advance();
