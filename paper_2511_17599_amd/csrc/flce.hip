@@ -184,14 +184,14 @@ bool plan_base(int64_t N, int64_t d, int64_t V, flce_dtype dt, const Tuning& tn,
   p.hkr = allow_h_copy && p.fast;
 
   p.tile = TILE;
-  // fp32: 64-row tiles while there are too few 128-row ones to give every CU work.  The 128-row ones compute with bf16 parts of
-  // the operands, which is faster per flop, so the backward's line lies lower than the forward's, whose windows fit fewer
-  // of them.  Backward with 64 and with 128, us: 256 x 256 x 4096 (64 tiles of 128) 40 / 52, 400 x 256 x 4096 (128) 52 / 58,
-  // 512 x 512 x 4096 (128) 88 / 84, 1170 x 96 x 2500 (200) 62 / 50, 1024 x 512 x 4096 (256) 150 / 114; forward 1024 x 512 x 4096
-  // 61 / 70, 300 x 304 x 12000 (282) 43 / 49, 2000 x 1024 x 2400 (304) 131 / 125.
-  const int64_t tiles128 = ceil_div(N, 128) * ceil_div(V, 128);
-  if (dt == FLCE_DTYPE_F32) p.tile = tiles128 < 160 ? 64 : 128;
-  p.fwd_tile = dt == FLCE_DTYPE_F32 && tiles128 < 320 ? 64 : p.tile;
+  // fp32: 64-row tiles while there are too few 128-row ones to give every CU more than one.  One line for both directions: the
+  // 128-row tiles compute with bf16 parts of the operands and the 64-row ones do not, and where the backward's logit is rounded
+  // otherwise than the forward's, exp(logit - lse) - 1 of a confident row is their difference instead of zero (1024 x 512 x 4096,
+  // target logits of 165: 2e-4, 5e-6 with the same tiles).  Forward with 64 and with 128, us: 1024 x 512 x 4096 (256 tiles of 128)
+  // 61 / 70, 300 x 304 x 12000 (282) 43 / 49, 2000 x 1024 x 2400 (304) 131 / 125; backward 512 x 512 x 4096 (128) 88 / 84,
+  // 1024 x 512 x 4096 150 / 114.
+  if (dt == FLCE_DTYPE_F32) p.tile = ceil_div(N, 128) * ceil_div(V, 128) < 320 ? 64 : 128;
+  p.fwd_tile = p.tile;
   // bf16: 256-row tiles are the faster loop (1.4 PFLOP/s against 0.8 with 128-row ones, which move twice the bytes per
   // flop), but one of them keeps a CU busy for K / 32 x 0.78 us + the work at its end, and where there are too few of them,
   // or K is short, the 128-row ones with two workgroups per CU are done earlier.  Times in us, fitted over 29 shapes from
