@@ -4,12 +4,14 @@
 // The fp32 matrix instruction is 16 times slower than the bf16 one (256 flops per clock and CU).  128-row tiles therefore
 // write each operand value as the exact sum of three bf16 numbers, x = h + m + l (8 bits of mantissa each), and add up the six
 // products hh, hm, mh, mm, hl, lh in the bf16 instruction's fp32 accumulators; what is left out is below 2^-24 of a product.
+// (The method: Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision
+// computations", ARITH 2019.)
 // Its sums round once per 16 products and part instead of once per 2 products, and the partial sums are kept
 // short (sum_stages), so the error against 64 bits is no larger: dH and dW 4.0e-7 -> 1.7e-7 (1000 x 512 x 10007), 4.2e-7 ->
-// 2.5e-7 and 4.1e-7 -> 1.8e-7 (4096 x 1024 x 16384), log-sum-exp level (its rounding to 32 bits dominates).  Forward + backward
-// 1000 x 512 x 10007 452 -> 360 us, 4096 x 1024 x 32768 8.50 -> 6.67 ms (both sides in turn).  What bounds it: the vector work of
-// taking the parts (44 instructions per eight values and block row) beside the 24 MFMAs of a K step of 16, of which two
-// wavefronts per SIMD overlap about two thirds.  64-row tiles serve problems too small to fill the chip, where one
+// 2.0e-7 and 4.1e-7 -> 1.8e-7 (4096 x 1024 x 8192), log-sum-exp level (its rounding to 32 bits dominates).  Forward and
+// backward, us (both sides in turn): 1000 x 512 x 10007 118 + 340 -> 108 + 271, 4096 x 1024 x 32768 2030 + 6258 -> 1633 + 5590.  What
+// bounds it: the vector work of taking the parts (52 instructions per eight values and block row) beside the 24 MFMAs of a K step of 16, of
+// which two wavefronts per SIMD overlap about two thirds.  64-row tiles serve problems too small to fill the chip, where one
 // wavefront per SIMD would do the two one after the other: they stay with the fp32 instruction (with parts 256 x 256 x 4096
 // forward 37.0 -> 39.2 us).  A 256-row tile of K = 512 keeps a CU busy for 109 us and
 // a problem of a few thousand rows by a few thousand vocabulary entries has fewer such tiles than the chip has CUs, hence
@@ -147,13 +149,19 @@ constexpr int stages() { return T == 128 ? 2 : 4; }         // 64 KiB of LDS eit
 template <int T>
 constexpr int lds_bytes() { return stages<T>() * 2 * T * BK * 4; }
 
-// Eight fp32 values as three bf16 each, x = h + m + l exactly (8 bits of mantissa each, rounded to nearest).
+// Eight fp32 values times 2^PART_SHIFT as three bf16 each, exactly (8 bits of mantissa each, rounded to nearest).  Without the factor
+// the third part of a value below 2^-109 falls under bf16's smallest normal number, 2^-126, and the parts lose bits: columns of
+// H or W or upstream gradients of 1e-36 gave gradients off by 5e-4.  With it the smallest fp32 subnormal becomes 2^-109, and
+// every value below 2^87 has its parts.  The factors leave a sum where it is added to the tile's; the multiplications cost 5 %
+// (1000 x 512 x 10007 102 + 255 -> 108 + 271 us, 4096 x 1024 x 32768 1540 + 5180 -> 1633 + 5590).
+constexpr int PART_SHIFT = 40;
+constexpr float PART_FACTOR = (float)(1ll << PART_SHIFT), SUM_FACTOR = 1.f / PART_FACTOR / PART_FACTOR;
 struct Split { bf16x8 h, m, l; };
 __device__ __forceinline__ Split split(const f32x4& x0, const f32x4& x1) {
   union { bf16x8 v; uint32_t w[4]; } h, m, l;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    const float a = p < 2 ? x0[2 * p] : x1[2 * p - 4], b = p < 2 ? x0[2 * p + 1] : x1[2 * p - 3];
+    const float a = PART_FACTOR * (p < 2 ? x0[2 * p] : x1[2 * p - 4]), b = PART_FACTOR * (p < 2 ? x0[2 * p + 1] : x1[2 * p - 3]);
     h.w[p] = f32x2_to_bf16x2_bits(a, b);
     const float ra = a - __uint_as_float(h.w[p] << 16), rb = b - __uint_as_float(h.w[p] & 0xFFFF0000u);
     m.w[p] = f32x2_to_bf16x2_bits(ra, rb);
@@ -254,7 +262,7 @@ __device__ __forceinline__ void mainloop_as(const Operand& A, const Operand& B, 
 #pragma unroll
       for (int j = 0; j < W; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] += part[i][j][r];
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = SPLIT ? fmaf(part[i][j][r], SUM_FACTOR, acc[i][j][r]) : acc[i][j][r] + part[i][j][r];
   }
   fast::wait_vm_and_lds<0>();
   __builtin_amdgcn_s_barrier();

@@ -11,7 +11,7 @@ from paper_2511_17599_amd.runner import Session           # noqa: E402
 from conftest import tile_edges                           # noqa: E402
 
 
-def _run(N, d, V, seed, change=None):
+def _run(N, d, V, seed, change=None, reduction="mean"):
     g = torch.Generator(device="cuda").manual_seed(seed)
     H = torch.randn(N, d, device="cuda", generator=g)
     W = torch.randn(V, d, device="cuda", generator=g) * 0.05
@@ -20,13 +20,14 @@ def _run(N, d, V, seed, change=None):
         change(H, W)
     assert tile_edges(N, d, V, "f32") == (128, 128)
     print(f"[case] f32 parts N={N} d={d} V={V} seed={seed}", flush=True)
-    s = Session(N, d, V, "f32", "mean", -100, H, W, y)
+    s = Session(N, d, V, "f32", reduction, -100, H, W, y)
     assert s.forward() == B.FLCE_OK and s.backward() == B.FLCE_OK
     z = H.double() @ W.double().t()
     lse = torch.logsumexp(z, 1)
     G = torch.exp(z - lse[:, None])
     G[torch.arange(N, device="cuda"), y] -= 1
-    G /= N
+    if reduction == "mean":
+        G /= N
     return s, lse, G, H.double(), W.double()
 
 
@@ -66,14 +67,32 @@ def test_values_next_to_the_largest():
     assert _rel(s.dH[:, keep], (G @ W)[:, keep]) < 1e-6
 
 
-def test_small_values():
-    """Parts of small numbers are smaller still: 1e-30 leaves them above the smallest normal bf16 number."""
+@pytest.mark.parametrize("factor", [1e-30, 2.0 ** -112, 1e-36])
+def test_small_values(factor):
+    """Columns whose parts would lie below the smallest normal bf16 number.  (Summed loss: the gradients of the last ones are
+    mostly normal numbers still, half a step of 2^-149 on 1e-38 is 7e-8.)"""
     def small(H, W):
-        W[:, 5] *= 1e-30
-        H[:, 6] *= 1e-30
-    s, lse, G, H, W = _run(1300, 72, 3800, 53, small)
-    assert _rel(s.dH[:, 5] * 1e30, (G @ W)[:, 5] * 1e30) < 2e-6
-    assert _rel(s.dW[:, 6] * 1e30, (G.t() @ H)[:, 6] * 1e30) < 2e-6
+        W[:, 5] *= factor
+        H[:, 6] *= factor
+    s, lse, G, H, W = _run(1300, 72, 3800, 53, small, reduction="sum")
+    assert _rel(s.dH[:, 5].double() / factor, (G @ W)[:, 5] / factor) < 2e-6
+    assert _rel(s.dW[:, 6].double() / factor, (G.t() @ H)[:, 6] / factor) < 2e-6
+
+
+@pytest.mark.parametrize("factor", [1e-30, 1e-34])
+def test_small_upstream_gradients(factor):
+    """One loss per row: G holds the rows' upstream gradients."""
+    from paper_2511_17599_amd.torch_api import linear_cross_entropy
+    g = torch.Generator(device="cuda").manual_seed(55)
+    H = torch.randn(1300, 72, device="cuda", generator=g).requires_grad_()
+    W = (torch.randn(3800, 72, device="cuda", generator=g) * 0.05).requires_grad_()
+    y = torch.randint(0, 3800, (1300,), device="cuda", generator=g)
+    print(f"[case] f32 row gradients of {factor}", flush=True)
+    rows = linear_cross_entropy(H, W, y, reduction="none")
+    one = torch.autograd.grad(rows, (H, W), torch.ones_like(rows), retain_graph=True)
+    few = torch.autograd.grad(rows, (H, W), torch.full_like(rows, factor))
+    for a, b in zip(few, one):
+        assert _rel(a.double() / factor, b.double()) < 1e-6
 
 
 def test_nan_stays_in_its_row():
