@@ -52,7 +52,7 @@ __host__ __device__ __forceinline__ int64_t packed_cols_offset(int q, int rows) 
 }
 
 // Main-loop policies.  A kernel is written once against this interface:
-//   THREADS, TILE (output tile edge), LDS (dynamic LDS bytes), WM x WN (accumulator blocks per wavefront, 16 values of a
+//   THREADS, MIN_WAVES (launch bounds), TILE (output tile edge), LDS (dynamic LDS bytes), WM x WN (accumulator blocks per wavefront, 16 values of a
 //   lane in one N column of ROWS rows each), Acc: a finished tile's accumulators, get(i, j, r) element r of block (i, j)
 //   (i, j, r constants after unrolling), tile_m(i, r) / tile_n(j): its position inside the tile; inside its block it is row
 //   (r / 4) QUAD + lane_row() + r % 4,
@@ -67,6 +67,7 @@ struct VectorAcc {        // of the loops that leave the accumulators to the com
 struct GenericLoop {      // bf16 where the tuned loop does not reach (address windows); 8 wavefronts 2 x 4
   static constexpr int TILE = flce::TILE, THREADS = flce::THREADS, WM = flce::WM, WN = flce::WN, LDS = LDS_BYTES;
   static constexpr bool TRANSPOSING = false, TUNED = false;
+  static constexpr int MIN_WAVES = 1;
   static constexpr int ROWS = 32, QUAD = 8, SLOTS = 4;
   using Acc = VectorAcc<WM, WN>;
   static __device__ __forceinline__ int lane_row() { return (threadIdx.x & 32) >> 3; }
@@ -106,6 +107,9 @@ template <int T>
 struct F32Loop {          // fp32; T x T tiles, 4 wavefronts 2 x 2, two workgroups per CU
   static constexpr int TILE = T, THREADS = f32::THREADS, WM = T / 64, WN = T / 64, LDS = f32::lds_bytes<T>();
   static constexpr bool TRANSPOSING = true, TUNED = false;
+  // wavefronts per SIMD that the compiler has to leave registers for: two workgroups of 128-row tiles need it told (64-row ones have
+  // room anyway, and are 1 % faster with their sums in the accumulation registers)
+  static constexpr int MIN_WAVES = T == 128 ? 2 : 1;
   static constexpr int ROWS = 32, QUAD = 8, SLOTS = 4;
   using Acc = VectorAcc<WM, WN>;
   static __device__ __forceinline__ int lane_row() { return (threadIdx.x & 32) >> 3; }
@@ -143,6 +147,7 @@ template <bool RAGGED, int B>
 struct TunedLoop {
   static constexpr int TILE = 64 * B, THREADS = fast::THREADS, WM = B / 2, WN = 2 * B;
   static constexpr bool TRANSPOSING = true, TUNED = true;
+  static constexpr int MIN_WAVES = 1;
   static constexpr int ROWS = 64, QUAD = 16, SLOTS = 8;
   using Acc = fast::Acc<2 * B, 2 * B>;
   // 256-row tiles: one workgroup per CU, 4 stages of 32 KiB; 128-row tiles: two, 5 stages of 16 KiB each
@@ -287,7 +292,7 @@ __device__ __forceinline__ void merge_fixed(const float (&m)[S], const float (&a
 // blocks), and the main loop reads that copy: every global -> LDS request is then 1 KiB of consecutive
 // bytes, where the rows of H themselves give it 64 bytes at a time.
 template <typename T, typename L, bool HKR>
-__global__ __launch_bounds__(L::THREADS) void fwd_tiles_kernel(
+__global__ __launch_bounds__(L::THREADS, L::MIN_WAVES) void fwd_tiles_kernel(
     const T* __restrict__ H, const T* __restrict__ HT, const T* __restrict__ W, const int64_t* __restrict__ y,
     int N, int d, int V, int64_t ignore_index, int64_t V_total, int64_t v_begin, int n_rb, int n_win, int n_vt,
     double vt_per_win, float* __restrict__ part, int64_t npad, int item_begin, Header* __restrict__ hdr) {
@@ -1039,7 +1044,7 @@ struct RowMeta {
 // it differs from row to row (Alg. 2 with a per-position Gamma); otherwise g = p - [v == y_row] and the
 // scalar Gamma is applied when the contractions write out.
 template <typename T, typename L, bool HKR, bool PER_ROW = false>
-__global__ __launch_bounds__(L::THREADS) void recompute_kernel(RecomputeArgs<T> a) {
+__global__ __launch_bounds__(L::THREADS, L::MIN_WAVES) void recompute_kernel(RecomputeArgs<T> a) {
   extern __shared__ __align__(16) char lds[];
   const T* __restrict__ Hc = a.Hc; const T* __restrict__ HcT = a.HcT; const T* __restrict__ W = a.W;
   const int npad = a.npad, d = a.d, V = a.V;
@@ -1504,7 +1509,7 @@ __device__ __forceinline__ void contract(const ContractArgs<T>& a, int wg, int n
 }
 
 template <typename T, typename L, int OPS>
-__global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a) {
+__global__ __launch_bounds__(L::THREADS, L::MIN_WAVES) void contract_kernel(ContractArgs<T> a) {
   extern __shared__ __align__(16) char lds[];
   contract<T, L, OPS>(a, blockIdx.x, gridDim.x, lds);
 }
@@ -1512,7 +1517,7 @@ __global__ __launch_bounds__(L::THREADS) void contract_kernel(ContractArgs<T> a)
 // dW and dH of one chunk side by side: the first wg_w workgroups take dW's items, the others dH's.  For problems whose
 // output tiles fit the chip together, at most two rounds of them K slices included: `contractions` in plan_backward.
 template <typename T, typename L, int OPS_W, int OPS_H>
-__global__ __launch_bounds__(L::THREADS) void contract_pair_kernel(ContractArgs<T> w, ContractArgs<T> h, int wg_w) {
+__global__ __launch_bounds__(L::THREADS, L::MIN_WAVES) void contract_pair_kernel(ContractArgs<T> w, ContractArgs<T> h, int wg_w) {
   extern __shared__ __align__(16) char lds[];
   if ((int)blockIdx.x < wg_w) contract<T, L, OPS_W, true>(w, blockIdx.x, wg_w, lds);
   else contract<T, L, OPS_H, true>(h, (int)blockIdx.x - wg_w, (int)gridDim.x - wg_w, lds);

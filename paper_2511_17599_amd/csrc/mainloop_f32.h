@@ -274,16 +274,30 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
                                          f32x16 (&acc)[T / 64][T / 64]) {
   mainloop_as<T, LA, LB, T == 128>(A, B, k_elems, lds, acc);
   if constexpr (T == 128) {
-    // An infinity, a NaN or a value that rounds past bf16's largest has no such parts: its products are NaN.  The tile is
-    // then done again as it is.
-    float bad = 0.f;
+    // An infinity, a NaN, a value from 2^87 or a sum from 2^47 on has no such parts or sums: what it is in comes out as NaN or
+    // infinity.  The tile is then done again as it is, for those elements alone: which method an element is computed by depends
+    // on its own row and column, not on what shares the tile, so that the backward (which leaves out rows) repeats the forward's logits.
+    auto finite = [](float x) { return x * 0.f == 0.f; };
+    bool redo = false;
 #pragma unroll
     for (int i = 0; i < T / 64; ++i)
 #pragma unroll
-      for (int j = 0; j < T / 64; ++j)
+      for (int j = 0; j < T / 64; ++j) {
+        float bad = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) bad = fmaf(acc[i][j][r], 0.f, bad);
-    if (__syncthreads_or(bad != bad)) mainloop_as<T, LA, LB, false>(A, B, k_elems, lds, acc);
+        redo |= !finite(bad);
+      }
+    if (__syncthreads_or(redo)) {
+      f32x16 whole[T / 64][T / 64];
+      mainloop_as<T, LA, LB, false>(A, B, k_elems, lds, whole);
+#pragma unroll
+      for (int i = 0; i < T / 64; ++i)
+#pragma unroll
+        for (int j = 0; j < T / 64; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = finite(acc[i][j][r]) ? acc[i][j][r] : whole[i][j][r];
+    }
   }
 }
 

@@ -49,3 +49,20 @@ def test_confident_rows(dtype, edges, N, d, V, logit):
     s = Session(N, d, V, dtype, "mean", IGNORE, H, W, y)
     assert s.forward() == B.FLCE_OK and s.backward() == B.FLCE_OK
     check(s, y, logit)
+
+
+@pytest.mark.parametrize("logit", [40.0, 165.0])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e30])
+def test_confident_rows_beside_rows_left_out(value, logit):
+    """fp32 with bf16 parts: ignored rows hold values that have none, so the forward computes their tiles both ways; the backward
+    leaves those rows out and has tiles without them."""
+    N, d, V = 1300, 512, 4000
+    H, W, y = confident(N, d, V, "f32", logit, 71)
+    H[3::70] = value
+    y[3::70] = IGNORE
+    assert tile_edges(N, d, V, "f32") == (128, 128)
+    print(f"[case] confident beside {value} logit={logit}", flush=True)
+    s = Session(N, d, V, "f32", "mean", IGNORE, H, W, y)
+    assert s.forward() == B.FLCE_OK and s.backward() == B.FLCE_OK
+    check(s, y, logit)
+    assert not s.dH[3::70].any()
