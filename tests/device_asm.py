@@ -18,16 +18,22 @@ class Inst(NamedTuple):
 
 
 @functools.lru_cache(None)
-def kernels():
-    """{kernel name: (instructions, predecessors of each one)}; one compile per process."""
+def compiled():
+    """(assembly of the device code, the compiler's remarks on what each kernel uses); one compile per process."""
     with tempfile.TemporaryDirectory() as tmp:
         out = f"{tmp}/flce.s"
         flags = [f for f in BLD.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
-        res = subprocess.run([BLD.hipcc_path(), *flags, "-S", "--offload-device-only", BLD.SRC, "-o", out],
-                             capture_output=True, text=True)
+        res = subprocess.run([BLD.hipcc_path(), *flags, "-Rpass-analysis=kernel-resource-usage", "-S", "--offload-device-only",
+                              BLD.SRC, "-o", out], capture_output=True, text=True)
         assert res.returncode == 0, res.stderr[-2000:]
         with open(out) as f:
-            return parse(f.read())
+            return f.read(), res.stderr
+
+
+@functools.lru_cache(None)
+def kernels():
+    """{kernel name: (instructions, predecessors of each one)}"""
+    return parse(compiled()[0])
 
 
 def parse(text):
@@ -70,10 +76,11 @@ def _predecessors(insts, labels):
 
 def registers(arg, kind):
     """The numbers of the registers of a kind ('s', 'v', 'a') that an operand names."""
-    m = re.match(rf"^[-|]*{kind}(?:(\d+)|\[(\d+):(\d+)\])(?=\W|$)", arg)
+    m = re.match(rf"^[-|]*{kind}(?:(\d+)|\[(\d+)(?::(\d+))?\])(?=\W|$)", arg)
     if not m:
         return set()
-    return {int(m.group(1))} if m.group(1) else set(range(int(m.group(2)), int(m.group(3)) + 1))
+    first = int(m.group(1) or m.group(2))
+    return set(range(first, int(m.group(3) or first) + 1))
 
 
 def wait_states(x):

@@ -6,21 +6,13 @@ silently break the count, and spills anywhere turn into memory traffic per tile.
 source for gfx950 with the compiler's own resource-usage remarks and checks every kernel (no GPU needed).
 """
 import re
-import subprocess
 
-import pytest
-
-from paper_2511_17599_amd import build as BLD
+import device_asm as A
 
 
-def kernel_resource_usage(tmp_path):
-    out = tmp_path / "remarks.so"
-    flags = [f for f in BLD.HIPCC_FLAGS]
-    cmd = [BLD.hipcc_path(), *flags, "-Rpass-analysis=kernel-resource-usage", BLD.SRC, "-o", str(out)]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    assert res.returncode == 0, res.stderr[-2000:]
+def kernel_resource_usage():
     usage = {}
-    for block in re.split(r"remark: [^\n]*Function Name: ", res.stderr)[1:]:
+    for block in re.split(r"remark: [^\n]*Function Name: ", A.compiled()[1])[1:]:
         name = block.split()[0]
         fields = {}
         for key, pat in (("vgpr_spill", r"VGPRs Spill: (\d+)"), ("sgpr_spill", r"SGPRs Spill: (\d+)"),
@@ -33,8 +25,8 @@ def kernel_resource_usage(tmp_path):
     return usage
 
 
-def test_no_kernel_spills_or_uses_scratch(tmp_path):
-    usage = kernel_resource_usage(tmp_path)
+def test_no_kernel_spills_or_uses_scratch():
+    usage = kernel_resource_usage()
     tuned = [n for n in usage if "FastLoop" in n]
     # the benchmarked instantiations are all there: forward, recompute, both contractions
     for piece in ("fwd_tiles_kernel", "recompute_kernel", "contract_kernel"):
