@@ -116,9 +116,11 @@ TailSplit tail_split(int64_t out_row_tiles, int64_t n_mt, int n_split, int64_t k
 }
 
 // The tuned bf16 loop needs every tile's address window within reach of a buffer descriptor: offsets and the record count are unsigned 32-bit, and
-// the zero-filled overshoot of a last K stage (up to 32 rows) must not wrap 2^32.
+// the zero-filled overshoot of a last K stage (up to 32 rows, with the tile's columns and the bias of the offsets) must not wrap 2^32.
 // The `generic` knob forces the generic loop everywhere.
-bool window_ok(int64_t k_rows, int64_t ld_bytes) { return (k_rows + 32) * ld_bytes < ((int64_t)1 << 32); }
+bool window_ok(int64_t k_rows, int64_t ld_bytes) {
+  return (k_rows + 32) * ld_bytes + TILE * 2 + fast::BIAS < ((int64_t)1 << 32);
+}
 bool fast_loop_ok(const Plan& p, const Tuning& tn) {
   if (p.esize != 2 || tn.generic) return false;
   const int64_t vc = (int64_t)p.vc_tiles * TILE, nc = (int64_t)p.nc_tiles * TILE;

@@ -246,9 +246,6 @@ __device__ __forceinline__ int scalar(int x) {
   return m;
 }
 
-// the wait states between the last MFMA and the first plain read of its result (at most 11 for a 16x16x32)
-__device__ __forceinline__ void settle() { asm volatile("s_nop 15" ::: "memory"); }
-
 __device__ __forceinline__ int slot_of_lane() {      // fp32 loop: which of the 4 lanes sharing an N column this is
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   return (wave >> 1) * 2 + (lane >> 5);

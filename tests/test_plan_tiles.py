@@ -22,3 +22,11 @@ def test_one_edge_for_both_directions_everywhere():
     for _ in range(400):
         forward, backward = tile_edges(int(2 ** r.uniform(0, 15)), 8 * r.randint(1, 256), int(2 ** r.uniform(0, 17)), "f32")
         assert forward == backward
+
+
+def test_address_windows_leave_room_for_the_offsets_bias():
+    """289 rows of 2 d bytes, 512 of the tile's columns and 3072 of bias in 2^32: the next hidden size runs on the generic loop."""
+    from paper_2511_17599_amd import binding as B
+    last = max(d for d in range(7430000, 7432000, 8) if 289 * 2 * d + 512 + 3072 < 2 ** 32)
+    for d, loop in ((last, "tuned"), (last + 8, "generic")):
+        assert f"loop={loop} " in B.flce_plan_describe(1, d, 1, B.FLCE_DTYPE_BF16)
