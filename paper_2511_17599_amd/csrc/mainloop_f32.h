@@ -176,10 +176,11 @@ __device__ __forceinline__ Split split(const f32x4& x0, const f32x4& x1, float f
 // 5.46e-8, 2048 x 1024 x 32768 5.33 / 5.36 / 5.28e-8.
 __device__ __forceinline__ constexpr float block_sign(int i) { return i & 1 ? -1.f : 1.f; }
 
-// acc = A_tile . B_tile^T over k_elems of K.  On return every wavefront has passed a barrier after its last LDS read.
+// acc = A_tile . B_tile^T over k_elems of K.  On return every wavefront has passed a barrier after its last LDS read.  `blocks`: bit
+// (i, j) at i T / 64 + j, which blocks this wavefront multiplies (fp32 products; the others stay zero).
 template <int T, int LA, int LB, bool SPLIT>
 __device__ __forceinline__ void mainloop_as(const Operand& A, const Operand& B, int k_elems, char* lds,
-                                         f32x16 (&acc)[T / 64][T / 64]) {
+                                         f32x16 (&acc)[T / 64][T / 64], uint32_t blocks = ~0u) {
   constexpr int W = T / 64, NS = stages<T>(), OPER = T * BK * 4, STAGE = 2 * OPER, LOADS = 2 * (T / 32);
 #pragma unroll
   for (int i = 0; i < W; ++i)
@@ -254,12 +255,19 @@ __device__ __forceinline__ void mainloop_as(const Operand& A, const Operand& B, 
         f32x4 a[W], b[W];
         read_frags<T, LA>(a, st, wave >> 1, g);
         read_frags<T, LB>(b, st + OPER, wave & 1, g);
+        if constexpr (W == 1) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+          for (int k = 0; k < 4; ++k) part[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0][k], b[0][k], part[0][0], 0, 0, 0);
+        } else {
 #pragma unroll
           for (int i = 0; i < W; ++i)
 #pragma unroll
-            for (int j = 0; j < W; ++j) part[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][k], b[j][k], part[i][j], 0, 0, 0);
+            for (int j = 0; j < W; ++j)
+              if (blocks >> (i * W + j) & 1) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) part[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][k], b[j][k], part[i][j], 0, 0, 0);
+              }
+        }
       }
       asm volatile("" ::: "memory");
     }
@@ -281,10 +289,12 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
   mainloop_as<T, LA, LB, T == 128>(A, B, k_elems, lds, acc);
   if constexpr (T == 128) {
     // An infinity, a NaN, a value from 2^87 or a sum from 2^47 on has no such parts or sums: what it is in comes out as NaN or
-    // infinity.  The tile is then done again as it is, for those elements alone: which method an element is computed by depends
+    // infinity.  The tile is then done again as it is, for those elements alone (and blocks of them): which method an element is computed by depends
     // on its own row and column, not on what shares the tile, so that the backward (which leaves out rows) repeats the forward's logits.
+    // Such calls pay for both: 1000 x 512 x 10007 forward + backward 106 + 267 us, 123 + 390 with one infinity in W, 169 + 467 with a
+    // row of NaN in H (fp32 products throughout: 116 + 340 either way; whole tiles again: 134 + 432 and 204 + 523).
     auto finite = [](float x) { return x * 0.f == 0.f; };
-    bool redo = false;
+    uint32_t blocks = 0;      // of this wavefront that hold such an element
 #pragma unroll
     for (int i = 0; i < T / 64; ++i)
 #pragma unroll
@@ -292,11 +302,11 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
         float bad = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) bad = fmaf(acc[i][j][r], 0.f, bad);
-        redo |= !finite(bad);
+        blocks |= __ballot(!finite(bad)) ? 1u << (i * (T / 64) + j) : 0u;
       }
-    if (__syncthreads_or(redo)) {
+    if (__syncthreads_or(blocks)) {
       f32x16 whole[T / 64][T / 64];
-      mainloop_as<T, LA, LB, false>(A, B, k_elems, lds, whole);
+      mainloop_as<T, LA, LB, false>(A, B, k_elems, lds, whole, blocks);
 #pragma unroll
       for (int i = 0; i < T / 64; ++i)
 #pragma unroll
