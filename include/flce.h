@@ -16,6 +16,10 @@
  *     contiguous: H[N][d], W[V][d], dH[N][d], dW[V][d]; 16-byte aligned.
  *   - Element type of H, W, dH, dW is `dt`: bf16 (2 bytes) or fp32.  Logits,
  *     softmax statistics and all accumulations are fp32; loss and lse are fp32.
+ *     fp32 products: on the fp32 matrix instruction, or (problems of 320 and more
+ *     128 x 128 tiles of logits) as sums of bf16 parts of both factors, exact for every
+ *     value below 2^87 and with errors no larger; what the parts do not reach
+ *     (infinities, NaN, larger values) comes from the fp32 instruction and takes longer.
  *   - targets are int64, 0-based, in [0, V).  A row whose target equals
  *     `ignore_index` (any int64 value; compared first) does not count: its loss
  *     is 0, its dH row is all +0, it adds nothing to dW and it is left out of

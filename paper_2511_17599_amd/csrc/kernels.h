@@ -191,7 +191,8 @@ struct TunedLoop {
   // A wavefront's pieces of 16 rows x (32 B) columns of bf16 on their way through its slice of the free stage, rows of
   // ROW_BYTES in 16-byte chunks whose number is XOR-ed with mix(row), so that the 16 rows (x 2 neighbouring 8-byte halves)
   // one write cycle touches lie in different banks, and likewise the four rows x four neighbouring chunks of a read
-  // cycle (blocks of G; output rows are read in the order of the places, and the store takes the chunks as they come).
+  // cycle (blocks of G; output rows are read in the order of the places, and the store takes the chunks as they come).  Counted
+  // bank conflicts, of the LDS's busy cycles: recompute 3 % at 8192 x 4096 x 128256, 12 % at 4096 x 768 x 50257, dW up to 2.5 %.
   // piece_slot: where a lane writes its 4 columns of quad rq of block i in row r; piece_chunk: where chunk c of row r is read.
   static constexpr int ROW_BYTES = 64 * B, CHUNKS = ROW_BYTES / 16, ROWS_PER_STORE = 64 / CHUNKS;
   static __device__ __forceinline__ int mix(int r) {
@@ -1007,7 +1008,7 @@ __global__ __launch_bounds__(256) void transpose_pad_kernel(const U* __restrict_
 
 // ------------------------------------------------------------------------------------
 // Backward, step 1 (on the compacted rows): logit tile recomputed exactly as in the
-// forward, then
+// forward (the same products added up in the same order; fp32 on the same tile edge, see plan_base), then
 //   g = exp(z - lse_row) - [v == y_row]            (unscaled; Gamma comes later)
 // rounded to T and written to the staging tile
 //   G [row - chunk_n0][vocab - chunk_v0]   (ldG  elements per row; with the tuned loop in blocks of 16 rows x 32

@@ -9,7 +9,7 @@
 // Its sums round once per 16 products and part instead of once per 2 products, and the partial sums are kept
 // short (sum_stages), so the error against 64 bits is no larger: dH and dW 4.0e-7 -> 1.7e-7 (1000 x 512 x 10007), 4.2e-7 ->
 // 2.0e-7 and 4.1e-7 -> 1.8e-7 (4096 x 1024 x 8192), log-sum-exp level (its rounding to 32 bits dominates).  Forward and
-// backward, us (both sides in turn): 1000 x 512 x 10007 118 + 340 -> 108 + 271, 4096 x 1024 x 32768 2030 + 6258 -> 1633 + 5590.  What
+// backward, us (both sides in turn): 1000 x 512 x 10007 116 + 340 -> 106 + 267, 4096 x 1024 x 32768 2030 + 6258 -> 1587 + 5425.  What
 // bounds it: the vector work of taking the parts (52 instructions per eight values and block row) beside the 24 MFMAs of a K step of 16, of
 // which two wavefronts per SIMD overlap about two thirds.  64-row tiles serve problems too small to fill the chip, where one
 // wavefront per SIMD would do the two one after the other: they stay with the fp32 instruction (with parts 256 x 256 x 4096

@@ -1,5 +1,5 @@
 """The fp32 main loop at the edges of its tiles: 64-row tiles below 320 tiles of 128 x 128 logits, 128-row tiles from there
-on; K tails shorter than a 16-byte chunk row, K longer than one block of partial sums, rows and columns past the end."""
+on, in both directions; K tails shorter than a 16-byte chunk row, K longer than one block of partial sums, rows and columns past the end."""
 import pytest
 
 pytestmark = pytest.mark.gpu
