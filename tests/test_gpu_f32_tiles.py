@@ -15,6 +15,8 @@ from test_gpu_parity import check_against_oracle          # noqa: E402
     (64, 64, 32, 64, 0.0), (64, 65, 8, 129, 0.1), (64, 63, 72, 257, 0.0), (64, 300, 1064, 200, 0.3), (64, 5, 256, 2100, 0.0),
     (128, 1300, 72, 3800, 0.1), (128, 1281, 8, 3713, 0.5), (128, 130, 200, 20500, 0.0), (128, 20500, 40, 130, 0.02),
     (128, 1409, 1032, 3650, 0.0),
+    (64, 1401, 72, 3701, 0.1), (64, 1408, 40, 3712, 0.0), (128, 1280, 40, 4096, 0.0), (128, 1153, 72, 3969, 0.1),   # 319, 319, 320, 320
+    (64, 1170, 96, 2500, 0.0), (64, 2000, 264, 2400, 0.1),
 ], ids=str)
 def test_f32_tiles(tile, N, d, V, ignore):
     if not torch.cuda.is_available():
@@ -24,7 +26,7 @@ def test_f32_tiles(tile, N, d, V, ignore):
     check_against_oracle(wl, I.make_inputs(wl))
 
 
-@pytest.mark.parametrize("tile,N,V", [(64, 700, 1500), (128, 1300, 3800)])
+@pytest.mark.parametrize("tile,N,V", [(64, 700, 1500), (64, 1100, 2900), (128, 1300, 3800)])
 def test_f32_chunks_and_slices(monkeypatch, tile, N, V):
     """Several chunks with running sums and K slices, at both tile sizes."""
     set_plan(monkeypatch, FLCE_VC_TILES=3, FLCE_NC_TILES=2, FLCE_SPLITK_DH=3, FLCE_SPLITK_DW=2, FLCE_WINDOWS=3)
